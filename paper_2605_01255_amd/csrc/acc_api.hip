@@ -20,6 +20,7 @@
 #include "acc_sketch.h"
 #include "acc_gemm16.h"
 #include "acc_gemm8.h"
+#include "acc_gemm_ring.h"
 #include "acc_gemm_smallk.h"
 
 // Scratch of acc_linear_fwd_static (the entry point for callers that cannot allocate): the split-token partial
@@ -236,9 +237,9 @@ void generic_dw(const acc_linear_desc* d, const Shape& s, const void* Xs, const 
 // ---- tuned bf16 path ------------------------------------------------------------------------
 constexpr int64_t kMaxOperandBytes = 0xFFFFFFFFll;  // buffer resources address 4 GiB
 
-// C[M, N] = A[M, K] . B with the tuned kernel; B is [N, K] (KMAJ) or [K, N].
+// C[M, N] = A[M, K] . B with the tuned kernels; B is [N, K] (KMAJ) or [K, N].
 bool fast_gemm_ok(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
-  return K % 64 == 0 && N % 8 == 0 && M * lda * 2 <= kMaxOperandBytes &&
+  return K % 8 == 0 && N % 8 == 0 && M * lda * 2 <= kMaxOperandBytes &&
          (N > K ? N : K) * ldb * 2 <= kMaxOperandBytes && 256 * lda * 2 <= kMaxOperandBytes;
 }
 
@@ -252,6 +253,51 @@ struct ReduceJob {
   int out_bf16;
   int64_t row, ld;  // the result's rows hold `row` elements and are stored `ld` apart
 };
+
+// Which kernel and tile a product takes: the least of five estimates, launch + rounds x (cost of a tile + K tiles x time of
+// a K tile), in nanoseconds, with rounds = tiles over 256 compute units.  A larger tile needs fewer bytes from L2 per
+// multiply-add (a 128 x 128 K tile multiplies for 0.2 us and takes 0.36 to move, however many stages are in flight), a
+// smaller one leaves fewer compute units idle.  From two rounds on, two work-groups of two stages per compute unit cover
+// each other's waits better than one of four (4096 x 2048 x 2048 on 128 x 128: 34 against 41 us).  The constants are fits
+// to 45 shapes from 256 x 512 x 512 to 16384 x 3072 x 8192, good to about 15 %; measured us on 256 x 256 / 192 x 128 /
+// 128 x 128 / 128 x 64 / 64 x 64, with what the kernels this replaced took (256 x 256 from 192 tiles on, else a two-stage
+// 128 x 128) in brackets:
+//   16384 x 3072 x 3072 228 / 293 / 286 /  - /  - [228]    16384 x 1152 x 3072 139 / 116 / 129 / 166 / 222 [139]
+//   6000 x 4096 x 4096  188 / 168 / 180 /  - /  - [188]    4096 x 2048 x 2048   53 /  38 /  34 /  41 /   - [35]
+//   4096 x 1024 x 3072   71 /  30 /  29 / 30 / 39 [36-41]  1053 x 3048 x 1600   35 /  18 /  15 /  17 /  22
+//   384 x 3072 x 3072    57 /  28 /  23 / 17 / 16 [34]     2048 x 1024 x 1024   27 /  14 /  12 / 9.0 / 9.4
+enum class GemmTile { k256, k192x128, k128, k128x64, k64 };
+struct GemmChoice {
+  GemmTile tile;
+  bool one_round;
+};
+GemmChoice pick_gemm_tile(int64_t M, int64_t N, int64_t K, bool persist_ok) {
+  struct Cost { GemmTile tile; int bm, bn, launch, per_tile, per_k, alone_per_tile, alone_per_k; };  // alone: one round
+  static const Cost costs[] = {{GemmTile::k256, 256, 256, 5000, 2000, 1330, 2000, 1330},
+                               {GemmTile::k192x128, 192, 128, 3000, 1700, 580, 3500, 500},
+                               {GemmTile::k128, 128, 128, 3000, 2000, 460, 3000, 370},
+                               {GemmTile::k128x64, 128, 64, 3000, 1500, 280, 1500, 260},
+                               {GemmTile::k64, 64, 64, 3000, 500, 200, 500, 230}};
+  const int64_t kt = ceil_div(K, 64);
+  GemmChoice best{GemmTile::k128, true};
+  int64_t best_ns = INT64_MAX;
+  for (const Cost& c : costs) {
+    if (c.tile == GemmTile::k256 && !persist_ok) continue;
+    const int64_t rounds = ceil_div(ceil_div(M, c.bm) * ceil_div(N, c.bn), 256);
+    int64_t per_k = rounds == 1 ? c.alone_per_k : rounds * c.per_k;
+    if (c.tile == GemmTile::k64 && rounds == 2) per_k = 300;  // the second tile hides in the first one's waits
+    const int64_t ns = c.launch + rounds * (rounds == 1 ? c.alone_per_tile : c.per_tile) + kt * per_k;
+    if (ns < best_ns) { best_ns = ns; best = GemmChoice{c.tile, rounds == 1}; }
+  }
+  return best;
+}
+
+template <int TM, int TN, int NS, bool KMAJ, typename TC>
+void ring_gemm(FastGemmParams& p, Launcher& L) {
+  const unsigned grid = gemm_ring_plan(p, 32 * TM, 32 * TN);
+  p.red_stride = (int64_t)grid * 256 * 4;
+  L.launch_lds(gemm_ring_kernel<TM, TN, NS, KMAJ, TC>, dim3(grid), dim3(256), (size_t)gemm_ring_lds_bytes<TM, TN, NS>(), p);
+}
 
 template <bool KMAJ, typename TC>
 void fast_gemm(const void* A, const void* B, void* C, int64_t M, int64_t N, int64_t K, int64_t lda,
@@ -267,26 +313,34 @@ void fast_gemm(const void* A, const void* B, void* C, int64_t M, int64_t N, int6
     p.red_out_bf16 = job->out_bf16;
     p.red_row = job->row; p.red_ld = job->ld;
   }
-  const int64_t big_tiles = ceil_div(M, 256) * ceil_div(N, 256);
-  if (big_tiles >= 192) {  // 256 x 256 tiles: enough tiles to fill 256 CUs
+  const bool persist_ok = sizeof(TC) == 2 && !accumulate && K > 128;  // three K tiles
+  if (!persist_ok && ceil_div(M, 256) * ceil_div(N, 256) >= 192) {  // a short K, a sum into C or float output: no pipeline across tiles
     const unsigned grid = gemm_bf16_plan(p, 256, 256);  // a multiple of 256 slots
     p.red_stride = (int64_t)grid * 256 * 4;
-    if constexpr (sizeof(TC) == 2) {
-      if (!accumulate && K >= 192) {
-        // 256 persistent work-groups on the 16x16x32 instruction; one round of tiles takes it too (a 3072 -> 1024
-        // projection: GEMM 84.3 against 86.4 us on the 32x32x16 kernel below)
-        p.red_stride = (int64_t)256 * 256 * 4;
-        L.launch_lds(gemm16_persist_kernel<KMAJ>, dim3(256), dim3(256), (size_t)160 * 1024, p, (int)grid);
-        return;
-      }
-    }
     L.launch_lds(gemm_bf16_kernel<2, 2, 4, 4, KMAJ, TC>, dim3(grid), dim3(256),
                  (size_t)gemm_bf16_lds_bytes<2, 2, 4, 4>(), p);
-  } else {                 // 128 x 128 tiles, 4 waves
-    const unsigned grid = gemm_bf16_plan(p, 128, 128);
-    p.red_stride = (int64_t)grid * 256 * 4;
-    L.launch_lds(gemm_bf16_kernel<2, 2, 2, 2, KMAJ, TC>, dim3(grid), dim3(256),
-                 (size_t)gemm_bf16_lds_bytes<2, 2, 2, 2>(), p);
+    return;
+  }
+  const GemmChoice c = pick_gemm_tile(M, N, K, persist_ok);
+  switch (c.tile) {
+    case GemmTile::k256:
+      if constexpr (sizeof(TC) == 2) {
+        const unsigned slots = gemm_bf16_plan(p, 256, 256);
+        p.red_stride = (int64_t)256 * 256 * 4;
+        if (K % 64) L.launch_lds(gemm16_persist_kernel<KMAJ, true>, dim3(256), dim3(256), (size_t)160 * 1024, p, (int)slots);
+        else L.launch_lds(gemm16_persist_kernel<KMAJ>, dim3(256), dim3(256), (size_t)160 * 1024, p, (int)slots);
+      }
+      break;
+    case GemmTile::k192x128:
+      if (c.one_round) ring_gemm<6, 4, 4, KMAJ, TC>(p, L);
+      else ring_gemm<6, 4, 2, KMAJ, TC>(p, L);
+      break;
+    case GemmTile::k128:
+      if (c.one_round) ring_gemm<4, 4, 4, KMAJ, TC>(p, L);
+      else ring_gemm<4, 4, 2, KMAJ, TC>(p, L);
+      break;
+    case GemmTile::k128x64: ring_gemm<4, 2, 3, KMAJ, TC>(p, L); break;
+    case GemmTile::k64: ring_gemm<2, 2, 3, KMAJ, TC>(p, L); break;
   }
 }
 
@@ -436,7 +490,7 @@ void fast_sketch(const acc_linear_desc* d, const SketchPlan& sp, const void* A, 
 // A [n, lda] is both the GEMM's left operand and the sketched matrix (X forward, dY backward).
 bool fused_ok(const acc_linear_desc* d, const SketchPlan& sp, int64_t n, int64_t N, int64_t K, int64_t lda,
               int64_t ldb) {
-  return (d->flags & ACC_FLAG_ONE_LAUNCH) && !(d->flags & ACC_FLAG_W_OUT_IN) && d->io_dtype == ACC_BF16 && fast_gemm_ok(n, N, K, lda, ldb) &&
+  return (d->flags & ACC_FLAG_ONE_LAUNCH) && !(d->flags & ACC_FLAG_W_OUT_IN) && d->io_dtype == ACC_BF16 && K % 64 == 0 && fast_gemm_ok(n, N, K, lda, ldb) &&
          ceil_div(n, 256) * ceil_div(N, 256) >= 192 &&
          sp.fast && sp.rc == 128;
 }

@@ -9,7 +9,8 @@
 // Tiles travel global -> LDS directly (global_load_lds_dwordx4, no staging registers); LDS is double
 // buffered, one barrier per K tile, and the MFMAs run one k-step behind the LDS reads so that the
 // reads after the barrier are covered by the last k-step of the previous tile.
-// K % 64 == 0; M and N arbitrary (loads past the last row read zero through the buffer resource,
+// K % 8 == 0: the 16-byte chunks of the last K tile past K are sent out of the buffer's range and read as zero.
+// M and N arbitrary (loads past the last row read zero through the buffer resource,
 // stores are predicated); N % 8 == 0; every operand smaller than 4 GiB.
 #pragma once
 #include <type_traits>
@@ -189,15 +190,10 @@ __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, c
     }
   }
   const uint32_t b_kstep = B_KMAJOR ? BK * 2 : (uint32_t)(BK * p.ldb * 2);  // bytes per K tile
-
-  auto issue_loads = [&](int kt, uint32_t stage) {
-#pragma unroll
-    for (int t = 0; t < A_LOADS; ++t)
-      buffer_to_lds_b128(a_rsrc, a_src[t], (uint32_t)kt * (BK * 2), stage + (t * NW + wave) * 1024);
-#pragma unroll
-    for (int t = 0; t < B_LOADS; ++t)
-      buffer_to_lds_b128(b_rsrc, b_src[t], (uint32_t)kt * b_kstep, stage + A_BYTES + (t * NW + wave) * 1024);
-  };
+  // last K tile: this lane's chunk lies past the K range (rows NW * 8 apart share their swizzle: NW is even)
+  static_assert(NW % 2 == 0, "swizzle period");
+  const int KT = (int)((k1 - k0 + BK - 1) / BK);
+  const uint32_t tail = ((lane & 7) ^ swz(wave * 8 + (lane >> 3))) * 8 >= k1 - k0 - (int64_t)(KT - 1) * BK ? 0xFFFFFFF0u : 0u;
 
   // ---- LDS read offsets of this lane's MFMA operands ----
   const int lrow = lane & 31, kg = lane >> 5;
@@ -231,7 +227,6 @@ __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, c
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  const int KT = (int)((k1 - k0) / BK);
   bf16x8 af[2][TM], bfr[2][TN];
 
   auto read_a1 = [&](const char* st, int s, int i, bf16x8(&dst)[TM]) {
@@ -247,8 +242,9 @@ __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, c
     }
   };
   auto issue_one = [&](int g, int kt, uint32_t stage) {  // g-th wave-load of a K tile (A first, then B)
-    if (g < A_LOADS) buffer_to_lds_b128(a_rsrc, a_src[g], (uint32_t)kt * (BK * 2), stage + (g * NW + wave) * 1024);
-    else buffer_to_lds_b128(b_rsrc, b_src[g - A_LOADS], (uint32_t)kt * b_kstep,
+    const uint32_t oob = kt == KT - 1 ? tail : 0u;
+    if (g < A_LOADS) buffer_to_lds_b128(a_rsrc, a_src[g] | oob, (uint32_t)kt * (BK * 2), stage + (g * NW + wave) * 1024);
+    else buffer_to_lds_b128(b_rsrc, B_KMAJOR ? b_src[g - A_LOADS] | oob : b_src[g - A_LOADS], (uint32_t)kt * b_kstep,
                             stage + A_BYTES + ((g - A_LOADS) * NW + wave) * 1024);
   };
 
@@ -312,7 +308,10 @@ __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, c
 
   // prologue: tile 0 -> stage 0, operands of its first k-step -> registers
   const uint32_t smem_lds = (uint32_t)(uintptr_t)smem;  // LDS byte address of the dynamic segment
-  if (has_tile) issue_loads(0, smem_lds);
+  if (has_tile) {
+#pragma unroll
+    for (int g = 0; g < NG_TOTAL; ++g) issue_one(g, 0, smem_lds);
+  }
   if (p.red_count) {  // side job: this work-group's share of the partial sums, 4 elements per lane
     for (int64_t e = ((int64_t)b * (NW * 64) + tid) * 4; e < p.red_count; e += p.red_stride) {
       f32x4 sum = *(const f32x4*)(p.red_part + e);
@@ -447,8 +446,10 @@ constexpr int gemm_bf16_lds_bytes() {
 static inline unsigned gemm_bf16_plan(FastGemmParams& p, int BM, int BN) {
   p.tiles_m = (int)ceil_div(p.M, BM);
   p.tiles_n = (int)ceil_div(p.N, BN);
-  // 32 tiles per XCD at a time: prefer 8 x 4, shrink along a short dimension
+  // 32 tiles per XCD at a time: prefer 8 x 4, shrink along a short dimension (616 x 14016 x 1216, three rows of tiles:
+  // 8 x 4 blocks left 20 of their 32 slots empty and took 50 us, 4 x 8 blocks 33)
   int sn = p.tiles_n >= 4 ? 4 : (p.tiles_n >= 2 ? 2 : 1);
+  if (sn == 4 && p.tiles_m < 8) sn = p.tiles_m > 4 ? 4 : (p.tiles_m > 2 ? 8 : (p.tiles_m == 2 ? 16 : 32));
   int sm = 32 / sn;
   p.super_m = sm;
   p.super_n = sn;

@@ -70,8 +70,11 @@ __device__ __forceinline__ int swz_n16(int krow) { return ((krow & 3) << 2) | ((
 //     staged in those slots instead the kernel measured the same, 0.5472 against 0.5509 ms per step; the compiler
 //     then keeps two register assignments of the accumulators and 130 copies between them.)
 // LDS: two 64 KB stages + 32 KB of staging regions = 160 KB.  Restrictions (host): bf16 output, no accumulation
-// into C, no K split, K >= 192.
-template <bool B_KMAJOR, int N1 = 12, int S1 = 4, int S0 = 4>
+// into C, no K split, more than two K tiles.
+// RAGGED_K: K % 64 != 0 (K % 8 == 0).  The 16-byte chunks of the last K tile past K are sent out of the buffer's range and
+// read as zero; a lane's chunk is the same in all its wave-loads, so that is one select per K tile and one OR per
+// transfer, which an instantiation of its own keeps out of the slots of the K % 64 == 0 form.
+template <bool B_KMAJOR, bool RAGGED_K = false, int N1 = 12, int S1 = 4, int S0 = 4>
 __global__ __launch_bounds__(256) void gemm16_persist_kernel(FastGemmParams p, int n_slots) {
   // schedule of k-step 1: the barrier sits before its slot BAR_Q; N1 wave-loads go out after it, one every S1
   // slots, the other 16 - N1 in the next K tile's k-step 0, one every S0 slots from slot 2
@@ -91,7 +94,7 @@ __global__ __launch_bounds__(256) void gemm16_persist_kernel(FastGemmParams p, i
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
   const int l16 = lane & 15, g4 = lane >> 4;
-  const int KT = (int)(p.K / BK);
+  const int KT = RAGGED_K ? (int)((p.K + BK - 1) / BK) : (int)(p.K / BK);
 
   // ---- global -> LDS sources (relative to a tile's buffer resources) ----
   uint32_t a_src[A_LOADS], b_src[B_LOADS];
@@ -111,6 +114,9 @@ __global__ __launch_bounds__(256) void gemm16_persist_kernel(FastGemmParams p, i
       b_src[t] = (uint32_t)(krow * p.ldb * 2 + (((lane % BN_CHUNKS) ^ swz_n16(krow)) << 4));
     }
   }
+  // this lane's chunk of the last K tile lies past K (rows a multiple of 32 apart share their swizzle)
+  const uint32_t tail = RAGGED_K && (((lane & 7) ^ swz(wave * 8 + (lane >> 3))) * 8 >= p.K - (int64_t)(KT - 1) * BK) ? 0xFFFFFFF0u : 0u;
+  auto past_k = [&](int kt) -> uint32_t { return RAGGED_K && kt == KT - 1 ? tail : 0u; };
   const uint32_t b_kstep = B_KMAJOR ? BK * 2 : (uint32_t)(BK * p.ldb * 2);
   const uint32_t smem_lds = (uint32_t)(uintptr_t)smem;
 
@@ -144,11 +150,11 @@ __global__ __launch_bounds__(256) void gemm16_persist_kernel(FastGemmParams p, i
     const int part = g < A_LOADS ? g * NW * 1024 : A_BYTES + (g - A_LOADS) * NW * 1024;  // a constant per wave-load
     asm volatile("s_add_u32 m0, %1, %2" : "={m0}"(m0_token) : "s"(stage_wave), "s"(part) : "scc");
   };
-  auto issue_at_m0 = [&](const TileRef& r, int g, int kt) {
+  auto issue_at_m0 = [&](const TileRef& r, int g, int kt, uint32_t oob) {  // oob: past_k(kt)
     if (g < A_LOADS)
-      asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(a_src[g]), "s"(r.a_rsrc), "s"((uint32_t)kt * (BK * 2)), "{m0}"(m0_token) : "memory");
+      asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(RAGGED_K ? a_src[g] | oob : a_src[g]), "s"(r.a_rsrc), "s"((uint32_t)kt * (BK * 2)), "{m0}"(m0_token) : "memory");
     else
-      asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(b_src[g - A_LOADS]), "s"(r.b_rsrc), "s"((uint32_t)kt * b_kstep), "{m0}"(m0_token) : "memory");
+      asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(RAGGED_K && B_KMAJOR ? b_src[g - A_LOADS] | oob : b_src[g - A_LOADS]), "s"(r.b_rsrc), "s"((uint32_t)kt * b_kstep), "{m0}"(m0_token) : "memory");
   };
 
   // ---- LDS read offsets of the operands (see gemm16_tile) ----
@@ -257,6 +263,7 @@ __global__ __launch_bounds__(256) void gemm16_persist_kernel(FastGemmParams p, i
     const char* cur = smem + sc * STAGE;
     const char* nxt = smem + (sc ^ 1) * STAGE;
     const uint32_t cur_lds = smem_lds + sc * STAGE, nxt_lds = smem_lds + (sc ^ 1) * STAGE;
+    const uint32_t oob1 = past_k(k1), oob2 = past_k(k2);
     __builtin_amdgcn_sched_barrier(0);
     static_for<0, 64>([&](auto slot) {  // k-step 0
       constexpr int q = decltype(slot)::value;
@@ -269,7 +276,7 @@ __global__ __launch_bounds__(256) void gemm16_persist_kernel(FastGemmParams p, i
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b0[j], a[i], acc[i][j], 0, 0, 0);
       }
       pin(acc[i][j]);
-      if (q >= 2 && (q - 2) % S0 == 0 && (q - 2) / S0 < NG - N1) issue_at_m0(ref1, N1 + (q - 2) / S0, k1);
+      if (q >= 2 && (q - 2) % S0 == 0 && (q - 2) / S0 < NG - N1) issue_at_m0(ref1, N1 + (q - 2) / S0, k1, oob1);
       if (j == 0 && i >= 1) a[i - 1] = read_a(cur, 1, i - 1);
       if (j == 4) b1[i] = read_b(cur, 1, i);
       if (CARRY && q < 16) carry_slot(q);
@@ -288,7 +295,7 @@ __global__ __launch_bounds__(256) void gemm16_persist_kernel(FastGemmParams p, i
       acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b1[j], a[i], acc[i][j], 0, 0, 0);
       pin(acc[i][j]);
       if (q >= BAR_Q + 2 && (q - BAR_Q - 2) % S1 == 0 && (q - BAR_Q - 2) / S1 < N1)
-        issue_at_m0(ref2, (q - BAR_Q - 2) / S1, k2);
+        issue_at_m0(ref2, (q - BAR_Q - 2) / S1, k2, oob2);
       // operands of the next K tile's k-step 0: A operand i once block row i is done and the barrier is passed
       static_for<0, AEARLY>([&](auto early) {
         constexpr int e = decltype(early)::value;

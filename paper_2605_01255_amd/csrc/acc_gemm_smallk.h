@@ -14,7 +14,9 @@
 // B each) and for tile k + 3 as soon as tile k is consumed, so one latency is exposed at the start and little
 // after it.  The tile is 192 x 192: 16 x 16 = 256 work-groups for a 3072 x 3072 gradient, one round of the chip.
 // Four waves of 96 x 96 = 6 x 6 blocks of the 16x16x32 matrix instruction (144 accumulators per lane); operands
-// of a k-step are read while the previous k-step multiplies.  K % 64 == 0, N % 8 == 0, operands below 4 GiB.
+// of a k-step are read while the previous k-step multiplies.  N % 8 == 0, operands below 4 GiB.  K % 8 == 0: the 16-byte
+// chunks of the last K tile past K are sent out of the buffer's range and read as zero (ranks 8 ... 48 included, which went
+// to the generic kernel before: 3072 x 3072 at r = 32 21.5 us there).
 #pragma once
 #include "acc_gemm16.h"
 
@@ -40,7 +42,7 @@ __global__ __launch_bounds__(256) void gemm16_smallk_kernel(FastGemmParams p) {
   const int wm = wave / WN, wn = wave % WN;
   const int l16 = lane & 15, g4 = lane >> 4;
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
-  const int KT = (int)(p.K / BK);
+  const int KT = (int)((p.K + BK - 1) / BK);
 
   // ---- global -> LDS: wave-load t of wave w fills LDS bytes [(t * NW + w) * 1024, +1024) of the operand tile ----
   const u32x4 a_rsrc = make_rsrc(p.A + m0 * p.lda, ((p.M - m0 - 1) * p.lda + p.K) * 2);
@@ -68,14 +70,17 @@ __global__ __launch_bounds__(256) void gemm16_smallk_kernel(FastGemmParams p) {
   }
   const uint32_t b_kstep = B_KMAJOR ? BK * 2 : (uint32_t)(BK * p.ldb * 2);
   const uint32_t smem_lds = (uint32_t)(uintptr_t)smem;
+  // last K tile: this lane's chunk lies past K (rows 32 apart share their swizzle)
+  const uint32_t tail = ((lane & 7) ^ swz(wave * 8 + (lane >> 3))) * 8 >= p.K - (int64_t)(KT - 1) * BK ? 0xFFFFFFF0u : 0u;
   auto issue_tile = [&](int kt, int stage) {
     const uint32_t st = smem_lds + stage * STAGE;
+    const uint32_t oob = kt == KT - 1 ? tail : 0u;
 #pragma unroll
     for (int g = 0; g < A_LOADS; ++g)
-      buffer_to_lds_b128(a_rsrc, a_src[g], (uint32_t)kt * (BK * 2), st + (g * NW + wave) * 1024);
+      buffer_to_lds_b128(a_rsrc, a_src[g] | oob, (uint32_t)kt * (BK * 2), st + (g * NW + wave) * 1024);
 #pragma unroll
     for (int g = 0; g < B_LOADS; ++g)
-      buffer_to_lds_b128(b_rsrc, b_src[g], (uint32_t)kt * b_kstep, st + A_BYTES + (g * NW + wave) * 1024);
+      buffer_to_lds_b128(b_rsrc, B_KMAJOR ? b_src[g] | oob : b_src[g], (uint32_t)kt * b_kstep, st + A_BYTES + (g * NW + wave) * 1024);
   };
 
   // ---- LDS read offsets of this lane's operands (see gemm16_persist_kernel) ----
