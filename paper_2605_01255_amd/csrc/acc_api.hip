@@ -20,6 +20,7 @@
 #include "acc_sketch.h"
 #include "acc_gemm16.h"
 #include "acc_gemm8.h"
+#include "acc_gemm_f32.h"
 #include "acc_gemm_ring.h"
 #include "acc_gemm_smallk.h"
 
@@ -155,6 +156,71 @@ SketchParams make_sketch_params(const acc_linear_desc* d) {
   return sk;
 }
 
+constexpr int64_t kMaxOperandBytes = 0xFFFFFFFFll;  // buffer resources address 4 GiB
+
+// ---- float32 path ---------------------------------------------------------------------------
+// An operand of the float32 kernel: X[rows, K] with K contiguous (kmajor), or Xt[K, rows] with the rows contiguous.
+struct F32Operand {
+  const float* ptr;
+  int64_t ld;
+  bool kmajor;
+};
+
+bool f32_operand_ok(const F32Operand& x, int64_t rows, int64_t K) {
+  return x.ld % 4 == 0 && aligned16(x.ptr) && (!x.kmajor || K % 4 == 0) &&
+         (x.kmajor ? (rows > 256 ? rows : 256) : K + 32) * x.ld * 4 <= kMaxOperandBytes;
+}
+bool f32_gemm_ok(const F32Operand& a, const F32Operand& b, int64_t M, int64_t N, int64_t K, const void* C, int64_t ldc) {
+  return f32_operand_ok(a, M, K) && f32_operand_ok(b, N, K) && N % 4 == 0 && ldc % 4 == 0 && aligned16(C);
+}
+
+template <int TM, int TN, int NS, typename TC>
+void f32_launch(bool a_kmajor, bool b_kmajor, F32GemmParams& p, int splits, Launcher& L) {
+  const unsigned grid = gemm_ring_plan(p, 32 * TM, 32 * TN);
+  p.tile_blocks = (int)grid;
+  auto go = [&](auto kernel) {
+    L.launch_lds(kernel, dim3(grid * (unsigned)splits), dim3(256), (size_t)gemm_f32_lds_bytes<TM, TN, NS>(), p);
+  };
+  if (a_kmajor && b_kmajor) go(gemm_f32_kernel<TM, TN, NS, true, true, TC>);
+  else if (a_kmajor) go(gemm_f32_kernel<TM, TN, NS, true, false, TC>);
+  else if constexpr (sizeof(TC) == 4) {  // a transposed left operand only feeds float32 results
+    if (b_kmajor) go(gemm_f32_kernel<TM, TN, NS, false, true, TC>);
+    else go(gemm_f32_kernel<TM, TN, NS, false, false, TC>);
+  } else L.err = hipErrorInvalidValue;
+}
+
+// C[M, N] (op)= A . B, f32_gemm_ok; `splits` > 1 writes partial products c_split_stride apart.
+template <typename TC>
+void f32_gemm(const F32Operand& a, const F32Operand& b, void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, Launcher& L,
+              bool accumulate = false, float alpha = 1.f, float beta = 1.f, int64_t k_per_split = 0,
+              int64_t c_split_stride = 0) {
+  F32GemmParams p{};
+  p.A = a.ptr; p.B = b.ptr; p.C = C;
+  p.M = M; p.N = N; p.K = K; p.lda = a.ld; p.ldb = b.ld; p.ldc = ldc;
+  p.accumulate = accumulate ? 1 : 0; p.alpha = alpha; p.beta = beta;
+  p.k_per_split = k_per_split ? k_per_split : round_up(K, 32);
+  p.c_split_stride = c_split_stride;
+  const int splits = (int)ceil_div(K, p.k_per_split);
+  // The tile with the least estimate, rounds of 256 compute units x K tiles x time of a K tile in ns.  The matrix pipe
+  // bounds all of them, so the estimates follow the area, and a small tile only loses by its operands' latency; what decides
+  // is how much of the last round is empty.  Measured us, 128 x 64 / 64 x 64 / 64 x 32 / 32 x 32 [generic kernel]:
+  //   2048 x 2048 x 1024  64 /  66 /  79 /  79 [188]      2048 x 1024 x 2048  67 / 66 / 105 /  80 [347]
+  //   300 x 4096 x 2048   66 /  66 /  57 /  76            256 x 512 x 256   11.5 / 7.6 / 5.7 / 4.6 [22]
+  struct Cost { int bm, bn, per_k, alone_per_k; };
+  static const Cost costs[] = {{128, 64, 960, 1000}, {64, 64, 520, 560}, {64, 32, 320, 330}, {32, 32, 165, 210}};
+  int best = 0;
+  int64_t best_ns = INT64_MAX;
+  for (int i = 0; i < 4; ++i) {
+    const int64_t rounds = ceil_div(ceil_div(M, costs[i].bm) * ceil_div(N, costs[i].bn) * splits, 256);
+    const int64_t ns = rounds == 1 ? costs[i].alone_per_k : rounds * costs[i].per_k;
+    if (ns < best_ns) { best_ns = ns; best = i; }
+  }
+  if (best == 0) f32_launch<4, 2, 3, TC>(a.kmajor, b.kmajor, p, splits, L);
+  else if (best == 1) f32_launch<2, 2, 4, TC>(a.kmajor, b.kmajor, p, splits, L);
+  else if (best == 2) f32_launch<2, 1, 4, TC>(a.kmajor, b.kmajor, p, splits, L);
+  else f32_launch<1, 1, 4, TC>(a.kmajor, b.kmajor, p, splits, L);
+}
+
 // ---- generic path --------------------------------------------------------------------------
 // Token splits of the sketch contraction: enough work-groups to fill 256 CUs, at most 32 partials.
 int generic_sketch_splits(int64_t n, int64_t c, int64_t r) {
@@ -169,6 +235,15 @@ int generic_sketch_splits(int64_t n, int64_t c, int64_t r) {
 
 template <typename TA, typename TB, typename TC, typename CT, bool SK, bool ACCURATE>
 void launch_generic(const GemmParams& p, int splits, Launcher& L) {
+  if constexpr (sizeof(TA) == 4 && sizeof(TB) == 4 && !SK) {  // two float32 operands: the tuned kernel where strides allow
+    const bool a_k = p.a_sk == 1, b_k = p.b_sk == 1;
+    const F32Operand a{(const float*)p.A, a_k ? p.a_sm : p.a_sk, a_k}, b{(const float*)p.B, b_k ? p.b_sn : p.b_sk, b_k};
+    if ((a_k || p.a_sm == 1) && (b_k || p.b_sn == 1) && p.c_sn == 1 && (a_k || sizeof(TC) == 4) &&
+        f32_gemm_ok(a, b, p.M, p.N, p.K, p.C, p.c_sm)) {
+      f32_gemm<TC>(a, b, p.C, p.c_sm, p.M, p.N, p.K, L, p.accumulate != 0, p.alpha, p.beta, p.k_per_split, p.c_split_stride);
+      return;
+    }
+  }
   dim3 grid((unsigned)ceil_div(p.M, 64), (unsigned)ceil_div(p.N, 64), (unsigned)splits);
   L(gemm_generic_kernel<TA, TB, TC, CT, SK, ACCURATE>, grid, dim3(256), p);
 }
@@ -177,6 +252,44 @@ void launch_generic(const GemmParams& p, int splits, Launcher& L) {
 void generic_gemm_io(int32_t dt, const GemmParams& p, Launcher& L) {
   if (dt == ACC_BF16) launch_generic<bf16, bf16, bf16, bf16, false, false>(p, 1, L);
   else launch_generic<float, float, float, float, false, true>(p, 1, L);
+}
+
+template <typename T>
+void launch_reduce(const float* part, int G, int64_t count, void* out, int64_t row, int64_t ld, Launcher& L) {
+  L(reduce_partials_kernel<T>, dim3((unsigned)ceil_div(count, 1024)), dim3(256), part, G, count, count, (T*)out, row, ld);
+}
+
+// Sketch of a float32 layer with S written out once, into the part of the workspace that the partial products leave free:
+// the libm-grade generator then runs once per entry of S instead of once per entry and 64 channels.  Token splits: enough work-groups to fill the chip as far
+// as that room goes (the workspace's size is that of generic_sketch); one split writes a float32 factor directly.
+// Returns false when S does not fit (few channels) or the kernel does not take the operands.
+bool f32_sketch(const acc_linear_desc* d, const void* A, int64_t lda, int64_t channels, int64_t n, bool transposed,
+                void* out, int64_t out_ld, float* ws, Launcher& L) {
+  const int64_t r = d->r, count = channels * r, room = generic_sketch_splits(n, channels, r) * count, s_size = n * r;
+  if (s_size > room) return false;
+  const bool direct = d->factor_dtype == ACC_F32;
+  int64_t G = ceil_div(256, ceil_div(channels, 32) * ceil_div(r, 32));
+  if (G > ceil_div(n, 256)) G = ceil_div(n, 256);
+  if (G > (room - s_size) / count) G = (room - s_size) / count;
+  if (G < 1) {
+    if (!direct) return false;
+    G = 1;
+  }
+  const int64_t k_per_split = round_up(ceil_div(n, G), 32);
+  G = ceil_div(n, k_per_split);
+  const F32Operand x{(const float*)A, lda, false}, sm{ws, r, false};
+  float* part = ws + s_size;   // n r floats: r % 8 == 0 keeps the alignment
+  float* dst = G == 1 && direct ? (float*)out : part;
+  const int64_t M = transposed ? r : channels, N = transposed ? channels : r;
+  const int64_t ldc = dst == part ? N : out_ld;
+  if (!f32_gemm_ok(transposed ? sm : x, transposed ? x : sm, M, N, n, dst, ldc)) return false;
+  L(sketch_matrix_kernel, dim3((unsigned)ceil_div(ceil_div(n, 4) * r, 256)), dim3(256), make_sketch_params(d), n, r, ws);
+  f32_gemm<float>(transposed ? sm : x, transposed ? x : sm, dst, ldc, M, N, n, L, false, 1.f, 1.f, k_per_split, count);
+  if (dst == part) {
+    if (direct) launch_reduce<float>(part, (int)G, count, out, N, out_ld, L);
+    else launch_reduce<bf16>(part, (int)G, count, out, N, out_ld, L);
+  }
+  return true;
 }
 
 // partial[g][...] = A^T-slab . S-slab, fp32, then K4 reduce into `out` (factor dtype).
@@ -235,8 +348,6 @@ void generic_dw(const acc_linear_desc* d, const Shape& s, const void* Xs, const 
 }
 
 // ---- tuned bf16 path ------------------------------------------------------------------------
-constexpr int64_t kMaxOperandBytes = 0xFFFFFFFFll;  // buffer resources address 4 GiB
-
 // C[M, N] = A[M, K] . B with the tuned kernels; B is [N, K] (KMAJ) or [K, N].
 bool fast_gemm_ok(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
   return K % 8 == 0 && N % 8 == 0 && M * lda * 2 <= kMaxOperandBytes &&
@@ -524,6 +635,7 @@ void run_sketch(const acc_linear_desc* d, const void* A, int64_t lda, int64_t ch
                 bool transposed, void* out, int64_t ldf, float* ws, Launcher& L, ReduceJob* defer = nullptr) {
   const SketchPlan sp = plan_sketch(d, n, channels, lda);
   const int64_t row = transposed ? channels : d->r, ld = transposed ? channels : ldf;
+  if (d->io_dtype == ACC_F32 && f32_sketch(d, A, lda, channels, n, transposed, out, ld, ws, L)) return;
   if (sp.fast) fast_sketch(d, sp, A, lda, channels, n, transposed, out, row, ld, ws, L, defer);
   else if (transposed) generic_sketch(d, A, lda, channels, n, 1, channels, out, row, ld, ws, L);
   else generic_sketch(d, A, lda, channels, n, d->r, 1, out, row, ld, ws, L);

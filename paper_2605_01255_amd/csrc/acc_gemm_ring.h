@@ -31,7 +31,7 @@ template <int BN> __device__ __forceinline__ int swz_ring(int krow) {
 
 // Tile number -> tile: XCD x (work-groups are dealt round-robin) owns a contiguous run of tile numbers, and consecutive
 // numbers walk down super_m tile rows before they move one column on, so that a run is a compact block of the output.
-__device__ __forceinline__ bool ring_tile(const FastGemmParams& p, int b, int& tm, int& tn) {
+template <typename P> __device__ __forceinline__ bool ring_tile(const P& p, int b, int& tm, int& tn) {
   const int total = p.tiles_m * p.tiles_n, per = (total + 7) >> 3;
   const int id = (b & 7) * per + (b >> 3);
   if ((b >> 3) >= per || id >= total) return false;
@@ -263,7 +263,7 @@ constexpr int gemm_ring_lds_bytes() {
 }
 
 // Fill the tiling fields of p for the ring kernel's BM x BN tile; returns the 1-D grid size.
-static inline unsigned gemm_ring_plan(FastGemmParams& p, int BM, int BN) {
+template <typename P> static inline unsigned gemm_ring_plan(P& p, int BM, int BN) {
   p.tiles_m = (int)ceil_div(p.M, BM);
   p.tiles_n = (int)ceil_div(p.N, BN);
   const int64_t total = (int64_t)p.tiles_m * p.tiles_n, per = ceil_div(total, 8);
