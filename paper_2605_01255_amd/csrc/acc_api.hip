@@ -644,7 +644,8 @@ void run_sketch(const acc_linear_desc* d, const void* A, int64_t lda, int64_t ch
 // ---- RSVD compressor ------------------------------------------------------------------------
 // Forward chain: Yr = X.Omega -> Cholesky QR twice -> U -> V = X^T.U; every product on the generic MFMA
 // kernel (fp32 matrix instructions wherever an fp32 operand is involved), K-splits reduced by K4.
-constexpr size_t kCholImageBytes = (size_t)(kRsvdMaxRank * kRsvdMaxRank + 2 * kRsvdMaxRank) * 4;  // chol_factor_kernel's output
+constexpr int64_t kQrSmallRank = 64;     // up to here a pass needs little scratch: 256 Gram partials and the image
+constexpr size_t kQrImageRoom = (size_t)(64 * 64 + 2 * 64) * 4;
 struct RsvdPlan {
   bool tuned;   // bf16 inputs and factors, sizes the tuned GEMM kernel takes: skinny products via split K
   int g_gram;   // token splits of the k x k Gram products
@@ -655,22 +656,22 @@ struct RsvdPlan {
   size_t off_rt;  // ranks above 64: the transposed triangular factor [k, k] of the blocked Cholesky
 };
 
-// Scratch of one Cholesky-QR pass at rank k.  Up to 64 the k x k factorisation is one launch on one wave; above it
-// runs blocked on 64 x 64 diagonal blocks and needs the full Gram matrix, the transposed factor and one triangular
-// image per block.
+// Scratch of one Cholesky-QR pass at rank k: Gram partials, their sum, and the triangular factor's image.  Above 64 the
+// image of one factorisation (up to rank 256) lies in `rt`; above 256, where rt holds the transposed factor of the blocked
+// form, the images lie where the Gram partials were, and rinv holds the matrix's largest diagonal entry.
 constexpr int kGramSplitsBlocked = 16;
 struct QrScratch { size_t gram_part, gram, rinv, rt; };
 template <typename Take>
 QrScratch take_qr_scratch(int64_t k, int g_gram, Take& take) {
   QrScratch q{};
-  if (k <= kRsvdMaxRank) {
+  if (k <= kQrSmallRank) {
     q.gram_part = take((size_t)g_gram * k * k * 4);
     q.gram = take((size_t)k * k * 4);
-    q.rinv = take(kCholImageBytes);
+    q.rinv = take(kQrImageRoom);
   } else {
     q.gram_part = take((size_t)kGramSplitsBlocked * k * k * 4);
     q.gram = take((size_t)k * k * 4);
-    q.rinv = take(kCholImageBytes * (size_t)ceil_div(k, kRsvdMaxRank) + 256);  // + the matrix's largest diagonal entry
+    q.rinv = take(kQrImageRoom * (size_t)ceil_div(k, kQrSmallRank) + 256);
     q.rt = take((size_t)k * k * 4);
   }
   return q;
@@ -743,44 +744,77 @@ void reduce_to(int out_dt, const float* part, int G, int64_t count, void* out, L
     L(reduce_partials_kernel<float>, dim3(blocks), dim3(256), part, G, count, count, (float*)out, count, count);
 }
 
-// The same pass for ranks above 64 (up to 512), built from the rank-64 kernels: blocked right-looking Cholesky of
-// the Gram matrix (diagonal block -> chol_factor_kernel<64>; the block column below it -> tall_solve_kernel<64>,
-// which gives the transposed row panel of R; trailing update on the generic GEMM), then Q = Yin . R^-1 block column
-// by block column (Y_j -= Q_{<j} . R_{<j, j} on the generic GEMM, Q_j = Y_j . R_jj^-1 by tall_solve_kernel<64>).
-// Yin is used as scratch: its columns are overwritten.  Q goes to Qf (fp32; Yin itself when Qf is null), Qt, Ut as
-// in cholesky_qr_pass.
+// Gram = Yin^T . Yin [k, k] into the pass's gram buffer: the row range split, the partials added in order.
+void gram_matrix(const RsvdPlan& pl, char* ws, int64_t m, int64_t k, const float* Yin, Launcher& L) {
+  float* gram_part = (float*)(ws + pl.off_gram_part);
+  float* gram = (float*)(ws + pl.off_gram);
+  const int64_t tiles = ceil_div(k, 32) * ceil_div(k, 32);
+  int64_t splits = 512 / tiles;   // at least 256 rows each, two work-groups per compute unit
+  const int64_t most = k <= kQrSmallRank ? pl.g_gram : kGramSplitsBlocked;
+  if (splits > most) splits = most;
+  if (splits > ceil_div(m, 256)) splits = ceil_div(m, 256);
+  if (splits < 1) splits = 1;
+  GemmParams g{};
+  g.A = Yin; g.B = Yin; g.C = gram_part;
+  g.M = k; g.N = k; g.K = m;
+  g.a_sm = 1; g.a_sk = k; g.b_sk = k; g.b_sn = 1; g.c_sm = k; g.c_sn = 1;
+  g.k_per_split = round_up(ceil_div(m, splits), 32);
+  g.c_split_stride = k * k;
+  splits = ceil_div(m, g.k_per_split);
+  if (splits == 1) g.C = gram;
+  launch_generic<float, float, float, float, false, true>(g, (int)splits, L);
+  if (splits > 1)
+    L(sum_parts_kernel, dim3((unsigned)ceil_div(k * k, 64)), dim3(1024), (const float*)gram_part, (int)splits, k * k, gram);
+}
+
+// Image of the triangular factor of G [w, w] (row stride ldg), w <= 256.
+void chol_factor(const float* G, int64_t ldg, int64_t w, float* image, const float* scale_ref, float rel_tol, Launcher& L) {
+  // above 128 always the most it can need: a kernel's LDS limit is raised once, to what its first launch asks for
+  L.launch_lds(chol_factor_kernel, dim3(1), dim3(kCholThreads), (size_t)chol_lds_bytes(w > 128 ? kQrMaxRank : (int)w), G, image,
+               (int)w, ldg, scale_ref, rel_tol);
+}
+
+// Q = Y . R^-1 (see chol_solve_kernel), Y [m, w] with row stride ldy, w <= 256.
+template <typename TU>
+void chol_solve(const float* Y, int64_t m, int64_t w, const float* image, float* Qf, void* Qt, bf16* Ut, int64_t ldt,
+                int64_t rows_out, bool hilo, int64_t ldy, int64_t ldq, int64_t lo_rows, Launcher& L) {
+  // four waves (64 rows) share an image; fewer where that leaves compute units idle (3072 rows of a projector), eight where
+  // the image is most of a compute unit's LDS
+  const int64_t waves = w > 128 ? 8 : (rows_out >= 64 * 256 ? 4 : (rows_out >= 32 * 256 ? 2 : 1));
+  const dim3 grid((unsigned)ceil_div(rows_out, 16 * waves)), block((unsigned)(64 * waves));
+  const size_t lds = (size_t)tri_block(w > 128 ? kQrMaxRank / 16 : (int)ceil_div(w, 16), 0) * 1024;  // see chol_factor
+  auto go = [&](auto kernel) {
+    L.launch_lds(kernel, grid, block, lds, Y, m, (int)w, image, Qf, (TU*)Qt, Ut, ldt, rows_out, hilo ? 1 : 0, ldy, ldq, (int)lo_rows);
+  };
+  if (w <= 64) go(chol_solve_kernel<4, TU>);
+  else if (w <= 128) go(chol_solve_kernel<8, TU>);
+  else go(chol_solve_kernel<16, TU>);
+}
+
+// The same pass for ranks above 256 (up to 512): blocked right-looking Cholesky of the Gram matrix on 256 x 256 diagonal
+// blocks (diagonal block -> chol_factor; the block column below it -> chol_solve, which gives the transposed row panel of
+// R; trailing update on the float32 GEMM), then Q = Yin . R^-1 block column by block column (Y_j -= Q_{<j} . R_{<j, j} on
+// the float32 GEMM, Q_j = Y_j . R_jj^-1 by chol_solve).  Yin is used as scratch: its columns are overwritten.  Q goes to Qf
+// (fp32; Yin itself when Qf is null), Qt, Ut as in cholesky_qr_pass.
 void cholesky_qr_pass_blocked(const Shape& s, const RsvdPlan& pl, char* ws, int64_t m, int64_t m_pad, float* Yin,
                               float* Qf, void* Qt, int qt_dt, bf16* Ut, int64_t ldt, bool hilo, Launcher& L) {
   const int64_t k = s.r;
-  float* gram_part = (float*)(ws + pl.off_gram_part);
   float* gram = (float*)(ws + pl.off_gram);
   float* rt = (float*)(ws + pl.off_rt);
+  float* scale_ref = (float*)(ws + pl.off_rinv);
   float* W = Qf ? Qf : Yin;
-  const int nb = (int)ceil_div(k, kRsvdMaxRank);
-  auto rimg = [&](int j) { return (float*)(ws + pl.off_rinv + (size_t)j * kCholImageBytes); };
-  float* scale_ref = rimg(nb);  // behind the last image
-  {  // Gram = Yin^T . Yin, the row range split, partials folded in a fixed order
-    GemmParams g{};
-    g.A = Yin; g.B = Yin; g.C = gram_part;
-    g.M = k; g.N = k; g.K = m;
-    g.a_sm = 1; g.a_sk = k; g.b_sk = k; g.b_sn = 1; g.c_sm = k; g.c_sn = 1;
-    g.k_per_split = round_up(ceil_div(m, kGramSplitsBlocked), 32);
-    g.c_split_stride = k * k;
-    const int splits = (int)ceil_div(m, g.k_per_split);
-    launch_generic<float, float, float, float, false, true>(g, splits, L);
-    L(sum_parts_kernel, dim3((unsigned)ceil_div(k * k, 64)), dim3(1024), (const float*)gram_part, splits, k * k, gram);
-    L(diag_max_kernel, dim3(1), dim3(64), (const float*)gram, (int)k, k, scale_ref);
-  }
+  const int nb = (int)ceil_div(k, kQrMaxRank);
+  auto image = [&](int j) { return (float*)(ws + pl.off_gram_part) + (int64_t)j * tri_block(kQrMaxRank / 16, 0) * 256; };
+  gram_matrix(pl, ws, m, k, Yin, L);
+  L(diag_max_kernel, dim3(1), dim3(64), (const float*)gram, (int)k, k, scale_ref);
   for (int j = 0; j < nb; ++j) {
-    const int64_t jb = (int64_t)j * kRsvdMaxRank;
-    const int64_t w = k - jb < kRsvdMaxRank ? k - jb : kRsvdMaxRank, rest = k - jb - w;
-    L(chol_factor_kernel<64>, dim3(1), dim3(64), (const float*)(gram + jb * k + jb), rimg(j), (int)w, k,
-      (const float*)scale_ref, (float)k * 1.1920929e-7f);
+    const int64_t jb = (int64_t)j * kQrMaxRank;
+    const int64_t w = k - jb < kQrMaxRank ? k - jb : kQrMaxRank, rest = k - jb - w;
+    chol_factor(gram + jb * k + jb, k, w, image(j), scale_ref, (float)k * 1.1920929e-7f, L);
     if (rest == 0) break;
     // Rt[rows below, block column j] = G[rows below, block column j] . R_jj^-1  (= the row panel of R, transposed)
-    L(tall_solve_kernel<64, float>, dim3((unsigned)ceil_div(rest, 64)), dim3(64), (const float*)(gram + (jb + w) * k + jb),
-      rest, (int)w, (const float*)rimg(j), rt + (jb + w) * k + jb, (float*)nullptr, (bf16*)nullptr, (int64_t)0, rest, 0, k,
-      k, 0);
+    chol_solve<float>(gram + (jb + w) * k + jb, rest, w, image(j), rt + (jb + w) * k + jb, nullptr, nullptr, 0, rest, false, k, k,
+                      0, L);
     GemmParams u{};  // trailing block -= panel^T . panel, both triangles (the panels below read the lower one)
     u.A = rt + (jb + w) * k + jb; u.B = u.A; u.C = gram + (jb + w) * k + (jb + w);
     u.M = rest; u.N = rest; u.K = w;
@@ -790,10 +824,9 @@ void cholesky_qr_pass_blocked(const Shape& s, const RsvdPlan& pl, char* ws, int6
     launch_generic<float, float, float, float, false, true>(u, 1, L);
   }
   const int64_t rows_out = Ut ? m_pad : m;
-  const int hl = hilo ? 1 : 0;
   for (int j = 0; j < nb; ++j) {
-    const int64_t jb = (int64_t)j * kRsvdMaxRank;
-    const int64_t w = k - jb < kRsvdMaxRank ? k - jb : kRsvdMaxRank;
+    const int64_t jb = (int64_t)j * kQrMaxRank;
+    const int64_t w = k - jb < kQrMaxRank ? k - jb : kQrMaxRank;
     if (j > 0) {  // Y_j -= Q_{<j} . R_{<j, j};  R[t][jb + c] = Rt[(jb + c) * k + t]
       GemmParams u{};
       u.A = W; u.B = rt + jb * k; u.C = Yin + jb;
@@ -803,54 +836,32 @@ void cholesky_qr_pass_blocked(const Shape& s, const RsvdPlan& pl, char* ws, int6
       u.accumulate = 1; u.alpha = -1.f; u.beta = 1.f;
       launch_generic<float, float, float, float, false, true>(u, 1, L);
     }
-    const dim3 grid((unsigned)ceil_div(rows_out, 64));
     bf16* ut_j = Ut ? Ut + jb * ldt : nullptr;
     if (qt_dt == ACC_BF16)
-      L(tall_solve_kernel<64, bf16>, grid, dim3(64), (const float*)(Yin + jb), m, (int)w, (const float*)rimg(j), W + jb,
-        Qt ? (bf16*)Qt + jb : (bf16*)nullptr, ut_j, ldt, rows_out, hl, k, k, (int)k);
+      chol_solve<bf16>(Yin + jb, m, w, image(j), W + jb, Qt ? (bf16*)Qt + jb : nullptr, ut_j, ldt, rows_out, hilo, k, k, k, L);
     else
-      L(tall_solve_kernel<64, float>, grid, dim3(64), (const float*)(Yin + jb), m, (int)w, (const float*)rimg(j), W + jb,
-        Qt ? (float*)Qt + jb : (float*)nullptr, ut_j, ldt, rows_out, hl, k, k, (int)k);
+      chol_solve<float>(Yin + jb, m, w, image(j), W + jb, Qt ? (float*)Qt + jb : nullptr, ut_j, ldt, rows_out, hilo, k, k, k, L);
   }
 }
 
 // One Cholesky-QR pass on a tall matrix Yin [m, k] fp32: Q = Yin . R^-1 with Yin^T.Yin = R^T.R.  Q goes to any
 // of: Qf (fp32 [m, k]), Qt (factor dtype [m, k]), Ut (bf16 [k, ldt] zero-padded transpose up to column
-// m_pad; [2k, ldt] hi / lo parts with `hilo`).  Ranks above 64 take the blocked form, which overwrites Yin.
+// m_pad; [2k, ldt] hi / lo parts with `hilo`).  Ranks above 256 take the blocked form, which overwrites Yin.
+// A pivot counts as zero at 1e-6 of the largest diagonal entry up to rank 64, above at the rank times 2^-23 of it (the
+// size of the rounding noise that `rank` elimination steps leave on an exactly dependent column).
 void cholesky_qr_pass(const Shape& s, const RsvdPlan& pl, char* ws, int64_t m, int64_t m_pad, float* Yin,
                       float* Qf, void* Qt, int qt_dt, bf16* Ut, int64_t ldt, bool hilo, Launcher& L) {
   const int64_t k = s.r;
-  if (k > kRsvdMaxRank) {
+  if (k > kQrMaxRank) {
     cholesky_qr_pass_blocked(s, pl, ws, m, m_pad, Yin, Qf, Qt, qt_dt, Ut, ldt, hilo, L);
     return;
   }
-  float* gram_part = (float*)(ws + pl.off_gram_part);
-  float* rinv = (float*)(ws + pl.off_rinv);
-  float* gram = (float*)(ws + pl.off_gram);
-  const int rows = (int)round_up(ceil_div(m, pl.g_gram), 64);
-  const int parts = (int)ceil_div(m, rows);
-  L(gram_partial_kernel, dim3((unsigned)parts), dim3(256), (const float*)Yin, m, (int)k, rows, gram_part);
-  L(sum_parts_kernel, dim3((unsigned)ceil_div(k * k, 64)), dim3(1024), (const float*)gram_part, parts, k * k, gram);
-  if (k <= 32) L(chol_factor_kernel<32>, dim3(1), dim3(64), (const float*)gram, rinv, (int)k, k, (const float*)nullptr, 1e-6f);
-  else L(chol_factor_kernel<64>, dim3(1), dim3(64), (const float*)gram, rinv, (int)k, k, (const float*)nullptr, 1e-6f);
+  float* image = (float*)(ws + (k <= kQrSmallRank ? pl.off_rinv : pl.off_rt));
+  gram_matrix(pl, ws, m, k, Yin, L);
+  chol_factor((const float*)(ws + pl.off_gram), k, k, image, nullptr, k <= kQrSmallRank ? 1e-6f : (float)k * 1.1920929e-7f, L);
   const int64_t rows_out = Ut ? m_pad : m;
-  const dim3 grid((unsigned)ceil_div(rows_out, 64));
-  const int hl = hilo ? 1 : 0;
-  if (k <= 32) {
-    if (qt_dt == ACC_BF16)
-      L(tall_solve_kernel<32, bf16>, grid, dim3(64), (const float*)Yin, m, (int)k, (const float*)rinv, Qf,
-        (bf16*)Qt, Ut, ldt, rows_out, hl, k, k, (int)k);
-    else
-      L(tall_solve_kernel<32, float>, grid, dim3(64), (const float*)Yin, m, (int)k, (const float*)rinv, Qf,
-        (float*)Qt, Ut, ldt, rows_out, hl, k, k, (int)k);
-  } else {
-    if (qt_dt == ACC_BF16)
-      L(tall_solve_kernel<64, bf16>, grid, dim3(64), (const float*)Yin, m, (int)k, (const float*)rinv, Qf,
-        (bf16*)Qt, Ut, ldt, rows_out, hl, k, k, (int)k);
-    else
-      L(tall_solve_kernel<64, float>, grid, dim3(64), (const float*)Yin, m, (int)k, (const float*)rinv, Qf,
-        (float*)Qt, Ut, ldt, rows_out, hl, k, k, (int)k);
-  }
+  if (qt_dt == ACC_BF16) chol_solve<bf16>(Yin, m, k, image, Qf, Qt, Ut, ldt, rows_out, hilo, k, k, k, L);
+  else chol_solve<float>(Yin, m, k, image, Qf, Qt, Ut, ldt, rows_out, hilo, k, k, k, L);
 }
 
 // out[channels, k] (or its transpose) = A^T . U over the token axis, A [n, lda]; splits reduced by K4.

@@ -4,116 +4,278 @@
 // GEMM kernels.
 #pragma once
 #include "acc_common.h"
+#include "acc_gemm.h"
 #include "acc_rng.h"
 
 namespace acc {
 
-constexpr int kRsvdMaxRank = 64;   // a k x k factorisation of this size runs on one wave, one matrix row per lane
-constexpr int kRsvdMaxRankBlocked = 512;  // larger ranks: the same kernels on 64 x 64 diagonal blocks (blocked Cholesky)
+constexpr int kQrMaxRank = 256;            // a k x k factorisation up to this size is one launch of one work-group
+constexpr int kRsvdMaxRankBlocked = 512;   // larger ranks: the same kernels on 256 x 256 diagonal blocks (blocked Cholesky)
+constexpr int kCholThreads = 512;
+
+// Storage of a k x k triangle for the two kernels below: 16 x 16 blocks (i, l), i >= l, of 1 KB, row by row; block (i, l)
+// at index i (i + 1) / 2 + l.  A lane that owns row l16 and columns 4 g4 .. 4 g4 + 3 of a block (the accumulator layout of
+// the 16x16x4 instruction with its operands swapped, and the layout of its operands when instruction t of four takes
+// element t) reads 16 bytes at 64 l16 + 16 g4: a wave reads a whole block contiguously.
+__host__ __device__ constexpr int tri_block(int i, int l) { return i * (i + 1) / 2 + l; }
+
+struct TriIndex { int i, l; };
+// block b -> (i, l), wave-uniform; b < 2^15
+__device__ __forceinline__ TriIndex tri_index(int b) {
+  int i = __builtin_amdgcn_readfirstlane((int)((__builtin_amdgcn_sqrtf(8.f * (float)b + 1.f) - 1.f) * 0.5f));
+  i += tri_block(i + 1, 0) <= b ? 1 : 0;   // the root may be off by a rounding either way
+  i -= tri_block(i, 0) > b ? 1 : 0;
+  return TriIndex{i, b - tri_block(i, 0)};
+}
 
 __device__ __forceinline__ float lane_bcast(float v, int src_lane) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), src_lane));
 }
 
-// G [k, k] (symmetric positive semi-definite, fp32) -> the upper triangular factor R of G = R^T R with positive
-// diagonal, for k <= K (K = 32 or 64), by ONE wave: lane i holds row i of the symmetric matrix (padded to K
-// with the identity) in registers; at each step the pivot row goes through LDS to all lanes (same-address reads
-// broadcast; v_readlane broadcasts of the same values measured 20 % slower).  The elimination is done in the
-// square-root-free form (A = L D L^T: one reciprocal per step on the critical path, no square root), eight
-// steps per trip of a rolled loop: after each trip the eight finished rows go to LDS and every lane's registers
-// move down by eight columns, so register indices stay compile-time constants while the loop body stays small.
-// Work done on columns that are already eliminated is harmless: those registers are never read again.  The k
-// steps are a serial chain (LDS round trip, reciprocal, K multiply-adds): 11.9 us at K = 32, 38 us at K = 64.
-// Output, in the form tall_solve_kernel copies to its LDS: Rimg [K * K + 2 K] floats, Rimg[t * K + c] = R[t][c]
-// for t < c < k and zero elsewhere up to index K * K + K, then 1 / R[c][c] for c < k (zero for c >= k).  A pivot
-// that is not positive beyond rounding (column j of the factored matrix depends on the earlier ones) is dropped:
-// its reciprocal is stored as 0 and row j of R is zero, so the corresponding basis vector comes out as zero and
-// the span of the others is unchanged.
-template <int K>
-__global__ __launch_bounds__(64) void chol_factor_kernel(const float* __restrict__ G, float* __restrict__ Rimg,
-                                                         int k, int64_t ldg, const float* __restrict__ scale_ref,
-                                                         float rel_tol) {
-  // ldg: row stride of G.  scale_ref: when not null, the largest diagonal entry of the WHOLE matrix this block
-  // belongs to (blocked factorisation: a trailing block that is nothing but rounding noise must be measured against
-  // the matrix it came from, not against itself); null: the largest diagonal entry of G itself.  rel_tol: a pivot
-  // at or below rel_tol times that scale counts as zero (1e-6 for one block; the blocked form passes its rank
-  // times 2^-23, the size of the rounding noise that `rank` elimination steps leave on an exactly dependent column).
-  __shared__ float rows[K][K + 1];
-  __shared__ float scale[K];
-  const int lane = threadIdx.x;
-  float a[K];
-  {  // every lane loads from a valid address (clamped), then selects: no branches around the loads
-    const int lr = lane < k ? lane : k - 1;
+// The upper triangular factor R of G = R^T R (G [k, k] symmetric positive semi-definite, fp32, k <= 256, positive diagonal
+// of R) in the form chol_solve_kernel multiplies with, by ONE work-group.  The k steps of an elimination are a serial chain;
+// what a step costs is everything.  Blocked by 16 columns, G in LDS:
+//   panel     every wave eliminates the same 16 x 16 diagonal block in its lanes 0 .. 15 and 48 rows below it in the others
+//             (one row per lane, its 16 panel columns in registers): the pivot row comes by v_readlane, so the 16 steps need
+//             neither LDS nor a barrier, and no wave waits for another
+//   trailing  A_il -= (V_i D^-1) V_l^T on the 16x16x4 instruction, blocks dealt to the waves
+// in the square-root-free form (A = L D L^T, one reciprocal per step on the chain).  Rows of finished panels are never read
+// again above the diagonal, so the elimination runs unmasked.
+// Image (tri_block layout): off-diagonal block (J, I): [n][t] = -R[16 I + t][16 J + n]; diagonal block: the inverse of
+// R_JJ, transposed, [n][t] = (R_JJ^-1)[t][n].
+// A pivot at or below rel_tol times the largest diagonal entry (of G, or *scale_ref: of the matrix G is a block of) counts
+// as zero: column j of the factored matrix depends on the earlier ones.  Its row and column of the image are zero, so the
+// corresponding basis vector comes out as zero and the span of the others is unchanged.
+// Measured at k = 32 / 64 / 128 / 256: 8.7 / 12.7 / 25 / 73 us.  The one-wave elimination this replaced (the pivot row
+// through LDS at every step, one matrix row per lane, 64 columns at most) took 12 / 39 us, and ranks above 64 a chain of
+// three launches per 64 columns: about 115 us at k = 128.
+__global__ __launch_bounds__(kCholThreads) void chol_factor_kernel(const float* __restrict__ G, float* __restrict__ image,
+                                                                   int k, int64_t ldg, const float* __restrict__ scale_ref, float rel_tol) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  constexpr int NW = kCholThreads / 64;
+  float* const A = (float*)smem;                                     // tri_block storage
+  const int nb = (k + 15) / 16;
+  float* const inv = A + tri_block(nb, 0) * 256;                     // 1 / pivot per column, 0 for a dropped one
+  float* const scale = inv + nb * 16;                                // 1 / sqrt(pivot), likewise
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g4 = lane >> 4;
+  auto at = [&](int i, int l) -> f32x4* { return (f32x4*)(A + tri_block(i, l) * 256 + l16 * 16 + g4 * 4); };
+
+  // ---- load: block b of the triangle by wave b mod NW, four requested at a time; rows and columns past k as the identity ----
+  const int blocks = tri_block(nb, 0);
+  for (int b0 = wave; b0 < blocks; b0 += 4 * NW) {
+    f32x4 v[4];
 #pragma unroll
-    for (int c = 0; c < K; ++c) {
-      const float g = G[lr * ldg + (c < k ? c : k - 1)];
-      a[c] = (lane < k && c < k) ? g : (lane == c ? 1.f : 0.f);
+    for (int u = 0; u < 4; ++u) {
+      const int b = b0 + u * NW;
+      if (b < blocks) {
+        const TriIndex x = tri_index(b);
+        const int row = x.i * 16 + l16, col = x.l * 16 + g4 * 4;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[u][t] = row == col + t ? 1.f : 0.f;
+        if (row < k && col < k) v[u] = *(const f32x4*)(G + row * ldg + col);  // k % 4 == 0
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int b = b0 + u * NW;
+      if (b < blocks) *(f32x4*)(A + b * 256 + l16 * 16 + g4 * 4) = v[u];
     }
   }
-  float diag = 0.f;
-#pragma unroll
-  for (int c = 0; c < K; ++c) diag = (c == lane && lane < k) ? a[c] : diag;
+  __syncthreads();
   float maxdiag = 0.f;
+  for (int c = lane; c < k; c += 64) {
+    const float d = A[tri_block(c >> 4, c >> 4) * 256 + (c & 15) * 17];
+    maxdiag = d > maxdiag ? d : maxdiag;
+  }
 #pragma unroll
-  for (int l = 0; l < K; ++l) {
-    const float d = lane_bcast(diag, l);
+  for (int m = 1; m < 64; m <<= 1) {
+    const float d = __shfl_xor(maxdiag, m);
     maxdiag = d > maxdiag ? d : maxdiag;
   }
   const float tol = (scale_ref ? *scale_ref : maxdiag) * rel_tol;
-  float my_piv = 0.f;   // pivot of my row, 0 for a dropped one
-  __shared__ __attribute__((aligned(16))) float bc[2][K];   // the pivot row of a step, for all lanes to read
-#pragma unroll 1
-  for (int jb = 0; jb < K; jb += 8) {
+
+  // Inverse of diagonal block J by lanes 0 .. 15 of one wave: lane n solves R x = e_n from the last row up.
+  // R[j][t] = V[t][j] scale[j] with V the stored lower triangle; a dropped row has scale 0, which makes x[j] zero.
+  auto invert = [&](int J) {
+    const float* V = A + tri_block(J, J) * 256;
+    float x[16];
 #pragma unroll
-    for (int jj = 0; jj < 8; ++jj) {
-      const int j = jb + jj;
-      // lane j publishes its row (columns j .. of the current register window) through LDS: one wave, so LDS
-      // operations complete in order and no hardware barrier is needed; two buffers alternate so that a step's
-      // writes cannot overtake the previous step's reads
-      float* row = bc[jj & 1];
-      if (lane == j) {
+    for (int j = 15; j >= 0; --j) {
+      const float s = scale[J * 16 + j];
+      float sum = 0.f;
 #pragma unroll
-        for (int c = jj & ~3; c < K; c += 4) *(f32x4*)(&row[c]) = f32x4{a[c], a[c + 1], a[c + 2], a[c + 3]};
+      for (int t = j + 1; t < 16; ++t) sum = fmaf(V[t * 16 + j], x[t], sum);
+      x[j] = l16 == j ? s : (l16 > j ? -(s * s) * sum : 0.f);
+    }
+    float* dst = image + tri_block(J, J) * 256 + l16 * 16;
+    if (lane < 16) {
+#pragma unroll
+      for (int c = 0; c < 16; c += 4) *(f32x4*)(dst + c) = f32x4{x[c], x[c + 1], x[c + 2], x[c + 3]};
+    }
+  };
+
+  for (int p = 0; p < nb; ++p) {
+    // ---- panel: lane < 16 row `lane` of the diagonal block, lane >= 16 one of the rows below (at most 240: the last
+    //      waves are free, one of them inverts the block before) ----
+    const int below = (nb - p - 1) * 16;
+    float a[16];
+    if (wave == NW - 1 && p > 0) invert(p - 1);
+    if (wave == 0 || wave * 48 < below) {
+      const int r = lane < 16 ? lane : 16 + wave * 48 + lane - 16;     // row inside the panel
+      const bool real = r < 16 + below;
+      float* row = A + tri_block(p + (r >> 4), p) * 256 + (r & 15) * 16;
+#pragma unroll
+      for (int c = 0; c < 16; c += 4) {
+        const f32x4 v = real ? *(const f32x4*)(row + c) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < 4; ++t) a[c + t] = v[t];
       }
-      // other lanes' writes become visible to this lane's reads only across a fence the compiler honours (without
-      // it the reads are hoisted out of the loop as if no one else wrote); at wavefront scope it costs nothing
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      f32x4 rj[K / 4];
+      float my_inv = 0.f, my_piv = 0.f;
 #pragma unroll
-      for (int c = jj & ~3; c < K; c += 4) rj[c / 4] = *(const f32x4*)(&row[c]);
-      const float piv = rj[jj / 4][jj % 4];
-      const bool dead = !(piv > tol);
-      // reciprocal: hardware estimate + one Newton step (about 1 ulp); the elimination needs no more, the
-      // factor's own scaling below uses exact square roots
-      float inv_p = __builtin_amdgcn_rcpf(piv);
-      inv_p = fmaf(fmaf(-piv, inv_p, 1.f), inv_p, inv_p);
-      inv_p = dead ? 0.f : inv_p;
-      my_piv = lane == j ? (dead ? 0.f : piv) : my_piv;
-      const float t = lane > j ? a[jj] * inv_p : 0.f;
+      for (int j = 0; j < 16; ++j) {
+        const float piv = lane_bcast(a[j], j);
+        const bool dead = !(piv > tol);
+        // reciprocal: hardware estimate + one Newton step (about 1 ulp); the factor's own scaling uses square roots
+        float inv_p = __builtin_amdgcn_rcpf(piv);
+        inv_p = fmaf(fmaf(-piv, inv_p, 1.f), inv_p, inv_p);
+        inv_p = dead ? 0.f : inv_p;
+        my_inv = lane == j ? inv_p : my_inv;
+        my_piv = lane == j && !dead ? piv : my_piv;
+        const float t = a[j] * inv_p;
 #pragma unroll
-      for (int c = jj + 1; c < K; ++c) a[c] = fmaf(-t, rj[c / 4][c % 4], a[c]);
+        for (int c = j + 1; c < 16; ++c) a[c] = fmaf(-t, lane_bcast(a[c], j), a[c]);
+      }
+      if (real && lane >= 16) {
+#pragma unroll
+        for (int c = 0; c < 16; c += 4) *(f32x4*)(row + c) = f32x4{a[c], a[c + 1], a[c + 2], a[c + 3]};
+      }
+      if (wave == 0 && lane < 16) {
+        inv[p * 16 + lane] = my_inv;
+        scale[p * 16 + lane] = my_piv > 0.f ? 1.f / sqrtf(my_piv) : 0.f;
+      }
     }
-    if (lane >= jb && lane < jb + 8) {
+    __syncthreads();
+    if (wave == 0 && lane < 16) {  // only now: until the barrier the other waves were reading the block; all their copies are the same
+      float* row = A + tri_block(p, p) * 256 + lane * 16;
 #pragma unroll
-      for (int c = 0; c < K; ++c)
-        if (jb + c < K) rows[lane][jb + c] = a[c];
+      for (int c = 0; c < 16; c += 4) *(f32x4*)(row + c) = f32x4{a[c], a[c + 1], a[c + 2], a[c + 3]};
     }
+    // ---- trailing blocks (i, l), p < l <= i: rows of V_i against rows of V_l over the panel's 16 columns, two at a time ----
+    {
+      const f32x4 d = *(const f32x4*)(inv + p * 16 + g4 * 4);
+      const int count = (nb - p - 1) * (nb - p) / 2;
+      for (int b0 = wave; b0 < count; b0 += 2 * NW) {
+        f32x4 c[2], vi[2], vl[2];
+        f32x4* dst[2];
 #pragma unroll
-    for (int c = 0; c < K - 8; ++c) a[c] = a[c + 8];
+        for (int u = 0; u < 2; ++u) {
+          const int b = b0 + u * NW;
+          const TriIndex x = tri_index(b < count ? b : b0);
+          const int i = x.i + p + 1, l = x.l + p + 1;
+          vi[u] = *at(i, p); vl[u] = *at(l, p); dst[u] = at(i, l);
+          c[u] = *dst[u];
+        }
 #pragma unroll
-    for (int c = K - 8; c < K; ++c) a[c] = 0.f;
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+            c[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(vl[u][t], -(vi[u][t] * d[t]), c[u], 0, 0, 0);
+        *dst[0] = c[0];
+        if (b0 + NW < count) *dst[1] = c[1];
+      }
+    }
+    __syncthreads();
   }
-  if (lane < K) scale[lane] = (lane < k && my_piv > 0.f) ? 1.f / sqrtf(my_piv) : 0.f;
-  __syncthreads();
+  if (wave == NW - 1) invert(nb - 1);
+
+  // ---- off-diagonal blocks of the image ----
+  for (int b = wave; b < blocks; b += NW) {
+    const TriIndex x = tri_index(b);
+    if (x.l < x.i) {
+      const f32x4 s = *(const f32x4*)(scale + x.l * 16 + g4 * 4);
+      const f32x4 v = *(const f32x4*)(A + b * 256 + l16 * 16 + g4 * 4);
+      *(f32x4*)(image + b * 256 + l16 * 16 + g4 * 4) = f32x4{-(v[0] * s[0]), -(v[1] * s[1]), -(v[2] * s[2]), -(v[3] * s[3])};
+    }
+  }
+}
+
+constexpr int chol_lds_bytes(int k) { return tri_block((k + 15) / 16, 0) * 1024 + (k + 15) / 16 * 16 * 2 * 4; }
+
+// Q = Y . R^-1 for a tall Y [n, k] fp32 by forward substitution over 16-column blocks:
+//   Q_J = (Y_J - sum_{I < J} Q_I R_IJ) R_JJ^-1
+// with the 16 x 16 inverses of chol_factor_kernel's image; every product on the 16x16x4 instruction.  A wave owns 16 rows
+// and keeps all their columns in registers: a finished block sits in the accumulator layout, which is the layout the next
+// products want their left operand in, so nothing moves between lanes.  The image is copied to LDS once per work-group.
+// Replaced one lane per row with the columns in registers and R broadcast from LDS, 64 columns at most (22 us each).
+// Outputs, each optional, rows up to n_rows_out (>= n; rows past n count as zero):
+//   Qf  [n, k] fp32 (may be Y itself: a wave reads its rows before it writes them);  Qt [n, k] in TU (the stored factor);
+//   Ut [k, ldt] bf16, the transpose with its columns n .. n_rows_out - 1 written as zero (K padding of the later products
+//   over tokens); with `hilo` rows lo_rows .. hold the bf16 rounding of what the rounding of Q^T leaves, so that hi + lo
+//   carries Q to about 2^-17 relative through a bf16 matrix product.
+// Work-groups of any number of waves; grid: rows of the launch / 16.  k % 8 == 0, k <= 16 KB.
+template <int KB, typename TU>
+__global__ __launch_bounds__(512) void chol_solve_kernel(const float* __restrict__ Y, int64_t n, int k,
+                                                         const float* __restrict__ image, float* Qf,
+                                                         TU* __restrict__ Qt, bf16* __restrict__ Ut, int64_t ldt,
+                                                         int64_t n_rows_out, int hilo, int64_t ldy, int64_t ldq, int lo_rows) {
+  // ldy: row stride of Y; ldq: row stride of Qf and Qt (a column block of a wider matrix passes the wide stride)
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int nb = (k + 15) / 16, blocks = tri_block(nb, 0);
+  const int tid = threadIdx.x, lane = tid & 63, waves = (int)(blockDim.x >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g4 = lane >> 4;
+  {
+    const u32x4 rsrc = make_rsrc(image, (int64_t)blocks * 1024);
+    const uint32_t smem_lds = (uint32_t)(uintptr_t)smem;
+    for (int b = wave; b < blocks; b += waves) buffer_to_lds_b128(rsrc, (uint32_t)(lane * 16), (uint32_t)(b * 1024), smem_lds + b * 1024);
+  }
+  const int64_t row = ((int64_t)blockIdx.x * waves + wave) * 16 + l16;
+  f32x4 q[KB];
 #pragma unroll
-  for (int i = 0; i < (K * K + 2 * K) / 64; ++i) {
-    const int e = lane + 64 * i, t = e / K, c = e % K;
-    float v = 0.f;
-    if (t < K) v = (t < c && c < k) ? rows[t][c] * scale[t] : 0.f;
-    else if (t == K + 1) v = scale[c];
-    Rimg[e] = v;
+  for (int J = 0; J < KB; ++J) {
+    q[J] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int col = J * 16 + g4 * 4;
+    if (row < n && col < k) q[J] = *(const f32x4*)(Y + row * ldy + col);
+  }
+  wait_vmcnt0();
+  __syncthreads();
+  auto block = [&](int J, int I) -> f32x4 { return *(const f32x4*)(smem + tri_block(J, I) * 1024 + l16 * 64 + g4 * 16); };
+#pragma unroll
+  for (int J = 0; J < KB; ++J) {
+    if (J < nb) {
+      f32x4 c[2] = {q[J], f32x4{0.f, 0.f, 0.f, 0.f}};   // two chains
+#pragma unroll
+      for (int I = 0; I < J; ++I) {
+        const f32x4 r = block(J, I);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) c[I & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(r[t], q[I][t], c[I & 1], 0, 0, 0);
+      }
+      const f32x4 rest = c[0] + c[1], d = block(J, J);
+      f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < 4; ++t) o = __builtin_amdgcn_mfma_f32_16x16x4f32(d[t], rest[t], o, 0, 0, 0);
+      q[J] = o;
+      const int col = J * 16 + g4 * 4;
+      if (col < k) {
+        if (row < n) {
+          if (Qf) *(f32x4*)(Qf + row * ldq + col) = o;
+          if (Qt) {
+            if constexpr (sizeof(TU) == 2) *(bf16x4*)(Qt + row * ldq + col) = bf16x4{(bf16)o[0], (bf16)o[1], (bf16)o[2], (bf16)o[3]};
+            else *(f32x4*)(Qt + row * ldq + col) = o;
+          }
+        }
+        if (Ut && row < n_rows_out) {
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const bf16 hi = row < n ? (bf16)o[t] : (bf16)0.f;
+            Ut[(int64_t)(col + t) * ldt + row] = hi;
+            if (hilo) Ut[(int64_t)(lo_rows + col + t) * ldt + row] = row < n ? (bf16)(o[t] - (float)hi) : (bf16)0.f;
+          }
+        }
+      }
+    }
   }
 }
 
@@ -131,119 +293,6 @@ __global__ __launch_bounds__(64) void diag_max_kernel(const float* __restrict__ 
     if (threadIdx.x == 0 && l > 0) m = d > m ? d : m;
   }
   if (threadIdx.x == 0) out[0] = m;
-}
-
-// Q = Y . R^-1 for a tall Y [n, k] fp32 by forward substitution along each row, q_c = (y_c - sum_{t<c} q_t
-// R[t][c]) / R[c][c]: one row per lane, the row in registers, R read from LDS (all lanes read the same address).
-// No explicit inverse is formed.  Columns are taken eight at a time in a rolled loop: substitution inside the
-// block, then the block's contribution is removed from all later columns and the registers move down by eight,
-// so register indices are compile-time constants and the loop body stays small.  Updates that fall on columns
-// past the end touch registers that are never read.
-// Rimg as written by chol_factor_kernel<K>.  Outputs, each optional, rows up to n_rows_out (>= n; rows past n
-// count as zero):
-//   Qf  [n, k] fp32;  Qt [n, k] in TU (the stored factor);  Ut [k, ldt] bf16, the transpose with its
-//   columns n .. n_rows_out - 1 written as zero (K padding of the later products over tokens); with
-//   `hilo` Ut is [2k, ldt]: rows 0 .. k-1 the bf16 rounding of Q^T, rows k .. 2k-1 the bf16 rounding of
-//   the remainder, so that hi + lo carries Q to about 2^-17 relative through a bf16 matrix product.
-// Grid: ceil(n_rows_out / 64) x 64 threads.  k % 8 == 0, k <= K.
-template <int K, typename TU>
-__global__ __launch_bounds__(64) void tall_solve_kernel(const float* __restrict__ Y, int64_t n, int k,
-                                                        const float* __restrict__ Rimg, float* __restrict__ Qf,
-                                                        TU* __restrict__ Qt, bf16* __restrict__ Ut, int64_t ldt,
-                                                        int64_t n_rows_out, int hilo, int64_t ldy, int64_t ldq,
-                                                        int lo_rows) {
-  // ldy: row stride of Y; ldq: row stride of Qf and Qt (a column block of a wider matrix passes the wide stride);
-  // lo_rows: row of Ut where the lo parts start (the full rank when this call handles one column block)
-  // Rs[t * K + c] = R[t][c] for t < c < k, zero elsewhere; one spare row: the update of the last columns reads
-  // up to K - 9 elements past a row's end
-  __shared__ __attribute__((aligned(16))) float Rs[K * K + 2 * K];
-  const float* Ds = Rs + K * K + K;
-  const int tid = threadIdx.x;
-  {
-    constexpr int V4 = (K * K + 2 * K) / 4, PER = (V4 + 63) / 64;
-    f32x4 tmp[PER];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int e = tid + 64 * i;
-      tmp[i] = *(const f32x4*)(Rimg + 4 * (e < V4 ? e : V4 - 1));
-    }
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int e = tid + 64 * i;
-      if (e < V4) *(f32x4*)(&Rs[4 * e]) = tmp[i];
-    }
-  }
-  const int64_t row = (int64_t)blockIdx.x * 64 + tid;
-  float y[K];
-#pragma unroll
-  for (int c = 0; c < K; c += 4) {
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    if (row < n && c < k) v = *(const f32x4*)(Y + row * ldy + c);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) y[c + t] = v[t];
-  }
-  __syncthreads();
-#pragma unroll 1
-  for (int cb = 0; cb < k; cb += 8) {
-    float q[8];
-#pragma unroll
-    for (int jj = 0; jj < 8; ++jj) {
-      float s = y[jj];
-#pragma unroll
-      for (int t = 0; t < jj; ++t) s = fmaf(-q[t], Rs[(cb + t) * K + cb + jj], s);
-      q[jj] = s * Ds[cb + jj];
-    }
-    // four later columns at a time: their eight R entries each are read one group ahead of the multiplies; the
-    // fences keep the compiler from hoisting every read of the trip to its top (450 registers, spills)
-    f32x4 r[8], rn[8];
-#pragma unroll
-    for (int jj = 0; jj < 8; ++jj) r[jj] = *(const f32x4*)(&Rs[(cb + jj) * K + cb + 8]);
-#pragma unroll
-    for (int c4 = 8; c4 < K; c4 += 4) {
-      if (c4 + 4 < K) {
-#pragma unroll
-        for (int jj = 0; jj < 8; ++jj) rn[jj] = *(const f32x4*)(&Rs[(cb + jj) * K + cb + c4 + 4]);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int jj = 0; jj < 8; ++jj) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) y[c4 + u] = fmaf(-q[jj], r[jj][u], y[c4 + u]);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int jj = 0; jj < 8; ++jj) r[jj] = rn[jj];
-    }
-    if (row < n) {
-      if (Qf) {
-        *(f32x4*)(Qf + row * ldq + cb) = f32x4{q[0], q[1], q[2], q[3]};
-        *(f32x4*)(Qf + row * ldq + cb + 4) = f32x4{q[4], q[5], q[6], q[7]};
-      }
-      if (Qt) {
-        if constexpr (sizeof(TU) == 2) {
-          bf16x8 o;
-#pragma unroll
-          for (int t = 0; t < 8; ++t) o[t] = (bf16)q[t];
-          *(bf16x8*)(Qt + row * ldq + cb) = o;
-        } else {
-          *(f32x4*)(Qt + row * ldq + cb) = f32x4{q[0], q[1], q[2], q[3]};
-          *(f32x4*)(Qt + row * ldq + cb + 4) = f32x4{q[4], q[5], q[6], q[7]};
-        }
-      }
-    }
-    if (Ut && row < n_rows_out) {
-#pragma unroll
-      for (int jj = 0; jj < 8; ++jj) {
-        const bf16 hi = row < n ? (bf16)q[jj] : (bf16)0.f;
-        Ut[(int64_t)(cb + jj) * ldt + row] = hi;
-        if (hilo) Ut[(int64_t)(lo_rows + cb + jj) * ldt + row] = row < n ? (bf16)(q[jj] - (float)hi) : (bf16)0.f;
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < K - 8; ++c) y[c] = y[c + 8];
-#pragma unroll
-    for (int c = K - 8; c < K; ++c) y[c] = 0.f;
-  }
 }
 
 // out[e] = sum over p of part[p * E + e], p in order within fixed groups: a work-group owns 64 elements, its
@@ -265,78 +314,6 @@ __global__ __launch_bounds__(1024) void sum_parts_kernel(const float* __restrict
 #pragma unroll
     for (int w = 1; w < 16; ++w) sum += red[w][lane];
     out[e] = sum;
-  }
-}
-
-// Partial Gram matrices of a tall matrix: part[g] [k, k] = Y[rows of slab g]^T . Y[rows of slab g], fp32
-// matrix instructions (v_mfma_f32_32x32x2_f32).  Y [n, k] fp32 row-major; grid = slabs of `rows_per_wg`
-// rows; 4 waves share the (k/32)^2 output blocks (k is padded to a multiple of 32 with zero columns).
-__global__ __launch_bounds__(256) void gram_partial_kernel(const float* __restrict__ Y, int64_t n, int k,
-                                                           int rows_per_wg, float* __restrict__ part) {
-  constexpr int CH = 64;                       // rows staged at a time
-  __shared__ float Ys[CH * (kRsvdMaxRank + 32)];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int kp = (k + 31) / 32 * 32, nb = kp / 32, blocks = nb * nb;
-  const int ld = (kp % 64 == 0) ? kp + 32 : kp;  // rows r and r + 1 on different halves of the 64 banks
-  const int64_t r0 = (int64_t)blockIdx.x * rows_per_wg;
-  const int64_t r1 = r0 + rows_per_wg < n ? r0 + rows_per_wg : n;
-  f32x16 acc[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[q][e] = 0.f;
-  for (int64_t c0 = r0; c0 < r1; c0 += CH) {
-    for (int e = tid; e < CH * kp; e += 256) {
-      const int r = e / kp, c = e % kp;
-      Ys[r * ld + c] = (c0 + r < r1 && c < k) ? Y[(c0 + r) * k + c] : 0.f;
-    }
-    __syncthreads();
-    if (blocks == 1) {  // k <= 32: the four waves split the rows of the chunk, their sums are added below
-      for (int rr = wave * (CH / 4); rr < (wave + 1) * (CH / 4); rr += 2) {
-        const float a = Ys[(rr + (lane >> 5)) * ld + (lane & 31)];
-        acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, a, acc[0], 0, 0, 0);
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int blk = wave + 4 * q;
-        if (blk < blocks) {
-          const int i0 = (blk / nb) * 32, j0 = (blk % nb) * 32;
-          for (int rr = 0; rr < CH; rr += 2) {
-            const float a = Ys[(rr + (lane >> 5)) * ld + i0 + (lane & 31)];
-            const float b = Ys[(rr + (lane >> 5)) * ld + j0 + (lane & 31)];
-            acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc[q], 0, 0, 0);
-          }
-        }
-      }
-    }
-    __syncthreads();
-  }
-  if (blocks == 1) {  // fold the four waves' sums in a fixed order (Ys is free: the loop ended on a barrier)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) Ys[(wave * 16 + e) * 64 + lane] = acc[0][e];
-    __syncthreads();
-    if (wave == 0) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e)
-        acc[0][e] = ((Ys[e * 64 + lane] + Ys[(16 + e) * 64 + lane]) + Ys[(32 + e) * 64 + lane]) + Ys[(48 + e) * 64 + lane];
-    } else {
-      return;  // wave 0 stores
-    }
-  }
-  float* out = part + (int64_t)blockIdx.x * k * k;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int blk = wave + 4 * q;
-    if (blk < blocks) {
-      const int i0 = (blk / nb) * 32, j0 = (blk % nb) * 32;
-      const int col = j0 + (lane & 31);
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int row = i0 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
-        if (row < k && col < k) out[row * k + col] = acc[q][e];
-      }
-    }
   }
 }
 
