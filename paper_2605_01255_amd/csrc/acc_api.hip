@@ -161,64 +161,108 @@ constexpr int64_t kMaxOperandBytes = 0xFFFFFFFFll;  // buffer resources address 
 // ---- float32 path ---------------------------------------------------------------------------
 // An operand of the float32 kernel: X[rows, K] with K contiguous (kmajor), or Xt[K, rows] with the rows contiguous.
 struct F32Operand {
-  const float* ptr;
+  const void* ptr;
   int64_t ld;
   bool kmajor;
+  bool b16;  // bfloat16 elements
 };
 
 bool f32_operand_ok(const F32Operand& x, int64_t rows, int64_t K) {
-  return x.ld % 4 == 0 && aligned16(x.ptr) && (!x.kmajor || K % 4 == 0) &&
-         (x.kmajor ? (rows > 256 ? rows : 256) : K + 32) * x.ld * 4 <= kMaxOperandBytes;
+  const int64_t es = x.b16 ? 2 : 4, chunk = 16 / es;
+  return x.ld % chunk == 0 && aligned16(x.ptr) && (!x.kmajor || K % chunk == 0) &&
+         (x.kmajor ? (rows > 256 ? rows : 256) : K + 32) * x.ld * es <= kMaxOperandBytes;
 }
 bool f32_gemm_ok(const F32Operand& a, const F32Operand& b, int64_t M, int64_t N, int64_t K, const void* C, int64_t ldc) {
   return f32_operand_ok(a, M, K) && f32_operand_ok(b, N, K) && N % 4 == 0 && ldc % 4 == 0 && aligned16(C);
 }
 
-template <int TM, int TN, int NS, typename TC>
-void f32_launch(bool a_kmajor, bool b_kmajor, F32GemmParams& p, int splits, Launcher& L) {
+template <int TM, int TN, int NS, bool A_K, bool B_K, typename TA, typename TB, typename Output>
+void f32_launch(F32GemmParams& p, const Output& out, int splits, Launcher& L) {
   const unsigned grid = gemm_ring_plan(p, 32 * TM, 32 * TN);
   p.tile_blocks = (int)grid;
-  auto go = [&](auto kernel) {
-    L.launch_lds(kernel, dim3(grid * (unsigned)splits), dim3(256), (size_t)gemm_f32_lds_bytes<TM, TN, NS>(), p);
-  };
-  if (a_kmajor && b_kmajor) go(gemm_f32_kernel<TM, TN, NS, true, true, TC>);
-  else if (a_kmajor) go(gemm_f32_kernel<TM, TN, NS, true, false, TC>);
-  else if constexpr (sizeof(TC) == 4) {  // a transposed left operand only feeds float32 results
-    if (b_kmajor) go(gemm_f32_kernel<TM, TN, NS, false, true, TC>);
-    else go(gemm_f32_kernel<TM, TN, NS, false, false, TC>);
-  } else L.err = hipErrorInvalidValue;
+  L.launch_lds(gemm_f32_kernel<TM, TN, NS, A_K, B_K, TA, TB, Output>, dim3(grid * (unsigned)splits), dim3(256),
+               (size_t)gemm_f32_lds_bytes<TM, TN, NS, TA, TB>(), p, out);
 }
 
-// C[M, N] (op)= A . B, f32_gemm_ok; `splits` > 1 writes partial products c_split_stride apart.
+// The tile with the least estimate, rounds of 256 compute units x K tiles x time of a K tile in ns.  The matrix pipe
+// bounds all of them, so the estimates follow the area, and a small tile only loses by its operands' latency; what decides
+// is how much of the last round is empty.  Measured us, 128 x 64 / 64 x 64 / 64 x 32 / 32 x 32 [generic kernel]:
+//   2048 x 2048 x 1024  64 /  66 /  79 /  79 [188]      2048 x 1024 x 2048  67 / 66 / 105 /  80 [347]
+//   300 x 4096 x 2048   66 /  66 /  57 /  76            256 x 512 x 256   11.5 / 7.6 / 5.7 / 4.6 [22]
+// Products with a bfloat16 factor are small: 32 x 32 and 64 x 64 only.
+template <bool A_K, bool B_K, typename TA, typename TB, typename Output>
+void f32_tiled(F32GemmParams& p, const Output& out, Launcher& L) {
+  const int splits = (int)ceil_div(p.K, p.k_per_split);
+  struct Cost { int bm, bn, per_k, alone_per_k; };
+  static const Cost costs[] = {{64, 64, 520, 560}, {32, 32, 165, 210}, {128, 64, 960, 1000}, {64, 32, 320, 330}};
+  constexpr bool both_f32 = sizeof(TA) == 4 && sizeof(TB) == 4;
+  int best = 0;
+  int64_t best_ns = INT64_MAX;
+  for (int i = 0; i < (both_f32 ? 4 : 2); ++i) {
+    const int64_t rounds = ceil_div(ceil_div(p.M, costs[i].bm) * ceil_div(p.N, costs[i].bn) * splits, 256);
+    const int64_t ns = rounds == 1 ? costs[i].alone_per_k : rounds * costs[i].per_k;
+    if (ns < best_ns) { best_ns = ns; best = i; }
+  }
+  if (best == 0) return f32_launch<2, 2, 4, A_K, B_K, TA, TB>(p, out, splits, L);
+  if (best == 1) return f32_launch<1, 1, 4, A_K, B_K, TA, TB>(p, out, splits, L);
+  if constexpr (both_f32) {
+    if (best == 2) f32_launch<4, 2, 3, A_K, B_K, TA, TB>(p, out, splits, L);
+    else f32_launch<2, 1, 4, A_K, B_K, TA, TB>(p, out, splits, L);
+  }
+}
+
+F32GemmParams f32_params(const F32Operand& a, const F32Operand& b, void* C, int64_t ldc, int64_t M, int64_t N, int64_t K) {
+  F32GemmParams p{};
+  p.A = a.ptr; p.B = b.ptr; p.C = C;
+  p.M = M; p.N = N; p.K = K; p.lda = a.ld; p.ldb = b.ld; p.ldc = ldc;
+  p.k_per_split = round_up(K, 32);
+  p.alpha = p.beta = 1.f;
+  return p;
+}
+
+// C[M, N] (op)= A . B, f32_gemm_ok; a K range shorter than K writes partial products c_split_stride apart.  Orders: any of
+// two float32 operands (a transposed left one for float32 results only); of a bfloat16 left operand those with an
+// N-contiguous right one that is float32, or bfloat16 where the left one is transposed.
 template <typename TC>
 void f32_gemm(const F32Operand& a, const F32Operand& b, void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, Launcher& L,
               bool accumulate = false, float alpha = 1.f, float beta = 1.f, int64_t k_per_split = 0,
               int64_t c_split_stride = 0) {
-  F32GemmParams p{};
-  p.A = a.ptr; p.B = b.ptr; p.C = C;
-  p.M = M; p.N = N; p.K = K; p.lda = a.ld; p.ldb = b.ld; p.ldc = ldc;
+  F32GemmParams p = f32_params(a, b, C, ldc, M, N, K);
   p.accumulate = accumulate ? 1 : 0; p.alpha = alpha; p.beta = beta;
-  p.k_per_split = k_per_split ? k_per_split : round_up(K, 32);
+  if (k_per_split) p.k_per_split = k_per_split;
   p.c_split_stride = c_split_stride;
-  const int splits = (int)ceil_div(K, p.k_per_split);
-  // The tile with the least estimate, rounds of 256 compute units x K tiles x time of a K tile in ns.  The matrix pipe
-  // bounds all of them, so the estimates follow the area, and a small tile only loses by its operands' latency; what decides
-  // is how much of the last round is empty.  Measured us, 128 x 64 / 64 x 64 / 64 x 32 / 32 x 32 [generic kernel]:
-  //   2048 x 2048 x 1024  64 /  66 /  79 /  79 [188]      2048 x 1024 x 2048  67 / 66 / 105 /  80 [347]
-  //   300 x 4096 x 2048   66 /  66 /  57 /  76            256 x 512 x 256   11.5 / 7.6 / 5.7 / 4.6 [22]
-  struct Cost { int bm, bn, per_k, alone_per_k; };
-  static const Cost costs[] = {{128, 64, 960, 1000}, {64, 64, 520, 560}, {64, 32, 320, 330}, {32, 32, 165, 210}};
-  int best = 0;
-  int64_t best_ns = INT64_MAX;
-  for (int i = 0; i < 4; ++i) {
-    const int64_t rounds = ceil_div(ceil_div(M, costs[i].bm) * ceil_div(N, costs[i].bn) * splits, 256);
-    const int64_t ns = rounds == 1 ? costs[i].alone_per_k : rounds * costs[i].per_k;
-    if (ns < best_ns) { best_ns = ns; best = i; }
+  const StoreProduct<TC> out{};
+  if (!a.b16 && !b.b16) {
+    if (a.kmajor && b.kmajor) return f32_tiled<true, true, float, float>(p, out, L);
+    if (a.kmajor) return f32_tiled<true, false, float, float>(p, out, L);
+    if constexpr (sizeof(TC) == 4) {
+      if (b.kmajor) return f32_tiled<false, true, float, float>(p, out, L);
+      return f32_tiled<false, false, float, float>(p, out, L);
+    }
+  } else if constexpr (sizeof(TC) == 4) {
+    if (a.b16 && !b.kmajor) {
+      if (!b.b16 && a.kmajor) return f32_tiled<true, false, bf16, float>(p, out, L);
+      if (!b.b16) return f32_tiled<false, false, bf16, float>(p, out, L);
+      if (!a.kmajor) return f32_tiled<false, false, bf16, bf16>(p, out, L);
+    }
   }
-  if (best == 0) f32_launch<4, 2, 3, TC>(a.kmajor, b.kmajor, p, splits, L);
-  else if (best == 1) f32_launch<2, 2, 4, TC>(a.kmajor, b.kmajor, p, splits, L);
-  else if (best == 2) f32_launch<2, 1, 4, TC>(a.kmajor, b.kmajor, p, splits, L);
-  else f32_launch<1, 1, 4, TC>(a.kmajor, b.kmajor, p, splits, L);
+  L.err = hipErrorInvalidValue;  // an order of operands no caller has
+}
+
+// Moments and normalised step from the projected gradient, formed as the product's output: [k, d_out] = T1 . Gr, or
+// [d_out, k] = Gr . T1^T in the paper's orientation.  T1 fp32 [k, r]; TF: type of Gr and N.
+template <typename TF>
+void project_adam(bool w_oi, const float* t1, const void* Gr, float* M, float* V, void* N, int64_t k, int64_t r, int64_t d_out,
+                  const AdamParams& h, Launcher& L) {
+  const F32Operand t{t1, r, true, false}, g{Gr, w_oi ? r : d_out, w_oi, sizeof(TF) == 2};
+  const AdamOutput<TF> out{M, V, (TF*)N, h};
+  if (w_oi) {
+    F32GemmParams p = f32_params(g, t, nullptr, k, d_out, k, r);
+    f32_tiled<true, true, TF, float>(p, out, L);
+  } else {
+    F32GemmParams p = f32_params(t, g, nullptr, d_out, k, d_out, r);
+    f32_tiled<true, false, float, TF>(p, out, L);
+  }
 }
 
 // ---- generic path --------------------------------------------------------------------------
@@ -237,7 +281,7 @@ template <typename TA, typename TB, typename TC, typename CT, bool SK, bool ACCU
 void launch_generic(const GemmParams& p, int splits, Launcher& L) {
   if constexpr (sizeof(TA) == 4 && sizeof(TB) == 4 && !SK) {  // two float32 operands: the tuned kernel where strides allow
     const bool a_k = p.a_sk == 1, b_k = p.b_sk == 1;
-    const F32Operand a{(const float*)p.A, a_k ? p.a_sm : p.a_sk, a_k}, b{(const float*)p.B, b_k ? p.b_sn : p.b_sk, b_k};
+    const F32Operand a{p.A, a_k ? p.a_sm : p.a_sk, a_k, false}, b{p.B, b_k ? p.b_sn : p.b_sk, b_k, false};
     if ((a_k || p.a_sm == 1) && (b_k || p.b_sn == 1) && p.c_sn == 1 && (a_k || sizeof(TC) == 4) &&
         f32_gemm_ok(a, b, p.M, p.N, p.K, p.C, p.c_sm)) {
       f32_gemm<TC>(a, b, p.C, p.c_sm, p.M, p.N, p.K, L, p.accumulate != 0, p.alpha, p.beta, p.k_per_split, p.c_split_stride);
@@ -277,7 +321,7 @@ bool f32_sketch(const acc_linear_desc* d, const void* A, int64_t lda, int64_t ch
   }
   const int64_t k_per_split = round_up(ceil_div(n, G), 32);
   G = ceil_div(n, k_per_split);
-  const F32Operand x{(const float*)A, lda, false}, sm{ws, r, false};
+  const F32Operand x{A, lda, false, false}, sm{ws, r, false, false};
   float* part = ws + s_size;   // n r floats: r % 8 == 0 keeps the alignment
   float* dst = G == 1 && direct ? (float*)out : part;
   const int64_t M = transposed ? r : channels, N = transposed ? channels : r;
@@ -1055,6 +1099,21 @@ LowrankPlan plan_lowrank(const acc_linear_desc* d, const Shape& s, int64_t k) {
   return pl;
 }
 
+// C [M, N] fp32 (dense) = A . B with a long K and a small result: the K range split over up to `most` groups of
+// work-groups (at least 128 elements each, one work-group per compute unit), the partials in `part` added in order.
+void lowrank_product(const F32Operand& a, const F32Operand& b, int64_t M, int64_t N, int64_t K, int64_t most, float* part,
+                     float* C, Launcher& L) {
+  int64_t splits = 256 / (ceil_div(M, 32) * ceil_div(N, 32));
+  if (splits > K / 128) splits = K / 128;
+  if (splits > most) splits = most;
+  if (splits < 1) splits = 1;
+  const int64_t k_per_split = round_up(ceil_div(K, splits), 32);
+  splits = ceil_div(K, k_per_split);
+  f32_gemm<float>(a, b, splits > 1 ? part : C, N, M, N, K, L, false, 1.f, 1.f, k_per_split, M * N);
+  if (splits > 1)
+    L(sum_parts_kernel, dim3((unsigned)ceil_div(M * N, 64)), dim3(1024), (const float*)part, (int)splits, M * N, C);
+}
+
 size_t workspace_bytes(const acc_linear_desc* d, const Shape& s, bool backward) {
   const int64_t channels = backward ? s.d_out : s.d_in;
   const SketchPlan sp = plan_sketch(d, s.n, channels, backward ? s.ldy : s.ldx);
@@ -1423,26 +1482,40 @@ int acc_lowrank_projector(const acc_linear_desc* desc, int64_t k, const void* le
   float* z = (float*)(ws + pl.off_z);
   float* yp = (float*)(ws + pl.off_yp);
   float* q1 = (float*)(ws + pl.off_q1);
-  // Z [r, k] = Gr . Omega over the output channels, Omega[o, j] from the Philox map with the channel index in
-  // the token's place, generated in fp32 while it is staged; the channel range split, partials folded by K4
+  // Z [r, k] = Gr . Omega over the output channels, Omega[o, j] from the Philox map with the channel index in the token's
+  // place.  Omega is written once (where a step keeps its projected gradient, the same size), the channel range split and
+  // the partials added in order: generated while it was staged it took 13 to 39 us, its partial sums 13.
+  const bool fb = desc->factor_dtype == ACC_BF16;
   {
     acc_linear_desc od = *desc;
     od.row_offset = 0;
     od.r = k;
-    GemmParams p{};
-    p.A = Gr; p.B = nullptr; p.C = ws + pl.off_part;
-    p.M = s.r; p.N = k; p.K = s.d_out;
-    p.a_sm = w_oi ? 1 : s.d_out; p.a_sk = w_oi ? s.r : 1;
-    p.c_sm = k; p.c_sn = 1;
-    p.k_per_split = pl.z_k_per_split;
-    p.c_split_stride = s.r * k;
-    p.sk = make_sketch_params(&od);
-    if (desc->factor_dtype == ACC_BF16) launch_generic<bf16, bf16, float, float, true, true>(p, pl.z_splits, L);
-    else launch_generic<float, float, float, float, true, true>(p, pl.z_splits, L);
-    reduce_to(ACC_F32, (const float*)(ws + pl.off_part), pl.z_splits, s.r * k, z, L);
+    float* omega = (float*)(ws + pl.off_r);
+    float* part = (float*)(ws + pl.off_part);
+    const F32Operand g{Gr, w_oi ? s.r : s.d_out, !w_oi, fb}, om{omega, k, false, false};
+    if (f32_gemm_ok(g, om, s.r, k, s.d_out, z, k)) {
+      L(sketch_matrix_kernel, dim3((unsigned)ceil_div(ceil_div(s.d_out, 4) * k, 256)), dim3(256), make_sketch_params(&od), s.d_out,
+        k, omega);
+      lowrank_product(g, om, s.r, k, s.d_out, pl.z_splits, part, z, L);
+    } else {
+      GemmParams p{};
+      p.A = Gr; p.B = nullptr; p.C = part;
+      p.M = s.r; p.N = k; p.K = s.d_out;
+      p.a_sm = w_oi ? 1 : s.d_out; p.a_sk = w_oi ? s.r : 1;
+      p.c_sm = k; p.c_sn = 1;
+      p.k_per_split = pl.z_k_per_split;
+      p.c_split_stride = s.r * k;
+      p.sk = make_sketch_params(&od);
+      if (fb) launch_generic<bf16, bf16, float, float, true, true>(p, pl.z_splits, L);
+      else launch_generic<float, float, float, float, true, true>(p, pl.z_splits, L);
+      reduce_to(ACC_F32, part, pl.z_splits, s.r * k, z, L);
+    }
   }
   // Yp [d_in, k] = left . Z
-  {
+  const F32Operand lf{left, s.r, true, fb}, zf{z, k, false, false};
+  if (f32_gemm_ok(lf, zf, s.d_in, k, s.r, yp, k)) {
+    f32_gemm<float>(lf, zf, yp, k, s.d_in, k, s.r, L);
+  } else {
     GemmParams p{};
     p.A = left; p.B = z; p.C = yp;
     p.M = s.d_in; p.N = k; p.K = s.r;
@@ -1497,7 +1570,10 @@ int acc_lowrank_adamw_step(const acc_linear_desc* desc, const acc_adamw_hyper* h
     // R = T1 . Gr [k, d_out] (or Gr . T1^T [d_out, k]) in fp32
     float* t1 = (float*)(ws + pl.off_t1);
     float* proj = (float*)(ws + pl.off_r);
-    {
+    const F32Operand pa{P, k, false, fb}, lb{left, s.r, false, fb};
+    if (f32_gemm_ok(pa, lb, k, s.r, s.d_in, t1, s.r)) {
+      lowrank_product(pa, lb, k, s.r, s.d_in, pl.t1_splits, (float*)(ws + pl.off_part), t1, L);
+    } else {
       GemmParams p{};
       p.A = P; p.B = left; p.C = ws + pl.off_part;
       p.M = k; p.N = s.r; p.K = s.d_in;
@@ -1508,14 +1584,10 @@ int acc_lowrank_adamw_step(const acc_linear_desc* desc, const acc_adamw_hyper* h
       L(sum_parts_kernel, dim3((unsigned)ceil_div(k * s.r, 64)), dim3(1024), (const float*)(ws + pl.off_part),
         pl.t1_splits, k * s.r, t1);
     }
-    if (fb) {  // projected gradient, moments and normalised step in one launch
-      ProjectAdamParams q{};
-      q.T1 = t1; q.Gr = (const bf16*)Gr; q.M = M; q.V = V; q.N = (bf16*)nrm;
-      q.k = k; q.r = s.r; q.d_out = s.d_out;
-      q.b_sk = w_oi ? 1 : s.d_out; q.b_sn = w_oi ? s.r : 1;
-      q.c_sm = w_oi ? 1 : s.d_out; q.c_sn = w_oi ? k : 1;
-      q.h = h;
-      L(project_adam_kernel, dim3((unsigned)ceil_div(k, 64), (unsigned)ceil_div(s.d_out, 64)), dim3(256), q);
+    const F32Operand t{t1, s.r, true, false}, g{Gr, w_oi ? s.r : s.d_out, w_oi, fb};
+    if (w_oi ? f32_gemm_ok(g, t, s.d_out, k, s.r, M, k) : f32_gemm_ok(t, g, k, s.d_out, s.r, M, s.d_out)) {
+      if (fb) project_adam<bf16>(w_oi, t1, Gr, M, V, nrm, k, s.r, s.d_out, h, L);
+      else project_adam<float>(w_oi, t1, Gr, M, V, nrm, k, s.r, s.d_out, h, L);
     } else {
       GemmParams p{};
       p.C = proj; p.K = s.r;
@@ -1529,7 +1601,8 @@ int acc_lowrank_adamw_step(const acc_linear_desc* desc, const acc_adamw_hyper* h
         p.a_sm = s.r; p.a_sk = 1; p.b_sk = s.d_out; p.b_sn = 1; p.c_sm = s.d_out; p.c_sn = 1;
         rsvd_gemm(ACC_F32, desc->factor_dtype, ACC_F32, p, 1, L);
       }
-      L(adam_factor_kernel<float, float>, dim3(blocks), dim3(256), (const float*)proj, M, V, (float*)nrm, count, h);
+      if (fb) L(adam_factor_kernel<float, bf16>, dim3(blocks), dim3(256), (const float*)proj, M, V, (bf16*)nrm, count, h);
+      else L(adam_factor_kernel<float, float>, dim3(blocks), dim3(256), (const float*)proj, M, V, (float*)nrm, count, h);
     }
   }
   Shape sb = s;

@@ -1,5 +1,6 @@
-// float32 GEMM on a ring of LDS stages (the exact products, the sketch's product with a stored S, the factor products
-// and the Gram matrices of float32 layers):  C[M, N] = A . B, optionally C = beta C + alpha (A . B), and a split of the K range.
+// GEMM with float32 arithmetic on a ring of LDS stages, operands float32 or bfloat16 (the exact products, the sketch's
+// product with a stored S, the factor products and the Gram matrices of float32 layers; products of a bfloat16 factor that
+// have to keep 32 bits):  C[M, N] = A . B, optionally C = beta C + alpha (A . B), and a split of the K range.
 //
 //   A_KMAJOR: A[M, K], K contiguous;  else A is given transposed, At[K, M], M contiguous (X^T of the sketch).
 //   B_KMAJOR: Bt[N, K], K contiguous; else B[K, N], N contiguous.
@@ -7,22 +8,24 @@
 // v_mfma_f32_16x16x4 multiplies 64 flops a clock and SIMD, so a 64 x 64 x 32 tile takes 1024 clocks against 256 for its 16 KB
 // from L2: the matrix pipe bounds every tile from there on, and what matters is that it never waits.  As in gemm_ring_kernel
 // the operands go global -> LDS directly, NS stages in flight, waited for by count, one barrier per K tile.
-// A K tile is 32 floats = 128 bytes of a K-contiguous row, the same chunks and swizzle as 64 bfloat16.  A lane reads one
-// 16-byte chunk (four consecutive k) of its row per k-step of 16: instruction t of the step takes element t, so the four
-// lane groups cover k = 4 g4 + t, in another order than memory but the same for A and B.  An operand that is contiguous
-// along M or N lies in LDS as 32 rows of k and is read as four single floats at those k.
-// Any M, N, K with 16-byte aligned rows: chunks past K of a K-contiguous operand (K % 4 == 0) and rows past K of the other
-// kind are out of the buffer's range and read as zero.  Operands below 4 GiB.
+// A K tile is 32 elements.  A lane takes four consecutive k of its row per k-step of 16: instruction t of the step takes
+// element t, so the four lane groups cover k = 4 g4 + t, in another order than memory but the same for A and B.
+//   K contiguous  a row is 128 (float32) or 64 bytes; one 16- or 8-byte read
+//   otherwise     LDS holds 32 rows of k; four single floats at those k, or one transposing read of bfloat16
+// bfloat16 operands are widened in registers (exact).
+// Any M, N, K with 16-byte aligned rows: chunks past K of a K-contiguous operand (K a multiple of the chunk) and rows past K
+// of the other kind are out of the buffer's range and read as zero.  Operands below 4 GiB.
 #pragma once
 #include <type_traits>
 
 #include "acc_gemm_ring.h"
+#include "acc_rng.h"
 
 namespace acc {
 
 struct F32GemmParams {
-  const float* A;
-  const float* B;
+  const void* A;
+  const void* B;
   void* C;
   int64_t M, N, K;
   int64_t lda, ldb, ldc;   // row strides in elements
@@ -34,13 +37,89 @@ struct F32GemmParams {
   int64_t c_split_stride;
 };
 
-template <int TM, int TN, int NS, bool A_KMAJOR, bool B_KMAJOR, typename TC>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(F32GemmParams p) {
+// One operand of the kernel: R rows of the output dimension (BM or BN) per tile, K_MAJOR its memory order.
+template <typename T, int R, bool K_MAJOR> struct F32Tile {
+  static constexpr int ES = sizeof(T), NW = 4;
+  static constexpr int BYTES = R * 32 * ES, WAVE_LOADS = BYTES / 1024;
+  static constexpr int LOADS = WAVE_LOADS < NW ? 1 : WAVE_LOADS / NW;   // per wave; a tile of two is moved twice
+  static constexpr int ROW = K_MAJOR ? 32 * ES : R * ES;                // bytes of an LDS row
+  static constexpr int CHUNKS = ROW / 16;
+  // Position of chunk c of LDS row `row`: c XOR this.  What one clock of a read touches must lie on different banks (64 of
+  // four bytes): 16 rows of one chunk (K contiguous); four rows of k, four apart, 64 bytes of each (float32; a 32-row tile only
+  // has halves to give); eight rows of k, 32 bytes of each (bfloat16).
+  __device__ static __forceinline__ int swizzle(int row) {
+    if constexpr (K_MAJOR) return ES == 4 ? swz(row) : (row >> 2) & 3;
+    else if constexpr (ES == 4) return R == 32 ? ((row >> 2) & 1) << 2 : ((row >> 2) & 3) << 2;
+    else return (R == 32 ? (row >> 2) & 1 : R == 64 ? (row >> 1) & 3 : row & 7) << 1;
+  }
+  __device__ static __forceinline__ int lds_block(int t, int wave) { return (t * NW + wave) % WAVE_LOADS; }
+  // byte offset of the chunk this lane moves in wave-load t
+  __device__ static __forceinline__ uint32_t source(int t, int wave, int lane, int64_t ld) {
+    const int row = lds_block(t, wave) * (64 / CHUNKS) + lane / CHUNKS;
+    return (uint32_t)(row * ld * ES + (((lane % CHUNKS) ^ swizzle(row)) << 4));
+  }
+  // K contiguous: this lane's chunk lies past the last K tile's `left` elements (all its rows share their swizzle)
+  __device__ static __forceinline__ bool past(int wave, int lane, int64_t left) {
+    return K_MAJOR && ((lane % CHUNKS) ^ swizzle(lds_block(0, wave) * (64 / CHUNKS) + lane / CHUNKS)) * (16 / ES) >= left;
+  }
+  // LDS offset of tile row x0 + l16 (x0 % 16 == 0), k = 4 g4; read() adds the k-step
+  __device__ static __forceinline__ int base(int x0, int l16, int g4) {
+    const int x = x0 + l16;
+    if constexpr (K_MAJOR) return x * ROW;
+    else if constexpr (ES == 4) return 4 * g4 * ROW + (((x >> 2) ^ swizzle(4 * g4)) << 4) + (x & 3) * 4;
+    else {  // transposing read: lane i of a group gives row i / 4 of its four, four columns at 4 (i % 4)
+      const int row = 4 * g4 + (l16 >> 2), col = x0 + 4 * (l16 & 3);
+      return row * ROW + (((col >> 3) ^ swizzle(row)) << 4) + (col & 7) * 2;
+    }
+  }
+  __device__ static __forceinline__ f32x4 read(const char* tile, int base, int s, int l16, int g4) {
+    if constexpr (K_MAJOR && ES == 4) return *(const f32x4*)(tile + base + (((4 * s + g4) ^ swz(l16)) << 4));
+    else if constexpr (ES == 4) {
+      f32x4 v;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[t] = *(const float*)(tile + base + (16 * s + t) * ROW);
+      return v;
+    } else {
+      bf16x4 h;
+      if constexpr (K_MAJOR) h = *(const bf16x4*)(tile + base + (((2 * s + (g4 >> 1)) ^ swizzle(l16)) << 4) + (g4 & 1) * 8);
+      else h = __builtin_bit_cast(bf16x4, lds_read_tr16_b64(tile, base + 16 * s * ROW));  // row bits the swizzle uses stay
+      return f32x4{(float)h[0], (float)h[1], (float)h[2], (float)h[3]};
+    }
+  }
+};
+
+// What becomes of four consecutive columns gn .. gn + 3 of output row gm.  `Old` is requested before the first transfer.
+template <typename TC> struct StoreProduct {
+  struct Old {};
+  __device__ __forceinline__ Old load(const F32GemmParams&, int64_t, int64_t) const { return Old{}; }
+  __device__ __forceinline__ void store(const F32GemmParams& p, int split, int64_t gm, int64_t gn, f32x4 v, const Old&) const {
+    TC* dst = (TC*)p.C + (int64_t)split * p.c_split_stride + gm * p.ldc + gn;
+    if constexpr (sizeof(TC) == 4) {
+      if (p.accumulate) v = p.alpha * v + p.beta * *(const f32x4*)dst;
+      *(f32x4*)dst = v;
+    } else {
+      bf16x4 o;
+      if (p.accumulate) {
+        const bf16x4 old = *(const bf16x4*)dst;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t] = p.alpha * v[t] + p.beta * (float)old[t];
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t) o[t] = (bf16)v[t];
+      *(bf16x4*)dst = o;
+    }
+  }
+};
+
+template <int TM, int TN, int NS, bool A_KMAJOR, bool B_KMAJOR, typename TA, typename TB, typename Output>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(F32GemmParams p, Output output) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   constexpr int NW = 4, WN = 2;
   constexpr int BM = 2 * TM * 16, BN = 2 * TN * 16, BK = 32;
-  constexpr int A_BYTES = BM * BK * 4, B_BYTES = BN * BK * 4, STAGE = A_BYTES + B_BYTES;
-  constexpr int A_LOADS = A_BYTES / 1024 / NW, B_LOADS = B_BYTES / 1024 / NW, NG = A_LOADS + B_LOADS;
+  using TileA = F32Tile<TA, BM, A_KMAJOR>;
+  using TileB = F32Tile<TB, BN, B_KMAJOR>;
+  constexpr int A_BYTES = TileA::BYTES, STAGE = A_BYTES + TileB::BYTES;
+  constexpr int A_LOADS = TileA::LOADS, B_LOADS = TileB::LOADS, NG = A_LOADS + B_LOADS;
   static_assert((NS - 1) * NG <= 63, "vmcnt range");
 
   const int split = (int)blockIdx.x / p.tile_blocks;
@@ -56,69 +135,57 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32GemmParams p) {
   const int KT = (int)((kn + BK - 1) / BK);
 
   // ---- global -> LDS ----
-  // The same code for both operands: R rows of the output dimension in the tile, `kmajor` its memory order.
-  auto rsrc_of = [&](const float* X, int64_t x0, int64_t X_total, int64_t ld, bool kmajor) {
-    return kmajor ? make_rsrc(X + x0 * ld + k0, ((X_total - x0 - 1) * ld + kn) * 4)
-                  : make_rsrc(X + k0 * ld + x0, ((kn - 1) * ld + (X_total - x0)) * 4);
+  auto rsrc_of = [&](const auto* X, int64_t x0, int64_t X_total, int64_t ld, bool kmajor) {
+    constexpr int64_t ES = sizeof(*X);
+    return kmajor ? make_rsrc(X + x0 * ld + k0, ((X_total - x0 - 1) * ld + kn) * ES)
+                  : make_rsrc(X + k0 * ld + x0, ((kn - 1) * ld + (X_total - x0)) * ES);
   };
-  const u32x4 a_rsrc = rsrc_of(p.A, m0, p.M, p.lda, A_KMAJOR), b_rsrc = rsrc_of(p.B, n0, p.N, p.ldb, B_KMAJOR);
-  const int kchunk = (lane & 7) ^ swz(wave * 8 + (lane >> 3));  // rows 32 apart share swz
-  auto src_of = [&](int t, int64_t ld, bool kmajor, int R) -> uint32_t {
-    if (kmajor) return (uint32_t)(((t * NW + wave) * 8 + (lane >> 3)) * ld * 4 + (kchunk << 4));
-    const int chunks = R / 4, rows = 64 / chunks;  // 16-byte chunks per k row, k rows per wave-load
-    const int krow = (t * NW + wave) * rows + lane / chunks;
-    // the four lane groups of a read sit four k rows apart: sent to different quarters of the 64 banks (a 32-row tile
-    // only has halves to give)
-    const int sw = R == 32 ? ((krow >> 2) & 1) << 2 : ((krow >> 2) & 3) << 2;
-    return (uint32_t)(krow * ld * 4 + (((lane % chunks) ^ sw) << 4));
-  };
+  const u32x4 a_rsrc = rsrc_of((const TA*)p.A, m0, p.M, p.lda, A_KMAJOR), b_rsrc = rsrc_of((const TB*)p.B, n0, p.N, p.ldb, B_KMAJOR);
   uint32_t a_src[A_LOADS], b_src[B_LOADS];
 #pragma unroll
-  for (int t = 0; t < A_LOADS; ++t) a_src[t] = src_of(t, p.lda, A_KMAJOR, BM);
+  for (int t = 0; t < A_LOADS; ++t) a_src[t] = TileA::source(t, wave, lane, p.lda);
 #pragma unroll
-  for (int t = 0; t < B_LOADS; ++t) b_src[t] = src_of(t, p.ldb, B_KMAJOR, BN);
-  const uint32_t tail = kchunk * 4 >= kn - (int64_t)(KT - 1) * BK ? 0xFFFFFFF0u : 0u;  // chunk past K in the last K tile
-  const uint32_t a_kstep = A_KMAJOR ? BK * 4 : (uint32_t)(BK * p.lda * 4);
-  const uint32_t b_kstep = B_KMAJOR ? BK * 4 : (uint32_t)(BK * p.ldb * 4);
+  for (int t = 0; t < B_LOADS; ++t) b_src[t] = TileB::source(t, wave, lane, p.ldb);
+  const int64_t left = kn - (int64_t)(KT - 1) * BK;
+  const uint32_t a_tail = TileA::past(wave, lane, left) ? 0xFFFFFFF0u : 0u, b_tail = TileB::past(wave, lane, left) ? 0xFFFFFFF0u : 0u;
+  const uint32_t a_kstep = (uint32_t)((A_KMAJOR ? BK : BK * p.lda) * sizeof(TA));
+  const uint32_t b_kstep = (uint32_t)((B_KMAJOR ? BK : BK * p.ldb) * sizeof(TB));
   const uint32_t smem_lds = (uint32_t)(uintptr_t)smem;
   auto issue_one = [&](int g, int kt, uint32_t stage) {
-    const uint32_t oob = kt == KT - 1 ? tail : 0u;
+    const bool last = kt == KT - 1;
     if (g < A_LOADS)
-      buffer_to_lds_b128(a_rsrc, A_KMAJOR ? a_src[g] | oob : a_src[g], (uint32_t)kt * a_kstep, stage + (g * NW + wave) * 1024);
+      buffer_to_lds_b128(a_rsrc, A_KMAJOR ? a_src[g] | (last ? a_tail : 0u) : a_src[g], (uint32_t)kt * a_kstep,
+                         stage + TileA::lds_block(g, wave) * 1024);
     else
-      buffer_to_lds_b128(b_rsrc, B_KMAJOR ? b_src[g - A_LOADS] | oob : b_src[g - A_LOADS], (uint32_t)kt * b_kstep,
-                         stage + A_BYTES + ((g - A_LOADS) * NW + wave) * 1024);
+      buffer_to_lds_b128(b_rsrc, B_KMAJOR ? b_src[g - A_LOADS] | (last ? b_tail : 0u) : b_src[g - A_LOADS], (uint32_t)kt * b_kstep,
+                         stage + A_BYTES + TileB::lds_block(g - A_LOADS, wave) * 1024);
   };
 
-  // ---- LDS reads: element t of operand row x of k-step s is k = 16 s + 4 g4 + t ----
-  const int rswz = swz(l16);
-  auto base_of = [&](int x, int R, bool kmajor) -> int {  // x: row of the tile this lane reads
-    if (kmajor) return x * 128;
-    const int sw = R == 32 ? (g4 & 1) << 2 : g4 << 2;
-    return 4 * g4 * (R * 4) + (((x >> 2) ^ sw) << 4) + (x & 3) * 4;
-  };
+  // ---- LDS reads: element t of an operand row of k-step s is k = 16 s + 4 g4 + t ----
   int a_rd[TM], b_rd[TN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i) a_rd[i] = base_of((wm * TM + i) * 16 + l16, BM, A_KMAJOR);
+  for (int i = 0; i < TM; ++i) a_rd[i] = TileA::base((wm * TM + i) * 16, l16, g4);
 #pragma unroll
-  for (int j = 0; j < TN; ++j) b_rd[j] = A_BYTES + base_of((wn * TN + j) * 16 + l16, BN, B_KMAJOR);
-  auto read = [&](const char* st, int rd, int s, int R, bool kmajor) -> f32x4 {
-    if (kmajor) return *(const f32x4*)(st + rd + (((4 * s + g4) ^ rswz) << 4));
-    f32x4 v;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) v[t] = *(const float*)(st + rd + (16 * s + t) * (R * 4));
-    return v;
-  };
+  for (int j = 0; j < TN; ++j) b_rd[j] = TileB::base((wn * TN + j) * 16, l16, g4);
   f32x4 a[2][TM], b[2][TN], acc[TM][TN];
   auto read_one = [&](const char* st, int s, int r) {
-    if (r < TM) a[s][r] = read(st, a_rd[r], s, BM, A_KMAJOR);
-    else b[s][r - TM] = read(st, b_rd[r - TM], s, BN, B_KMAJOR);
+    if (r < TM) a[s][r] = TileA::read(st, a_rd[r], s, l16, g4);
+    else b[s][r - TM] = TileB::read(st + A_BYTES, b_rd[r - TM], s, l16, g4);
   };
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+  // lane holds output row l16 of each 16 x 16 block and columns 4 g4 .. + 3 (N % 4 == 0)
+  typename Output::Old old[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int64_t gm = m0 + (wm * TM + i) * 16 + l16, gn = n0 + (wn * TN + j) * 16 + 4 * g4;
+      if (gm < p.M && gn < p.N) old[i][j] = output.load(p, gm, gn);
+    }
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
     if (s < KT) {
@@ -174,39 +241,18 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32GemmParams p) {
   for (; kt + 1 < KT; step()) ktile(kt, sc, after(), F{}, F{});
   ktile(kt, sc, sc, F{}, T{});
 
-  // ---- lane holds output row l16 of each 16 x 16 block and columns 4 g4 .. + 3 ----
-  TC* __restrict__ C = (TC*)p.C + (int64_t)split * p.c_split_stride;
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int64_t gm = m0 + (wm * TM + i) * 16 + l16;
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      const int64_t gn = n0 + (wn * TN + j) * 16 + 4 * g4;
-      if (gm < p.M && gn < p.N) {  // N % 4 == 0
-        TC* dst = C + gm * p.ldc + gn;
-        f32x4 v = acc[i][j];
-        if constexpr (sizeof(TC) == 4) {
-          if (p.accumulate) v = p.alpha * v + p.beta * *(const f32x4*)dst;
-          *(f32x4*)dst = v;
-        } else {
-          bf16x4 o;
-          if (p.accumulate) {
-            const bf16x4 old = *(const bf16x4*)dst;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) v[t] = p.alpha * v[t] + p.beta * (float)old[t];
-          }
-#pragma unroll
-          for (int t = 0; t < 4; ++t) o[t] = (bf16)v[t];
-          *(bf16x4*)dst = o;
-        }
-      }
+      const int64_t gm = m0 + (wm * TM + i) * 16 + l16, gn = n0 + (wn * TN + j) * 16 + 4 * g4;
+      if (gm < p.M && gn < p.N) output.store(p, split, gm, gn, acc[i][j], old[i][j]);
     }
-  }
 }
 
-template <int TM, int TN, int NS>
+template <int TM, int TN, int NS, typename TA, typename TB>
 constexpr int gemm_f32_lds_bytes() {
-  return NS * (2 * TM * 16 + 2 * TN * 16) * 32 * 4;
+  return NS * (F32Tile<TA, 32 * TM, true>::BYTES + F32Tile<TB, 32 * TN, true>::BYTES);
 }
 
 // S [n, r] in float32, the generator of the fp32 layers (rows past n are not written).  One thread per four tokens of a
