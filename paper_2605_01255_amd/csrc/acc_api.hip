@@ -814,7 +814,8 @@ void gram_matrix(const RsvdPlan& pl, char* ws, int64_t m, int64_t k, const float
 // Image of the triangular factor of G [w, w] (row stride ldg), w <= 256.
 void chol_factor(const float* G, int64_t ldg, int64_t w, float* image, const float* scale_ref, float rel_tol, Launcher& L) {
   // above 128 always the most it can need: a kernel's LDS limit is raised once, to what its first launch asks for
-  L.launch_lds(chol_factor_kernel, dim3(1), dim3(kCholThreads), (size_t)chol_lds_bytes(w > 128 ? kQrMaxRank : (int)w), G, image,
+  const unsigned threads = w <= 64 ? 256 : (w <= 128 ? 512 : kCholMaxThreads);
+  L.launch_lds(chol_factor_kernel, dim3(1), dim3(threads), (size_t)chol_lds_bytes(w > 128 ? kQrMaxRank : (int)w), G, image,
                (int)w, ldg, scale_ref, rel_tol);
 }
 

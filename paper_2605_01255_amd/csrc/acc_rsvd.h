@@ -11,7 +11,7 @@ namespace acc {
 
 constexpr int kQrMaxRank = 256;            // a k x k factorisation up to this size is one launch of one work-group
 constexpr int kRsvdMaxRankBlocked = 512;   // larger ranks: the same kernels on 256 x 256 diagonal blocks (blocked Cholesky)
-constexpr int kCholThreads = 512;
+constexpr int kCholMaxThreads = 1024;
 
 // Storage of a k x k triangle for the two kernels below: 16 x 16 blocks (i, l), i >= l, of 1 KB, row by row; block (i, l)
 // at index i (i + 1) / 2 + l.  A lane that owns row l16 and columns 4 g4 .. 4 g4 + 3 of a block (the accumulator layout of
@@ -28,6 +28,11 @@ __device__ __forceinline__ TriIndex tri_index(int b) {
   return TriIndex{i, b - tri_block(i, 0)};
 }
 
+// v of lane J of each aligned group of 16 lanes, to all of them (DPP row_newbcast).
+template <int J> __device__ __forceinline__ float bcast16(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x150 + J, 0xF, 0xF, true));
+}
+
 __device__ __forceinline__ float lane_bcast(float v, int src_lane) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), src_lane));
 }
@@ -35,9 +40,10 @@ __device__ __forceinline__ float lane_bcast(float v, int src_lane) {
 // The upper triangular factor R of G = R^T R (G [k, k] symmetric positive semi-definite, fp32, k <= 256, positive diagonal
 // of R) in the form chol_solve_kernel multiplies with, by ONE work-group.  The k steps of an elimination are a serial chain;
 // what a step costs is everything.  Blocked by 16 columns, G in LDS:
-//   panel     every wave eliminates the same 16 x 16 diagonal block in its lanes 0 .. 15 and 48 rows below it in the others
-//             (one row per lane, its 16 panel columns in registers): the pivot row comes by v_readlane, so the 16 steps need
-//             neither LDS nor a barrier, and no wave waits for another
+//   panel     one row below the diagonal block per lane, its 16 panel columns in registers, and beside it row lane % 16 of
+//             the block itself, the same in every 16 lanes: the pivot row comes from lane j of each 16 by a DPP broadcast
+//             inside the multiply-add, so the 16 steps need neither LDS, scalar registers nor a barrier, and no wave
+//             waits for another.  (With v_readlane broadcasts instead, two wait states each: 25 / 73 us at k = 128 / 256.)
 //   trailing  A_il -= (V_i D^-1) V_l^T on the 16x16x4 instruction, blocks dealt to the waves
 // in the square-root-free form (A = L D L^T, one reciprocal per step on the chain).  Rows of finished panels are never read
 // again above the diagonal, so the elimination runs unmasked.
@@ -46,13 +52,14 @@ __device__ __forceinline__ float lane_bcast(float v, int src_lane) {
 // A pivot at or below rel_tol times the largest diagonal entry (of G, or *scale_ref: of the matrix G is a block of) counts
 // as zero: column j of the factored matrix depends on the earlier ones.  Its row and column of the image are zero, so the
 // corresponding basis vector comes out as zero and the span of the others is unchanged.
-// Measured at k = 32 / 64 / 128 / 256: 8.7 / 12.7 / 25 / 73 us.  The one-wave elimination this replaced (the pivot row
+// Measured at k = 32 / 64 / 128 / 256: 8 / 12 / 23 / 62 us.  The one-wave elimination this replaced (the pivot row
 // through LDS at every step, one matrix row per lane, 64 columns at most) took 12 / 39 us, and ranks above 64 a chain of
 // three launches per 64 columns: about 115 us at k = 128.
-__global__ __launch_bounds__(kCholThreads) void chol_factor_kernel(const float* __restrict__ G, float* __restrict__ image,
-                                                                   int k, int64_t ldg, const float* __restrict__ scale_ref, float rel_tol) {
+__global__ __launch_bounds__(kCholMaxThreads) void chol_factor_kernel(const float* __restrict__ G, float* __restrict__ image,
+                                                                      int k, int64_t ldg, const float* __restrict__ scale_ref,
+                                                                      float rel_tol) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  constexpr int NW = kCholThreads / 64;
+  const int NW = (int)(blockDim.x >> 6);
   float* const A = (float*)smem;                                     // tri_block storage
   const int nb = (k + 15) / 16;
   float* const inv = A + tri_block(nb, 0) * 256;                     // 1 / pivot per column, 0 for a dropped one
@@ -117,50 +124,61 @@ __global__ __launch_bounds__(kCholThreads) void chol_factor_kernel(const float* 
   };
 
   for (int p = 0; p < nb; ++p) {
-    // ---- panel: lane < 16 row `lane` of the diagonal block, lane >= 16 one of the rows below (at most 240: the last
-    //      waves are free, one of them inverts the block before) ----
+    // ---- panel ----
     const int below = (nb - p - 1) * 16;
-    float a[16];
-    if (wave == NW - 1 && p > 0) invert(p - 1);
-    if (wave == 0 || wave * 48 < below) {
-      const int r = lane < 16 ? lane : 16 + wave * 48 + lane - 16;     // row inside the panel
-      const bool real = r < 16 + below;
-      float* row = A + tri_block(p + (r >> 4), p) * 256 + (r & 15) * 16;
+    float d[16];
+    if (wave == 0 || wave * 64 < below) {
+      const int r = wave * 64 + lane;     // row below the diagonal block
+      const bool real = r < below;
+      const float* diag = A + tri_block(p, p) * 256 + l16 * 16;
+      float* row = A + tri_block(p + 1 + (r >> 4), p) * 256 + l16 * 16;
+      float a[16], pivots[16], inverses[16];
 #pragma unroll
       for (int c = 0; c < 16; c += 4) {
-        const f32x4 v = real ? *(const f32x4*)(row + c) : f32x4{0.f, 0.f, 0.f, 0.f};
+        const f32x4 v = real ? *(const f32x4*)(row + c) : f32x4{0.f, 0.f, 0.f, 0.f}, w = *(const f32x4*)(diag + c);
 #pragma unroll
-        for (int t = 0; t < 4; ++t) a[c + t] = v[t];
+        for (int t = 0; t < 4; ++t) { a[c + t] = v[t]; d[c + t] = w[t]; }
       }
-      float my_inv = 0.f, my_piv = 0.f;
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const float piv = lane_bcast(a[j], j);
+      static_for<0, 16>([&](auto step) {
+        constexpr int j = decltype(step)::value;
+        const float piv = bcast16<j>(d[j]);
         const bool dead = !(piv > tol);
         // reciprocal: hardware estimate + one Newton step (about 1 ulp); the factor's own scaling uses square roots
         float inv_p = __builtin_amdgcn_rcpf(piv);
         inv_p = fmaf(fmaf(-piv, inv_p, 1.f), inv_p, inv_p);
         inv_p = dead ? 0.f : inv_p;
-        my_inv = lane == j ? inv_p : my_inv;
-        my_piv = lane == j && !dead ? piv : my_piv;
-        const float t = a[j] * inv_p;
+        inverses[j] = inv_p;
+        pivots[j] = dead ? 0.f : piv;
+        const float td = -(d[j] * inv_p), ta = -(a[j] * inv_p);
 #pragma unroll
-        for (int c = j + 1; c < 16; ++c) a[c] = fmaf(-t, lane_bcast(a[c], j), a[c]);
-      }
-      if (real && lane >= 16) {
+        for (int c = j + 1; c < 16; ++c) {
+          const float u = bcast16<j>(d[c]);
+          d[c] = fmaf(u, td, d[c]);
+          a[c] = fmaf(u, ta, a[c]);
+          // used under a condition only: without this the compiler moves the rows' updates there, behind the block's
+          // sixteen steps, and keeps (spills) all their broadcasts until then
+          asm volatile("" : "+v"(a[c]));
+        }
+      });
+      if (real) {
 #pragma unroll
         for (int c = 0; c < 16; c += 4) *(f32x4*)(row + c) = f32x4{a[c], a[c + 1], a[c + 2], a[c + 3]};
       }
-      if (wave == 0 && lane < 16) {
-        inv[p * 16 + lane] = my_inv;
-        scale[p * 16 + lane] = my_piv > 0.f ? 1.f / sqrtf(my_piv) : 0.f;
+      if (wave == 0 && lane == 0) {  // every lane holds all 16 pivots
+#pragma unroll
+        for (int c = 0; c < 16; c += 4) {
+          *(f32x4*)(inv + p * 16 + c) = f32x4{inverses[c], inverses[c + 1], inverses[c + 2], inverses[c + 3]};
+          *(f32x4*)(scale + p * 16 + c) = f32x4{pivots[c], pivots[c + 1], pivots[c + 2], pivots[c + 3]};
+        }
       }
     }
     __syncthreads();
     if (wave == 0 && lane < 16) {  // only now: until the barrier the other waves were reading the block; all their copies are the same
       float* row = A + tri_block(p, p) * 256 + lane * 16;
 #pragma unroll
-      for (int c = 0; c < 16; c += 4) *(f32x4*)(row + c) = f32x4{a[c], a[c + 1], a[c + 2], a[c + 3]};
+      for (int c = 0; c < 16; c += 4) *(f32x4*)(row + c) = f32x4{d[c], d[c + 1], d[c + 2], d[c + 3]};
+      const float piv = scale[p * 16 + lane];
+      scale[p * 16 + lane] = piv > 0.f ? 1.f / sqrtf(piv) : 0.f;
     }
     // ---- trailing blocks (i, l), p < l <= i: rows of V_i against rows of V_l over the panel's 16 columns, two at a time ----
     {
@@ -188,7 +206,7 @@ __global__ __launch_bounds__(kCholThreads) void chol_factor_kernel(const float* 
     }
     __syncthreads();
   }
-  if (wave == NW - 1) invert(nb - 1);
+  for (int J = wave; J < nb; J += NW) invert(J);  // all at once: one beside each panel was the slower of the two
 
   // ---- off-diagonal blocks of the image ----
   for (int b = wave; b < blocks; b += NW) {
