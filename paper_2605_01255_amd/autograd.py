@@ -94,8 +94,8 @@ class CompressedLinearFunction(torch.autograd.Function):
         db = None
         if has_bias:
             db = torch.empty(d_out, dtype=dt, device=dev)
-            bdesc = acc.make_desc(n, d_in, d_out, rank, seed=seed, io_dtype=code)
-            acc.acc_linear_bias_grad(bdesc, dy2, db, _workspace(acc.acc_linear_workspace_bytes(bdesc, True), dev))
+            # the backward pass is done with its workspace in stream order, and it is large enough for both
+            acc.acc_linear_bias_grad(desc, dy2, db, ws)
         return dx.reshape(x_shape), dw, db, None, None, None, None, None
 
 
