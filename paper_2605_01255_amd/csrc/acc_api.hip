@@ -409,19 +409,21 @@ struct ReduceJob {
   int64_t row, ld;  // the result's rows hold `row` elements and are stored `ld` apart
 };
 
-// Which kernel and tile a product takes: the least of five estimates, launch + rounds x (cost of a tile + K tiles x time of
+// Which kernel and tile a product takes: the least of six estimates, launch + rounds x (cost of a tile + K tiles x time of
 // a K tile), in nanoseconds, with rounds = tiles over 256 compute units.  A larger tile needs fewer bytes from L2 per
 // multiply-add (a 128 x 128 K tile multiplies for 0.2 us and takes 0.36 to move, however many stages are in flight), a
 // smaller one leaves fewer compute units idle.  From two rounds on, two work-groups of two stages per compute unit cover
 // each other's waits better than one of four (4096 x 2048 x 2048 on 128 x 128: 34 against 41 us).  The constants are fits
-// to 45 shapes from 256 x 512 x 512 to 16384 x 3072 x 8192, good to about 15 %; measured us on 256 x 256 / 192 x 128 /
+// to 45 shapes from 256 x 512 x 512 to 16384 x 3072 x 8192, good to about 15 %.  256 x 192 is there for the shapes that it
+// makes one full round of: 4096 x 3072 x 3072 62 us (192 tiles of 256 x 256: 72), 8192 x 1032 x 4096 68 (73); where both fill
+// the chip the persistent 256 x 256 kernel is ahead (16384 x 3072 x 3072: 255).  Measured us on 256 x 256 / 192 x 128 /
 // 128 x 128 / 128 x 64 / 64 x 64, with what the kernels this replaced took (256 x 256 from 192 tiles on, else a two-stage
 // 128 x 128) in brackets:
 //   16384 x 3072 x 3072 228 / 293 / 286 /  - /  - [228]    16384 x 1152 x 3072 139 / 116 / 129 / 166 / 222 [139]
 //   6000 x 4096 x 4096  188 / 168 / 180 /  - /  - [188]    4096 x 2048 x 2048   53 /  38 /  34 /  41 /   - [35]
 //   4096 x 1024 x 3072   71 /  30 /  29 / 30 / 39 [36-41]  1053 x 3048 x 1600   35 /  18 /  15 /  17 /  22
 //   384 x 3072 x 3072    57 /  28 /  23 / 17 / 16 [34]     2048 x 1024 x 1024   27 /  14 /  12 / 9.0 / 9.4
-enum class GemmTile { k256, k192x128, k128, k128x64, k64 };
+enum class GemmTile { k256, k256x192, k192x128, k128, k128x64, k64 };
 struct GemmChoice {
   GemmTile tile;
   bool one_round;
@@ -429,6 +431,7 @@ struct GemmChoice {
 GemmChoice pick_gemm_tile(int64_t M, int64_t N, int64_t K, bool persist_ok) {
   struct Cost { GemmTile tile; int bm, bn, launch, per_tile, per_k, alone_per_tile, alone_per_k; };  // alone: one round
   static const Cost costs[] = {{GemmTile::k256, 256, 256, 5000, 2000, 1330, 2000, 1330},
+                               {GemmTile::k256x192, 256, 192, 3000, 3500, 1180, 5000, 1120},
                                {GemmTile::k192x128, 192, 128, 3000, 1700, 580, 3500, 500},
                                {GemmTile::k128, 128, 128, 3000, 2000, 460, 3000, 370},
                                {GemmTile::k128x64, 128, 64, 3000, 1500, 280, 1500, 260},
@@ -486,6 +489,7 @@ void fast_gemm(const void* A, const void* B, void* C, int64_t M, int64_t N, int6
         else L.launch_lds(gemm16_persist_kernel<KMAJ>, dim3(256), dim3(256), (size_t)160 * 1024, p, (int)slots);
       }
       break;
+    case GemmTile::k256x192: ring_gemm<8, 6, 2, KMAJ, TC>(p, L); break;
     case GemmTile::k192x128:
       if (c.one_round) ring_gemm<6, 4, 4, KMAJ, TC>(p, L);
       else ring_gemm<6, 4, 2, KMAJ, TC>(p, L);

@@ -1,4 +1,4 @@
-// bf16 GEMM on a ring of LDS stages, for products that do not fill the chip with 256 x 256 tiles (steps F1, B1, B3):
+// bf16 GEMM on a ring of LDS stages, for products that do not fill whole rounds of the chip with 256 x 256 tiles (steps F1, B1, B3):
 // C[M, N] = A[M, K] . B, fp32 accumulate, bf16 or fp32 output, optionally C = beta C + alpha (A . B).
 //
 //   A is row-major with K contiguous.  B_KMAJOR = true: Bt[N, K];  false: B[K, N], N contiguous.
@@ -25,7 +25,8 @@ namespace acc {
 // Swizzles of an N-contiguous B tile (see swz_n16): the 4 k rows x 2 groups that 32 lanes of a transposing read touch
 // fall on 8 different 32-byte bank groups.  A 64-column row covers half the banks, rows alternate between the halves.
 template <int BN> __device__ __forceinline__ int swz_ring(int krow) {
-  if constexpr (BN == 64) return (((krow >> 1) & 1) << 1) | (((krow >> 3) & 1) << 2);
+  // (so do the 384-byte rows of 192 columns, whose chunks stay inside an aligned group of eight)
+  if constexpr (BN == 64 || BN == 192) return (((krow >> 1) & 1) << 1) | (((krow >> 3) & 1) << 2);
   else return swz_n16(krow);
 }
 
@@ -53,7 +54,7 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(FastGemmParams p) {
   constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE = A_BYTES + B_BYTES;
   constexpr int A_LOADS = A_BYTES / 1024 / NW, B_LOADS = B_BYTES / 1024 / NW, NG = A_LOADS + B_LOADS;
   constexpr int BN_CHUNKS = BN / 8;
-  static_assert(BN == 64 || BN == 128, "N-contiguous swizzle");
+  static_assert(BN == 64 || BN == 128 || BN == 192, "N-contiguous swizzle");
   static_assert((NS - 1) * NG <= 63, "vmcnt range");
 
   int tm, tn;
@@ -79,9 +80,9 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(FastGemmParams p) {
     if (B_KMAJOR) {
       b_src[t] = (uint32_t)(((t * NW + wave) * 8 + (lane >> 3)) * p.ldb * 2 + (kchunk << 4));
     } else {
-      constexpr int ROWS = 64 / BN_CHUNKS;
-      const int krow = (t * NW + wave) * ROWS + lane / BN_CHUNKS;
-      b_src[t] = (uint32_t)(krow * p.ldb * 2 + (((lane % BN_CHUNKS) ^ swz_ring<BN>(krow)) << 4));
+      const int c = (t * NW + wave) * 64 + lane;  // 16-byte chunk of the tile in LDS order
+      const int krow = c / BN_CHUNKS;
+      b_src[t] = (uint32_t)(krow * p.ldb * 2 + (((c % BN_CHUNKS) ^ swz_ring<BN>(krow)) << 4));
     }
   }
   // last K tile: this lane's chunk lies past K (whole chunks: K % 8 == 0)

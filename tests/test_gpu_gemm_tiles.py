@@ -28,6 +28,7 @@ SHAPES = [
     (2050, 3080, 1000),   # 128 x 128, several tiles per compute unit
     (1100, 5000, 2000),   # 192 x 128, one round of tiles
     (4000, 2056, 392),    # 192 x 128, several tiles per compute unit
+    (4090, 3064, 392),    # 256 x 192, one round of tiles
     (8200, 4104, 136),    # 256 x 256, three K tiles, several tiles per work-group
     (600, 18008, 136),    # 256 x 256, three rows of tiles
 ]
