@@ -543,37 +543,41 @@ void gemm8(const void* A, int a_format, const void* B, void* C, int64_t M, int64
   else L.launch_lds(gemm8_persist_kernel<KMAJ, 0>, dim3(256), dim3(256), (size_t)160 * 1024, p, (int)slots);
 }
 
-// K splits of a skinny product: as many as fill the chip's resident work-group slots exactly once (a
-// second, partly filled round would cost a whole extra pass of load latencies), each with at least
-// four K tiles.  lds_bytes: dynamic LDS of the kernel variant (4 waves per work-group).
-int64_t splitk_count(int64_t tiles, int64_t K, int lds_bytes) {
-  int64_t per_cu = (160 * 1024) / lds_bytes;
-  if (per_cu > 4) per_cu = 4;  // measured: five resident 64 x 64 work-groups per CU run slower than four
+// Most K splits of a skinny product: what the workspace has room for.  tile_bytes: LDS of two stages of the product's
+// tile; splits of at least four K tiles.
+int64_t splitk_count(int64_t tiles, int64_t K, int tile_bytes) {
+  int64_t per_cu = (160 * 1024) / tile_bytes;
+  if (per_cu > 4) per_cu = 4;
   int64_t splits = (256 * per_cu) / tiles;
   if (splits > K / 256) splits = K / 256;
   return splits < 1 ? 1 : splits;
 }
+template <int TM, int TN> constexpr int splitk_tile_bytes() { return gemm_ring_lds_bytes<TM, TN, 2>(); }
 
-// Skinny product through the tuned kernel, the K range split over groups of work-groups (splitk_count):
-// part[s][M][ldc] = A[:, K range s] . B[K range s, :], fp32.  Returns the number of splits.  kb_rows: rows of an N-contiguous B that exist (K may be A's zero-padded length).
-template <int WM, int WN, int TM, int TN, bool KMAJ>
+// Skinny product on the ring kernel, the K range split over groups of work-groups:
+// part[s][M][ldc] = A[:, K range s] . B[K range s, :], fp32.  Returns the number of splits.  kb_rows: rows of an
+// N-contiguous B that exist (K may be A's zero-padded length).  Bound by the transfer of the wide operand, so two
+// work-groups per compute unit with three stages each in flight, and no more splits than that takes: the partials are
+// written and read back (16384 x 3072 by 3072 x 64: four splits on the two-stage kernel before, 34 us; RING_US).
+template <int TM, int TN, bool KMAJ>
 int fast_gemm_splitk(const void* A, const void* B, float* part, int64_t M, int64_t N, int64_t K, int64_t lda,
                      int64_t ldb, int64_t ldc, int64_t kb_rows, Launcher& L) {
-  constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
+  constexpr int BM = 32 * TM, BN = 32 * TN, NS = 3;
   FastGemmParams p{};
   p.A = (const bf16*)A; p.B = (const bf16*)B; p.C = part;
   p.M = M; p.N = N; p.K = K; p.lda = lda; p.ldb = ldb; p.ldc = ldc;
   p.kb_rows = kb_rows;
-  gemm_bf16_plan(p, BM, BN);  // tiles_m, tiles_n; the XCD super-tile order is not used with splits
+  const unsigned grid = gemm_ring_plan(p, BM, BN);
   const int64_t tiles = ceil_div(M, BM) * ceil_div(N, BN);
-  const unsigned tile_blocks = (unsigned)tiles;
-  int64_t splits = splitk_count(tiles, K, gemm_bf16_lds_bytes<WM, WN, TM, TN>());
+  int64_t splits = ceil_div(512, tiles);
+  const int64_t most = splitk_count(tiles, K, splitk_tile_bytes<TM, TN>());
+  if (splits > most) splits = most;
   p.k_per_split = round_up(ceil_div(K, splits), 64);
   splits = ceil_div(K, p.k_per_split);
-  p.tile_blocks = (int)tile_blocks;
+  p.tile_blocks = (int)grid;
   p.c_split_stride = M * ldc;
-  L.launch_lds(gemm_bf16_kernel<WM, WN, TM, TN, KMAJ, float>, dim3(tile_blocks * (unsigned)splits), dim3(WM * WN * 64),
-               (size_t)gemm_bf16_lds_bytes<WM, WN, TM, TN>(), p);
+  L.launch_lds(gemm_ring_kernel<TM, TN, NS, KMAJ, float, true>, dim3(grid * (unsigned)splits), dim3(256),
+               (size_t)gemm_ring_lds_bytes<TM, TN, NS>(), p);
   return (int)splits;
 }
 
@@ -753,15 +757,15 @@ RsvdPlan plan_rsvd(const acc_linear_desc* d, const Shape& s, bool backward) {
     }
   }
   if (pl.tuned) {
-    const int64_t fact_splits = splitk_count(ceil_div(k, 64) * ceil_div(channels, 128), pl.n_pad, gemm_bf16_lds_bytes<2, 2, 1, 2>());
+    const int64_t fact_splits = splitk_count(ceil_div(k, 64) * ceil_div(channels, 128), pl.n_pad, splitk_tile_bytes<2, 4>());
     pl.off_fact_part = take((size_t)fact_splits * k * channels * 4);
     pl.off_ut = take((size_t)2 * k * pl.n_pad * 2);  // U^T, or [U_hi; U_lo]^T during subspace iterations
     if (!backward && rsvd_power_iters(d)) {
-      const int64_t zt_splits = splitk_count(ceil_div(2 * k, 64) * ceil_div(s.d_in, 128), pl.n_pad, gemm_bf16_lds_bytes<2, 2, 1, 2>());
+      const int64_t zt_splits = splitk_count(ceil_div(2 * k, 64) * ceil_div(s.d_in, 128), pl.n_pad, splitk_tile_bytes<2, 4>());
       pl.off_zt_part = take((size_t)zt_splits * 2 * k * s.d_in * 4);
     }
     if (!backward) {
-      const int64_t yr_splits = splitk_count(ceil_div(s.n, 64) * ceil_div(2 * k, 64), s.d_in, gemm_bf16_lds_bytes<2, 2, 1, 1>());
+      const int64_t yr_splits = splitk_count(ceil_div(s.n, 64) * ceil_div(2 * k, 64), s.d_in, splitk_tile_bytes<2, 2>());
       pl.off_omega = take((size_t)2 * k * s.d_in * 2);
       pl.off_yr_part = take((size_t)yr_splits * s.n * 2 * k * 4);
     }
@@ -941,7 +945,7 @@ void rsvd_factor_tuned(const acc_linear_desc* d, const Shape& s, const RsvdPlan&
   if (U)  // backward: rebuild the transpose from the stored factor; forward wrote it with the last QR pass
     L(transpose_pad_kernel<bf16>, dim3((unsigned)ceil_div(pl.n_pad * k, 256)), dim3(256), (const bf16*)U, s.n, (int)k,
       pl.n_pad, ut);
-  const int splits = fast_gemm_splitk<2, 2, 1, 2, false>(ut, A, part, k, channels, pl.n_pad, pl.n_pad, lda, channels,
+  const int splits = fast_gemm_splitk<2, 4, false>(ut, A, part, k, channels, pl.n_pad, pl.n_pad, lda, channels,
                                                        s.n, L);
   const unsigned blocks = (unsigned)ceil_div(k * channels, 256);
   if (transposed) L(reduce_store_kernel<bf16, false>, dim3(blocks), dim3(256), (const float*)part, splits, k, channels, (bf16*)out);
@@ -1318,7 +1322,7 @@ int acc_linear_fwd_rsvd(const acc_linear_desc* desc, const void* X, const void* 
   // halves and splits folded
   auto times_hilo = [&]() {
     float* yr_part = (float*)(ws + pl.off_yr_part);
-    const int splits = fast_gemm_splitk<2, 2, 1, 1, true>(X, omega, yr_part, s.n, 2 * k, s.d_in, s.ldx, s.d_in, 2 * k,
+    const int splits = fast_gemm_splitk<2, 2, true>(X, omega, yr_part, s.n, 2 * k, s.d_in, s.ldx, s.d_in, 2 * k,
                                                         0, L);
     L(combine_hilo_kernel, dim3((unsigned)ceil_div(s.n * k, 256)), dim3(256), (const float*)yr_part, splits, s.n, (int)k,
       y0);
@@ -1358,7 +1362,7 @@ int acc_linear_fwd_rsvd(const acc_linear_desc* desc, const void* X, const void* 
       // U as hi + lo parts, transposed; Z^T = [U_hi; U_lo] . X over the tokens with the K range split
       cholesky_qr_pass(s, pl, ws, s.n, pl.n_pad, y0, nullptr, nullptr, ACC_F32, ut, pl.n_pad, true, L);
       float* zt_part = (float*)(ws + pl.off_zt_part);
-      const int splits = fast_gemm_splitk<2, 2, 1, 2, false>(ut, X, zt_part, 2 * k, s.d_in, pl.n_pad, pl.n_pad, s.ldx,
+      const int splits = fast_gemm_splitk<2, 4, false>(ut, X, zt_part, 2 * k, s.d_in, pl.n_pad, pl.n_pad, s.ldx,
                                                            s.d_in, s.n, L);
       L(combine_hilo_t_kernel, dim3((unsigned)ceil_div(k * s.d_in, 256)), dim3(256), (const float*)zt_part, splits,
         s.d_in, (int)k, z0);

@@ -41,10 +41,9 @@ struct FastGemmParams {
   int64_t red_row, red_ld;  // the result has rows of red_row elements (red_row % 4 == 0) stored red_ld apart
   int accumulate;         // 0: C = A . B;  1: C = beta C + alpha (A . B) (a bf16 C rounds the product, then the sum)
   float alpha, beta;      // used when accumulate; 1, 1 is the plain sum
-  // Optional split of the K range over work-groups (skinny products whose M x N tiles alone do not fill
-  // the chip): tile_blocks == 0 means no split.  Block b works on tile b % tile_blocks and K range
-  // [s * k_per_split, min(K, (s + 1) * k_per_split)), s = b / tile_blocks, and stores its partial product
-  // at C + s * c_split_stride.  k_per_split % 64 == 0.
+  // Split of the K range over work-groups (gemm_ring_kernel with SPLIT: skinny products whose M x N tiles alone do
+  // not fill the chip).  Block b works on tile b % tile_blocks and K range [s * k_per_split, min(K, (s + 1) *
+  // k_per_split)), s = b / tile_blocks, and stores its partial product at C + s * c_split_stride.  k_per_split % 64 == 0.
   int tile_blocks;
   int64_t k_per_split;
   int64_t c_split_stride;
@@ -113,11 +112,6 @@ __device__ __forceinline__ void wait_vmcnt0() { asm volatile("s_waitcnt vmcnt(0)
 // (work-groups are dealt round-robin to the 8 XCDs) form a super_m x super_n block that shares
 // A and B panels in that XCD's L2.  Returns false for padding work-groups.
 __device__ __forceinline__ bool xcd_tile(const FastGemmParams& p, int b, int& tm, int& tn) {
-  if (p.tile_blocks) {  // split-K launches of skinny products: few tiles, plain order, no padding blocks
-    tm = b % p.tiles_m;
-    tn = b / p.tiles_m;
-    return tn < p.tiles_n;
-  }
   const int xcd = b & 7, local = b >> 3;
   const int sid = (local >> 5) * 8 + xcd;  // super-tile id, N fastest
   const int in = local & 31;
@@ -142,14 +136,6 @@ __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, c
   static_assert(B_KMAJOR || (BN_CHUNKS >= 16 && 64 % BN_CHUNKS == 0), "B tile shape");
 
   int tm, tn;
-  int64_t k0 = 0, k1 = p.K;  // this work-group's K range
-  int split = 0;
-  if (p.tile_blocks) {
-    split = b / p.tile_blocks;
-    b -= split * p.tile_blocks;
-    k0 = (int64_t)split * p.k_per_split;
-    k1 = k0 + p.k_per_split < p.K ? k0 + p.k_per_split : p.K;
-  }
   const bool has_tile = xcd_tile(p, b, tm, tn);
   if (!has_tile && p.red_count == 0) return;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -163,11 +149,10 @@ __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, c
   // buffer resources that start at the tile's first row / column; rows past the end of the matrix
   // read as zero (their products are never stored).
   const int64_t am0 = m0, bn0 = n0;
-  const int64_t kb = p.kb_rows ? p.kb_rows : p.K;
-  const u32x4 a_rsrc = make_rsrc(p.A + am0 * p.lda + k0, ((p.M - am0 - 1) * p.lda + p.K - k0) * 2);
+  const u32x4 a_rsrc = make_rsrc(p.A + am0 * p.lda, ((p.M - am0 - 1) * p.lda + p.K) * 2);
   const u32x4 b_rsrc =
-      B_KMAJOR ? make_rsrc(p.B + bn0 * p.ldb + k0, ((p.N - bn0 - 1) * p.ldb + p.K - k0) * 2)
-               : make_rsrc(p.B + k0 * p.ldb + bn0, kb > k0 ? ((kb - k0 - 1) * p.ldb + (p.N - bn0)) * 2 : 0);
+      B_KMAJOR ? make_rsrc(p.B + bn0 * p.ldb, ((p.N - bn0 - 1) * p.ldb + p.K) * 2)
+               : make_rsrc(p.B + bn0, ((p.K - 1) * p.ldb + (p.N - bn0)) * 2);
   uint32_t a_src[A_LOADS];
 #pragma unroll
   for (int t = 0; t < A_LOADS; ++t) {
@@ -190,10 +175,10 @@ __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, c
     }
   }
   const uint32_t b_kstep = B_KMAJOR ? BK * 2 : (uint32_t)(BK * p.ldb * 2);  // bytes per K tile
-  // last K tile: this lane's chunk lies past the K range (rows NW * 8 apart share their swizzle: NW is even)
+  // last K tile: this lane's chunk lies past K (rows NW * 8 apart share their swizzle: NW is even)
   static_assert(NW % 2 == 0, "swizzle period");
-  const int KT = (int)((k1 - k0 + BK - 1) / BK);
-  const uint32_t tail = ((lane & 7) ^ swz(wave * 8 + (lane >> 3))) * 8 >= k1 - k0 - (int64_t)(KT - 1) * BK ? 0xFFFFFFF0u : 0u;
+  const int KT = (int)((p.K + BK - 1) / BK);
+  const uint32_t tail = ((lane & 7) ^ swz(wave * 8 + (lane >> 3))) * 8 >= p.K - (int64_t)(KT - 1) * BK ? 0xFFFFFFF0u : 0u;
 
   // ---- LDS read offsets of this lane's MFMA operands ----
   const int lrow = lane & 31, kg = lane >> 5;
@@ -254,6 +239,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, c
   // while the texture path drains and starves the MFMA pipe.
   constexpr int NM = TM * TN;
   constexpr int NG_TOTAL = A_LOADS + B_LOADS;
+  static_assert(NM >= TM + TN && 2 * NM >= NG_TOTAL, "at most one operand read and one transfer per MFMA");
   // The transfers of a tile are spread over the first two k-steps after the barrier that releases their
   // stage (the last k-step of one loop trip and the first of the next): they then have two to three
   // k-steps to land before the next barrier.  Spread over the three k-steps that end at that barrier, as
@@ -280,27 +266,15 @@ __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, c
           else if (r <= TN) read_b1(rd_stage, rd_s, r - 1, nb);
           else if (r < TM + TN) read_a1(rd_stage, rd_s, r - TN, na);
         }
-      } else if constexpr (NM >= TM + TN) {
+      } else {
         if (q < TM) read_a1(rd_stage, rd_s, q, na);
         else if (q < TM + TN) read_b1(rd_stage, rd_s, q - TM, nb);
-      } else {  // small tiles: fewer MFMAs than operand reads, several reads per MFMA
-#pragma unroll
-        for (int i = q; i < TM + TN; i += NM) {
-          if (i < TM) read_a1(rd_stage, rd_s, i, na);
-          else read_b1(rd_stage, rd_s, i - TM, nb);
-        }
       }
-      if constexpr (NM < G_PER_STEP) {  // fewer MFMAs than wave-loads in a k-step: several loads per MFMA
-#pragma unroll
-        for (int i = q; i < G_PER_STEP; i += NM)
-          if (i < g_count && g_first + i < NG_TOTAL) issue_one(g_first + i, kt_next, nxt);
+      if constexpr (NM >= 2 * (TM + TN) && G_EVERY == 2) {  // transfers on the odd MFMAs, reads on the even ones
+        if (q % 2 == 1 && q / 2 < g_count && g_first + q / 2 < NG_TOTAL) issue_one(g_first + q / 2, kt_next, nxt);
       } else {
-        if constexpr (NM >= 2 * (TM + TN) && G_EVERY == 2) {  // transfers on the odd MFMAs, reads on the even ones
-          if (q % 2 == 1 && q / 2 < g_count && g_first + q / 2 < NG_TOTAL) issue_one(g_first + q / 2, kt_next, nxt);
-        } else {
-          if (q % G_EVERY == 0 && q / G_EVERY < g_count && g_first + q / G_EVERY < NG_TOTAL)
-            issue_one(g_first + q / G_EVERY, kt_next, nxt);
-        }
+        if (q % G_EVERY == 0 && q / G_EVERY < g_count && g_first + q / G_EVERY < NG_TOTAL)
+          issue_one(g_first + q / G_EVERY, kt_next, nxt);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -383,7 +357,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, c
   static_assert(NW * WAVE_B <= 2 * STAGE, "epilogue staging exceeds the pipeline's LDS");
   __syncthreads();                               // every wave is done with the pipeline's LDS
   char* stage_w = smem + wave * WAVE_B;
-  TC* __restrict__ C = (TC*)p.C + (int64_t)split * p.c_split_stride;
+  TC* __restrict__ C = (TC*)p.C;
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
 #pragma unroll

@@ -46,7 +46,9 @@ template <typename P> __device__ __forceinline__ bool ring_tile(const P& p, int 
 
 template <int N> __device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
-template <int TM, int TN, int NS, bool B_KMAJOR, typename TC>
+// SPLIT: the K range is split over groups of tile_blocks work-groups (skinny products of the RSVD path), each storing its
+// partial product at C + split * c_split_stride; kb_rows as in gemm_bf16_tile.
+template <int TM, int TN, int NS, bool B_KMAJOR, typename TC, bool SPLIT = false>
 __global__ __launch_bounds__(256) void gemm_ring_kernel(FastGemmParams p) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   constexpr int NW = 4, WN = 2;
@@ -58,19 +60,23 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(FastGemmParams p) {
   static_assert((NS - 1) * NG <= 63, "vmcnt range");
 
   int tm, tn;
-  const bool has_tile = ring_tile(p, (int)blockIdx.x, tm, tn);
+  const int split = SPLIT ? (int)blockIdx.x / p.tile_blocks : 0;
+  const bool has_tile = ring_tile(p, (int)blockIdx.x - split * (SPLIT ? p.tile_blocks : 0), tm, tn);
   if (!has_tile && p.red_count == 0) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
   const int l16 = lane & 15, g4 = lane >> 4;
   const int64_t m0 = has_tile ? (int64_t)tm * BM : 0, n0 = has_tile ? (int64_t)tn * BN : 0;
-  const int KT = (int)((p.K + BK - 1) / BK);
+  const int64_t k0 = SPLIT ? (int64_t)split * p.k_per_split : 0;
+  const int64_t kn = SPLIT && k0 + p.k_per_split < p.K ? p.k_per_split : p.K - k0;   // this work-group's K range
+  const int64_t kb = SPLIT && p.kb_rows && p.kb_rows < k0 + kn ? p.kb_rows - k0 : kn;  // rows of an N-contiguous B in it
+  const int KT = (int)((kn + BK - 1) / BK);
 
   // ---- global -> LDS: wave-load t of wave w fills LDS bytes [(t * NW + w) * 1024, +1024) of the operand tile ----
-  const u32x4 a_rsrc = make_rsrc(p.A + m0 * p.lda, ((p.M - m0 - 1) * p.lda + p.K) * 2);
-  const u32x4 b_rsrc = B_KMAJOR ? make_rsrc(p.B + n0 * p.ldb, ((p.N - n0 - 1) * p.ldb + p.K) * 2)
-                                : make_rsrc(p.B + n0, ((p.K - 1) * p.ldb + (p.N - n0)) * 2);
+  const u32x4 a_rsrc = make_rsrc(p.A + m0 * p.lda + k0, ((p.M - m0 - 1) * p.lda + kn) * 2);
+  const u32x4 b_rsrc = B_KMAJOR ? make_rsrc(p.B + n0 * p.ldb + k0, ((p.N - n0 - 1) * p.ldb + kn) * 2)
+                                : make_rsrc(p.B + k0 * p.ldb + n0, kb > 0 ? ((kb - 1) * p.ldb + (p.N - n0)) * 2 : 0);
   uint32_t a_src[A_LOADS], b_src[B_LOADS];
   const int kchunk = (lane & 7) ^ swz(wave * 8 + (lane >> 3));  // the same for every wave-load: rows 32 apart share swz
 #pragma unroll
@@ -86,7 +92,7 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(FastGemmParams p) {
     }
   }
   // last K tile: this lane's chunk lies past K (whole chunks: K % 8 == 0)
-  const uint32_t tail = kchunk * 8 >= p.K - (int64_t)(KT - 1) * BK ? 0xFFFFFFF0u : 0u;
+  const uint32_t tail = kchunk * 8 >= kn - (int64_t)(KT - 1) * BK ? 0xFFFFFFF0u : 0u;
   const uint32_t b_kstep = B_KMAJOR ? BK * 2 : (uint32_t)(BK * p.ldb * 2);
   const uint32_t smem_lds = (uint32_t)(uintptr_t)smem;
   auto issue_one = [&](int g, int kt, uint32_t stage) {
@@ -216,7 +222,7 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(FastGemmParams p) {
   static_assert(NW * 16 * PITCH <= NS * STAGE && (16 * CH16) % 64 == 0, "epilogue staging");
   __syncthreads();  // every wave is done with the ring; nothing is in flight (the last wait was for all)
   char* stage_w = smem + wave * (16 * PITCH);
-  TC* __restrict__ C = (TC*)p.C;
+  TC* __restrict__ C = (TC*)p.C + (SPLIT ? (int64_t)split * p.c_split_stride : 0);
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
 #pragma unroll
