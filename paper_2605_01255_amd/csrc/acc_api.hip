@@ -304,12 +304,13 @@ void launch_reduce(const float* part, int G, int64_t count, void* out, int64_t r
 }
 
 // Sketch of a float32 layer with S written out once, into the part of the workspace that the partial products leave free:
-// the libm-grade generator then runs once per entry of S instead of once per entry and 64 channels.  Token splits: enough work-groups to fill the chip as far
-// as that room goes (the workspace's size is that of generic_sketch); one split writes a float32 factor directly.
+// the libm-grade generator then runs once per entry of S instead of once per entry and 64 channels.  Token splits: enough
+// work-groups to fill the chip, as far as that room goes; one split writes a float32 factor directly.
 // Returns false when S does not fit (few channels) or the kernel does not take the operands.
 bool f32_sketch(const acc_linear_desc* d, const void* A, int64_t lda, int64_t channels, int64_t n, bool transposed,
                 void* out, int64_t out_ld, float* ws, Launcher& L) {
-  const int64_t r = d->r, count = channels * r, room = generic_sketch_splits(n, channels, r) * count, s_size = n * r;
+  const int64_t r = d->r, count = channels * r, s_size = n * r;
+  const int64_t room = generic_sketch_splits(n, channels, r) * count;
   if (s_size > room) return false;
   const bool direct = d->factor_dtype == ACC_F32;
   int64_t G = ceil_div(256, ceil_div(channels, 32) * ceil_div(r, 32));
@@ -558,7 +559,7 @@ template <int TM, int TN> constexpr int splitk_tile_bytes() { return gemm_ring_l
 // part[s][M][ldc] = A[:, K range s] . B[K range s, :], fp32.  Returns the number of splits.  kb_rows: rows of an
 // N-contiguous B that exist (K may be A's zero-padded length).  Bound by the transfer of the wide operand, so two
 // work-groups per compute unit with three stages each in flight, and no more splits than that takes: the partials are
-// written and read back (16384 x 3072 by 3072 x 64: four splits on the two-stage kernel before, 34 us; RING_US).
+// written and read back (16384 x 3072 by 3072 x 64: two splits, 29 us; four on the two-stage kernel it replaced, 34 us).
 template <int TM, int TN, bool KMAJ>
 int fast_gemm_splitk(const void* A, const void* B, float* part, int64_t M, int64_t N, int64_t K, int64_t lda,
                      int64_t ldb, int64_t ldc, int64_t kb_rows, Launcher& L) {
@@ -1108,16 +1109,12 @@ LowrankPlan plan_lowrank(const acc_linear_desc* d, const Shape& s, int64_t k) {
   return pl;
 }
 
-// C [M, N] fp32 (dense) = A . B with a long K and a small result: the K range split over up to `most` groups of
-// work-groups (at least 128 elements each, one work-group per compute unit), the partials in `part` added in order.
-void lowrank_product(const F32Operand& a, const F32Operand& b, int64_t M, int64_t N, int64_t K, int64_t most, float* part,
+// C [M, N] fp32 (dense) = A . B with a long K and a small result: the K range split as planned (lowrank_splits), the
+// partials in `part` added in order.  Splits of 64 elements, more than the chip needs: short sums are what keeps the
+// result's rounding where it was (splits of 384: 1.2 us faster, 25 % more error at 3072 x 3072).
+void lowrank_product(const F32Operand& a, const F32Operand& b, int64_t M, int64_t N, int64_t K, int64_t k_per_split, float* part,
                      float* C, Launcher& L) {
-  int64_t splits = 256 / (ceil_div(M, 32) * ceil_div(N, 32));
-  if (splits > K / 128) splits = K / 128;
-  if (splits > most) splits = most;
-  if (splits < 1) splits = 1;
-  const int64_t k_per_split = round_up(ceil_div(K, splits), 32);
-  splits = ceil_div(K, k_per_split);
+  const int64_t splits = ceil_div(K, k_per_split);
   f32_gemm<float>(a, b, splits > 1 ? part : C, N, M, N, K, L, false, 1.f, 1.f, k_per_split, M * N);
   if (splits > 1)
     L(sum_parts_kernel, dim3((unsigned)ceil_div(M * N, 64)), dim3(1024), (const float*)part, (int)splits, M * N, C);
@@ -1505,7 +1502,7 @@ int acc_lowrank_projector(const acc_linear_desc* desc, int64_t k, const void* le
     if (f32_gemm_ok(g, om, s.r, k, s.d_out, z, k)) {
       L(sketch_matrix_kernel, dim3((unsigned)ceil_div(ceil_div(s.d_out, 4) * k, 256)), dim3(256), make_sketch_params(&od), s.d_out,
         k, omega);
-      lowrank_product(g, om, s.r, k, s.d_out, pl.z_splits, part, z, L);
+      lowrank_product(g, om, s.r, k, s.d_out, pl.z_k_per_split, part, z, L);
     } else {
       GemmParams p{};
       p.A = Gr; p.B = nullptr; p.C = part;
@@ -1581,7 +1578,7 @@ int acc_lowrank_adamw_step(const acc_linear_desc* desc, const acc_adamw_hyper* h
     float* proj = (float*)(ws + pl.off_r);
     const F32Operand pa{P, k, false, fb}, lb{left, s.r, false, fb};
     if (f32_gemm_ok(pa, lb, k, s.r, s.d_in, t1, s.r)) {
-      lowrank_product(pa, lb, k, s.r, s.d_in, pl.t1_splits, (float*)(ws + pl.off_part), t1, L);
+      lowrank_product(pa, lb, k, s.r, s.d_in, pl.t1_k_per_split, (float*)(ws + pl.off_part), t1, L);
     } else {
       GemmParams p{};
       p.A = P; p.B = left; p.C = ws + pl.off_part;

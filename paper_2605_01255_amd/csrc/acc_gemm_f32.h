@@ -167,7 +167,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32GemmParams p, Output o
   for (int i = 0; i < TM; ++i) a_rd[i] = TileA::base((wm * TM + i) * 16, l16, g4);
 #pragma unroll
   for (int j = 0; j < TN; ++j) b_rd[j] = TileB::base((wn * TN + j) * 16, l16, g4);
-  f32x4 a[2][TM], b[2][TN], acc[TM][TN];
+  f32x4 a[2][TM], b[2][TN], acc[TM][TN], total[TM][TN];
   auto read_one = [&](const char* st, int s, int r) {
     if (r < TM) a[s][r] = TileA::read(st, a_rd[r], s, l16, g4);
     else b[s][r - TM] = TileB::read(st + A_BYTES, b_rd[r - TM], s, l16, g4);
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32GemmParams p, Output o
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < TN; ++j) acc[i][j] = total[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // lane holds output row l16 of each 16 x 16 block and columns 4 g4 .. + 3 (N % 4 == 0)
   typename Output::Old old[TM][TN];
@@ -237,8 +237,26 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32GemmParams p, Output o
   int kt = 0, sc = 0;
   auto step = [&]() { ++kt; sc = sc + 1 == NS ? 0 : sc + 1; };
   auto after = [&]() { return sc + 1 == NS ? 0 : sc + 1; };
-  for (; kt + NS < KT; step()) ktile(kt, sc, after(), T{}, F{});
-  for (; kt + 1 < KT; step()) ktile(kt, sc, after(), F{}, F{});
+  // Sums of 256 elements, then the sum of those: the rounding of one running sum grows with the root of its length
+  // (K = 4096: 1.2e-6 relative; 3e-7 so), and a sketch that keeps S in its workspace has few token splits left to cut it.
+  auto fold = [&]() {
+    if (kt % 8 != 7) return;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        total[i][j] += acc[i][j];
+        acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+  };
+  for (; kt + NS < KT; step()) {
+    ktile(kt, sc, after(), T{}, F{});
+    fold();
+  }
+  for (; kt + 1 < KT; step()) {
+    ktile(kt, sc, after(), F{}, F{});
+    fold();
+  }
   ktile(kt, sc, sc, F{}, T{});
 
 #pragma unroll
@@ -246,7 +264,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32GemmParams p, Output o
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int64_t gm = m0 + (wm * TM + i) * 16 + l16, gn = n0 + (wn * TN + j) * 16 + 4 * g4;
-      if (gm < p.M && gn < p.N) output.store(p, split, gm, gn, acc[i][j], old[i][j]);
+      if (gm < p.M && gn < p.N) output.store(p, split, gm, gn, total[i][j] + acc[i][j], old[i][j]);
     }
 }
 
