@@ -1001,7 +1001,7 @@ void factor_product(const acc_linear_desc* desc, const Shape& s, const void* Xs,
                     const FactorProductOut& o, Launcher& L) {
   const bool w_oi = (desc->flags & ACC_FLAG_W_OUT_IN) != 0;
   // A few K tiles and at most one round of 192 x 192 tiles: the three-stage kernel (one exposed latency per
-  // work-group).  More tiles than compute units: the pipelined kernel, two work-groups per compute unit covering
+  // work-group).  More tiles than compute units: the kernels of the exact products, whose work-groups cover
   // each other's waits (measured at 3072 x 8192, r = 256: 23.5 against 27.6 us).  One round, 3072 x 3072: 12.4 against
   // 14.2 us at r = 256, 8.4 against 9.8 at r = 64; read-modify-write of a bf16 W at r = 64: 11.4 against 14.5 us
   // (a plain in-place pass over the same 18.9 MB takes 7.4 us, a fill 4.7).

@@ -1,5 +1,5 @@
-// bf16 GEMM on the 16x16x32 matrix instruction for shapes with at least 192 output tiles of 256 x 256
-// (steps F1, B1):  C[M, N] = A[M, K] . B, fp32 accumulate, bf16 output.
+// bf16 GEMM on the 16x16x32 matrix instruction for shapes that fill rounds of the chip with 256 x 256 tiles
+// (steps F1, B1; pick_gemm_tile decides):  C[M, N] = A[M, K] . B, fp32 accumulate, bf16 output.
 //
 //   A is row-major with K contiguous (X, dY).
 //   B_KMAJOR = true : B is given as Bt[N, K], K contiguous      (dX = dY . W^T reads W as is)
