@@ -217,6 +217,7 @@ F32GemmParams f32_params(const F32Operand& a, const F32Operand& b, void* C, int6
   p.M = M; p.N = N; p.K = K; p.lda = a.ld; p.ldb = b.ld; p.ldc = ldc;
   p.k_per_split = round_up(K, 32);
   p.alpha = p.beta = 1.f;
+  p.sum_tiles = 8;
   return p;
 }
 
@@ -226,11 +227,12 @@ F32GemmParams f32_params(const F32Operand& a, const F32Operand& b, void* C, int6
 template <typename TC>
 void f32_gemm(const F32Operand& a, const F32Operand& b, void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, Launcher& L,
               bool accumulate = false, float alpha = 1.f, float beta = 1.f, int64_t k_per_split = 0,
-              int64_t c_split_stride = 0) {
+              int64_t c_split_stride = 0, int sum_tiles = 8) {
   F32GemmParams p = f32_params(a, b, C, ldc, M, N, K);
   p.accumulate = accumulate ? 1 : 0; p.alpha = alpha; p.beta = beta;
   if (k_per_split) p.k_per_split = k_per_split;
   p.c_split_stride = c_split_stride;
+  p.sum_tiles = sum_tiles;
   const StoreProduct<TC> out{};
   if (!a.b16 && !b.b16) {
     if (a.kmajor && b.kmajor) return f32_tiled<true, true, float, float>(p, out, L);
@@ -278,13 +280,13 @@ int generic_sketch_splits(int64_t n, int64_t c, int64_t r) {
 }
 
 template <typename TA, typename TB, typename TC, typename CT, bool SK, bool ACCURATE>
-void launch_generic(const GemmParams& p, int splits, Launcher& L) {
+void launch_generic(const GemmParams& p, int splits, Launcher& L, int sum_tiles = 8) {
   if constexpr (sizeof(TA) == 4 && sizeof(TB) == 4 && !SK) {  // two float32 operands: the tuned kernel where strides allow
     const bool a_k = p.a_sk == 1, b_k = p.b_sk == 1;
     const F32Operand a{p.A, a_k ? p.a_sm : p.a_sk, a_k, false}, b{p.B, b_k ? p.b_sn : p.b_sk, b_k, false};
     if ((a_k || p.a_sm == 1) && (b_k || p.b_sn == 1) && p.c_sn == 1 && (a_k || sizeof(TC) == 4) &&
         f32_gemm_ok(a, b, p.M, p.N, p.K, p.C, p.c_sm)) {
-      f32_gemm<TC>(a, b, p.C, p.c_sm, p.M, p.N, p.K, L, p.accumulate != 0, p.alpha, p.beta, p.k_per_split, p.c_split_stride);
+      f32_gemm<TC>(a, b, p.C, p.c_sm, p.M, p.N, p.K, L, p.accumulate != 0, p.alpha, p.beta, p.k_per_split, p.c_split_stride, sum_tiles);
       return;
     }
   }
@@ -797,15 +799,20 @@ void reduce_to(int out_dt, const float* part, int G, int64_t count, void* out, L
     L(reduce_partials_kernel<float>, dim3(blocks), dim3(256), part, G, count, count, (float*)out, count, count);
 }
 
-// Gram = Yin^T . Yin [k, k] into the pass's gram buffer: the row range split, the partials added in order.
-void gram_matrix(const RsvdPlan& pl, char* ws, int64_t m, int64_t k, const float* Yin, Launcher& L) {
+// Gram = Yin^T . Yin [k, k] into the pass's gram buffer: the row range split, the partials added in a fixed order.  The
+// final pass's matrix decides how orthonormal the result is, so its running sums are 32 rows long (|U^T U - I| / sqrt(k) of
+// U [512, 256]: 1.3e-7, 2.8e-7 with the usual 256).  An earlier pass's need not be: Yin . R^-1 has the same
+// thin QR factor whatever upper triangular R it is multiplied with.
+void gram_matrix(const RsvdPlan& pl, char* ws, int64_t m, int64_t k, const float* Yin, bool final_pass, Launcher& L) {
   float* gram_part = (float*)(ws + pl.off_gram_part);
   float* gram = (float*)(ws + pl.off_gram);
   const int64_t tiles = ceil_div(k, 32) * ceil_div(k, 32);
-  int64_t splits = 512 / tiles;   // at least 256 rows each, two work-groups per compute unit
+  int64_t splits = 512 / tiles;   // two work-groups per compute unit
   const int64_t most = k <= kQrSmallRank ? pl.g_gram : kGramSplitsBlocked;
   if (splits > most) splits = most;
-  if (splits > ceil_div(m, 256)) splits = ceil_div(m, 256);
+  const int64_t rows = final_pass && m < 16 * 256 ? 64 : 256;   // of a split, at least; few rows: up to 16 splits in the final sum's tree
+  if (splits > ceil_div(m, rows)) splits = ceil_div(m, rows);
+  if (rows == 64 && splits > 16) splits = 16;
   if (splits < 1) splits = 1;
   GemmParams g{};
   g.A = Yin; g.B = Yin; g.C = gram_part;
@@ -815,7 +822,7 @@ void gram_matrix(const RsvdPlan& pl, char* ws, int64_t m, int64_t k, const float
   g.c_split_stride = k * k;
   splits = ceil_div(m, g.k_per_split);
   if (splits == 1) g.C = gram;
-  launch_generic<float, float, float, float, false, true>(g, (int)splits, L);
+  launch_generic<float, float, float, float, false, true>(g, (int)splits, L, final_pass ? 1 : 8);
   if (splits > 1)
     L(sum_parts_kernel, dim3((unsigned)ceil_div(k * k, 64)), dim3(1024), (const float*)gram_part, (int)splits, k * k, gram);
 }
@@ -851,7 +858,7 @@ void chol_solve(const float* Y, int64_t m, int64_t w, const float* image, float*
 // the float32 GEMM, Q_j = Y_j . R_jj^-1 by chol_solve).  Yin is used as scratch: its columns are overwritten.  Q goes to Qf
 // (fp32; Yin itself when Qf is null), Qt, Ut as in cholesky_qr_pass.
 void cholesky_qr_pass_blocked(const Shape& s, const RsvdPlan& pl, char* ws, int64_t m, int64_t m_pad, float* Yin,
-                              float* Qf, void* Qt, int qt_dt, bf16* Ut, int64_t ldt, bool hilo, Launcher& L) {
+                              float* Qf, void* Qt, int qt_dt, bf16* Ut, int64_t ldt, bool hilo, bool final_pass, Launcher& L) {
   const int64_t k = s.r;
   float* gram = (float*)(ws + pl.off_gram);
   float* rt = (float*)(ws + pl.off_rt);
@@ -859,7 +866,7 @@ void cholesky_qr_pass_blocked(const Shape& s, const RsvdPlan& pl, char* ws, int6
   float* W = Qf ? Qf : Yin;
   const int nb = (int)ceil_div(k, kQrMaxRank);
   auto image = [&](int j) { return (float*)(ws + pl.off_gram_part) + (int64_t)j * tri_block(kQrMaxRank / 16, 0) * 256; };
-  gram_matrix(pl, ws, m, k, Yin, L);
+  gram_matrix(pl, ws, m, k, Yin, final_pass, L);
   L(diag_max_kernel, dim3(1), dim3(64), (const float*)gram, (int)k, k, scale_ref);
   for (int j = 0; j < nb; ++j) {
     const int64_t jb = (int64_t)j * kQrMaxRank;
@@ -904,14 +911,14 @@ void cholesky_qr_pass_blocked(const Shape& s, const RsvdPlan& pl, char* ws, int6
 // A pivot counts as zero at 1e-6 of the largest diagonal entry up to rank 64, above at the rank times 2^-23 of it (the
 // size of the rounding noise that `rank` elimination steps leave on an exactly dependent column).
 void cholesky_qr_pass(const Shape& s, const RsvdPlan& pl, char* ws, int64_t m, int64_t m_pad, float* Yin,
-                      float* Qf, void* Qt, int qt_dt, bf16* Ut, int64_t ldt, bool hilo, Launcher& L) {
+                      float* Qf, void* Qt, int qt_dt, bf16* Ut, int64_t ldt, bool hilo, bool final_pass, Launcher& L) {
   const int64_t k = s.r;
   if (k > kQrMaxRank) {
-    cholesky_qr_pass_blocked(s, pl, ws, m, m_pad, Yin, Qf, Qt, qt_dt, Ut, ldt, hilo, L);
+    cholesky_qr_pass_blocked(s, pl, ws, m, m_pad, Yin, Qf, Qt, qt_dt, Ut, ldt, hilo, final_pass, L);
     return;
   }
   float* image = (float*)(ws + (k <= kQrSmallRank ? pl.off_rinv : pl.off_rt));
-  gram_matrix(pl, ws, m, k, Yin, L);
+  gram_matrix(pl, ws, m, k, Yin, final_pass, L);
   chol_factor((const float*)(ws + pl.off_gram), k, k, image, nullptr, k <= kQrSmallRank ? 1e-6f : (float)k * 1.1920929e-7f, L);
   const int64_t rows_out = Ut ? m_pad : m;
   if (qt_dt == ACC_BF16) chol_solve<bf16>(Yin, m, k, image, Qf, Qt, Ut, ldt, rows_out, hilo, k, k, k, L);
@@ -1349,26 +1356,26 @@ int acc_linear_fwd_rsvd(const acc_linear_desc* desc, const void* X, const void* 
   // the same Q), and one pass is enough to keep the iterates well conditioned.
   for (int it = 0; it <= power_iters; ++it) {
     if (it == power_iters) {
-      cholesky_qr_pass(s, pl, ws, s.n, pl.n_pad, y0, q1, nullptr, ACC_F32, nullptr, 0, false, L);
+      cholesky_qr_pass(s, pl, ws, s.n, pl.n_pad, y0, q1, nullptr, ACC_F32, nullptr, 0, false, false, L);
       cholesky_qr_pass(s, pl, ws, s.n, pl.n_pad, q1, nullptr, U, desc->factor_dtype, pl.tuned ? ut : nullptr, pl.n_pad,
-                       false, L);
+                       false, true, L);
       break;
     }
     float* z0 = (float*)(ws + pl.off_z0);
     if (pl.tuned) {
       // U as hi + lo parts, transposed; Z^T = [U_hi; U_lo] . X over the tokens with the K range split
-      cholesky_qr_pass(s, pl, ws, s.n, pl.n_pad, y0, nullptr, nullptr, ACC_F32, ut, pl.n_pad, true, L);
+      cholesky_qr_pass(s, pl, ws, s.n, pl.n_pad, y0, nullptr, nullptr, ACC_F32, ut, pl.n_pad, true, false, L);
       float* zt_part = (float*)(ws + pl.off_zt_part);
       const int splits = fast_gemm_splitk<2, 4, false>(ut, X, zt_part, 2 * k, s.d_in, pl.n_pad, pl.n_pad, s.ldx,
                                                            s.d_in, s.n, L);
       L(combine_hilo_t_kernel, dim3((unsigned)ceil_div(k * s.d_in, 256)), dim3(256), (const float*)zt_part, splits,
         s.d_in, (int)k, z0);
       // orth(Z) written as hi + lo parts [2k, d_in]: the right factor of the next X . Z
-      cholesky_qr_pass(s, pl, ws, s.d_in, s.d_in, z0, nullptr, nullptr, ACC_F32, omega, s.d_in, true, L);
+      cholesky_qr_pass(s, pl, ws, s.d_in, s.d_in, z0, nullptr, nullptr, ACC_F32, omega, s.d_in, true, false, L);
       times_hilo();
     } else {
       float* z1 = (float*)(ws + pl.off_z1);
-      cholesky_qr_pass(s, pl, ws, s.n, pl.n_pad, y0, q1, nullptr, ACC_F32, nullptr, 0, false, L);  // U fp32 -> q1
+      cholesky_qr_pass(s, pl, ws, s.n, pl.n_pad, y0, q1, nullptr, ACC_F32, nullptr, 0, false, false, L);  // U fp32 -> q1
       float* part = (float*)(ws + pl.off_fact_part);
       GemmParams g{};  // Z [d_in, k] = X^T . U, token range split
       g.A = X; g.B = q1; g.C = part;
@@ -1379,7 +1386,7 @@ int acc_linear_fwd_rsvd(const acc_linear_desc* desc, const void* X, const void* 
       const int splits = (int)ceil_div(s.n, g.k_per_split);
       rsvd_gemm(desc->io_dtype, ACC_F32, ACC_F32, g, splits, L);
       reduce_to(ACC_F32, part, splits, s.d_in * k, z0, L);
-      cholesky_qr_pass(s, pl, ws, s.d_in, s.d_in, z0, z1, nullptr, ACC_F32, nullptr, 0, false, L);  // orth(Z) -> z1
+      cholesky_qr_pass(s, pl, ws, s.d_in, s.d_in, z0, z1, nullptr, ACC_F32, nullptr, 0, false, false, L);  // orth(Z) -> z1
       GemmParams y{};  // y0 [n, k] = X . Z
       y.A = X; y.B = z1; y.C = y0;
       y.M = s.n; y.N = k; y.K = s.d_in;
@@ -1535,8 +1542,8 @@ int acc_lowrank_projector(const acc_linear_desc* desc, int64_t k, const void* le
   RsvdPlan rp{};
   rp.g_gram = pl.g_gram; rp.off_gram_part = pl.off_gram_part; rp.off_gram = pl.off_gram; rp.off_rinv = pl.off_rinv;
   rp.off_rt = pl.off_rt;
-  cholesky_qr_pass(sk, rp, ws, s.d_in, s.d_in, yp, q1, nullptr, ACC_F32, nullptr, 0, false, L);
-  cholesky_qr_pass(sk, rp, ws, s.d_in, s.d_in, q1, nullptr, P, desc->factor_dtype, nullptr, 0, false, L);
+  cholesky_qr_pass(sk, rp, ws, s.d_in, s.d_in, yp, q1, nullptr, ACC_F32, nullptr, 0, false, false, L);
+  cholesky_qr_pass(sk, rp, ws, s.d_in, s.d_in, q1, nullptr, P, desc->factor_dtype, nullptr, 0, false, true, L);
   return L.status();
 }
 

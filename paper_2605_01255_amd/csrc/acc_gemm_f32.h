@@ -35,6 +35,7 @@ struct F32GemmParams {
   int tile_blocks;         // work-groups of one K split
   int64_t k_per_split;     // multiple of 32; split s writes its partial product at C + s * c_split_stride
   int64_t c_split_stride;
+  int sum_tiles;           // K tiles of one running sum, a power of two
 };
 
 // One operand of the kernel: R rows of the output dimension (BM or BN) per tile, K_MAJOR its memory order.
@@ -237,10 +238,12 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32GemmParams p, Output o
   int kt = 0, sc = 0;
   auto step = [&]() { ++kt; sc = sc + 1 == NS ? 0 : sc + 1; };
   auto after = [&]() { return sc + 1 == NS ? 0 : sc + 1; };
-  // Sums of 256 elements, then the sum of those: the rounding of one running sum grows with the root of its length
-  // (K = 4096: 1.2e-6 relative; 3e-7 so), and a sketch that keeps S in its workspace has few token splits left to cut it.
+  // Sums of sum_tiles K tiles (256 elements as a rule), then the sum of those: the rounding of one running sum grows with
+  // the root of its length (K = 4096: 1.2e-6 relative; 3e-7 so), and a sketch that keeps S in its workspace has few token
+  // splits left to cut it.
+  const int sum_mask = p.sum_tiles - 1;
   auto fold = [&]() {
-    if (kt % 8 != 7) return;
+    if ((kt & sum_mask) != sum_mask) return;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
