@@ -47,7 +47,10 @@ template <typename P> __device__ __forceinline__ bool ring_tile(const P& p, int 
 template <int N> __device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
 // SPLIT: the K range is split over groups of tile_blocks work-groups (skinny products of the RSVD path), each storing its
-// partial product at C + split * c_split_stride; kb_rows as in gemm_bf16_tile.
+// partial product at C + split * c_split_stride; kb_rows as in FastGemmParams.  A running sum is then four K tiles, 256
+// elements, long and these are added up: the number of splits (512 to 1536 elements each) does not decide how exact the
+// result is (error of a [16384, 3072] x [3072, 64] product: 6.3e-7 with one sum per split of 1536, 6.0e-7 so, 6.1e-7 with
+// the four splits of 768 that the two-stage kernel took; the time is the same).
 template <int TM, int TN, int NS, bool B_KMAJOR, typename TC, bool SPLIT = false>
 __global__ __launch_bounds__(256) void gemm_ring_kernel(FastGemmParams p) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -133,11 +136,14 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(FastGemmParams p) {
     }
   };
 
-  f32x4 acc[TM][TN];
+  f32x4 acc[TM][TN], total[SPLIT ? TM : 1][SPLIT ? TN : 1];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < TN; ++j) {
+      acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (SPLIT) total[i][j] = acc[i][j];
+    }
 
   if (has_tile) {
 #pragma unroll
@@ -211,9 +217,32 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(FastGemmParams p) {
   int kt = 0, sc = 0;
   auto step = [&]() { ++kt; sc = sc + 1 == NS ? 0 : sc + 1; };
   auto after = [&]() { return sc + 1 == NS ? 0 : sc + 1; };
-  for (; kt + NS < KT; step()) ktile(kt, sc, after(), T{}, F{});
-  for (; kt + 1 < KT; step()) ktile(kt, sc, after(), F{}, F{});
+  auto add_up = [&]() {
+    if constexpr (SPLIT) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          total[i][j] += acc[i][j];
+          acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+  };
+  for (; kt + NS < KT; step()) {
+    ktile(kt, sc, after(), T{}, F{});
+    if (kt % 4 == 3) add_up();
+  }
+  for (; kt + 1 < KT; step()) {
+    ktile(kt, sc, after(), F{}, F{});
+    if (kt % 4 == 3) add_up();
+  }
   ktile(kt, sc, sc, F{}, T{});
+  if constexpr (SPLIT) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] += total[i][j];
+  }
 
   // ---- epilogue: lane holds output row l16 of each 16 x 16 block and columns 4 g4 .. + 3; a wave stages one block
   //      row (16 x TN * 16) in a private padded LDS region and moves 16 bytes per lane (whole rows) ----
