@@ -76,8 +76,8 @@ enum {
                                       round costs two more passes over X.                                  */
   ACC_FLAG_DW_ACCUMULATE = 8u /* backward only, with dW != NULL: dW += Xs.Gr, not dW = Xs.Gr
                                 (gradient accumulation over micro-batches on the dense gradient,
-                                Sec. 4 update strategy (i)).  A float dW is rounded once per call;
-                                a bfloat16 dW rounds the product and then the sum.               */
+                                Sec. 4 update strategy (i)).  The product is kept in float; dW, float
+                                or bfloat16, is rounded once per call.                           */
 };
 
 #define ACC_FLAG_RSVD_POWER_SHIFT 8 /* flags bits 8..9: rounds of subspace iteration, 0..3 */
@@ -226,7 +226,7 @@ int acc_lowrank_projector(const acc_linear_desc* desc, int64_t k, const void* le
  * NULL; zero before step 1) and W ([d_in, ldw], or [d_out, ldw] under ACC_FLAG_W_OUT_IN, io_dtype) are
  * updated in place.  ACC_ERR_INVALID_ARG also for step < 1, beta outside [0, 1), eps < 0 or a non-finite
  * lr / weight_decay / scale, and for ACC_FLAG_SKIP_SKETCH, ACC_FLAG_ONE_LAUNCH or ACC_FLAG_DW_ACCUMULATE.
- * A bf16 W rounds the product P . N to bf16, then the updated weight. */
+ * The product P . N is kept in float; W, float or bf16, is rounded once. */
 int acc_lowrank_adamw_step(const acc_linear_desc* desc, const acc_adamw_hyper* hyper, const void* P, int64_t k,
                            const void* left, const void* Gr, float* M, float* V, void* W, void* workspace,
                            size_t ws_bytes, void* stream);

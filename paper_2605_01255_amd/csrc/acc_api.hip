@@ -453,19 +453,21 @@ GemmChoice pick_gemm_tile(int64_t M, int64_t N, int64_t K, bool persist_ok) {
   return best;
 }
 
-template <int TM, int TN, int NS, bool KMAJ, typename TC>
+template <int TM, int TN, int NS, bool KMAJ, typename TC, bool SUM>
 void ring_gemm(FastGemmParams& p, Launcher& L) {
   const unsigned grid = gemm_ring_plan(p, 32 * TM, 32 * TN);
   p.red_stride = (int64_t)grid * 256 * 4;
-  L.launch_lds(gemm_ring_kernel<TM, TN, NS, KMAJ, TC>, dim3(grid), dim3(256), (size_t)gemm_ring_lds_bytes<TM, TN, NS>(), p);
+  L.launch_lds(gemm_ring_kernel<TM, TN, NS, KMAJ, TC, false, SUM>, dim3(grid), dim3(256), (size_t)gemm_ring_lds_bytes<TM, TN, NS>(), p);
 }
 
-template <bool KMAJ, typename TC>
+// SUM: C = beta C + alpha (A . B), rounded once, on the ring kernel whatever the size: its work-groups, two to a compute unit,
+// cover each other's reads of C (4096 x 4096 at r = 256, bf16 23 us and float 35, 26 and 43 on the 256 x 256 kernel; 8192 x
+// 3072 27 to 37 and 39 to 54, against 47 and 72 to 77).
+template <bool KMAJ, typename TC, bool SUM = false>
 void fast_gemm(const void* A, const void* B, void* C, int64_t M, int64_t N, int64_t K, int64_t lda,
-               int64_t ldb, int64_t ldc, Launcher& L, const ReduceJob* job = nullptr, bool accumulate = false,
-               float alpha = 1.f, float beta = 1.f) {
+               int64_t ldb, int64_t ldc, Launcher& L, const ReduceJob* job = nullptr, float alpha = 1.f,
+               float beta = 1.f) {
   FastGemmParams p{};
-  p.accumulate = accumulate ? 1 : 0;
   p.alpha = alpha; p.beta = beta;
   p.A = (const bf16*)A; p.B = (const bf16*)B; p.C = C;
   p.M = M; p.N = N; p.K = K; p.lda = lda; p.ldb = ldb; p.ldc = ldc;
@@ -474,8 +476,8 @@ void fast_gemm(const void* A, const void* B, void* C, int64_t M, int64_t N, int6
     p.red_out_bf16 = job->out_bf16;
     p.red_row = job->row; p.red_ld = job->ld;
   }
-  const bool persist_ok = sizeof(TC) == 2 && !accumulate && K > 128;  // three K tiles
-  if (!persist_ok && ceil_div(M, 256) * ceil_div(N, 256) >= 192) {  // a short K, a sum into C or float output: no pipeline across tiles
+  const bool persist_ok = sizeof(TC) == 2 && !SUM && K > 128;  // three K tiles
+  if (!SUM && !persist_ok && ceil_div(M, 256) * ceil_div(N, 256) >= 192) {  // a short K or float output: no pipeline across tiles
     const unsigned grid = gemm_bf16_plan(p, 256, 256);  // a multiple of 256 slots
     p.red_stride = (int64_t)grid * 256 * 4;
     L.launch_lds(gemm_bf16_kernel<2, 2, 4, 4, KMAJ, TC>, dim3(grid), dim3(256),
@@ -485,40 +487,39 @@ void fast_gemm(const void* A, const void* B, void* C, int64_t M, int64_t N, int6
   const GemmChoice c = pick_gemm_tile(M, N, K, persist_ok);
   switch (c.tile) {
     case GemmTile::k256:
-      if constexpr (sizeof(TC) == 2) {
+      if constexpr (sizeof(TC) == 2 && !SUM) {
         const unsigned slots = gemm_bf16_plan(p, 256, 256);
         p.red_stride = (int64_t)256 * 256 * 4;
         if (K % 64) L.launch_lds(gemm16_persist_kernel<KMAJ, true>, dim3(256), dim3(256), (size_t)160 * 1024, p, (int)slots);
         else L.launch_lds(gemm16_persist_kernel<KMAJ>, dim3(256), dim3(256), (size_t)160 * 1024, p, (int)slots);
       }
       break;
-    case GemmTile::k256x192: ring_gemm<8, 6, 2, KMAJ, TC>(p, L); break;
+    case GemmTile::k256x192: ring_gemm<8, 6, 2, KMAJ, TC, SUM>(p, L); break;
     case GemmTile::k192x128:
-      if (c.one_round) ring_gemm<6, 4, 4, KMAJ, TC>(p, L);
-      else ring_gemm<6, 4, 2, KMAJ, TC>(p, L);
+      if (c.one_round) ring_gemm<6, 4, 4, KMAJ, TC, SUM>(p, L);
+      else ring_gemm<6, 4, 2, KMAJ, TC, SUM>(p, L);
       break;
     case GemmTile::k128:
-      if (c.one_round) ring_gemm<4, 4, 4, KMAJ, TC>(p, L);
-      else ring_gemm<4, 4, 2, KMAJ, TC>(p, L);
+      if (c.one_round) ring_gemm<4, 4, 4, KMAJ, TC, SUM>(p, L);
+      else ring_gemm<4, 4, 2, KMAJ, TC, SUM>(p, L);
       break;
-    case GemmTile::k128x64: ring_gemm<4, 2, 3, KMAJ, TC>(p, L); break;
-    case GemmTile::k64: ring_gemm<2, 2, 3, KMAJ, TC>(p, L); break;
+    case GemmTile::k128x64: ring_gemm<4, 2, 3, KMAJ, TC, SUM>(p, L); break;
+    case GemmTile::k64: ring_gemm<2, 2, 3, KMAJ, TC, SUM>(p, L); break;
   }
 }
 
 // C (op)= A[M, K] . B for a short K on the three-stage kernel of acc_gemm_smallk.h (the product of two gradient
 // factors: the dense dW, the optimizer's update of W).
-template <bool KMAJ, typename TC>
+template <bool KMAJ, typename TC, bool SUM>
 void smallk_gemm(const void* A, const void* B, void* C, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb,
-                 int64_t ldc, Launcher& L, bool accumulate, float alpha, float beta) {
+                 int64_t ldc, Launcher& L, float alpha, float beta) {
   FastGemmParams p{};
-  p.accumulate = accumulate ? 1 : 0;
   p.alpha = alpha; p.beta = beta;
   p.A = (const bf16*)A; p.B = (const bf16*)B; p.C = C;
   p.M = M; p.N = N; p.K = K; p.lda = lda; p.ldb = ldb; p.ldc = ldc;
   p.tiles_m = (int)ceil_div(M, 192);
   p.tiles_n = (int)ceil_div(N, 192);
-  L.launch_lds(gemm16_smallk_kernel<KMAJ, TC>, dim3((unsigned)(p.tiles_m * p.tiles_n)), dim3(256), (size_t)144 * 1024, p);
+  L.launch_lds(gemm16_smallk_kernel<KMAJ, TC, SUM>, dim3((unsigned)(p.tiles_m * p.tiles_n)), dim3(256), (size_t)144 * 1024, p);
 }
 
 // ---- exact products on 8-bit floating-point operands (acc_gemm8.h) ---------------------------------
@@ -1013,27 +1014,24 @@ void factor_product(const acc_linear_desc* desc, const Shape& s, const void* Xs,
   // 14.2 us at r = 256, 8.4 against 9.8 at r = 64; read-modify-write of a bf16 W at r = 64: 11.4 against 14.5 us
   // (a plain in-place pass over the same 18.9 MB takes 7.4 us, a fill 4.7).
   const bool short_k = s.r <= 1024 && ceil_div(s.d_in, 192) * ceil_div(s.d_out, 192) <= 256;
-  if (w_oi && desc->factor_dtype == ACC_BF16 && fast_gemm_ok(s.d_out, s.d_in, s.r, s.ldf, s.ldf)) {
-    if (short_k && o.dtype == ACC_BF16)
-      smallk_gemm<true, bf16>(Gr, Xs, o.C, s.d_out, s.d_in, s.r, s.ldf, s.ldf, o.ld, L, o.accumulate, o.alpha, o.beta);
-    else if (short_k)
-      smallk_gemm<true, float>(Gr, Xs, o.C, s.d_out, s.d_in, s.r, s.ldf, s.ldf, o.ld, L, o.accumulate, o.alpha, o.beta);
-    else if (o.dtype == ACC_BF16)
-      fast_gemm<true, bf16>(Gr, Xs, o.C, s.d_out, s.d_in, s.r, s.ldf, s.ldf, o.ld, L, nullptr, o.accumulate, o.alpha, o.beta);
-    else
-      fast_gemm<true, float>(Gr, Xs, o.C, s.d_out, s.d_in, s.r, s.ldf, s.ldf, o.ld, L, nullptr, o.accumulate, o.alpha, o.beta);
-  } else if (!w_oi && desc->factor_dtype == ACC_BF16 && fast_gemm_ok(s.d_in, s.d_out, s.r, s.ldf, s.d_out)) {
-    if (short_k && o.dtype == ACC_BF16)
-      smallk_gemm<false, bf16>(Xs, Gr, o.C, s.d_in, s.d_out, s.r, s.ldf, s.d_out, o.ld, L, o.accumulate, o.alpha, o.beta);
-    else if (short_k)
-      smallk_gemm<false, float>(Xs, Gr, o.C, s.d_in, s.d_out, s.r, s.ldf, s.d_out, o.ld, L, o.accumulate, o.alpha, o.beta);
-    else if (o.dtype == ACC_BF16)
-      fast_gemm<false, bf16>(Xs, Gr, o.C, s.d_in, s.d_out, s.r, s.ldf, s.d_out, o.ld, L, nullptr, o.accumulate, o.alpha, o.beta);
-    else
-      fast_gemm<false, float>(Xs, Gr, o.C, s.d_in, s.d_out, s.r, s.ldf, s.d_out, o.ld, L, nullptr, o.accumulate, o.alpha, o.beta);
-  } else {
+  auto tuned = [&](auto kmaj, auto type, auto sum, const void* A, const void* B, int64_t M, int64_t N, int64_t ldb) {
+    constexpr bool KMAJ = decltype(kmaj)::value, SUM = decltype(sum)::value;
+    using TC = decltype(type);
+    if (short_k) smallk_gemm<KMAJ, TC, SUM>(A, B, o.C, M, N, s.r, s.ldf, ldb, o.ld, L, o.alpha, o.beta);
+    else fast_gemm<KMAJ, TC, SUM>(A, B, o.C, M, N, s.r, s.ldf, ldb, o.ld, L, nullptr, o.alpha, o.beta);
+  };
+  auto typed = [&](auto kmaj, auto... args) {
+    const std::true_type sum{};
+    const std::false_type write{};
+    if (o.dtype == ACC_BF16) o.accumulate ? tuned(kmaj, bf16{}, sum, args...) : tuned(kmaj, bf16{}, write, args...);
+    else o.accumulate ? tuned(kmaj, float{}, sum, args...) : tuned(kmaj, float{}, write, args...);
+  };
+  if (w_oi && desc->factor_dtype == ACC_BF16 && fast_gemm_ok(s.d_out, s.d_in, s.r, s.ldf, s.ldf))
+    typed(std::true_type{}, Gr, Xs, s.d_out, s.d_in, s.ldf);
+  else if (!w_oi && desc->factor_dtype == ACC_BF16 && fast_gemm_ok(s.d_in, s.d_out, s.r, s.ldf, s.d_out))
+    typed(std::false_type{}, Xs, Gr, s.d_in, s.d_out, s.d_out);
+  else
     generic_dw(desc, s, Xs, Gr, o, L);
-  }
 }
 
 // dW = left . Gr: dense, of desc->dw_dtype, summed into the caller's dW under ACC_FLAG_DW_ACCUMULATE.

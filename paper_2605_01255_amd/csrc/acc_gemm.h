@@ -39,8 +39,7 @@ struct FastGemmParams {
   int red_G;
   int red_out_bf16;       // 1: red_out is bf16, 0: float
   int64_t red_row, red_ld;  // the result has rows of red_row elements (red_row % 4 == 0) stored red_ld apart
-  int accumulate;         // 0: C = A . B;  1: C = beta C + alpha (A . B) (a bf16 C rounds the product, then the sum)
-  float alpha, beta;      // used when accumulate; 1, 1 is the plain sum
+  float alpha, beta;      // of the kernels with SUM: C = beta C + alpha (A . B), one rounding; 1, 1 is the plain sum
   // Split of the K range over work-groups (gemm_ring_kernel with SPLIT: skinny products whose M x N tiles alone do
   // not fill the chip).  Block b works on tile b % tile_blocks and K range [s * k_per_split, min(K, (s + 1) *
   // k_per_split)), s = b / tile_blocks, and stores its partial product at C + s * c_split_stride.  k_per_split % 64 == 0.
@@ -107,6 +106,23 @@ __device__ __forceinline__ void buffer_to_lds_b128(u32x4 rsrc, uint32_t voffset,
 
 // s_waitcnt vmcnt(0) (expcnt / lgkmcnt untouched): all global -> LDS transfers of this wave landed.
 __device__ __forceinline__ void wait_vmcnt0() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// 16 bytes of C = alpha x + beta old for staged float products x, rounded once.
+template <typename TC> __device__ __forceinline__ u32x4 scaled_sum(const float* x, u32x4 old, float alpha, float beta) {
+  if constexpr (sizeof(TC) == 2) {
+    const f32x4 lo = *(const f32x4*)x, hi = *(const f32x4*)(x + 4);
+    const bf16x8 o = __builtin_bit_cast(bf16x8, old);
+    bf16x8 sum;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      sum[e] = (bf16)(alpha * lo[e] + beta * (float)o[e]);
+      sum[4 + e] = (bf16)(alpha * hi[e] + beta * (float)o[4 + e]);
+    }
+    return __builtin_bit_cast(u32x4, sum);
+  } else {
+    return __builtin_bit_cast(u32x4, alpha * *(const f32x4*)x + beta * __builtin_bit_cast(f32x4, old));
+  }
+}
 
 // Map the linear work-group id to an output tile so that the 32 tiles resident on one XCD
 // (work-groups are dealt round-robin to the 8 XCDs) form a super_m x super_n block that shares
@@ -385,21 +401,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, c
       const int64_t gm = m0 + (wm * TM + i) * 32 + row;
       const int64_t gn = n0 + wn * TN * 32 + ch * (16 / ES);
       if (gm < p.M && gn < p.N) {
-        u32x4* dst = (u32x4*)(C + gm * p.ldc + gn);
-        if (p.accumulate) {
-          const u32x4 old = *dst;
-          if constexpr (ES == 2) {
-            const bf16x8 a = __builtin_bit_cast(bf16x8, v), o = __builtin_bit_cast(bf16x8, old);
-            bf16x8 sum;
-#pragma unroll
-            for (int t = 0; t < 8; ++t) sum[t] = (bf16)(p.alpha * (float)a[t] + p.beta * (float)o[t]);
-            *dst = __builtin_bit_cast(u32x4, sum);
-          } else {
-            *dst = __builtin_bit_cast(u32x4, p.alpha * __builtin_bit_cast(f32x4, v) + p.beta * __builtin_bit_cast(f32x4, old));
-          }
-        } else {
-          *dst = v;
-        }
+        *(u32x4*)(C + gm * p.ldc + gn) = v;
       }
     }
   }

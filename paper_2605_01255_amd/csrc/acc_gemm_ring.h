@@ -51,7 +51,8 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() { asm volatile("s_
 // elements, long and these are added up: the number of splits (512 to 1536 elements each) does not decide how exact the
 // result is (error of a [16384, 3072] x [3072, 64] product: 6.3e-7 with one sum per split of 1536, 6.0e-7 so, 6.1e-7 with
 // the four splits of 768 that the two-stage kernel took; the time is the same).
-template <int TM, int TN, int NS, bool B_KMAJOR, typename TC, bool SPLIT = false>
+// SUM: C = beta C + alpha (A . B).  A form of its own: behind a branch its registers cost the plain one occupancy.
+template <int TM, int TN, int NS, bool B_KMAJOR, typename TC, bool SPLIT = false, bool SUM = false>
 __global__ __launch_bounds__(256) void gemm_ring_kernel(FastGemmParams p) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   constexpr int NW = 4, WN = 2;
@@ -245,19 +246,21 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(FastGemmParams p) {
   }
 
   // ---- epilogue: lane holds output row l16 of each 16 x 16 block and columns 4 g4 .. + 3; a wave stages one block
-  //      row (16 x TN * 16) in a private padded LDS region and moves 16 bytes per lane (whole rows) ----
-  constexpr int ES = sizeof(TC);
-  constexpr int ROW_B = TN * 16 * ES, PITCH = ROW_B + 16, CH16 = ROW_B / 16;
-  static_assert(NW * 16 * PITCH <= NS * STAGE && (16 * CH16) % 64 == 0, "epilogue staging");
+  //      row (16 x TN * 16) in a private padded LDS region and moves 16 bytes per lane (whole rows); a product that is added
+  //      to C is staged as float, so that only the sum is rounded ----
+  constexpr int ES = sizeof(TC), CH16 = TN * 16 * ES / 16;
+  static_assert((16 * CH16) % 64 == 0, "epilogue staging");
   __syncthreads();  // every wave is done with the ring; nothing is in flight (the last wait was for all)
-  char* stage_w = smem + wave * (16 * PITCH);
   TC* __restrict__ C = (TC*)p.C + (SPLIT ? (int64_t)split * p.c_split_stride : 0);
+  constexpr int SE = SUM ? 4 : ES, PITCH = TN * 16 * SE + 16;   // SE: bytes of a staged element
+  static_assert(NW * 16 * PITCH <= NS * STAGE, "epilogue staging");
+  char* stage_w = smem + wave * (16 * PITCH);
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      char* dst = stage_w + l16 * PITCH + (j * 16 + g4 * 4) * ES;
-      if constexpr (ES == 2) {
+      char* dst = stage_w + l16 * PITCH + (j * 16 + g4 * 4) * SE;
+      if constexpr (SE == 2) {
         bf16x4 v;
 #pragma unroll
         for (int t = 0; t < 4; ++t) v[t] = (bf16)acc[i][j][t];
@@ -269,25 +272,13 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(FastGemmParams p) {
 #pragma unroll
     for (int t = 0; t < 16 * CH16 / 64; ++t) {
       const int idx = t * 64 + lane, row = idx / CH16, ch = idx % CH16;
-      const u32x4 v = *(const u32x4*)(stage_w + row * PITCH + ch * 16);
+      const char* staged = stage_w + row * PITCH + ch * (16 / ES) * SE;
       const int64_t gm = m0 + (wm * TM + i) * 16 + row;
       const int64_t gn = n0 + wn * TN * 16 + ch * (16 / ES);
       if (gm < p.M && gn < p.N) {
         u32x4* dst = (u32x4*)(C + gm * p.ldc + gn);
-        if (p.accumulate) {
-          const u32x4 old = *dst;
-          if constexpr (ES == 2) {
-            const bf16x8 x = __builtin_bit_cast(bf16x8, v), o = __builtin_bit_cast(bf16x8, old);
-            bf16x8 sum;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) sum[e] = (bf16)(p.alpha * (float)x[e] + p.beta * (float)o[e]);
-            *dst = __builtin_bit_cast(u32x4, sum);
-          } else {
-            *dst = __builtin_bit_cast(u32x4, p.alpha * __builtin_bit_cast(f32x4, v) + p.beta * __builtin_bit_cast(f32x4, old));
-          }
-        } else {
-          *dst = v;
-        }
+        if constexpr (SUM) *dst = scaled_sum<TC>((const float*)staged, *dst, p.alpha, p.beta);
+        else *dst = *(const u32x4*)staged;
       }
     }
   }
