@@ -184,29 +184,16 @@ void f32_launch(F32GemmParams& p, const Output& out, int splits, Launcher& L) {
                (size_t)gemm_f32_lds_bytes<TM, TN, NS, TA, TB>(), p, out);
 }
 
-// The tile with the least estimate, rounds of 256 compute units x K tiles x time of a K tile in ns.  The matrix pipe
-// bounds all of them, so the estimates follow the area, and a small tile only loses by its operands' latency; what decides
-// is how much of the last round is empty.  Measured us, 128 x 64 / 64 x 64 / 64 x 32 / 32 x 32 [generic kernel]:
-//   2048 x 2048 x 1024  64 /  66 /  79 /  79 [188]      2048 x 1024 x 2048  67 / 66 / 105 /  80 [347]
-//   300 x 4096 x 2048   66 /  66 /  57 /  76            256 x 512 x 256   11.5 / 7.6 / 5.7 / 4.6 [22]
-// Products with a bfloat16 factor are small: 32 x 32 and 64 x 64 only.
+// The tile of pick_f32_tile.  Products with a bfloat16 factor are small: 64 x 64 and 32 x 32 only.
 template <bool A_K, bool B_K, typename TA, typename TB, typename Output>
 void f32_tiled(F32GemmParams& p, const Output& out, Launcher& L) {
   const int splits = (int)ceil_div(p.K, p.k_per_split);
-  struct Cost { int bm, bn, per_k, alone_per_k; };
-  static const Cost costs[] = {{64, 64, 520, 560}, {32, 32, 165, 210}, {128, 64, 960, 1000}, {64, 32, 320, 330}};
   constexpr bool both_f32 = sizeof(TA) == 4 && sizeof(TB) == 4;
-  int best = 0;
-  int64_t best_ns = INT64_MAX;
-  for (int i = 0; i < (both_f32 ? 4 : 2); ++i) {
-    const int64_t rounds = ceil_div(ceil_div(p.M, costs[i].bm) * ceil_div(p.N, costs[i].bn) * splits, 256);
-    const int64_t ns = rounds == 1 ? costs[i].alone_per_k : rounds * costs[i].per_k;
-    if (ns < best_ns) { best_ns = ns; best = i; }
-  }
-  if (best == 0) return f32_launch<2, 2, 4, A_K, B_K, TA, TB>(p, out, splits, L);
-  if (best == 1) return f32_launch<1, 1, 4, A_K, B_K, TA, TB>(p, out, splits, L);
+  const F32TileShape tile = pick_f32_tile(p.M, p.N, splits, both_f32).tile;
+  if (tile == F32TileShape::k64) return f32_launch<2, 2, 4, A_K, B_K, TA, TB>(p, out, splits, L);
+  if (tile == F32TileShape::k32) return f32_launch<1, 1, 4, A_K, B_K, TA, TB>(p, out, splits, L);
   if constexpr (both_f32) {
-    if (best == 2) f32_launch<4, 2, 3, A_K, B_K, TA, TB>(p, out, splits, L);
+    if (tile == F32TileShape::k128x64) f32_launch<4, 2, 3, A_K, B_K, TA, TB>(p, out, splits, L);
     else f32_launch<2, 1, 4, A_K, B_K, TA, TB>(p, out, splits, L);
   }
 }
@@ -411,47 +398,6 @@ struct ReduceJob {
   int out_bf16;
   int64_t row, ld;  // the result's rows hold `row` elements and are stored `ld` apart
 };
-
-// Which kernel and tile a product takes: the least of six estimates, launch + rounds x (cost of a tile + K tiles x time of
-// a K tile), in nanoseconds, with rounds = tiles over 256 compute units.  A larger tile needs fewer bytes from L2 per
-// multiply-add (a 128 x 128 K tile multiplies for 0.2 us and takes 0.36 to move, however many stages are in flight), a
-// smaller one leaves fewer compute units idle.  From two rounds on, two work-groups of two stages per compute unit cover
-// each other's waits better than one of four (4096 x 2048 x 2048 on 128 x 128: 34 against 41 us).  The constants are fits
-// to 45 shapes from 256 x 512 x 512 to 16384 x 3072 x 8192, good to about 15 %.  256 x 192 is there for the shapes that it
-// makes one full round of: 4096 x 3072 x 3072 62 us (192 tiles of 256 x 256: 72), 8192 x 1032 x 4096 68 (73); where both fill
-// the chip the persistent 256 x 256 kernel is ahead (16384 x 3072 x 3072: 255).  Measured us on 256 x 256 / 192 x 128 /
-// 128 x 128 / 128 x 64 / 64 x 64, with what the kernels this replaced took (256 x 256 from 192 tiles on, else a two-stage
-// 128 x 128) in brackets:
-//   16384 x 3072 x 3072 228 / 293 / 286 /  - /  - [228]    16384 x 1152 x 3072 139 / 116 / 129 / 166 / 222 [139]
-//   6000 x 4096 x 4096  188 / 168 / 180 /  - /  - [188]    4096 x 2048 x 2048   53 /  38 /  34 /  41 /   - [35]
-//   4096 x 1024 x 3072   71 /  30 /  29 / 30 / 39 [36-41]  1053 x 3048 x 1600   35 /  18 /  15 /  17 /  22
-//   384 x 3072 x 3072    57 /  28 /  23 / 17 / 16 [34]     2048 x 1024 x 1024   27 /  14 /  12 / 9.0 / 9.4
-enum class GemmTile { k256, k256x192, k192x128, k128, k128x64, k64 };
-struct GemmChoice {
-  GemmTile tile;
-  bool one_round;
-};
-GemmChoice pick_gemm_tile(int64_t M, int64_t N, int64_t K, bool persist_ok) {
-  struct Cost { GemmTile tile; int bm, bn, launch, per_tile, per_k, alone_per_tile, alone_per_k; };  // alone: one round
-  static const Cost costs[] = {{GemmTile::k256, 256, 256, 5000, 2000, 1330, 2000, 1330},
-                               {GemmTile::k256x192, 256, 192, 3000, 3500, 1180, 5000, 1120},
-                               {GemmTile::k192x128, 192, 128, 3000, 1700, 580, 3500, 500},
-                               {GemmTile::k128, 128, 128, 3000, 2000, 460, 3000, 370},
-                               {GemmTile::k128x64, 128, 64, 3000, 1500, 280, 1500, 260},
-                               {GemmTile::k64, 64, 64, 3000, 500, 200, 500, 230}};
-  const int64_t kt = ceil_div(K, 64);
-  GemmChoice best{GemmTile::k128, true};
-  int64_t best_ns = INT64_MAX;
-  for (const Cost& c : costs) {
-    if (c.tile == GemmTile::k256 && !persist_ok) continue;
-    const int64_t rounds = ceil_div(ceil_div(M, c.bm) * ceil_div(N, c.bn), 256);
-    int64_t per_k = rounds == 1 ? c.alone_per_k : rounds * c.per_k;
-    if (c.tile == GemmTile::k64 && rounds == 2) per_k = 300;  // the second tile hides in the first one's waits
-    const int64_t ns = c.launch + rounds * (rounds == 1 ? c.alone_per_tile : c.per_tile) + kt * per_k;
-    if (ns < best_ns) { best_ns = ns; best = GemmChoice{c.tile, rounds == 1}; }
-  }
-  return best;
-}
 
 template <int TM, int TN, int NS, bool KMAJ, typename TC, bool SUM>
 void ring_gemm(FastGemmParams& p, Launcher& L) {

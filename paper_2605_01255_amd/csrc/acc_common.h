@@ -6,6 +6,7 @@
 #include <type_traits>
 
 #include "../../include/acc.h"
+#include "acc_plan.h"
 
 namespace acc {
 
@@ -35,8 +36,5 @@ template <int B, int E, typename F> __device__ __forceinline__ void static_for(F
     static_for<B + 1, E>(f);
   }
 }
-
-static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
-static inline int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 
 }  // namespace acc

@@ -1,0 +1,85 @@
+// Host-side choices by size: which tile a product takes, how a float32 sketch is formed, and the table of raised LDS limits.
+// Plain C++ with no HIP in it, so that the choices can be checked without a GPU.
+#pragma once
+#include <stdint.h>
+
+#include <mutex>
+
+namespace acc {
+
+static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+static inline int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
+
+// Which kernel and tile a product takes: the least of six estimates, launch + rounds x (cost of a tile + K tiles x time of
+// a K tile), in nanoseconds, with rounds = tiles over 256 compute units.  A larger tile needs fewer bytes from L2 per
+// multiply-add (a 128 x 128 K tile multiplies for 0.2 us and takes 0.36 to move, however many stages are in flight), a
+// smaller one leaves fewer compute units idle.  From two rounds on, two work-groups of two stages per compute unit cover
+// each other's waits better than one of four (4096 x 2048 x 2048 on 128 x 128: 34 against 41 us).  The constants are fits
+// to 45 shapes from 256 x 512 x 512 to 16384 x 3072 x 8192, good to about 15 %.  256 x 192 is there for the shapes that it
+// makes one full round of: 4096 x 3072 x 3072 62 us (192 tiles of 256 x 256: 72), 8192 x 1032 x 4096 68 (73); where both fill
+// the chip the persistent 256 x 256 kernel is ahead (16384 x 3072 x 3072: 255).  Measured us on 256 x 256 / 192 x 128 /
+// 128 x 128 / 128 x 64 / 64 x 64, with what the kernels this replaced took (256 x 256 from 192 tiles on, else a two-stage
+// 128 x 128) in brackets:
+//   16384 x 3072 x 3072 228 / 293 / 286 /  - /  - [228]    16384 x 1152 x 3072 139 / 116 / 129 / 166 / 222 [139]
+//   6000 x 4096 x 4096  188 / 168 / 180 /  - /  - [188]    4096 x 2048 x 2048   53 /  38 /  34 /  41 /   - [35]
+//   4096 x 1024 x 3072   71 /  30 /  29 / 30 / 39 [36-41]  1053 x 3048 x 1600   35 /  18 /  15 /  17 /  22
+//   384 x 3072 x 3072    57 /  28 /  23 / 17 / 16 [34]     2048 x 1024 x 1024   27 /  14 /  12 / 9.0 / 9.4
+enum class GemmTile { k256, k256x192, k192x128, k128, k128x64, k64 };
+struct GemmChoice {
+  GemmTile tile;
+  bool one_round;
+};
+static inline GemmChoice pick_gemm_tile(int64_t M, int64_t N, int64_t K, bool persist_ok) {
+  struct Cost { GemmTile tile; int bm, bn, launch, per_tile, per_k, alone_per_tile, alone_per_k; };  // alone: one round
+  static const Cost costs[] = {{GemmTile::k256, 256, 256, 5000, 2000, 1330, 2000, 1330},
+                               {GemmTile::k256x192, 256, 192, 3000, 3500, 1180, 5000, 1120},
+                               {GemmTile::k192x128, 192, 128, 3000, 1700, 580, 3500, 500},
+                               {GemmTile::k128, 128, 128, 3000, 2000, 460, 3000, 370},
+                               {GemmTile::k128x64, 128, 64, 3000, 1500, 280, 1500, 260},
+                               {GemmTile::k64, 64, 64, 3000, 500, 200, 500, 230}};
+  const int64_t kt = ceil_div(K, 64);
+  GemmChoice best{GemmTile::k128, true};
+  int64_t best_ns = INT64_MAX;
+  for (const Cost& c : costs) {
+    if (c.tile == GemmTile::k256 && !persist_ok) continue;
+    const int64_t rounds = ceil_div(ceil_div(M, c.bm) * ceil_div(N, c.bn), 256);
+    int64_t per_k = rounds == 1 ? c.alone_per_k : rounds * c.per_k;
+    if (c.tile == GemmTile::k64 && rounds == 2) per_k = 300;  // the second tile hides in the first one's waits
+    const int64_t ns = c.launch + rounds * (rounds == 1 ? c.alone_per_tile : c.per_tile) + kt * per_k;
+    if (ns < best_ns) { best_ns = ns; best = GemmChoice{c.tile, rounds == 1}; }
+  }
+  return best;
+}
+
+// Which tile a float32 product takes: the least time of a K tile of 32, fixed + tiles per compute unit x per_tile
+// nanoseconds.  The matrix pipe bounds all of them, so the estimates follow the area, and a small tile only loses by its
+// operands' latency; what decides is how many tiles the fullest compute unit gets.  Constants fitted to 272 measurements
+// (68 shapes from 64 x 2048 x 8192 to 4096 x 4096 x 1024 in the four orders of the operands): the chosen tile is 0.7 %
+// behind the best one on average, 11 % at most (the first fit, rounds times a constant, 25 %).  Measured us, 128 x 64 / 64 x 64 / 64 x 32 / 32 x 32, the chosen one marked
+// [generic kernel before]:
+//   2048 x 2048 x 1024  68* / 73  / 82  / 88 [188]     2048 x 1024 x 2048  73 / 72* / 104 / 89 [347]
+//   300 x 4096 x 2048   77  / 73  / 57* / 60           2504 x 1000 x 3000  186 / 198 / 158* / 164
+//   256 x 512 x 256     12  / 8.0 / 5.9 / 5.0* [22]    3656 x 280 x 288    13.5 / 13.6 / 12.1* / 12.9
+enum class F32TileShape { k64, k32, k128x64, k64x32 };
+struct F32Choice {
+  F32TileShape tile;
+  int ns_per_k;   // estimate of a K tile
+};
+static inline F32Choice pick_f32_tile(int64_t M, int64_t N, int64_t splits, bool all_tiles) {
+  struct Cost { F32TileShape tile; int bm, bn, per_tile, fixed; };
+  static const Cost costs[] = {{F32TileShape::k64, 64, 64, 555, 50}, {F32TileShape::k32, 32, 32, 165, 90},
+                               {F32TileShape::k128x64, 128, 64, 955, 205}, {F32TileShape::k64x32, 64, 32, 274, 65}};
+  F32Choice best{F32TileShape::k64, 0};
+  int64_t best_ns = INT64_MAX;
+  for (int i = 0; i < (all_tiles ? 4 : 2); ++i) {
+    const int64_t per_cu = ceil_div(ceil_div(M, costs[i].bm) * ceil_div(N, costs[i].bn) * splits, 256);
+    const int64_t ns = costs[i].fixed + per_cu * costs[i].per_tile;
+    if (ns < best_ns) {
+      best_ns = ns;
+      best = F32Choice{costs[i].tile, (int)(ns < INT32_MAX ? ns : INT32_MAX)};
+    }
+  }
+  return best;
+}
+
+}  // namespace acc

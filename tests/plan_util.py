@@ -1,0 +1,42 @@
+"""The library's host-side choices by size (csrc/acc_plan.h), compiled with the host compiler: which kernel a call takes."""
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+_SOURCE = r'''
+#include "paper_2605_01255_amd/csrc/acc_plan.h"
+using namespace acc;
+extern "C" {
+int gemm_tile(int64_t M, int64_t N, int64_t K, int persist_ok) { return (int)pick_gemm_tile(M, N, K, persist_ok != 0).tile; }
+int gemm_one_round(int64_t M, int64_t N, int64_t K, int persist_ok) { return pick_gemm_tile(M, N, K, persist_ok != 0).one_round; }
+int f32_tile(int64_t M, int64_t N, int64_t splits, int all_tiles) { return (int)pick_f32_tile(M, N, splits, all_tiles != 0).tile; }
+}
+'''
+
+
+@functools.lru_cache(maxsize=None)
+def lib():
+    with tempfile.TemporaryDirectory() as tmp:
+        src, out = os.path.join(tmp, "plan.cpp"), os.path.join(tmp, "plan.so")
+        with open(src, "w") as f:
+            f.write(_SOURCE)
+        subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-O1", "-shared", "-fPIC", "-I" + ROOT, src, "-o", out], check=True)
+        so = ctypes.CDLL(out)
+    for name in ("gemm_tile", "gemm_one_round", "f32_tile"):
+        getattr(so, name).argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int]
+    return so
+
+
+def gemm_tile(m, n, k, float_or_sum=False):
+    """(tile of the bfloat16 product, whether it is one round): as fast_gemm chooses on the ring and persistent kernels."""
+    persist = not float_or_sum and k > 128
+    names = ("256x256", "256x192", "192x128", "128x128", "128x64", "64x64")
+    return names[lib().gemm_tile(m, n, k, persist)], bool(lib().gemm_one_round(m, n, k, persist))
+
+
+def f32_tile(m, n, splits=1, both_f32=True):
+    return ("64x64", "32x32", "128x64", "64x32")[lib().f32_tile(m, n, splits, both_f32)]
