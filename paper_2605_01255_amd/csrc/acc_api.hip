@@ -255,17 +255,6 @@ void project_adam(bool w_oi, const float* t1, const void* Gr, float* M, float* V
 }
 
 // ---- generic path --------------------------------------------------------------------------
-// Token splits of the sketch contraction: enough work-groups to fill 256 CUs, at most 32 partials.
-int generic_sketch_splits(int64_t n, int64_t c, int64_t r) {
-  const int64_t tiles = ceil_div(c, 64) * ceil_div(r, 64);
-  int64_t g = ceil_div(1024, tiles);
-  const int64_t max_by_k = ceil_div(n, 256);
-  if (g > max_by_k) g = max_by_k;
-  if (g > 32) g = 32;
-  if (g < 1) g = 1;
-  return (int)g;
-}
-
 template <typename TA, typename TB, typename TC, typename CT, bool SK, bool ACCURATE>
 void launch_generic(const GemmParams& p, int splits, Launcher& L, int sum_tiles = 8) {
   if constexpr (sizeof(TA) == 4 && sizeof(TB) == 4 && !SK) {  // two float32 operands: the tuned kernel where strides allow
@@ -292,25 +281,15 @@ void launch_reduce(const float* part, int G, int64_t count, void* out, int64_t r
   L(reduce_partials_kernel<T>, dim3((unsigned)ceil_div(count, 1024)), dim3(256), part, G, count, count, (T*)out, row, ld);
 }
 
-// Sketch of a float32 layer with S written out once, into the part of the workspace that the partial products leave free:
-// the libm-grade generator then runs once per entry of S instead of once per entry and 64 channels.  Token splits: enough
-// work-groups to fill the chip, as far as that room goes; one split writes a float32 factor directly.
-// Returns false when S does not fit (few channels) or the kernel does not take the operands.
+// Sketch of a float32 layer with a stored S (plan_f32_sketch).  Returns false when the generic form is to run: by the plan,
+// or because the kernel does not take the operands.
 bool f32_sketch(const acc_linear_desc* d, const void* A, int64_t lda, int64_t channels, int64_t n, bool transposed,
                 void* out, int64_t out_ld, float* ws, Launcher& L) {
   const int64_t r = d->r, count = channels * r, s_size = n * r;
-  const int64_t room = generic_sketch_splits(n, channels, r) * count;
-  if (s_size > room) return false;
   const bool direct = d->factor_dtype == ACC_F32;
-  int64_t G = ceil_div(256, ceil_div(channels, 32) * ceil_div(r, 32));
-  if (G > ceil_div(n, 256)) G = ceil_div(n, 256);
-  if (G > (room - s_size) / count) G = (room - s_size) / count;
-  if (G < 1) {
-    if (!direct) return false;
-    G = 1;
-  }
-  const int64_t k_per_split = round_up(ceil_div(n, G), 32);
-  G = ceil_div(n, k_per_split);
+  const F32SketchPlan plan = plan_f32_sketch(n, channels, r, direct);
+  if (!plan.stored) return false;
+  const int64_t G = plan.splits, k_per_split = plan.k_per_split;
   const F32Operand x{A, lda, false, false}, sm{ws, r, false, false};
   float* part = ws + s_size;   // n r floats: r % 8 == 0 keeps the alignment
   float* dst = G == 1 && direct ? (float*)out : part;

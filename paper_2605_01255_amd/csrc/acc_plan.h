@@ -82,4 +82,54 @@ static inline F32Choice pick_f32_tile(int64_t M, int64_t N, int64_t splits, bool
   return best;
 }
 
+// Token splits of the sketch contraction: enough work-groups to fill 256 CUs, at most 32 partials.
+static inline int generic_sketch_splits(int64_t n, int64_t c, int64_t r) {
+  const int64_t tiles = ceil_div(c, 64) * ceil_div(r, 64);
+  int64_t g = ceil_div(1024, tiles);
+  const int64_t max_by_k = ceil_div(n, 256);
+  if (g > max_by_k) g = max_by_k;
+  if (g > 32) g = 32;
+  if (g < 1) g = 1;
+  return (int)g;
+}
+
+// How the sketch of a float32 layer is formed.  Stored: S is written once, into the part of the workspace that the partial
+// products leave free (the libm-grade generator then runs once per entry of S instead of once per entry and 64 channels),
+// with token splits enough to fill the chip as far as that room goes; one split writes a float32 factor directly.  Generic:
+// S is generated inside the product, all splits that there is room for.  When S takes nearly all the room, one or two
+// splits are left, K tiles in series that few work-groups share, and the generic form is ahead.  The lesser of
+//   stored    4.6 us + 4 per million entries of S + K tiles of a split x a K tile's time (1.15 of pick_f32_tile's: both
+//             operands have their rows contiguous) + 5 us where partial products are added up
+//   generic   5 us + 256 tokens of a split x (20 us + 8 per work-group of 64 x 64 on a compute unit)
+// Measured us, tokens x channels at rank: stored / generic
+//   8192 x 256 r = 64    80 / 34     16384 x 512 r = 16  150 / 71     32768 x 1024 r = 64  300 / 153   (one split)
+//   4096 x 256 r = 64    42 / 29     3000 x 256 r = 256   35 / 28     65536 x 2048 r = 32  586 / 449
+//   2048 x 256 r = 64    24 / 27     14000 x 512 r = 64   40 / 62     24000 x 1024 r = 64   63 / 118   (four)
+//   60000 x 2048 r = 32  263 / 402   8192 x 512 r = 64    20 / 41     4096 x 4096 r = 256   93 / 194
+struct F32SketchPlan {
+  bool stored;
+  int64_t splits, k_per_split;
+};
+static inline F32SketchPlan plan_f32_sketch(int64_t n, int64_t channels, int64_t r, bool f32_factor) {
+  const int64_t count = channels * r, s_size = n * r, generic_splits = generic_sketch_splits(n, channels, r);
+  const int64_t room = generic_splits * count;
+  F32SketchPlan plan{false, 0, 0};
+  if (s_size > room) return plan;
+  int64_t G = ceil_div(256, ceil_div(channels, 32) * ceil_div(r, 32));
+  if (G > ceil_div(n, 256)) G = ceil_div(n, 256);
+  if (G > (room - s_size) / count) G = (room - s_size) / count;
+  if (G < 1) {
+    if (!f32_factor) return plan;
+    G = 1;
+  }
+  plan.k_per_split = round_up(ceil_div(n, G), 32);
+  plan.splits = ceil_div(n, plan.k_per_split);
+  const double k_tile = 1.15 * pick_f32_tile(channels, r, plan.splits, true).ns_per_k;
+  const double stored = 4600 + 0.004 * s_size + plan.k_per_split / 32 * k_tile + (plan.splits > 1 || !f32_factor ? 5000 : 0);
+  const int64_t groups = ceil_div(generic_splits * ceil_div(channels, 64) * ceil_div(r, 64), 256);
+  const double generic = 5000 + ceil_div(n, generic_splits) / 256.0 * (20000 + 8000 * groups);
+  plan.stored = stored < generic;
+  return plan;
+}
+
 }  // namespace acc

@@ -14,6 +14,15 @@ extern "C" {
 int gemm_tile(int64_t M, int64_t N, int64_t K, int persist_ok) { return (int)pick_gemm_tile(M, N, K, persist_ok != 0).tile; }
 int gemm_one_round(int64_t M, int64_t N, int64_t K, int persist_ok) { return pick_gemm_tile(M, N, K, persist_ok != 0).one_round; }
 int f32_tile(int64_t M, int64_t N, int64_t splits, int all_tiles) { return (int)pick_f32_tile(M, N, splits, all_tiles != 0).tile; }
+int f32_sketch_splits(int64_t n, int64_t channels, int64_t r, int f32_factor) {  // 0: the generic form
+  const F32SketchPlan p = plan_f32_sketch(n, channels, r, f32_factor != 0);
+  return p.stored ? (int)p.splits : 0;
+}
+int f32_sketch_fits(int64_t n, int64_t channels, int64_t r, int f32_factor) {
+  const F32SketchPlan p = plan_f32_sketch(n, channels, r, f32_factor != 0);
+  const int64_t partials = p.splits == 1 && f32_factor ? 0 : p.splits * channels * r;
+  return !p.stored || n * r + partials <= generic_sketch_splits(n, channels, r) * channels * r;
+}
 }
 '''
 
@@ -26,7 +35,7 @@ def lib():
             f.write(_SOURCE)
         subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-O1", "-shared", "-fPIC", "-I" + ROOT, src, "-o", out], check=True)
         so = ctypes.CDLL(out)
-    for name in ("gemm_tile", "gemm_one_round", "f32_tile"):
+    for name in ("gemm_tile", "gemm_one_round", "f32_tile", "f32_sketch_splits", "f32_sketch_fits"):
         getattr(so, name).argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int]
     return so
 
@@ -40,3 +49,13 @@ def gemm_tile(m, n, k, float_or_sum=False):
 
 def f32_tile(m, n, splits=1, both_f32=True):
     return ("64x64", "32x32", "128x64", "64x32")[lib().f32_tile(m, n, splits, both_f32)]
+
+
+def f32_sketch_splits(n, channels, r, f32_factor=True):
+    """Token splits of a float32 layer's sketch with a stored S; 0 when the generic form runs."""
+    return lib().f32_sketch_splits(n, channels, r, f32_factor)
+
+
+def f32_sketch_fits(n, channels, r, f32_factor=True):
+    """Whether S and the partial products fit the workspace of the generic form."""
+    return bool(lib().f32_sketch_fits(n, channels, r, f32_factor))
