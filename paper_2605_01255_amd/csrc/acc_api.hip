@@ -94,26 +94,7 @@ int check_device() {
   return cached[dev] == 1 ? ACC_OK : ACC_ERR_HIP;
 }
 
-// Kernels whose dynamic-LDS limit has been raised on a device (the attribute sticks to the function, so
-// it is set once per kernel and device, not per launch).  The table is shared by all host threads.
-struct RaisedEntry { const void* kernel; int device; };
-RaisedEntry g_raised[64];
-int g_raised_count = 0;
-std::mutex g_raised_mutex;
-bool lds_limit_raised(const void* kernel) {
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return false;
-  std::lock_guard<std::mutex> lock(g_raised_mutex);
-  for (int i = 0; i < g_raised_count; ++i)
-    if (g_raised[i].kernel == kernel && g_raised[i].device == dev) return true;
-  return false;
-}
-void lds_limit_note(const void* kernel) {
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return;
-  std::lock_guard<std::mutex> lock(g_raised_mutex);
-  if (g_raised_count < 64) g_raised[g_raised_count++] = RaisedEntry{kernel, dev};
-}
+RaisedLimits g_raised;
 
 // Enqueues kernels on one stream and remembers the first launch error.
 struct Launcher {
@@ -128,10 +109,13 @@ struct Launcher {
   void launch_lds(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds_bytes, Args... args) {
     if (err != hipSuccess) return;
     if (lds_bytes > 64 * 1024) {
-      if (!lds_limit_raised((const void*)kernel)) {
+      int dev = 0;
+      err = hipGetDevice(&dev);
+      if (err != hipSuccess) return;
+      if (!g_raised.has((const void*)kernel, dev)) {
         err = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (err != hipSuccess) return;
-        lds_limit_note((const void*)kernel);
+        g_raised.add((const void*)kernel, dev);
       }
     }
     std::tuple<KArgs...> vals{args...};

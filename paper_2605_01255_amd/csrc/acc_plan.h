@@ -132,4 +132,32 @@ static inline F32SketchPlan plan_f32_sketch(int64_t n, int64_t channels, int64_t
   return plan;
 }
 
+// Kernels whose dynamic-LDS limit has been raised, and on which devices (the attribute sticks to the function, so it is set
+// once per kernel and device, not per launch).  Shared by all host threads; holds every kernel of the library.
+class RaisedLimits {
+ public:
+  static constexpr int kKernels = 512, kDevices = 64;
+  bool has(const void* kernel, int device) {
+    std::lock_guard<std::mutex> lock(mutex_);
+    for (int i = 0; i < count_; ++i)
+      if (entries_[i].kernel == kernel) return device >= 0 && device < kDevices && (entries_[i].devices >> device & 1);
+    return false;
+  }
+  void add(const void* kernel, int device) {
+    if (device < 0 || device >= kDevices) return;
+    std::lock_guard<std::mutex> lock(mutex_);
+    int i = 0;
+    while (i < count_ && entries_[i].kernel != kernel) ++i;
+    if (i == kKernels) return;
+    if (i == count_) entries_[count_++] = Entry{kernel, 0};
+    entries_[i].devices |= (uint64_t)1 << device;
+  }
+
+ private:
+  struct Entry { const void* kernel; uint64_t devices; };
+  Entry entries_[kKernels];
+  int count_ = 0;
+  std::mutex mutex_;
+};
+
 }  // namespace acc

@@ -14,6 +14,19 @@ extern "C" {
 int gemm_tile(int64_t M, int64_t N, int64_t K, int persist_ok) { return (int)pick_gemm_tile(M, N, K, persist_ok != 0).tile; }
 int gemm_one_round(int64_t M, int64_t N, int64_t K, int persist_ok) { return pick_gemm_tile(M, N, K, persist_ok != 0).one_round; }
 int f32_tile(int64_t M, int64_t N, int64_t splits, int all_tiles) { return (int)pick_f32_tile(M, N, splits, all_tiles != 0).tile; }
+int raised_capacity() { return RaisedLimits::kKernels; }
+int raised_lost(int kernels, int devices) {  // entries the table has forgotten after all were added
+  static RaisedLimits table;
+  int lost = 0;
+  for (int d = 0; d < devices; ++d)
+    for (int k = 1; k <= kernels; ++k) {
+      if (table.has((const void*)(intptr_t)k, d)) ++lost;   // not added yet
+      table.add((const void*)(intptr_t)k, d);
+    }
+  for (int d = 0; d < devices; ++d)
+    for (int k = 1; k <= kernels; ++k) lost += table.has((const void*)(intptr_t)k, d) ? 0 : 1;
+  return lost;
+}
 int f32_sketch_splits(int64_t n, int64_t channels, int64_t r, int f32_factor) {  // 0: the generic form
   const F32SketchPlan p = plan_f32_sketch(n, channels, r, f32_factor != 0);
   return p.stored ? (int)p.splits : 0;

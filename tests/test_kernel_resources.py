@@ -22,6 +22,11 @@ def test_hot_kernels_use_no_scratch_memory():
     assert not bad, bad
 
 
+def test_the_table_of_raised_lds_limits_holds_every_kernel():
+    import plan_util
+    assert len(resources()) <= plan_util.lib().raised_capacity()
+
+
 def test_slot_programs_hold_one_matrix_instruction_per_slot():
     """Between two scheduling fences of the persistent GEMM kernels there is at most one matrix instruction, and every
     K-tile variant is there in full (bf16: three variants of 128 slots; 8-bit: three of 64)."""

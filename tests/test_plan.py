@@ -53,3 +53,8 @@ def test_stored_sketch_fits_the_workspace():
             for r in (8, 24, 64, 264, 512):
                 for f32_factor in (True, False):
                     assert plan.f32_sketch_fits(n, channels, r, f32_factor), (n, channels, r, f32_factor)
+
+
+def test_raised_lds_limits_are_remembered_for_every_kernel_and_device():
+    """A launch whose kernel is not in the table sets the limit again."""
+    assert plan.lib().raised_lost(plan.lib().raised_capacity(), 64) == 0
