@@ -610,37 +610,52 @@ void run_sketch(const acc_linear_desc* d, const void* A, int64_t lda, int64_t ch
 // Forward chain: Yr = X.Omega -> Cholesky QR twice -> U -> V = X^T.U; every product on the generic MFMA
 // kernel (fp32 matrix instructions wherever an fp32 operand is involved), K-splits reduced by K4.
 constexpr int64_t kQrSmallRank = 64;     // up to here a pass needs little scratch: 256 Gram partials and the image
-constexpr size_t kQrImageRoom = (size_t)(64 * 64 + 2 * 64) * 4;
-struct RsvdPlan {
-  bool tuned;   // bf16 inputs and factors, sizes the tuned GEMM kernel takes: skinny products via split K
-  int g_gram;   // token splits of the k x k Gram products
-  int g_fact;   // token splits of V = X^T.U (forward) or Gr = U^T.dY (backward), generic path
-  int64_t n_pad;  // tokens rounded up to 64 (K padding of the products over tokens)
-  size_t off_y0, off_q1, off_gram_part, off_gram, off_rinv, off_fact_part;  // byte offsets
-  size_t off_omega, off_ut, off_yr_part, off_z0, off_z1, off_zt_part, total;
-  size_t off_rt;  // ranks above 64: the transposed triangular factor [k, k] of the blocked Cholesky
-};
-
-// Scratch of one Cholesky-QR pass at rank k: Gram partials, their sum, and the triangular factor's image.  Above 64 the
-// image of one factorisation (up to rank 256) lies in `rt`; above 256, where rt holds the transposed factor of the blocked
-// form, the images lie where the Gram partials were, and rinv holds the matrix's largest diagonal entry.
+constexpr size_t kQrImageRoom = (size_t)(64 * 64 + 2 * 64) * 4;   // of an image up to that rank
+// Scratch of one Cholesky-QR pass at rank k, byte offsets: Gram partials, their sum, and the triangular factor's images, one
+// per 256 columns.  Up to rank 64 the image has room of its own; up to 256 it takes the k x k floats that the blocked form
+// needs for the transposed factor; above, the images take the Gram partials' place (added up by then).
 constexpr int kGramSplitsBlocked = 16;
-struct QrScratch { size_t gram_part, gram, rinv, rt; };
+constexpr size_t kQrImageBytes = (size_t)tri_block(kQrMaxRank / 16, 0) * 1024;   // of a factorisation of 256 columns
+struct QrScratch {
+  size_t gram_part, gram, image;
+  size_t rt, scale_ref;   // blocked form: the transposed factor [k, k], the matrix's largest diagonal entry
+};
 template <typename Take>
 QrScratch take_qr_scratch(int64_t k, int g_gram, Take& take) {
   QrScratch q{};
   if (k <= kQrSmallRank) {
     q.gram_part = take((size_t)g_gram * k * k * 4);
     q.gram = take((size_t)k * k * 4);
-    q.rinv = take(kQrImageRoom);
+    q.image = take(kQrImageRoom);
   } else {
     q.gram_part = take((size_t)kGramSplitsBlocked * k * k * 4);
     q.gram = take((size_t)k * k * 4);
-    q.rinv = take(kQrImageRoom * (size_t)ceil_div(k, kQrSmallRank) + 256);
+    q.scale_ref = take(kQrImageRoom * (size_t)ceil_div(k, kQrSmallRank) + 256);   // one float: the size callers have sized for
     q.rt = take((size_t)k * k * 4);
+    q.image = k <= kQrMaxRank ? q.rt : q.gram_part;
   }
   return q;
 }
+constexpr bool qr_images_fit() {
+  for (int k = 8; k <= kRsvdMaxRankBlocked; k += 8) {
+    const size_t image = (size_t)tri_block((k + 15) / 16, 0) * 1024, square = (size_t)k * k * 4;
+    if (k <= kQrSmallRank ? image > kQrImageRoom
+                          : k <= kQrMaxRank ? image > square : (k + kQrMaxRank - 1) / kQrMaxRank * kQrImageBytes > kGramSplitsBlocked * square)
+      return false;
+  }
+  return true;
+}
+static_assert(qr_images_fit(), "a triangular factor's image exceeds the room it takes");
+
+struct RsvdPlan {
+  QrScratch qr;
+  bool tuned;   // bf16 inputs and factors, sizes the tuned GEMM kernel takes: skinny products via split K
+  int g_gram;   // token splits of the k x k Gram products
+  int g_fact;   // token splits of V = X^T.U (forward) or Gr = U^T.dY (backward), generic path
+  int64_t n_pad;  // tokens rounded up to 64 (K padding of the products over tokens)
+  size_t off_y0, off_q1, off_fact_part;  // byte offsets
+  size_t off_omega, off_ut, off_yr_part, off_z0, off_z1, off_zt_part, total;
+};
 
 // Rounds of subspace iteration asked for in the descriptor (RSVD entry points only).
 int rsvd_power_iters(const acc_linear_desc* d) { return (int)((d->flags >> ACC_FLAG_RSVD_POWER_SHIFT) & 3u); }
@@ -662,8 +677,7 @@ RsvdPlan plan_rsvd(const acc_linear_desc* d, const Shape& s, bool backward) {
   if (!backward) {
     pl.off_y0 = take((size_t)s.n * k * 4);
     pl.off_q1 = take((size_t)s.n * k * 4);
-    const QrScratch q = take_qr_scratch(k, pl.g_gram, take);
-    pl.off_gram_part = q.gram_part; pl.off_gram = q.gram; pl.off_rinv = q.rinv; pl.off_rt = q.rt;
+    pl.qr = take_qr_scratch(k, pl.g_gram, take);
     if (rsvd_power_iters(d)) {  // Z = X^T.U and its orthonormalised form, [d_in, k] fp32
       pl.off_z0 = take((size_t)s.d_in * k * 4);
       pl.off_z1 = take((size_t)s.d_in * k * 4);
@@ -714,8 +728,8 @@ void reduce_to(int out_dt, const float* part, int G, int64_t count, void* out, L
 // U [512, 256]: 1.3e-7, 2.8e-7 with the usual 256).  An earlier pass's need not be: Yin . R^-1 has the same
 // thin QR factor whatever upper triangular R it is multiplied with.
 void gram_matrix(const RsvdPlan& pl, char* ws, int64_t m, int64_t k, const float* Yin, bool final_pass, Launcher& L) {
-  float* gram_part = (float*)(ws + pl.off_gram_part);
-  float* gram = (float*)(ws + pl.off_gram);
+  float* gram_part = (float*)(ws + pl.qr.gram_part);
+  float* gram = (float*)(ws + pl.qr.gram);
   const int64_t tiles = ceil_div(k, 32) * ceil_div(k, 32);
   int64_t splits = 512 / tiles;   // two work-groups per compute unit
   const int64_t most = k <= kQrSmallRank ? pl.g_gram : kGramSplitsBlocked;
@@ -770,12 +784,12 @@ void chol_solve(const float* Y, int64_t m, int64_t w, const float* image, float*
 void cholesky_qr_pass_blocked(const Shape& s, const RsvdPlan& pl, char* ws, int64_t m, int64_t m_pad, float* Yin,
                               float* Qf, void* Qt, int qt_dt, bf16* Ut, int64_t ldt, bool hilo, bool final_pass, Launcher& L) {
   const int64_t k = s.r;
-  float* gram = (float*)(ws + pl.off_gram);
-  float* rt = (float*)(ws + pl.off_rt);
-  float* scale_ref = (float*)(ws + pl.off_rinv);
+  float* gram = (float*)(ws + pl.qr.gram);
+  float* rt = (float*)(ws + pl.qr.rt);
+  float* scale_ref = (float*)(ws + pl.qr.scale_ref);
   float* W = Qf ? Qf : Yin;
   const int nb = (int)ceil_div(k, kQrMaxRank);
-  auto image = [&](int j) { return (float*)(ws + pl.off_gram_part) + (int64_t)j * tri_block(kQrMaxRank / 16, 0) * 256; };
+  auto image = [&](int j) { return (float*)(ws + pl.qr.image + j * kQrImageBytes); };
   gram_matrix(pl, ws, m, k, Yin, final_pass, L);
   L(diag_max_kernel, dim3(1), dim3(64), (const float*)gram, (int)k, k, scale_ref);
   for (int j = 0; j < nb; ++j) {
@@ -827,9 +841,9 @@ void cholesky_qr_pass(const Shape& s, const RsvdPlan& pl, char* ws, int64_t m, i
     cholesky_qr_pass_blocked(s, pl, ws, m, m_pad, Yin, Qf, Qt, qt_dt, Ut, ldt, hilo, final_pass, L);
     return;
   }
-  float* image = (float*)(ws + (k <= kQrSmallRank ? pl.off_rinv : pl.off_rt));
+  float* image = (float*)(ws + pl.qr.image);
   gram_matrix(pl, ws, m, k, Yin, final_pass, L);
-  chol_factor((const float*)(ws + pl.off_gram), k, k, image, nullptr, k <= kQrSmallRank ? 1e-6f : (float)k * 1.1920929e-7f, L);
+  chol_factor((const float*)(ws + pl.qr.gram), k, k, image, nullptr, k <= kQrSmallRank ? 1e-6f : (float)k * 1.1920929e-7f, L);
   const int64_t rows_out = Ut ? m_pad : m;
   if (qt_dt == ACC_BF16) chol_solve<bf16>(Yin, m, k, image, Qf, Qt, Ut, ldt, rows_out, hilo, k, k, k, L);
   else chol_solve<float>(Yin, m, k, image, Qf, Qt, Ut, ldt, rows_out, hilo, k, k, k, L);
@@ -977,7 +991,8 @@ struct LowrankPlan {
   int t1_splits, z_splits, g_gram;
   int64_t t1_k_per_split, z_k_per_split;
   size_t off_n, off_part, off_t1, off_r;                                  // the step
-  size_t off_z, off_yp, off_q1, off_gram_part, off_gram, off_rinv, off_rt;  // the projector (shares off_part)
+  size_t off_z, off_yp, off_q1;  // the projector (shares off_part)
+  QrScratch qr;
   size_t step_total, total;
 };
 
@@ -1016,8 +1031,7 @@ LowrankPlan plan_lowrank(const acc_linear_desc* d, const Shape& s, int64_t k) {
     pl.off_z = take((size_t)s.r * k * 4);
     pl.off_yp = take((size_t)s.d_in * k * 4);
     pl.off_q1 = take((size_t)s.d_in * k * 4);
-    const QrScratch q = take_qr_scratch(k, pl.g_gram, take);
-    pl.off_gram_part = q.gram_part; pl.off_gram = q.gram; pl.off_rinv = q.rinv; pl.off_rt = q.rt;
+    pl.qr = take_qr_scratch(k, pl.g_gram, take);
   }
   pl.total = off;
   return pl;
@@ -1447,8 +1461,8 @@ int acc_lowrank_projector(const acc_linear_desc* desc, int64_t k, const void* le
   Shape sk = s;
   sk.r = k;
   RsvdPlan rp{};
-  rp.g_gram = pl.g_gram; rp.off_gram_part = pl.off_gram_part; rp.off_gram = pl.off_gram; rp.off_rinv = pl.off_rinv;
-  rp.off_rt = pl.off_rt;
+  rp.g_gram = pl.g_gram;
+  rp.qr = pl.qr;
   cholesky_qr_pass(sk, rp, ws, s.d_in, s.d_in, yp, q1, nullptr, ACC_F32, nullptr, 0, false, false, L);
   cholesky_qr_pass(sk, rp, ws, s.d_in, s.d_in, q1, nullptr, P, desc->factor_dtype, nullptr, 0, false, true, L);
   return L.status();
