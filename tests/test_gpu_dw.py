@@ -1,7 +1,7 @@
 """The dense weight gradient from the two factors alone (acc_linear_dw: Sec. 4, update strategy (i)) against the
 oracle's product, over the shapes that choose between its kernels: the three-stage small-K kernel (at most 256
-tiles of 192 x 192), the pipelined kernel (more tiles), the generic kernels (fp32 factors, K % 64 != 0); ragged
-edges in both dimensions, both orientations, both output types, plain and accumulating."""
+tiles of 192 x 192), the kernels of the exact products (more tiles), the float32 kernel (fp32 factors), the generic kernels
+(factors beyond 4 GiB); ragged edges in both dimensions, both orientations, both output types, plain and accumulating."""
 import numpy as np
 import pytest
 
@@ -34,9 +34,9 @@ CASES = [
     (200, 392, 64, "bf16", "bf16"),        # ragged in both dimensions, one K tile
     (1000, 1160, 128, "bf16", "f32"),      # ragged, fp32 output
     (3000, 3080, 512, "bf16", "bf16"),     # eight K tiles: the ring of three stages wraps twice
-    (3072, 8192, 192, "bf16", "bf16"),     # 688 tiles: the pipelined kernel
-    (520, 264, 40, "bf16", "bf16"),        # K % 64 != 0: generic kernel
-    (264, 520, 32, "f32", "f32"),          # fp32 factors: generic kernel
+    (3072, 8192, 192, "bf16", "bf16"),     # 688 tiles: the persistent kernel, accumulating the ring kernel
+    (520, 264, 40, "bf16", "bf16"),        # K % 64 != 0: the last K tile masked
+    (264, 520, 32, "f32", "f32"),          # fp32 factors: the float32 kernel
 ]
 
 
@@ -72,3 +72,33 @@ def test_dense_gradient_from_factors(acc, d_in, d_out, r, fdt, ddt, w_out_in):
     acc.acc_linear_dw(desc_a, Xs, Gr, dW2)
     torch.cuda.synchronize()
     gu.assert_close(acc.to_host_f64(dW2), inputs.as_f64(start_h) + w, tol, "dW accumulated")
+
+
+@pytest.mark.parametrize("w_out_in", [False, True])
+@pytest.mark.parametrize("ddt", ["bf16", "f32"])
+def test_factors_beyond_4_gib_take_the_generic_kernel(acc, ddt, w_out_in):
+    """Rows of the left factor so far apart that it spans more than 4 GiB, which the tuned kernels cannot address."""
+    import torch
+    dev, d_in, d_out, r, ldf = "cuda:0", 264, 72, 40, (1 << 23) + 8
+    assert d_in * ldf * 2 > 1 << 32
+    xs_h, gr_h = _factors(d_in, d_out, r, "bf16", seed=3)
+    want = inputs.as_f64(xs_h) @ inputs.as_f64(gr_h)
+    want = want.T if w_out_in else want
+    Xs = torch.empty(d_in, ldf, dtype=torch.bfloat16, device=dev)
+    Xs[:, :r] = acc.to_device(xs_h, dev)
+    Xs[:, r:r + 64] = float("nan")
+    if w_out_in:
+        Gr = torch.empty(d_out, ldf, dtype=torch.bfloat16, device=dev)
+        Gr[:, :r] = acc.to_device(np.ascontiguousarray(gr_h.T), dev)
+        Gr[:, r:r + 64] = float("nan")
+    else:
+        Gr = acc.to_device(gr_h, dev)
+    code = acc.ACC_BF16 if ddt == "bf16" else acc.ACC_F32
+    flags = acc.ACC_FLAG_W_OUT_IN if w_out_in else 0
+    dW = torch.full(want.shape, 7.0, dtype=acc.torch_dtype(code), device=dev)
+    print(f"dW beyond 4 GiB {ddt} w_out_in={w_out_in}", flush=True)
+    acc.acc_linear_dw(acc.make_desc(256, d_in, d_out, r, dw_dtype=code, flags=flags, ldf=ldf), Xs, Gr, dW)
+    gu.assert_close(acc.to_host_f64(dW), want, 1e-2 if ddt == "bf16" else 1e-5, "dW")
+    start = acc.to_host_f64(dW)
+    acc.acc_linear_dw(acc.make_desc(256, d_in, d_out, r, dw_dtype=code, flags=flags | acc.ACC_FLAG_DW_ACCUMULATE, ldf=ldf), Xs, Gr, dW)
+    gu.assert_close(acc.to_host_f64(dW), start + want, 1e-2 if ddt == "bf16" else 1e-5, "dW accumulated")

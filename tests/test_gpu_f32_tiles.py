@@ -9,6 +9,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 from oracle import acc_oracle as orc
+import plan_util as plan
 
 
 @pytest.fixture(scope="module")
@@ -37,15 +38,22 @@ def _check(name, got, want, k, extra=0.0):
 
 
 @pytest.mark.parametrize("out_in", [False, True])
-@pytest.mark.parametrize("n,d_in,d_out,r", [
-    (1, 8, 8, 8),                # one chunk of everything
-    (33, 40, 72, 16),            # 32 x 32 tiles, second K tile of one or two chunks; S does not fit the workspace
-    (300, 328, 296, 24),         # K tiles more than stages, one token split, S beside nothing else
-    (1030, 520, 1032, 40),       # 64 x 32 and 64 x 64 tiles, several token splits
-    (2052, 1032, 2056, 64),      # 128 x 64 tiles
+@pytest.mark.parametrize("n,d_in,d_out,r,tiles", [   # tiles of Y, dX, dW and the forward sketch
+    (1, 8, 8, 8, ["32x32"] * 4),                     # one chunk of everything
+    (33, 40, 72, 16, ["32x32"] * 4),                 # second K tile of one or two chunks
+    (300, 328, 296, 24, ["32x32"] * 4),              # K tiles more than stages, one token split, S beside nothing else
+    (1030, 520, 1032, 40, ["64x32", "32x32", "32x32", "32x32"]),      # several token splits
+    (2052, 1032, 2056, 64, ["64x32", "64x32", "64x32", "64x32"]),
+    (1030, 1032, 1032, 1032, ["64x32"] * 4),         # 64 x 32 with both operands' rows contiguous, one split
+    (776, 2048, 2048, 24, ["64x64", "64x64", "128x64", "32x32"]),     # dW: one K tile of a ring of three
+    (2044, 2040, 2040, 40, ["128x64", "128x64", "128x64", "32x32"]),  # K ends inside a K tile
+    (300, 2040, 2040, 2040, ["32x32", "32x32", "128x64", "128x64"]),  # 128 x 64 with both operands' rows contiguous
 ])
-def test_layer(acc, n, d_in, d_out, r, out_in):
+def test_layer(acc, n, d_in, d_out, r, tiles, out_in):
     import torch
+    splits = plan.f32_sketch_splits(n, d_in, r)
+    assert splits > 0 and tiles == [plan.f32_tile(n, d_out), plan.f32_tile(n, d_in), plan.f32_tile(d_in, d_out),
+                                    plan.f32_tile(d_in, r, splits)]
     dev = "cuda:0"
     g = torch.Generator(device=dev).manual_seed(n)
     X, dY = torch.randn(n, d_in, generator=g, device=dev), torch.randn(n, d_out, generator=g, device=dev)

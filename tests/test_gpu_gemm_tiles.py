@@ -2,11 +2,14 @@
 
 The contraction length is no multiple of 64, so the last K tile is partly empty; X and W sit in wider rows whose padding
 is NaN, so a product that reads past K, or multiplies a zero by what lies there, shows.  Bound: the operands are exact
-bfloat16 and the output is rounded once, 2^-9 per element at most; the fp32 sums add 1e-5 at these lengths."""
+bfloat16 and the output is rounded once, half a unit in the last place, 2^-8 of the element at most; the fp32 sums add 1e-5
+at these lengths."""
 import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
+
+import plan_util as plan
 
 
 @pytest.fixture(scope="module")
@@ -18,19 +21,19 @@ def acc():
     return binding
 
 
-# (rows, columns, contraction): the tile the dispatch takes, and what is at an edge there
+# rows, columns, contraction, the tile the dispatch takes and whether it is one round of the chip; what is at an edge there
 SHAPES = [
-    (1, 8, 8),            # 64 x 64, less than one K tile
-    (65, 72, 72),         # 64 x 64, one row and one chunk into the second tile, second K tile of one chunk
-    (200, 520, 456),      # 64 x 64, more K tiles than stages
-    (1400, 1032, 1000),   # 128 x 64
-    (1053, 3048, 1592),   # 128 x 128, one round of tiles
-    (2050, 3080, 1000),   # 128 x 128, several tiles per compute unit
-    (1100, 5000, 2000),   # 192 x 128, one round of tiles
-    (4000, 2056, 392),    # 192 x 128, several tiles per compute unit
-    (4090, 3064, 392),    # 256 x 192, one round of tiles
-    (8200, 4104, 136),    # 256 x 256, three K tiles, several tiles per work-group
-    (600, 18008, 136),    # 256 x 256, three rows of tiles
+    (1, 8, 8, "64x64", True),               # less than one K tile
+    (65, 72, 72, "64x64", True),            # one row and one chunk into the second tile, second K tile of one chunk
+    (200, 520, 456, "64x64", True),         # more K tiles than stages
+    (1400, 1032, 1000, "128x64", True),
+    (1053, 3048, 1592, "128x128", True),
+    (2050, 3080, 1000, "128x128", False),
+    (1100, 5000, 2000, "192x128", True),
+    (4000, 2056, 392, "192x128", False),
+    (4090, 3064, 392, "256x192", True),
+    (8200, 4104, 136, "256x256", False),    # three K tiles, several tiles per work-group
+    (600, 18008, 136, "256x256", True),     # three rows of tiles
 ]
 
 
@@ -42,9 +45,10 @@ def _padded(t, extra):
 
 
 @pytest.mark.parametrize("out_in", [False, True])
-@pytest.mark.parametrize("m,n,k", SHAPES)
-def test_ragged_contraction(acc, m, n, k, out_in):
+@pytest.mark.parametrize("m,n,k,tile,one_round", SHAPES)
+def test_ragged_contraction(acc, m, n, k, tile, one_round, out_in):
     import torch
+    assert plan.gemm_tile(m, n, k) == (tile, one_round)
     g = torch.Generator(device="cuda").manual_seed(m + n + k)
     X = torch.randn(m, k, generator=g, device="cuda").bfloat16()
     W = (torch.randn(k, n, generator=g, device="cuda") * 0.02).bfloat16()
@@ -85,3 +89,43 @@ def test_dense_gradient_at_ragged_ranks(acc, r, out_in):
             acc.acc_linear_dw(desc, Xsp, Grp, dW)
             err = (dW.double() - passes * want).abs().max()
             assert err <= 1e-5 * want.square().mean().sqrt(), (passes, float(err))  # fp32 sums of r <= 200 exact products
+
+
+@pytest.mark.parametrize("out_in", [False, True])
+@pytest.mark.parametrize("d_in,d_out,r,tile", [
+    (3264, 3080, 40, "192x128"),     # 17 x 17 tiles of 192 x 192, 13 x 13 of 256 x 256: the ring kernel in every form
+    (3504, 3104, 200, "192x128"),
+    (520, 1032, 1096, "64x64"),      # rank above the short-contraction kernel's
+    (1400, 1032, 1032, "128x64"),
+    (1056, 3048, 1592, "128x128"),
+    (4096, 3072, 1032, "256x192"),
+])
+def test_dense_gradient_on_the_ring_kernel(acc, d_in, d_out, r, tile, out_in):
+    """dW written and accumulated, in float and in bfloat16; the factor's padding columns are NaN, dW's neighbours stay."""
+    import torch
+    M, N = (d_out, d_in) if out_in else (d_in, d_out)
+    assert -(-d_in // 192) * -(-d_out // 192) > 256 or r > 1024
+    assert -(-d_in // 256) * -(-d_out // 256) < 192 or tile == "256x192"
+    assert out_in or plan.gemm_tile(M, N, r, float_or_sum=True)[0] == tile
+    g = torch.Generator(device="cuda").manual_seed(r + d_in)
+    Xs = torch.randn(d_in, r, generator=g, device="cuda").bfloat16()
+    Gr = (torch.randn(r, d_out, generator=g, device="cuda") * 0.01).bfloat16()
+    Xsp = _padded(Xs, 8)
+    Grp = _padded(Gr.T.contiguous(), 8) if out_in else Gr
+    want = Xs.double() @ Gr.double()
+    want = want.T if out_in else want
+    scale = want.square().mean().sqrt()
+    print(f"ring dense gradient {d_in} x {d_out} r={r} out_in={out_in}", flush=True)
+    for code, dt in ((acc.ACC_F32, torch.float32), (acc.ACC_BF16, torch.bfloat16)):
+        buf = torch.full((M + 2, N), 7.0, dtype=dt, device="cuda")      # a row of guard on either side
+        dW = buf[1:M + 1]
+        exact = torch.zeros_like(want)
+        for flag in (0, acc.ACC_FLAG_DW_ACCUMULATE, acc.ACC_FLAG_DW_ACCUMULATE):
+            desc = acc.make_desc(1, d_in, d_out, r, ldf=r + 8, dw_dtype=code,
+                                 flags=flag | (acc.ACC_FLAG_W_OUT_IN if out_in else 0))
+            before = dW.double() if flag else torch.zeros_like(want)
+            acc.acc_linear_dw(desc, Xsp, Grp, dW)
+            exact = before + want
+            allowed = 1e-5 * scale + (2.0 ** -8 * exact.abs() if dt == torch.bfloat16 else 1e-6 * exact.abs())
+            assert torch.all((dW.double() - exact).abs() <= allowed), (dt, flag)
+        assert torch.all(buf[0] == 7.0) and torch.all(buf[M + 1] == 7.0)

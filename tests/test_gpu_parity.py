@@ -11,6 +11,7 @@ pytestmark = pytest.mark.gpu
 from paper_2605_01255_amd import inputs
 from oracle import acc_oracle as orc
 import gpu_util as gu
+import plan_util as plan
 
 
 @pytest.fixture(scope="module")
@@ -43,7 +44,7 @@ SHAPES_BF16 = [
     # n, d_in, d_out, r : several tiles plus ragged tails in every dimension
     (512, 512, 768, 64),
     (1000, 512, 640, 8),        # the paper's smallest rank, tuned kernels (surplus sketch columns masked)
-    (515, 264, 136, 8),         # the same on the generic kernels
+    (515, 264, 136, 8),         # the same with K % 64 != 0
     (2049, 1024, 1544, 24),
     (777, 520, 264, 48),
     (1000, 8, 8, 16),
@@ -165,6 +166,39 @@ def test_tuned_gemm_with_one_to_five_k_tiles(acc, d_in, d_out, r):
     _check(acc, inputs.Linear(f"ktiles_{d_in}x{d_out}_r{r}", 4100, d_in, d_out, r, dtype="bf16"))
 
 
+@pytest.mark.parametrize("w_oi", [False, True])
+def test_operands_beyond_4_gib_take_the_generic_kernels(acc, w_oi):
+    """Rows of X (forward) and of dY (backward) so far apart that the operand spans more than 4 GiB, which the tuned products
+    and sketch cannot address."""
+    import torch
+    dev, bf = "cuda:0", torch.bfloat16
+    n, d_in, d_out, r, ld = 264, 72, 40, 16, (1 << 23) + 8
+    assert n * ld * 2 > 1 << 32
+    lin = inputs.Linear("beyond_4_gib", n, d_in, d_out, r, dtype="bf16")
+    data = inputs.make(lin)
+    want = gu.run_oracle(lin, data)
+    flags = acc.ACC_FLAG_W_OUT_IN if w_oi else 0
+    W = acc.to_device(np.ascontiguousarray(data["W"].T) if w_oi else data["W"], dev)
+    wide = torch.empty(n, ld, dtype=bf, device=dev)
+
+    def spread(a):
+        wide[:, :a.shape[1]] = acc.to_device(a, dev)
+        wide[:, a.shape[1]:a.shape[1] + 64] = float("nan")
+        return wide
+
+    print(f"operands beyond 4 GiB w_oi={w_oi}", flush=True)
+    fwd = acc.make_desc(n, d_in, d_out, r, seed=lin.seed, ldx=ld, flags=flags)
+    Y, Xs = torch.full((n, d_out), 7.0, dtype=bf, device=dev), torch.full((d_in, r), 7.0, dtype=bf, device=dev)
+    acc.acc_linear_fwd(fwd, spread(data["X"]), W, Y, Xs, acc.alloc_workspace(fwd, False, dev))
+    bwd = acc.make_desc(n, d_in, d_out, r, seed=lin.seed, ldy=ld, flags=flags)
+    dX = torch.full((n, d_in), 7.0, dtype=bf, device=dev)
+    Gr = torch.full((d_out, r) if w_oi else (r, d_out), 7.0, dtype=bf, device=dev)
+    got = {"Y": acc.to_host_f64(Y), "Xs": acc.to_host_f64(Xs)}
+    acc.acc_linear_bwd(bwd, spread(data["dY"]), W, None, dX, Gr, None, acc.alloc_workspace(bwd, True, dev))
+    got.update(dX=acc.to_host_f64(dX), Gr=acc.to_host_f64(Gr).T if w_oi else acc.to_host_f64(Gr))
+    gu.check_outputs(got, {k: want[k] for k in got}, 1e-2, lin.name)
+
+
 def test_tuned_kernels_fp32_dw_and_strides(acc):
     lin = inputs.Linear("fast_strided", 1500, 512, 768, 128, dtype="bf16")
     _check(acc, lin, dw_dtype=0, pad=(64, 8, 72), row_offset=4 * 77, seed=0xABCDEF0123)
@@ -182,11 +216,12 @@ def test_big_tile_gemm_with_strides(acc):
     (16384, 256, 3072, 64, (64, 8, 24)),    # four K tiles (stage parity unchanged from tile to tile), strided
     (16384, 320, 3072, 64, (0, 0, 0)),      # five K tiles (stage parity alternates)
     (16384, 3072, 3136, 64, (0, 0, 0)),     # backward: 49 K tiles, three output tiles per work-group
-    (2304, 256, 8456, 64, (0, 0, 0)),       # 9 x 34 tiles in a map of 768 slots: empty slots between a work-group's tiles
+    (2304, 256, 13560, 64, (0, 0, 0)),      # 9 x 53 tiles in a map of 1024 slots: empty slots between a work-group's tiles
 ])
 def test_persistent_gemm_across_output_tiles(acc, n, d_in, d_out, r, pad):
     """More than 256 slots in the map of 256 x 256 output tiles: 256 persistent work-groups whose K pipeline
     runs across the tile boundary (next tile requested inside the last K tiles of the one before)."""
+    assert "256x256" in (plan.gemm_tile(n, d_out, d_in)[0], plan.gemm_tile(n, d_in, d_out)[0])
     _check(acc, inputs.Linear(f"persist_{n}x{d_in}x{d_out}", n, d_in, d_out, r, dtype="bf16"), pad=pad)
 
 
@@ -195,10 +230,10 @@ def _seeded_big_shapes(count, seed):
     out = []
     while len(out) < count:
         n = int(rng.integers(3000, 9000))
-        d_in = 8 * int(rng.integers(24, 160))        # 192 ... 1272; K % 64 != 0 takes the generic kernels
+        d_in = 8 * int(rng.integers(24, 160))        # 192 ... 1272; at K % 64 != 0 the last K tile is masked
         d_out = 8 * int(rng.integers(380, 640))      # 3040 ... 5112
         if rng.integers(0, 3):
-            d_in = 64 * max(3, d_in // 64)           # mostly multiples of 64: the tuned kernels
+            d_in = 64 * max(3, d_in // 64)           # mostly multiples of 64
         r = int(rng.choice([16, 32, 64, 128, 192, 256]))
         if -(-n // 256) * -(-d_out // 256) >= 192:
             out.append((n, d_in, d_out, r))
@@ -226,10 +261,10 @@ def test_one_launch_flag_gives_identical_results(acc):
 
 # ---- the paper's weight orientation ([d_out, d_in], Def. 3.1) and the bias gradient ------------------
 @pytest.mark.parametrize("n,d_in,d_out,r,dtype", [
-    (130, 72, 40, 16, "f32"),          # generic kernels, float32
-    (777, 520, 264, 48, "bf16"),       # generic kernels, bfloat16
-    (1000, 512, 640, 128, "bf16"),     # tuned kernels, 128 x 128 tiles
-    (4100, 1024, 3080, 256, "bf16"),   # tuned kernels, 256 x 256 tiles, ragged M and N
+    (130, 72, 40, 16, "f32"),          # float32 kernel
+    (777, 520, 264, 48, "bf16"),       # ring kernel, last K tile masked
+    (1000, 512, 640, 128, "bf16"),     # one round of small tiles
+    (4100, 1024, 3080, 256, "bf16"),   # large tiles, ragged M and N
     (2500, 576, 1096, 64, "bf16"),     # one column slice of the sketch tile, ragged channel slab
 ])
 def test_weight_out_in_orientation_and_bias_gradient(acc, n, d_in, d_out, r, dtype):
@@ -343,7 +378,7 @@ def test_calls_can_be_captured_in_a_hip_graph_and_replayed(acc):
     (1000, 512, 640, 128, "bf16", False),   # 512 x 64 sketch tile
     (1000, 512, 640, 128, "bf16", True),    # the 512 x 128 tile that the one-launch flag selects
     (777, 520, 264, 48, "bf16", False),     # surplus sketch columns masked
-    (700, 72, 40, 16, "f32", False),        # generic kernels
+    (700, 72, 40, 16, "f32", False),        # float32 kernel
 ])
 def test_row_offsets_crossing_2_pow_34(acc, n, d_in, d_out, r, dtype, one_launch):
     """A shard whose global token indices cross 2^34: the high bits move into the fourth counter word."""

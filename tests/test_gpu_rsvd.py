@@ -93,10 +93,10 @@ SHAPES = [
     (2049, 1032, 1544, 64, "bf16"),     # largest rank, ragged everything (generic kernels: d_in % 64 != 0)
     (3001, 1024, 1544, 48, "bf16"),     # rank padded to 64 inside the kernels, split-K path, ragged token count
     (16384, 3072, 3072, 32, "bf16"),    # the 3B-shaped projection at the paper's rank
-    # ranks above 64: the blocked Cholesky QR on 64 x 64 diagonal blocks
-    (700, 264, 136, 72, "f32"),         # one full block and a ragged one of 8, generic kernels, float32
-    (1030, 520, 264, 128, "bf16"),      # two blocks, generic kernels
-    (4100, 1024, 1544, 192, "bf16"),    # three blocks, split-K path, ragged tokens
+    # ranks above 64: the factorisation in one launch up to 256, above blocked on 256 x 256 diagonal blocks
+    (700, 264, 136, 72, "f32"),         # five blocks of 16 columns, the last one half full, float32
+    (1030, 520, 264, 128, "bf16"),      # generic kernels for the products (d_in % 64 != 0)
+    (4100, 1024, 1544, 192, "bf16"),    # split-K path, ragged tokens
     (4096, 1024, 1024, 256, "bf16"),    # the rank of the 3B-shaped configurations
     (16384, 3072, 3072, 256, "bf16"),   # the 3B-shaped projection at its own sketch rank
 ]
@@ -152,7 +152,7 @@ def test_rsvd_is_exact_for_low_rank_inputs_and_drops_dependent_columns(acc):
 
 
 def test_rsvd_blocked_rank_drops_dependent_columns(acc):
-    """rank(X) = 40 < k = 96 (two diagonal blocks): the surplus basis vectors come out as zero in both blocks and
+    """rank(X) = 40 < k = 96 (six blocks of 16 columns): the surplus basis vectors come out as zero in all of them and
     U.V^T still reproduces X."""
     rng = np.random.default_rng(11)
     n, d_in, d_out, k = 900, 256, 96, 96
@@ -196,9 +196,9 @@ def test_rsvd_strided_operands_and_accumulated_gradient(acc, n, d_in, d_out, k):
 
 
 @pytest.mark.parametrize("n,d_in,d_out,k,dtype,q", [
-    (1030, 520, 264, 128, "bf16", 1),    # blocked Cholesky QR (two blocks), generic kernels
-    (4100, 1024, 1544, 192, "bf16", 2),  # blocked (three blocks), split-K path with hi / lo parts
-    (515, 264, 136, 8, "f32", 1),        # generic kernels, float32
+    (1030, 520, 264, 128, "bf16", 1),    # rank above 64, generic kernels for the products of X
+    (4100, 1024, 1544, 192, "bf16", 2),  # rank above 128, split-K path with hi / lo parts
+    (515, 264, 136, 8, "f32", 1),        # float32 kernel
     (777, 520, 264, 32, "bf16", 2),      # generic kernels, bfloat16
     (1000, 512, 640, 8, "bf16", 1),      # split-K path
     (4100, 1024, 3080, 32, "bf16", 2),   # split-K path, ragged tokens
