@@ -5,7 +5,7 @@
  * Notation (row-major everywhere):
  *   X  [n, d_in]      input activation          W  [d_in, d_out]  weight
  *   Y  [n, d_out]     exact output  Y = X.W     dY [n, d_out]     incoming gradient
- *   S  [n, r]         random-projection compressor, i.i.d. N(0, 1/r); NEVER stored:
+ *   S  [n, r]         random-projection compressor, i.i.d. N(0, 1/r); never kept between calls:
  *                     S[i, j] is a pure function of (seed, row_offset + i, j)
  *   Xs [d_in, r]      Xs = X^T.S   the only activation kept for backward
  *   dX [n, d_in]      dX = dY.W^T  exact input gradient
@@ -263,8 +263,8 @@ int acc_linear_bwd_rsvd(const acc_linear_desc* desc, const void* dY, const void*
 int acc_philox_dump_u32(uint64_t seed, uint64_t row_offset, int64_t n, int64_t r, uint32_t* out,
                         void* stream);
 
-/* Test hook: S itself as float32 [n, r] (device).  io_dtype ACC_F32 gives the fp32 generator of the generic
- * kernels (libm-grade log / sincos); ACC_BF16 the hardware-transcendental Box-Muller of the bf16 kernels,
+/* Test hook: S itself as float32 [n, r] (device).  io_dtype ACC_F32 gives the generator of the fp32
+ * layers (libm-grade log / sincos); ACC_BF16 the hardware-transcendental Box-Muller of the bf16 kernels,
  * rounded to bfloat16 and widened.  The hook runs the straightforward form of that arithmetic (one call per
  * lane, acc_rng.h); the tuned sketch kernels carry their own interleaved copy with its own counter
  * arithmetic, which is pinned separately by running the layer calls on identity inputs (X = I gives Xs = S).

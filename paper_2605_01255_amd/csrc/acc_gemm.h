@@ -39,7 +39,7 @@ struct FastGemmParams {
   int red_G;
   int red_out_bf16;       // 1: red_out is bf16, 0: float
   int64_t red_row, red_ld;  // the result has rows of red_row elements (red_row % 4 == 0) stored red_ld apart
-  float alpha, beta;      // of the kernels with SUM: C = beta C + alpha (A . B), one rounding; 1, 1 is the plain sum
+  float alpha, beta;      // kernels with SUM: C = beta C + alpha (A . B), one rounding; alpha alone: the 8-bit product's scale
   // Split of the K range over work-groups (gemm_ring_kernel with SPLIT: skinny products whose M x N tiles alone do
   // not fill the chip).  Block b works on tile b % tile_blocks and K range [s * k_per_split, min(K, (s + 1) *
   // k_per_split)), s = b / tile_blocks, and stores its partial product at C + s * c_split_stride.  k_per_split % 64 == 0.
