@@ -609,13 +609,15 @@ void run_sketch(const acc_linear_desc* d, const void* A, int64_t lda, int64_t ch
 // ---- RSVD compressor ------------------------------------------------------------------------
 // Forward chain: Yr = X.Omega -> Cholesky QR twice -> U -> V = X^T.U; every product on the generic MFMA
 // kernel (fp32 matrix instructions wherever an fp32 operand is involved), K-splits reduced by K4.
+constexpr int64_t kQrOneLaunchRank = 128;  // up to here the factor stays in LDS (chol_factor_solve)
 constexpr int64_t kQrSmallRank = 64;     // up to here a pass needs little scratch: 256 Gram partials and the image
 constexpr size_t kQrImageRoom = (size_t)(64 * 64 + 2 * 64) * 4;   // of an image up to that rank
 // Scratch of one Cholesky-QR pass at rank k, byte offsets: Gram partials, their sum, and the triangular factor's images, one
-// per 256 columns.  Up to rank 64 the image has room of its own; up to 256 it takes the k x k floats that the blocked form
-// needs for the transposed factor; above, the images take the Gram partials' place (added up by then).
+// per 256 columns.  Up to rank 128 the factor stays on the chip and its room is not used (callers have sized for it); up to
+// 256 the image takes the k x k floats that the blocked form needs for the transposed factor; above, the images take the Gram
+// partials' place (added up by then).
 constexpr int kGramSplitsBlocked = 16;
-constexpr size_t kQrImageBytes = (size_t)tri_block(kQrMaxRank / 16, 0) * 1024;   // of a factorisation of 256 columns
+constexpr size_t kQrImageBytes = (size_t)chol_image_bytes(kQrMaxRank);   // of a factorisation of 256 columns
 struct QrScratch {
   size_t gram_part, gram, image;
   size_t rt, scale_ref;   // blocked form: the transposed factor [k, k], the matrix's largest diagonal entry
@@ -638,9 +640,9 @@ QrScratch take_qr_scratch(int64_t k, int g_gram, Take& take) {
 }
 constexpr bool qr_images_fit() {
   for (int k = 8; k <= kRsvdMaxRankBlocked; k += 8) {
-    const size_t image = (size_t)tri_block((k + 15) / 16, 0) * 1024, square = (size_t)k * k * 4;
-    if (k <= kQrSmallRank ? image > kQrImageRoom
-                          : k <= kQrMaxRank ? image > square : (k + kQrMaxRank - 1) / kQrMaxRank * kQrImageBytes > kGramSplitsBlocked * square)
+    const size_t image = (size_t)chol_image_bytes(k), square = (size_t)k * k * 4;
+    if (k > kQrOneLaunchRank &&
+        (k <= kQrMaxRank ? image > square : (k + kQrMaxRank - 1) / kQrMaxRank * kQrImageBytes > kGramSplitsBlocked * square))
       return false;
   }
   return true;
@@ -753,27 +755,42 @@ void gram_matrix(const RsvdPlan& pl, char* ws, int64_t m, int64_t k, const float
 
 // Image of the triangular factor of G [w, w] (row stride ldg), w <= 256.
 void chol_factor(const float* G, int64_t ldg, int64_t w, float* image, const float* scale_ref, float rel_tol, Launcher& L) {
-  // above 128 always the most it can need: a kernel's LDS limit is raised once, to what its first launch asks for
-  const unsigned threads = w <= 64 ? 256 : (w <= 128 ? 512 : kCholMaxThreads);
-  L.launch_lds(chol_factor_kernel, dim3(1), dim3(threads), (size_t)chol_lds_bytes(w > 128 ? kQrMaxRank : (int)w), G, image,
-               (int)w, ldg, scale_ref, rel_tol);
+  auto go = [&](auto kernel, int KB) {  // a kernel's LDS limit is raised once, to what its first launch asks for: always the most
+    L.launch_lds(kernel, dim3(1), dim3((unsigned)chol_threads(KB)), (size_t)chol_lds_bytes(16 * KB), G, image, (int)w, ldg, scale_ref, rel_tol);
+  };
+  if (w <= 128) go(chol_factor_kernel<8>, 8);
+  else go(chol_factor_kernel<16>, 16);
 }
 
-// Q = Y . R^-1 (see chol_solve_kernel), Y [m, w] with row stride ldy, w <= 256.
+// Q = Y . R^-1 (see chol_solve_kernel), Y [m, w] with row stride ldy, w <= 256: a block column of the blocked form.
 template <typename TU>
-void chol_solve(const float* Y, int64_t m, int64_t w, const float* image, float* Qf, void* Qt, bf16* Ut, int64_t ldt,
-                int64_t rows_out, bool hilo, int64_t ldy, int64_t ldq, int64_t lo_rows, Launcher& L) {
-  // four waves (64 rows) share an image; fewer where that leaves compute units idle (3072 rows of a projector), eight where
-  // the image is most of a compute unit's LDS
-  const int64_t waves = w > 128 ? 8 : (rows_out >= 64 * 256 ? 4 : (rows_out >= 32 * 256 ? 2 : 1));
-  const dim3 grid((unsigned)ceil_div(rows_out, 16 * waves)), block((unsigned)(64 * waves));
-  const size_t lds = (size_t)tri_block(w > 128 ? kQrMaxRank / 16 : (int)ceil_div(w, 16), 0) * 1024;  // see chol_factor
-  auto go = [&](auto kernel) {
-    L.launch_lds(kernel, grid, block, lds, Y, m, (int)w, image, Qf, (TU*)Qt, Ut, ldt, rows_out, hilo ? 1 : 0, ldy, ldq, (int)lo_rows);
-  };
-  if (w <= 64) go(chol_solve_kernel<4, TU>);
-  else if (w <= 128) go(chol_solve_kernel<8, TU>);
-  else go(chol_solve_kernel<16, TU>);
+void chol_solve(const TriSolve<TU>& t, const float* image, Launcher& L) {
+  // four waves (64 rows) share an image; fewer where that leaves compute units idle, eight where the image is most of a
+  // compute unit's LDS
+  const int64_t waves = t.k > 128 ? 8 : (t.n_rows_out >= 64 * 256 ? 4 : (t.n_rows_out >= 32 * 256 ? 2 : 1));
+  const dim3 grid((unsigned)ceil_div(t.n_rows_out, 16 * waves)), block((unsigned)(64 * waves));
+  const size_t lds = (size_t)round_up(chol_image_bytes(t.k > 128 ? kQrMaxRank : t.k), 1024);  // see chol_factor; whole transfers
+  if (t.k <= 64) L.launch_lds(chol_solve_kernel<4, TU>, grid, block, lds, t, image);
+  else if (t.k <= 128) L.launch_lds(chol_solve_kernel<8, TU>, grid, block, lds, t, image);
+  else L.launch_lds(chol_solve_kernel<16, TU>, grid, block, lds, t, image);
+}
+
+// Q = Y . R^-1 with R from Gram [k, k].  Up to 128 columns factor and solve are one launch (see cholesky_qr_kernel), of one
+// work-group per compute unit at most: they all run the same chain, and two on one compute unit would share its pipes.  Above,
+// the factor wants sixteen waves and the solve more registers than sixteen waves have: two launches, the factor by way of
+// memory.  Measured us at 4096 rows, k = 32 / 64 / 128 / 256: one launch 5.2 / 8.6 / 18.7 / -, two 6.8 / 10.6 / 21.0 / 69; the
+// elimination by all waves together, a barrier on either side of its one-wave panel, that this replaced 9.2 / 15.0 / 29.6 / 87.
+template <typename TU>
+void chol_factor_solve(const TriSolve<TU>& t, const float* gram, float* image, float rel_tol, Launcher& L) {
+  if (t.k > kQrOneLaunchRank) {
+    chol_factor(gram, t.k, t.k, image, nullptr, rel_tol, L);
+    chol_solve(t, image, L);
+    return;
+  }
+  const int64_t row_blocks = ceil_div(t.n_rows_out, 16);
+  const dim3 grid((unsigned)(row_blocks < 256 ? row_blocks : 256));
+  if (t.k <= 64) L.launch_lds(cholesky_qr_kernel<4, TU>, grid, dim3(512), (size_t)chol_lds_bytes(64), t, gram, rel_tol);
+  else L.launch_lds(cholesky_qr_kernel<8, TU>, grid, dim3(512), (size_t)chol_lds_bytes(128), t, gram, rel_tol);
 }
 
 // The same pass for ranks above 256 (up to 512): blocked right-looking Cholesky of the Gram matrix on 256 x 256 diagonal
@@ -798,8 +815,8 @@ void cholesky_qr_pass_blocked(const Shape& s, const RsvdPlan& pl, char* ws, int6
     chol_factor(gram + jb * k + jb, k, w, image(j), scale_ref, (float)k * 1.1920929e-7f, L);
     if (rest == 0) break;
     // Rt[rows below, block column j] = G[rows below, block column j] . R_jj^-1  (= the row panel of R, transposed)
-    chol_solve<float>(gram + (jb + w) * k + jb, rest, w, image(j), rt + (jb + w) * k + jb, nullptr, nullptr, 0, rest, false, k, k,
-                      0, L);
+    chol_solve(TriSolve<float>{gram + (jb + w) * k + jb, rt + (jb + w) * k + jb, nullptr, nullptr, rest, k, k, 0, rest, (int)w, 0, 0},
+               image(j), L);
     GemmParams u{};  // trailing block -= panel^T . panel, both triangles (the panels below read the lower one)
     u.A = rt + (jb + w) * k + jb; u.B = u.A; u.C = gram + (jb + w) * k + (jb + w);
     u.M = rest; u.N = rest; u.K = w;
@@ -822,10 +839,13 @@ void cholesky_qr_pass_blocked(const Shape& s, const RsvdPlan& pl, char* ws, int6
       launch_generic<float, float, float, float, false, true>(u, 1, L);
     }
     bf16* ut_j = Ut ? Ut + jb * ldt : nullptr;
-    if (qt_dt == ACC_BF16)
-      chol_solve<bf16>(Yin + jb, m, w, image(j), W + jb, Qt ? (bf16*)Qt + jb : nullptr, ut_j, ldt, rows_out, hilo, k, k, k, L);
-    else
-      chol_solve<float>(Yin + jb, m, w, image(j), W + jb, Qt ? (float*)Qt + jb : nullptr, ut_j, ldt, rows_out, hilo, k, k, k, L);
+    auto solve = [&](auto* q) {
+      using TU = std::remove_pointer_t<decltype(q)>;
+      chol_solve(TriSolve<TU>{Yin + jb, W + jb, q ? q + jb : nullptr, ut_j, m, k, k, ldt, rows_out, (int)w, hilo ? 1 : 0, (int)k},
+                 image(j), L);
+    };
+    if (qt_dt == ACC_BF16) solve((bf16*)Qt);
+    else solve((float*)Qt);
   }
 }
 
@@ -841,12 +861,14 @@ void cholesky_qr_pass(const Shape& s, const RsvdPlan& pl, char* ws, int64_t m, i
     cholesky_qr_pass_blocked(s, pl, ws, m, m_pad, Yin, Qf, Qt, qt_dt, Ut, ldt, hilo, final_pass, L);
     return;
   }
-  float* image = (float*)(ws + pl.qr.image);
   gram_matrix(pl, ws, m, k, Yin, final_pass, L);
-  chol_factor((const float*)(ws + pl.qr.gram), k, k, image, nullptr, k <= kQrSmallRank ? 1e-6f : (float)k * 1.1920929e-7f, L);
-  const int64_t rows_out = Ut ? m_pad : m;
-  if (qt_dt == ACC_BF16) chol_solve<bf16>(Yin, m, k, image, Qf, Qt, Ut, ldt, rows_out, hilo, k, k, k, L);
-  else chol_solve<float>(Yin, m, k, image, Qf, Qt, Ut, ldt, rows_out, hilo, k, k, k, L);
+  auto solve = [&](auto* q) {
+    using TU = std::remove_pointer_t<decltype(q)>;
+    chol_factor_solve(TriSolve<TU>{Yin, Qf, q, Ut, m, k, k, ldt, Ut ? m_pad : m, (int)k, hilo ? 1 : 0, (int)k},
+                      (const float*)(ws + pl.qr.gram), (float*)(ws + pl.qr.image), k <= kQrSmallRank ? 1e-6f : (float)k * 1.1920929e-7f, L);
+  };
+  if (qt_dt == ACC_BF16) solve((bf16*)Qt);
+  else solve((float*)Qt);
 }
 
 // out[channels, k] (or its transpose) = A^T . U over the token axis, A [n, lda]; splits reduced by K4.
