@@ -265,10 +265,19 @@ void launch_reduce(const float* part, int G, int64_t count, void* out, int64_t r
   L(reduce_partials_kernel<T>, dim3((unsigned)ceil_div(count, 1024)), dim3(256), part, G, count, count, (T*)out, row, ld);
 }
 
+// The exact product of a pass, C[n, N] = A . B with the sketch's input A as its left operand, handed to the sketch for a launch
+// they share (gemm_f32_pair_kernel); `done` says that it has been enqueued.
+struct F32Exact {
+  F32Operand b;
+  void* C;
+  int64_t N, K, ldc;
+  bool done;
+};
+
 // Sketch of a float32 layer with a stored S (plan_f32_sketch).  Returns false when the generic form is to run: by the plan,
 // or because the kernel does not take the operands.
 bool f32_sketch(const acc_linear_desc* d, const void* A, int64_t lda, int64_t channels, int64_t n, bool transposed,
-                void* out, int64_t out_ld, float* ws, Launcher& L) {
+                void* out, int64_t out_ld, float* ws, Launcher& L, F32Exact* exact = nullptr) {
   const int64_t r = d->r, count = channels * r, s_size = n * r;
   const bool direct = d->factor_dtype == ACC_F32;
   const F32SketchPlan plan = plan_f32_sketch(n, channels, r, direct);
@@ -281,7 +290,23 @@ bool f32_sketch(const acc_linear_desc* d, const void* A, int64_t lda, int64_t ch
   const int64_t ldc = dst == part ? N : out_ld;
   if (!f32_gemm_ok(transposed ? sm : x, transposed ? x : sm, M, N, n, dst, ldc)) return false;
   L(sketch_matrix_kernel, dim3((unsigned)ceil_div(ceil_div(n, 4) * r, 256)), dim3(256), make_sketch_params(d), n, r, ws);
-  f32_gemm<float>(transposed ? sm : x, transposed ? x : sm, dst, ldc, M, N, n, L, false, 1.f, 1.f, k_per_split, count);
+  const F32Operand a{A, lda, true, false};
+  if (exact && f32_gemm_ok(a, exact->b, n, exact->N, exact->K, exact->C, exact->ldc) &&
+      pick_f32_tile(M, N, G, true).tile == F32TileShape::k32 && pick_f32_tile(n, exact->N, 1, true).tile == F32TileShape::k32) {
+    F32GemmParams p = f32_params(transposed ? sm : x, transposed ? x : sm, dst, ldc, M, N, n);
+    p.k_per_split = k_per_split; p.c_split_stride = count;
+    F32GemmParams q = f32_params(a, exact->b, exact->C, exact->ldc, n, exact->N, exact->K);
+    p.tile_blocks = (int)gemm_ring_plan(p, 32, 32);
+    q.tile_blocks = (int)gemm_ring_plan(q, 32, 32);
+    const int sketch_blocks = p.tile_blocks * (int)G;
+    const dim3 grid((unsigned)(sketch_blocks + q.tile_blocks));
+    const size_t lds = (size_t)gemm_f32_lds_bytes<1, 1, 4, float, float>();
+    if (exact->b.kmajor) L.launch_lds(gemm_f32_pair_kernel<true>, grid, dim3(256), lds, p, q, sketch_blocks);
+    else L.launch_lds(gemm_f32_pair_kernel<false>, grid, dim3(256), lds, p, q, sketch_blocks);
+    exact->done = true;
+  } else {
+    f32_gemm<float>(transposed ? sm : x, transposed ? x : sm, dst, ldc, M, N, n, L, false, 1.f, 1.f, k_per_split, count);
+  }
   if (dst == part) {
     if (direct) launch_reduce<float>(part, (int)G, count, out, N, out_ld, L);
     else launch_reduce<bf16>(part, (int)G, count, out, N, out_ld, L);
@@ -597,10 +622,11 @@ void fused_pass(const acc_linear_desc* d, const SketchPlan& sp, const void* A, c
 // filled in when the tuned sketch ran (its partials are pending), left empty otherwise.
 // The factor comes out [channels, r] with rows `ldf` apart, or transposed [r, channels] (dense).
 void run_sketch(const acc_linear_desc* d, const void* A, int64_t lda, int64_t channels, int64_t n,
-                bool transposed, void* out, int64_t ldf, float* ws, Launcher& L, ReduceJob* defer = nullptr) {
+                bool transposed, void* out, int64_t ldf, float* ws, Launcher& L, ReduceJob* defer = nullptr,
+                F32Exact* exact = nullptr) {
   const SketchPlan sp = plan_sketch(d, n, channels, lda);
   const int64_t row = transposed ? channels : d->r, ld = transposed ? channels : ldf;
-  if (d->io_dtype == ACC_F32 && f32_sketch(d, A, lda, channels, n, transposed, out, ld, ws, L)) return;
+  if (d->io_dtype == ACC_F32 && f32_sketch(d, A, lda, channels, n, transposed, out, ld, ws, L, exact)) return;
   if (sp.fast) fast_sketch(d, sp, A, lda, channels, n, transposed, out, row, ld, ws, L, defer);
   else if (transposed) generic_sketch(d, A, lda, channels, n, 1, channels, out, row, ld, ws, L);
   else generic_sketch(d, A, lda, channels, n, d->r, 1, out, row, ld, ws, L);
@@ -1108,10 +1134,12 @@ int enqueue_forward(const acc_linear_desc* desc, const Shape& s, const void* X, 
   // Sketch first: it pulls X through the memory-side cache, so the GEMM that follows starts from
   // there rather than from HBM (measured 4 % on the whole pass against the opposite order).
   ReduceJob job{};  // with a tuned GEMM next, the sketch leaves its K4 reduction to that launch
+  const bool w_oi = (desc->flags & ACC_FLAG_W_OUT_IN) != 0;
+  F32Exact exact{{W, s.ldw, w_oi, false}, Y, s.d_out, s.d_in, s.ldy, false};
   if (sketch)
     run_sketch(desc, X, s.ldx, s.d_in, s.n, false, Xs, s.ldf, workspace, L,
-               forward_gemm_is_tuned(desc, s) ? &job : nullptr);
-  exact_forward_gemm(desc, s, X, W, Y, L, &job);
+               forward_gemm_is_tuned(desc, s) ? &job : nullptr, &exact);
+  if (!exact.done) exact_forward_gemm(desc, s, X, W, Y, L, &job);
   return L.status();
 }
 
@@ -1183,9 +1211,10 @@ int acc_linear_bwd(const acc_linear_desc* desc, const void* dY, const void* W, c
                            (float*)workspace, L);
   } else {
     ReduceJob job{};
+    F32Exact exact{{W, s.ldw, !w_oi, false}, dX, s.d_in, s.d_out, s.ldx, false};
     run_sketch(desc, dY, s.ldy, s.d_out, s.n, !w_oi, Gr, s.ldf, (float*)workspace, L,
-               backward_gemm_is_tuned(desc, s) ? &job : nullptr);
-    exact_backward_gemm(desc, s, dY, W, dX, L, &job);
+               backward_gemm_is_tuned(desc, s) ? &job : nullptr, &exact);
+    if (!exact.done) exact_backward_gemm(desc, s, dY, W, dX, L, &job);
   }
   if (dW) dense_dw(desc, s, Xs, Gr, dW, L);
   return L.status();

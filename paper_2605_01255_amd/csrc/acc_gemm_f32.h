@@ -112,9 +112,9 @@ template <typename TC> struct StoreProduct {
   }
 };
 
+// Work-group `block` of the product.
 template <int TM, int TN, int NS, bool A_KMAJOR, bool B_KMAJOR, typename TA, typename TB, typename Output>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(F32GemmParams p, Output output) {
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
+__device__ __forceinline__ void gemm_f32_block(const F32GemmParams& p, const Output& output, int block, char* smem) {
   constexpr int NW = 4, WN = 2;
   constexpr int BM = 2 * TM * 16, BN = 2 * TN * 16, BK = 32;
   using TileA = F32Tile<TA, BM, A_KMAJOR>;
@@ -123,9 +123,9 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32GemmParams p, Output o
   constexpr int A_LOADS = TileA::LOADS, B_LOADS = TileB::LOADS, NG = A_LOADS + B_LOADS;
   static_assert((NS - 1) * NG <= 63, "vmcnt range");
 
-  const int split = (int)blockIdx.x / p.tile_blocks;
+  const int split = block / p.tile_blocks;
   int tm, tn;
-  if (!ring_tile(p, (int)blockIdx.x - split * p.tile_blocks, tm, tn)) return;
+  if (!ring_tile(p, block - split * p.tile_blocks, tm, tn)) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
@@ -269,6 +269,24 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32GemmParams p, Output o
       const int64_t gm = m0 + (wm * TM + i) * 16 + l16, gn = n0 + (wn * TN + j) * 16 + 4 * g4;
       if (gm < p.M && gn < p.N) output.store(p, split, gm, gn, total[i][j] + acc[i][j], old[i][j]);
     }
+}
+
+template <int TM, int TN, int NS, bool A_KMAJOR, bool B_KMAJOR, typename TA, typename TB, typename Output>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(F32GemmParams p, Output output) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  gemm_f32_block<TM, TN, NS, A_KMAJOR, B_KMAJOR, TA, TB>(p, output, (int)blockIdx.x, smem);
+}
+
+// Two products that do not depend on each other in one launch, both on 32 x 32 tiles: the sketch's (both operands with their
+// rows contiguous; the first `sketch_blocks` work-groups, a multiple of eight) and the exact one.  A small layer's launch is its
+// latency: at 256 x 256 x 512, rank 16, the sketch's 5.1 us (backward 5.4) and the product's 5.5 (7.4) follow each other no
+// more; a forward and backward pass with the dense dW takes 20.4 us, 29.6 with seven launches instead of five.
+template <bool B_KMAJOR>
+__global__ __launch_bounds__(256) void gemm_f32_pair_kernel(F32GemmParams sketch, F32GemmParams exact, int sketch_blocks) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int block = (int)blockIdx.x;
+  if (block < sketch_blocks) gemm_f32_block<1, 1, 4, false, false, float, float>(sketch, StoreProduct<float>{}, block, smem);
+  else gemm_f32_block<1, 1, 4, true, B_KMAJOR, float, float>(exact, StoreProduct<float>{}, block - sketch_blocks, smem);
 }
 
 template <int TM, int TN, int NS, typename TA, typename TB>
