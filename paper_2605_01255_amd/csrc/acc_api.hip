@@ -394,13 +394,16 @@ void ring_gemm(FastGemmParams& p, Launcher& L) {
   L.launch_lds(gemm_ring_kernel<TM, TN, NS, KMAJ, TC, false, SUM>, dim3(grid), dim3(256), (size_t)gemm_ring_lds_bytes<TM, TN, NS>(), p);
 }
 
-// SUM: C = beta C + alpha (A . B), rounded once, on the ring kernel whatever the size: its work-groups, two to a compute unit,
-// cover each other's reads of C (4096 x 4096 at r = 256, bf16 23 us and float 35, 26 and 43 on the 256 x 256 kernel; 8192 x
-// 3072 27 to 37 and 39 to 54, against 47 and 72 to 77).
-template <bool KMAJ, typename TC, bool SUM = false>
-void fast_gemm(const void* A, const void* B, void* C, int64_t M, int64_t N, int64_t K, int64_t lda,
-               int64_t ldb, int64_t ldc, Launcher& L, const ReduceJob* job = nullptr, float alpha = 1.f,
-               float beta = 1.f) {
+// C = beta C + alpha (A . B), C bf16, for a short K on the three-stage kernel of acc_gemm_smallk.h.
+template <bool KMAJ>
+void smallk_gemm(FastGemmParams& p, Launcher& L) {
+  p.tiles_m = (int)ceil_div(p.M, 192);
+  p.tiles_n = (int)ceil_div(p.N, 192);
+  L.launch_lds(gemm16_smallk_kernel<KMAJ>, dim3((unsigned)(p.tiles_m * p.tiles_n)), dim3(256), (size_t)144 * 1024, p);
+}
+
+FastGemmParams fast_params(const void* A, const void* B, void* C, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb,
+                           int64_t ldc, const ReduceJob* job, float alpha, float beta) {
   FastGemmParams p{};
   p.alpha = alpha; p.beta = beta;
   p.A = (const bf16*)A; p.B = (const bf16*)B; p.C = C;
@@ -410,50 +413,61 @@ void fast_gemm(const void* A, const void* B, void* C, int64_t M, int64_t N, int6
     p.red_out_bf16 = job->out_bf16;
     p.red_row = job->row; p.red_ld = job->ld;
   }
-  const bool persist_ok = sizeof(TC) == 2 && !SUM && K > 128;  // three K tiles
-  if (!SUM && !persist_ok && ceil_div(M, 256) * ceil_div(N, 256) >= 192) {  // a short K or float output: no pipeline across tiles
-    const unsigned grid = gemm_bf16_plan(p, 256, 256);  // a multiple of 256 slots
-    p.red_stride = (int64_t)grid * 256 * 4;
-    L.launch_lds(gemm_bf16_kernel<2, 2, 4, 4, KMAJ, TC>, dim3(grid), dim3(256),
-                 (size_t)gemm_bf16_lds_bytes<2, 2, 4, 4>(), p);
-    return;
+  return p;
+}
+
+template <bool KMAJ>
+void persist_gemm(FastGemmParams& p, Launcher& L) {
+  const unsigned slots = gemm_bf16_plan(p, 256, 256);
+  p.red_stride = (int64_t)256 * 256 * 4;
+  if (p.K % 64) L.launch_lds(gemm16_persist_kernel<KMAJ, true>, dim3(256), dim3(256), (size_t)160 * 1024, p, (int)slots);
+  else L.launch_lds(gemm16_persist_kernel<KMAJ>, dim3(256), dim3(256), (size_t)160 * 1024, p, (int)slots);
+}
+
+// The product of up to kFactorMaxK elements, on the kernel of pick_factor_tile.
+template <bool KMAJ, typename TC, bool SUM>
+void short_gemm(FastGemmParams& p, Launcher& L) {
+  constexpr bool BF16_C = sizeof(TC) == 2;
+  switch (pick_factor_tile(p.M, p.N, p.K, BF16_C, SUM)) {
+    case FactorTile::k64: ring_gemm<2, 2, SUM ? 2 : 3, KMAJ, TC, SUM>(p, L); break;
+    case FactorTile::k128x64: ring_gemm<4, 2, 2, KMAJ, TC, SUM>(p, L); break;
+    case FactorTile::k128: ring_gemm<4, 4, 2, KMAJ, TC, SUM>(p, L); break;
+    case FactorTile::k192x128: ring_gemm<6, 4, 2, KMAJ, TC, SUM>(p, L); break;
+    case FactorTile::kThreeStage:
+      if constexpr (BF16_C && SUM) smallk_gemm<KMAJ>(p, L);
+      break;
+    case FactorTile::kPersist:
+      if constexpr (BF16_C && !SUM) persist_gemm<KMAJ>(p, L);
+      break;
   }
+}
+
+// SUM: C = beta C + alpha (A . B), rounded once, on the ring kernel whatever the size: its work-groups, two to a compute unit,
+// cover each other's reads of C.
+template <bool KMAJ, typename TC, bool SUM = false>
+void fast_gemm(const void* A, const void* B, void* C, int64_t M, int64_t N, int64_t K, int64_t lda,
+               int64_t ldb, int64_t ldc, Launcher& L, const ReduceJob* job = nullptr, float alpha = 1.f,
+               float beta = 1.f) {
+  FastGemmParams p = fast_params(A, B, C, M, N, K, lda, ldb, ldc, job, alpha, beta);
+  const bool persist_ok = sizeof(TC) == 2 && !SUM && K > 128;  // three K tiles
+  if (!SUM && K <= 128 && ceil_div(M, 256) * ceil_div(N, 256) >= 192) return short_gemm<KMAJ, TC, SUM>(p, L);
   const GemmChoice c = pick_gemm_tile(M, N, K, persist_ok);
   switch (c.tile) {
     case GemmTile::k256:
-      if constexpr (sizeof(TC) == 2 && !SUM) {
-        const unsigned slots = gemm_bf16_plan(p, 256, 256);
-        p.red_stride = (int64_t)256 * 256 * 4;
-        if (K % 64) L.launch_lds(gemm16_persist_kernel<KMAJ, true>, dim3(256), dim3(256), (size_t)160 * 1024, p, (int)slots);
-        else L.launch_lds(gemm16_persist_kernel<KMAJ>, dim3(256), dim3(256), (size_t)160 * 1024, p, (int)slots);
-      }
+      if constexpr (sizeof(TC) == 2 && !SUM) persist_gemm<KMAJ>(p, L);
       break;
     case GemmTile::k256x192: ring_gemm<8, 6, 2, KMAJ, TC, SUM>(p, L); break;
     case GemmTile::k192x128:
-      if (c.one_round) ring_gemm<6, 4, 4, KMAJ, TC, SUM>(p, L);
+      if (c.one_round) ring_gemm<6, 4, 3, KMAJ, TC, SUM>(p, L);
       else ring_gemm<6, 4, 2, KMAJ, TC, SUM>(p, L);
       break;
     case GemmTile::k128:
-      if (c.one_round) ring_gemm<4, 4, 4, KMAJ, TC, SUM>(p, L);
+      if (c.one_round) ring_gemm<4, 4, 3, KMAJ, TC, SUM>(p, L);
       else ring_gemm<4, 4, 2, KMAJ, TC, SUM>(p, L);
       break;
     case GemmTile::k128x64: ring_gemm<4, 2, 3, KMAJ, TC, SUM>(p, L); break;
     case GemmTile::k64: ring_gemm<2, 2, 3, KMAJ, TC, SUM>(p, L); break;
   }
-}
-
-// C (op)= A[M, K] . B for a short K on the three-stage kernel of acc_gemm_smallk.h (the product of two gradient
-// factors: the dense dW, the optimizer's update of W).
-template <bool KMAJ, typename TC, bool SUM>
-void smallk_gemm(const void* A, const void* B, void* C, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb,
-                 int64_t ldc, Launcher& L, float alpha, float beta) {
-  FastGemmParams p{};
-  p.alpha = alpha; p.beta = beta;
-  p.A = (const bf16*)A; p.B = (const bf16*)B; p.C = C;
-  p.M = M; p.N = N; p.K = K; p.lda = lda; p.ldb = ldb; p.ldc = ldc;
-  p.tiles_m = (int)ceil_div(M, 192);
-  p.tiles_n = (int)ceil_div(N, 192);
-  L.launch_lds(gemm16_smallk_kernel<KMAJ, TC, SUM>, dim3((unsigned)(p.tiles_m * p.tiles_n)), dim3(256), (size_t)144 * 1024, p);
 }
 
 // ---- exact products on 8-bit floating-point operands (acc_gemm8.h) ---------------------------------
@@ -466,15 +480,7 @@ bool gemm8_ok(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool km
 template <bool KMAJ>
 void gemm8(const void* A, int a_format, const void* B, void* C, int64_t M, int64_t N, int64_t K, int64_t lda,
            int64_t ldb, int64_t ldc, float alpha, Launcher& L, const ReduceJob* job) {
-  FastGemmParams p{};
-  p.alpha = alpha; p.beta = 0.f;
-  p.A = (const bf16*)A; p.B = (const bf16*)B; p.C = C;
-  p.M = M; p.N = N; p.K = K; p.lda = lda; p.ldb = ldb; p.ldc = ldc;
-  if (job && job->count) {
-    p.red_part = job->part; p.red_out = job->out; p.red_count = job->count; p.red_G = job->G;
-    p.red_out_bf16 = job->out_bf16;
-    p.red_row = job->row; p.red_ld = job->ld;
-  }
+  FastGemmParams p = fast_params(A, B, C, M, N, K, lda, ldb, ldc, job, alpha, 0.f);
   const unsigned slots = gemm_bf16_plan(p, 256, 256);
   p.red_stride = (int64_t)256 * 256 * 4;
   if (a_format == ACC_FP8_E5M2) L.launch_lds(gemm8_persist_kernel<KMAJ, 1>, dim3(256), dim3(256), (size_t)160 * 1024, p, (int)slots);
@@ -979,17 +985,18 @@ void exact_backward_gemm(const acc_linear_desc* desc, const Shape& s, const void
 void factor_product(const acc_linear_desc* desc, const Shape& s, const void* Xs, const void* Gr,
                     const FactorProductOut& o, Launcher& L) {
   const bool w_oi = (desc->flags & ACC_FLAG_W_OUT_IN) != 0;
-  // A few K tiles and at most one round of 192 x 192 tiles: the three-stage kernel (one exposed latency per
-  // work-group).  More tiles than compute units: the kernels of the exact products, whose work-groups cover
-  // each other's waits (measured at 3072 x 8192, r = 256: 23.5 against 27.6 us).  One round, 3072 x 3072: 12.4 against
-  // 14.2 us at r = 256, 8.4 against 9.8 at r = 64; read-modify-write of a bf16 W at r = 64: 11.4 against 14.5 us
-  // (a plain in-place pass over the same 18.9 MB takes 7.4 us, a fill 4.7).
-  const bool short_k = s.r <= 1024 && ceil_div(s.d_in, 192) * ceil_div(s.d_out, 192) <= 256;
+  // Up to 256: pick_factor_tile.  Above, the estimates of the exact products; but a bf16 C that is added to keeps the three-stage
+  // kernel where that makes one full round (3072 x 3072 at r = 512 19.0 us, 128 x 64 tiles 20.0; at 1024 27.0 and 29.8).
   auto tuned = [&](auto kmaj, auto type, auto sum, const void* A, const void* B, int64_t M, int64_t N, int64_t ldb) {
     constexpr bool KMAJ = decltype(kmaj)::value, SUM = decltype(sum)::value;
     using TC = decltype(type);
-    if (short_k) smallk_gemm<KMAJ, TC, SUM>(A, B, o.C, M, N, s.r, s.ldf, ldb, o.ld, L, o.alpha, o.beta);
-    else fast_gemm<KMAJ, TC, SUM>(A, B, o.C, M, N, s.r, s.ldf, ldb, o.ld, L, nullptr, o.alpha, o.beta);
+    FastGemmParams p = fast_params(A, B, o.C, M, N, s.r, s.ldf, ldb, o.ld, nullptr, o.alpha, o.beta);
+    if (s.r <= kFactorMaxK) return short_gemm<KMAJ, TC, SUM>(p, L);
+    if constexpr (SUM && sizeof(TC) == 2) {
+      if (s.r <= 1024 && ceil_div(M, 192) * ceil_div(N, 192) <= 256 && ceil_div(M, 128) * ceil_div(N, 64) > 768)
+        return smallk_gemm<KMAJ>(p, L);
+    }
+    fast_gemm<KMAJ, TC, SUM>(A, B, o.C, M, N, s.r, s.ldf, ldb, o.ld, L, nullptr, o.alpha, o.beta);
   };
   auto typed = [&](auto kmaj, auto... args) {
     const std::true_type sum{};

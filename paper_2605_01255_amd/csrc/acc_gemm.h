@@ -407,17 +407,6 @@ __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, c
   }
 }
 
-template <int WM, int WN, int TM, int TN, bool B_KMAJOR, typename TC>
-__global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(FastGemmParams p) {
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
-  gemm_bf16_tile<WM, WN, TM, TN, B_KMAJOR, TC>(p, blockIdx.x, smem);
-}
-
-template <int WM, int WN, int TM, int TN>
-constexpr int gemm_bf16_lds_bytes() {
-  return 2 * (WM * TM * 32 + WN * TN * 32) * 64 * 2;
-}
-
 // Fill the tiling fields of p for a BM x BN work-group tile; returns the 1-D grid size.
 static inline unsigned gemm_bf16_plan(FastGemmParams& p, int BM, int BN) {
   p.tiles_m = (int)ceil_div(p.M, BM);

@@ -1,22 +1,19 @@
-// Product of the two gradient factors, C[M, N] = A[M, K] . B with a SHORT contraction (K = the sketch rank, or the
-// optimizer's projector rank: 64 ... 512), fp32 accumulate (steps B3 and the weight update of the optimizer step):
+// Product of the two gradient factors added to C (bf16) with a SHORT contraction (K = the sketch rank, or the optimizer's projector
+// rank), fp32 accumulate (steps B3 and the weight update of the optimizer step):
 //
-//   C = A . B                      dW = Xs . Gr   (Sec. 4, update strategy (i))
-//   C = beta C + alpha (A . B)     dW += ..., W <- (1 - lr wd) W - lr scale (P . N)   (update strategy (ii))
+//   C = beta C + alpha (A . B)     dW += ..., W <- (1 - lr wd) W - lr scale (P . N)   (Sec. 4, both update strategies)
 //
 //   A is row-major with K contiguous (Xs, P; Gr in the paper's orientation).
 //   B_KMAJOR = false: B[K, N], N contiguous (Gr);  B_KMAJOR = true: Bt[N, K], K contiguous (Xs in the paper's
-//   orientation).  C row-major, bf16 or fp32.
+//   orientation).
 //
-// With four to eight K tiles a work-group's time is the latency of its transfers, not its arithmetic: a kernel
-// that asks for K tile k + 1 while it multiplies K tile k (gemm_bf16_tile) waits for memory once per K tile.  Here
-// a work-group asks for its first three K tiles at once (three LDS stages of 48 KB: 192 x 64 of A and 64 x 192 of
-// B each) and for tile k + 3 as soon as tile k is consumed, so one latency is exposed at the start and little
-// after it.  The tile is 192 x 192: 16 x 16 = 256 work-groups for a 3072 x 3072 gradient, one round of the chip.
+// Bound by the read and write of C.  A work-group asks for its first three K tiles at once (three LDS stages of 48 KB: 192 x
+// 64 of A and 64 x 192 of B each), for its piece of C right behind them, and for tile k + 3 as soon as tile k is consumed, so one
+// latency is exposed at the start and little after it.  The tile is 192 x 192: 16 x 16 = 256 work-groups for a 3072 x 3072
+// gradient, one round of the chip.  Where the ring kernel's smaller tiles are ahead: pick_factor_tile.
 // Four waves of 96 x 96 = 6 x 6 blocks of the 16x16x32 matrix instruction (144 accumulators per lane); operands
 // of a k-step are read while the previous k-step multiplies.  N % 8 == 0, operands below 4 GiB.  K % 8 == 0: the 16-byte
-// chunks of the last K tile past K are sent out of the buffer's range and read as zero (ranks 8 ... 48 included, which went
-// to the generic kernel before: 3072 x 3072 at r = 32 21.5 us there).
+// chunks of the last K tile past K are sent out of the buffer's range and read as zero.
 #pragma once
 #include "acc_gemm16.h"
 
@@ -27,7 +24,7 @@ namespace acc {
 // k rows x two 16-lane groups of a transposing read to eight different 32-byte bank groups.
 __device__ __forceinline__ int swz_n192(int krow) { return (((krow >> 1) & 1) << 1) | (((krow >> 3) & 1) << 2); }
 
-template <bool B_KMAJOR, typename TC, bool SUM>
+template <bool B_KMAJOR>
 __global__ __launch_bounds__(256) void gemm16_smallk_kernel(FastGemmParams p) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   constexpr int NW = 4, WN = 2, TB = 6;
@@ -125,14 +122,13 @@ __global__ __launch_bounds__(256) void gemm16_smallk_kernel(FastGemmParams p) {
   for (int s = 0; s < NS; ++s)
     if (s < KT) issue_tile(s, s);
 
-  // Read-modify-write of a bf16 C (the optimizer's update of W): the old values are requested now, in the layout the
+  // The old values of C are requested now, in the layout the
   // epilogue moves them in (block row i, 16-byte chunk t * 64 + lane of its 16 x 96 piece), so that they arrive
   // under the K loop instead of after it.  They are PREFETCH = 18 loads of this wave, issued after the first
   // three K tiles and before the fourth, which the waits below count.
-  constexpr bool RMW_PREFETCH = SUM && sizeof(TC) == 2;
-  constexpr int PREFETCH = RMW_PREFETCH ? TB * 3 : 0;
-  u32x4 old_c[RMW_PREFETCH ? TB : 1][3];
-  if constexpr (RMW_PREFETCH) {
+  constexpr int PREFETCH = TB * 3;
+  u32x4 old_c[TB][3];
+  {
     __builtin_amdgcn_sched_barrier(0);
     // buffer resource over this wave's 96 x 96 piece of C: offsets stay below 4 GiB whatever the size of C
     const int64_t gm_base = m0 + wm * TB * 16, gn_base = n0 + wn * TB * 16;
@@ -159,7 +155,7 @@ __global__ __launch_bounds__(256) void gemm16_smallk_kernel(FastGemmParams p) {
     // K tile kt has landed when at most the wave-loads of the tiles requested after it (and, for the first three
     // K tiles, the prefetch of C, which was issued after them) are outstanding
     const int later = (kt + NS - 1 < KT ? kt + NS - 1 : KT - 1) - kt;
-    if (RMW_PREFETCH && kt < NS) {
+    if (kt < NS) {
       if (later >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NG + PREFETCH) : "memory");
       else if (later == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NG + PREFETCH) : "memory");
       else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PREFETCH) : "memory");
@@ -196,45 +192,22 @@ __global__ __launch_bounds__(256) void gemm16_smallk_kernel(FastGemmParams p) {
   }
 
   // ---- epilogue: lane holds output row l16 of each 16 x 16 block and columns 4 g4 .. + 3; a wave stages one block
-  //      row (16 x 96) in a private padded LDS region (the stages are free: the loop ended on a barrier with nothing
-  //      in flight) and moves 16 bytes per lane; a product that is added to C is staged as float, so that only the sum
-  //      is rounded (added to a 3072 x 3072 bf16 C at r = 64: 9.2 us; 9.9 with the product staged as bf16 and one
-  //      kernel for both forms) ----
-  constexpr int ES = sizeof(TC), CH16 = TB * 16 * ES / 16;
-  TC* __restrict__ C = (TC*)p.C;
-  constexpr int SE = SUM ? 4 : ES, PITCH = TB * 16 * SE + 16;   // SE: bytes of a staged element
+  //      row (16 x 96) as float in a private padded LDS region (the stages are free: the loop ended on a barrier with nothing
+  //      in flight) and moves 16 bytes per lane, so that only the sum is rounded ----
+  constexpr int CH16 = TB * 16 * 2 / 16, PITCH = TB * 16 * 4 + 16;
+  bf16* __restrict__ C = (bf16*)p.C;
   char* stage_w = smem + wave * (16 * PITCH);
 #pragma unroll
   for (int i = 0; i < TB; ++i) {
 #pragma unroll
-    for (int j = 0; j < TB; ++j) {
-      char* dst = stage_w + l16 * PITCH + (j * 16 + g4 * 4) * SE;
-      if constexpr (SE == 2) {
-        bf16x4 v;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) v[t] = (bf16)acc[i][j][t];
-        *(bf16x4*)dst = v;
-      } else {
-        *(f32x4*)dst = acc[i][j];
-      }
-    }
+    for (int j = 0; j < TB; ++j) *(f32x4*)(stage_w + l16 * PITCH + (j * 16 + g4 * 4) * 4) = acc[i][j];
 #pragma unroll
     for (int t = 0; t < 16 * CH16 / 64; ++t) {
       const int idx = t * 64 + lane, row = idx / CH16, ch = idx % CH16;
-      const char* staged = stage_w + row * PITCH + ch * (16 / ES) * SE;
       const int64_t gm = m0 + (wm * TB + i) * 16 + row;
-      const int64_t gn = n0 + wn * TB * 16 + ch * (16 / ES);
-      if (gm < p.M && gn < p.N) {
-        u32x4* dst = (u32x4*)(C + gm * p.ldc + gn);
-        if constexpr (SUM) {
-          u32x4 old;
-          if constexpr (RMW_PREFETCH) old = old_c[i][t];
-          else old = *dst;
-          *dst = scaled_sum<TC>((const float*)staged, old, p.alpha, p.beta);
-        } else {
-          *dst = *(const u32x4*)staged;
-        }
-      }
+      const int64_t gn = n0 + wn * TB * 16 + ch * 8;
+      if (gm < p.M && gn < p.N)
+        *(u32x4*)(C + gm * p.ldc + gn) = scaled_sum<bf16>((const float*)(stage_w + row * PITCH + ch * 32), old_c[i][t], p.alpha, p.beta);
     }
   }
 }

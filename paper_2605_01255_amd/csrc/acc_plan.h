@@ -24,6 +24,8 @@ static inline int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b
 //   6000 x 4096 x 4096  188 / 168 / 180 /  - /  - [188]    4096 x 2048 x 2048   53 /  38 /  34 /  41 /   - [35]
 //   4096 x 1024 x 3072   71 /  30 /  29 / 30 / 39 [36-41]  1053 x 3048 x 1600   35 /  18 /  15 /  17 /  22
 //   384 x 3072 x 3072    57 /  28 /  23 / 17 / 16 [34]     2048 x 1024 x 1024   27 /  14 /  12 / 9.0 / 9.4
+// In one round three stages in flight are as good as four or better, the LDS they leave free included (2049 x 1544 x 1032 on
+// 128 x 128: 13.7 us against 14.2; 2049 x 1032 x 1544 17.3 and 17.8; 192 x 128 2 to 3 % likewise).
 enum class GemmTile { k256, k256x192, k192x128, k128, k128x64, k64 };
 struct GemmChoice {
   GemmTile tile;
@@ -50,6 +52,48 @@ static inline GemmChoice pick_gemm_tile(int64_t M, int64_t N, int64_t K, bool pe
   }
   return best;
 }
+
+// Which kernel a product of up to 256 elements takes (the product of two gradient factors, whose contraction is their rank).
+// With four K tiles at most there is no pipeline to fill: a tile costs its latency, its write and, where it is added to C, its
+// read, and work-groups that share a compute unit cover each other's.  So the ring kernel with two stages and as many
+// work-groups as LDS holds (128 x 64 three, 64 x 64 five), larger tiles where the output gives every compute unit several; one
+// work-group per compute unit with everything requested at once, the three-stage kernel of 192 x 192 tiles, lost by 41 % on
+// average over 84 outputs of at most one round of it (512 x 512 at rank 256 8.6 us against 3.8, 1032 x 1544 at rank 128 7.1
+// against 4.4, 3072 x 1024 at rank 256 9.1 against 5.7, 3072 x 3072 at 256 11.3 against 10.9).
+//   written        the least of base + (tiles of the fullest compute unit) x (tile + K tiles x time of one), in nanoseconds,
+//                  and from three K tiles on the persistent kernel's: 1.6 % behind the best of nine candidates on average over
+//                  138 outputs (13 % at most), 3 % where C is float
+//   added to C     by size: the read of C counts more than the products.  The three-stage kernel requests C with its operands
+//                  and stays where its one round is nearly full (3072 x 3072 at rank 64: 10.6 us, 128 x 64 10.9) and at short ranks
+//                  of outputs beyond 1024 of its tiles (8192 x 8192 at rank 64: 67 us, 128 x 64 88).  2.2 % behind the best on
+//                  average (14 % at most), 1 % where C is float
+enum class FactorTile { k64, k128x64, k128, k192x128, kThreeStage, kPersist };
+static inline FactorTile pick_factor_tile(int64_t M, int64_t N, int64_t K, bool bf16_c, bool sum) {
+  auto tiles = [&](int64_t bm, int64_t bn) { return ceil_div(M, bm) * ceil_div(N, bn); };
+  if (sum) {
+    if (K > 192 && tiles(192, 128) >= 2048) return FactorTile::k192x128;
+    if (!bf16_c || tiles(64, 64) <= 768) return FactorTile::k64;
+    const int64_t t192 = tiles(192, 192);
+    if ((t192 <= 256 && tiles(128, 64) > 768) || (t192 > 1024 && K <= 128)) return FactorTile::kThreeStage;
+    return FactorTile::k128x64;
+  }
+  struct Cost { FactorTile tile; int bm, bn, base, per_tile, per_k; };
+  static const Cost costs[] = {{FactorTile::k64, 64, 64, 3000, 450, 180},
+                               {FactorTile::k128x64, 128, 64, 3000, 600, 270},
+                               {FactorTile::k128, 128, 128, 3200, 1300, 430},
+                               {FactorTile::k192x128, 192, 128, 3600, 1700, 580},
+                               {FactorTile::kPersist, 256, 256, 3500, 3500, 1400}};
+  const int64_t kt = ceil_div(K, 64);
+  FactorTile best = FactorTile::k64;
+  int64_t best_ns = INT64_MAX;
+  for (const Cost& c : costs) {
+    if (c.tile == FactorTile::kPersist && !(bf16_c && K > 128)) continue;
+    const int64_t ns = c.base + ceil_div(tiles(c.bm, c.bn), 256) * (c.per_tile + kt * c.per_k);
+    if (ns < best_ns) { best_ns = ns; best = c.tile; }
+  }
+  return best;
+}
+constexpr int64_t kFactorMaxK = 256;   // above, pick_gemm_tile's estimates hold
 
 // Which tile a float32 product takes: the least time of a K tile of 32, fixed + tiles per compute unit x per_tile
 // nanoseconds.  The matrix pipe bounds all of them, so the estimates follow the area, and a small tile only loses by its

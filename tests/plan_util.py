@@ -14,6 +14,7 @@ extern "C" {
 int gemm_tile(int64_t M, int64_t N, int64_t K, int persist_ok) { return (int)pick_gemm_tile(M, N, K, persist_ok != 0).tile; }
 int gemm_one_round(int64_t M, int64_t N, int64_t K, int persist_ok) { return pick_gemm_tile(M, N, K, persist_ok != 0).one_round; }
 int f32_tile(int64_t M, int64_t N, int64_t splits, int all_tiles) { return (int)pick_f32_tile(M, N, splits, all_tiles != 0).tile; }
+int factor_tile(int64_t M, int64_t N, int64_t K, int form) { return (int)pick_factor_tile(M, N, K, (form & 1) != 0, (form & 2) != 0); }
 int raised_capacity() { return RaisedLimits::kKernels; }
 int raised_lost(int kernels, int devices) {  // entries the table has forgotten after all were added
   static RaisedLimits table;
@@ -48,7 +49,7 @@ def lib():
             f.write(_SOURCE)
         subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-O1", "-shared", "-fPIC", "-I" + ROOT, src, "-o", out], check=True)
         so = ctypes.CDLL(out)
-    for name in ("gemm_tile", "gemm_one_round", "f32_tile", "f32_sketch_splits", "f32_sketch_fits"):
+    for name in ("gemm_tile", "gemm_one_round", "f32_tile", "f32_sketch_splits", "f32_sketch_fits", "factor_tile"):
         getattr(so, name).argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int]
     return so
 
@@ -72,3 +73,9 @@ def f32_sketch_splits(n, channels, r, f32_factor=True):
 def f32_sketch_fits(n, channels, r, f32_factor=True):
     """Whether S and the partial products fit the workspace of the generic form."""
     return bool(lib().f32_sketch_fits(n, channels, r, f32_factor))
+
+
+def factor_tile(m, n, k, bf16_c=True, added=False):
+    """Kernel of a product of two gradient factors, k <= 256."""
+    names = ("64x64", "128x64", "128x128", "192x128", "three-stage", "persistent")
+    return names[lib().factor_tile(m, n, k, int(bf16_c) + 2 * int(added))]
