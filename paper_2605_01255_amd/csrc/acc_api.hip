@@ -541,7 +541,7 @@ SketchPlan plan_sketch(const acc_linear_desc* d, int64_t n, int64_t channels, in
     sp.G = generic_sketch_splits(n, channels, d->r);
     return sp;
   }
-  // 8-wave tiles of 512 channels, one work-group per compute unit.  64 sketch columns (64 accumulators per
+  // 8-wave tiles of 512 channels as a rule, one work-group per compute unit.  64 sketch columns (64 accumulators per
   // lane) by default: half the partial bytes of the 128-column tile for the same generator and matrix work.
   // The 128-column tile stays where eight or more column slices would re-read a long token range from L2
   // (measured: r = 512 at 65536 tokens), and in the one-launch kernel, which interleaves it with GEMM tiles;
@@ -558,6 +558,11 @@ SketchPlan plan_sketch(const acc_linear_desc* d, int64_t n, int64_t channels, in
   if (G < 1) G = 1;
   sp.tokens_per_split = (int)round_up(ceil_div(n, G), 32);
   sp.G = (int)ceil_div(n, sp.tokens_per_split);
+  // The token splits of few tokens leave compute units idle: the narrowest slab that still makes one work-group per compute
+  // unit at most (two of them on one get in each other's way: 4096 x 1024 at rank 256, 128 / 256 / 512 work-groups of 512 / 256 /
+  // 128 channels 12.2 / 10.6 / 11.5 us).  The splits, and with them the workspace and every sum's order, stay.
+  while (!wide && sp.ch > 128 && ceil_div(channels, sp.ch / 2) * sp.n_js * sp.G <= 256) sp.ch /= 2;
+  sp.n_cslab = (int)ceil_div(channels, sp.ch);
   if ((int64_t)sp.tokens_per_split * ld * 2 + 64 * ld * 2 > kMaxOperandBytes) sp.fast = false;
   if (!sp.fast) sp.G = generic_sketch_splits(n, channels, d->r);
   return sp;
@@ -586,8 +591,14 @@ void fast_sketch(const acc_linear_desc* d, const SketchPlan& sp, const void* A, 
     if (transposed) L.launch_lds(sketch8_kernel<true, 4>, grid, dim3(512), (size_t)sketch8_lds_bytes<4>(), p);
     else L.launch_lds(sketch8_kernel<false, 4>, grid, dim3(512), (size_t)sketch8_lds_bytes<4>(), p);
   } else {
-    if (transposed) L.launch_lds(sketch8_kernel<true, 2>, grid, dim3(512), (size_t)sketch8_lds_bytes<2>(), p);
-    else L.launch_lds(sketch8_kernel<false, 2>, grid, dim3(512), (size_t)sketch8_lds_bytes<2>(), p);
+    auto go = [&](auto width) {
+      constexpr int CH = decltype(width)::value;
+      if (transposed) L.launch_lds(sketch8_kernel<true, 2, CH>, grid, dim3(512), (size_t)sketch8_lds_bytes<2, CH>(), p);
+      else L.launch_lds(sketch8_kernel<false, 2, CH>, grid, dim3(512), (size_t)sketch8_lds_bytes<2, CH>(), p);
+    };
+    if (sp.ch == 128) go(std::integral_constant<int, 128>{});
+    else if (sp.ch == 256) go(std::integral_constant<int, 256>{});
+    else go(std::integral_constant<int, 512>{});
   }
   if (defer) *defer = ReduceJob{ws, out, channels * d->r, sp.G, d->factor_dtype == ACC_BF16 ? 1 : 0, out_row, out_ld};
   else reduce_partials(d, ws, sp.G, channels * d->r, out, out_row, out_ld, L);

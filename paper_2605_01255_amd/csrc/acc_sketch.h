@@ -6,7 +6,7 @@
 // A is X [n, d_in] or dY [n, d_out] (row-major, channels contiguous); S[t, j] is regenerated from the
 // Philox counter (token, column) in registers, directly in MFMA operand layout, and never stored.
 //
-// Work-group = 8 waves on a tile of 512 channels x 64 or 128 sketch columns, fp32 accumulators in registers
+// Work-group = 8 waves on a tile of 512 (256, 128) channels x 64 or 128 sketch columns, fp32 accumulators in registers
 // for the whole token range of the split.  Tokens stream through LDS in stages of 16 or 32 rows, global ->
 // LDS directly, in a ring with 96 KB in flight: the input is read once from HBM, so enough bytes must be
 // outstanding per CU to cover DRAM latency.  The channel-major MFMA operand is formed from the token-major
@@ -63,27 +63,37 @@ __device__ __forceinline__ void store_partial_tile(const f32x16 (&acc)[CWB], flo
   }
 }
 
-// 8-wave sketch work-group: tile 512 channels x (WJ * 32) sketch columns, waves WC = 8 / WJ (channels) x WJ
-// (columns), each wave (512 / WC) channels x 32 columns.  An iteration is eight MFMAs per wave:
+// Stages of the transfer ring.
+template <int WJ, int CH> constexpr int sketch8_stages() { return WJ == 4 ? 7 : CH == 512 ? 4 : CH == 256 ? 7 : 8; }
+
+// 8-wave sketch work-group: tile CH channels x (WJ * 32) sketch columns, waves WC = 8 / WJ (channels) x WJ
+// (columns), each wave (CH / WC) channels x 32 columns.  At 512 channels an iteration is eight MFMAs per wave:
 //   WJ = 4: 512 x 128 tile, waves 2 x 4, 8 channel blocks x one 16-token k-step  (128 accumulators per lane)
 //   WJ = 2: 512 x  64 tile, waves 4 x 2, 4 channel blocks x two 16-token k-steps ( 64 accumulators per lane)
 // The WC waves that share 32 columns each generate one Philox call per lane and iteration (4 of the 8 * WC / 2
 // tokens a lane's operands need) and trade them through LDS, so S is generated once per work-group, not
 // once per wave.  The narrow tile keeps half as many accumulators per compute unit: a work-group covers
 // twice the tokens and the launch writes (and the fold reads) half as many bytes of partial tiles.
-template <bool TRANSPOSED, int WJ = 4>
+// Narrower slabs of the 64-column tile (CH = 256 or 128: four or two MFMAs) for launches that 512 channels leave short of
+// work-groups: each generates S for itself, on compute units that would be idle, and has a half or a quarter of the transfers,
+// matrix work and partial tile to wait for.  2049 x 1032 at rank 128: 54
+// work-groups of 512 channels 10.4 us, 162 of 128 7.0; 384 x 3072 at rank 64: 12 and 48, 8.4 and 5.6.
+template <bool TRANSPOSED, int WJ = 4, int CH = 512>
 __device__ __forceinline__ void sketch8_tile(const SketchFastParams& p, int b, char* smem) {
   static_assert(WJ == 4 || WJ == 2, "column groups");
+  static_assert(CH == 512 || (WJ == 2 && (CH == 256 || CH == 128)), "channel slabs");
   constexpr int NW = 8, WC = NW / WJ;
-  constexpr int CH = 512, RC = WJ * 32;
-  constexpr int CWB = CH / (WC * 32);            // channel blocks per wave: 8 or 4
-  constexpr int KS = 8 / CWB;                    // k-steps per iteration: 1 or 2
+  constexpr int RC = WJ * 32;
+  constexpr int CWB = CH / (WC * 32);            // channel blocks per wave: 8, or 4, 2, 1
+  constexpr int KS = WC / 2;                     // k-steps per iteration: 1 or 2
+  constexpr int SLOTS = CWB * KS;                // MFMAs per iteration: 8, 4 or 2
   constexpr int BT = 16 * KS;                    // tokens per stage
   constexpr int ROW_BYTES = CH * 2;
-  constexpr int STAGE = BT * ROW_BYTES;          // 16 or 32 KB
-  constexpr int NSTAGE = KS == 1 ? 7 : 4;        // ring of 112 or 128 KB,
-  constexpr int DEPTH = NSTAGE - 1;              // 96 KB in flight
-  constexpr int LOADS = BT / NW;                 // 1 KB wave-loads per wave and stage (one per token row)
+  constexpr int STAGE = BT * ROW_BYTES;          // 16 or 32 KB; 16 or 8 of the narrow slabs
+  constexpr int NSTAGE = sketch8_stages<WJ, CH>(); // ring of 112 or 128 KB, 112 or 64
+  constexpr int DEPTH = NSTAGE - 1;              // 96 KB in flight, 56 of the narrowest slab
+  constexpr int LOADS = STAGE / 1024 / NW;       // 1 KB wave-loads per wave and stage
+  constexpr int ROW_CHUNKS = ROW_BYTES / 16;     // 16-byte chunks of a token row: a wave-load is one, two or four rows
   constexpr int XBUF = NSTAGE * STAGE;           // S exchange: 2 slots x KS k-steps x WJ column groups x 64 lanes x 16 B
   constexpr int XSLOT = KS * WJ * 1024;          // 4 KB either way
 
@@ -102,14 +112,14 @@ __device__ __forceinline__ void sketch8_tile(const SketchFastParams& p, int b, c
   const int NS = t_end > t_begin ? (int)((t_end - t_begin + BT - 1) / BT) : 0;  // stages = iterations
   if (NS == 0) return;
 
-  // ---- global -> LDS: wave-load t of wave w is token row t * NW + w of the stage ----
+  // ---- global -> LDS: wave-load t of wave w fills LDS bytes [(t * NW + w) * 1024, + 1024) of the stage ----
   const u32x4 rsrc = make_rsrc(p.A + t_begin * p.lda + c0, ((p.n - t_begin - 1) * p.lda + (p.C - c0)) * 2);
   uint32_t src[LOADS], dst[LOADS];
 #pragma unroll
   for (int t = 0; t < LOADS; ++t) {
-    const int row = t * NW + wave;
-    src[t] = (uint32_t)(row * p.lda * 2 + ((lane ^ swz_n(row)) << 4));
-    dst[t] = (uint32_t)(row * ROW_BYTES);
+    const int row = (t * NW + wave) * (64 / ROW_CHUNKS) + lane / ROW_CHUNKS;
+    src[t] = (uint32_t)(row * p.lda * 2 + (((lane % ROW_CHUNKS) ^ swz_n(row)) << 4));
+    dst[t] = (uint32_t)((t * NW + wave) * 1024);
   }
   const uint32_t smem_lds = (uint32_t)(uintptr_t)smem;
   auto issue_stage = [&](int st, uint32_t stage_lds) {
@@ -130,7 +140,8 @@ __device__ __forceinline__ void sketch8_tile(const SketchFastParams& p, int b, c
   for (int v = 0; v < 4; ++v) {
     const int row = 8 * (gq >> 1) + (i16 >> 2);
     const int col16 = 2 * (gq & 1) + ((i16 & 3) >> 1);
-    rd_base[v] = row * ROW_BYTES + (((v ^ xr) & 3) << 6) + (col16 << 4) + ((i16 & 1) << 3) + wc * (CWB * 64);
+    const int block = wc * CWB + (CWB < 4 ? v % CWB : v);   // channel block v of the wave, in the slab
+    rd_base[v] = row * ROW_BYTES + (((block ^ xr) & 3) << 6) + (block >> 2) * 256 + (col16 << 4) + ((i16 & 1) << 3);
   }
   // operand of slot s = k-step (s / CWB) of the stage, channel block (s % CWB) of the wave
   auto read_block = [&](const char* st, int s) -> bf16x8 {
@@ -196,7 +207,7 @@ __device__ __forceinline__ void sketch8_tile(const SketchFastParams& p, int b, c
   // MFMA on the operands in registers, the reads of the operands of iteration t + 1, and a slice of this
   // wave's share of S for iteration t + 2.  Branch-free: past the end the last stage is fetched again.
   HalfGen hg;
-  auto iteration = [&](int t, const bf16x8(&af)[8], const SOps& sf, bf16x8(&nf)[8], SOps& s_next) {
+  auto iteration = [&](int t, const bf16x8(&af)[SLOTS], const SOps& sf, bf16x8(&nf)[SLOTS], SOps& s_next) {
     const int t_load = t + DEPTH < NS ? t + DEPTH : NS - 1;
     __builtin_amdgcn_sched_barrier(0);
     issue_stage(t_load, smem_lds + ((t + DEPTH) % NSTAGE) * STAGE);
@@ -206,17 +217,19 @@ __device__ __forceinline__ void sketch8_tile(const SketchFastParams& p, int b, c
     const char* rd_stage = smem + ((t + 1) % NSTAGE) * STAGE;
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
-      const int mb = s % CWB, ks = s / CWB;
-      if (TRANSPOSED) acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sf.s[ks], af[s], acc[mb], 0, 0, 0);
-      else acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[s], sf.s[ks], acc[mb], 0, 0, 0);
+      if (s < SLOTS) {
+        const int mb = s % CWB, ks = s / CWB;
+        if (TRANSPOSED) acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sf.s[ks], af[s], acc[mb], 0, 0, 0);
+        else acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[s], sf.s[ks], acc[mb], 0, 0, 0);
+      }
       if (s == 0) s_next = read_s(t + 1);
-      nf[s] = read_block(rd_stage, s);
+      if (s < SLOTS) nf[s] = read_block(rd_stage, s);
       gen_slot(hg, s, t + 2);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
 
-  bf16x8 fa[8], fb[8];
+  bf16x8 fa[SLOTS], fb[SLOTS];
 #pragma unroll
   for (int d = 0; d < DEPTH; ++d) issue_stage(d < NS ? d : NS - 1, smem_lds + d * STAGE);
 #pragma unroll
@@ -227,7 +240,7 @@ __device__ __forceinline__ void sketch8_tile(const SketchFastParams& p, int b, c
   wait_oldest_stage();
   __syncthreads();
 #pragma unroll
-  for (int s = 0; s < 8; ++s) fa[s] = read_block(smem, s);
+  for (int s = 0; s < SLOTS; ++s) fa[s] = read_block(smem, s);
   SOps s_a = read_s(0), s_b = s_a;
   int t = 0;
   for (; t + 1 < NS; t += 2) {
@@ -242,16 +255,17 @@ __device__ __forceinline__ void sketch8_tile(const SketchFastParams& p, int b, c
 }
 
 // The 8-wave sketch tile as a kernel of its own: grid = 8 * n_js * ceil(n_cslab * G / 8) work-groups.
-template <bool TRANSPOSED, int WJ = 4>
+template <bool TRANSPOSED, int WJ = 4, int CH = 512>
 __global__ __launch_bounds__(512) void sketch8_kernel(SketchFastParams sp) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  sketch8_tile<TRANSPOSED, WJ>(sp, blockIdx.x, smem);
+  sketch8_tile<TRANSPOSED, WJ, CH>(sp, blockIdx.x, smem);
 }
 
-// Dynamic LDS of sketch8_kernel: the stage ring plus the 8 KB S exchange.
-template <int WJ>
+// Dynamic LDS of sketch8_kernel: the stage ring plus the S exchange (two slots of 4 KB; 128 KB with the 128-column tile, as the
+// one-launch kernel has it).
+template <int WJ, int CH = 512>
 constexpr int sketch8_lds_bytes() {
-  return WJ == 4 ? 128 * 1024 : 136 * 1024;
+  return WJ == 4 ? 128 * 1024 : sketch8_stages<WJ, CH>() * 32 * CH * 2 + 8 * 1024;
 }
 
 }  // namespace acc
