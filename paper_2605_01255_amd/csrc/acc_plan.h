@@ -97,30 +97,39 @@ constexpr int64_t kFactorMaxK = 256;   // above, pick_gemm_tile's estimates hold
 
 // Which tile a float32 product takes: the least time of a K tile of 32, fixed + tiles per compute unit x per_tile
 // nanoseconds.  The matrix pipe bounds all of them, so the estimates follow the area, and a small tile only loses by its
-// operands' latency; what decides is how many tiles the fullest compute unit gets.  Constants fitted to 272 measurements
-// (68 shapes from 64 x 2048 x 8192 to 4096 x 4096 x 1024 in the four orders of the operands): the chosen tile is 0.7 %
-// behind the best one on average, 11 % at most (the first fit, rounds times a constant, 25 %).  Measured us, 128 x 64 / 64 x 64 / 64 x 32 / 32 x 32, the chosen one marked
-// [generic kernel before]:
-//   2048 x 2048 x 1024  68* / 73  / 82  / 88 [188]     2048 x 1024 x 2048  73 / 72* / 104 / 89 [347]
-//   300 x 4096 x 2048   77  / 73  / 57* / 60           2504 x 1000 x 3000  186 / 198 / 158* / 164
-//   256 x 512 x 256     12  / 8.0 / 5.9 / 5.0* [22]    3656 x 280 x 288    13.5 / 13.6 / 12.1* / 12.9
+// operands' latency; what decides is how many tiles the fullest compute unit gets.  Two stages and as many work-groups as LDS
+// holds (64 x 64 five, 64 x 32 six, 32 x 32 eight): they start, wait and store at different times, which is worth more than
+// transfers further ahead (2048 x 2048 x 1024 66.5 us against 70.7 on 128 x 64 with three stages, two work-groups; 2504 x 1000 x
+// 3000 128 against 160 on 64 x 32 with four).  Only where 32 x 32 tiles are 2.5 or fewer to a compute unit, or 64 x 32 one,
+// there is nobody to cover a wait: four stages.  128 x 64 where it is exactly two to a compute unit: as fast as four of 64 x 64, with a
+// quarter less to move.  Constants fitted to 150 measurements (50 shapes from 128 x 128 x 4096 to 4096 x 4096 x 1024 in three
+// orders of the operands): the chosen form is 2.9 % behind the best of eleven on average, 13 % at
+// most (three and four stages everywhere and their own fit: 5.4 and 29 %).
+// Measured us, 64 x 64 / 64 x 32 / 32 x 32, the chosen one marked [before]:
+//   2048 x 2048 x 1024  68 / 79  / 85 (67* on 128 x 64) [69-71]     2048 x 1024 x 2048  71* / 73 / 89 [72]
+//   300 x 4096 x 2048   70  / 56* / 58 [57]                         2504 x 1000 x 3000  143 / 129* / 166 [159]
+//   4096 x 4096 x 1024  255* / 288 / 346 [264]                      3072 x 1024 x 3072  148* / 152 / 196 [163]
+//   256 x 512 x 256     8.0 / 10.3 / 6.1* [6.1]                     3000 x 3000 x 1000  147* / 159 / 191 [162]
 enum class F32TileShape { k64, k32, k128x64, k64x32 };
 struct F32Choice {
   F32TileShape tile;
   int ns_per_k;   // estimate of a K tile
+  bool deep;      // 32 x 32 and 64 x 32: four stages
 };
 static inline F32Choice pick_f32_tile(int64_t M, int64_t N, int64_t splits, bool all_tiles) {
-  struct Cost { F32TileShape tile; int bm, bn, per_tile, fixed; };
-  static const Cost costs[] = {{F32TileShape::k64, 64, 64, 555, 50}, {F32TileShape::k32, 32, 32, 165, 90},
-                               {F32TileShape::k128x64, 128, 64, 955, 205}, {F32TileShape::k64x32, 64, 32, 274, 65}};
-  F32Choice best{F32TileShape::k64, 0};
+  struct Cost { F32TileShape tile; int bm, bn, per_tile, fixed, resident, more_per_tile, more_fixed; };  // more: above `resident`
+  static const Cost costs[] = {{F32TileShape::k64, 64, 64, 460, 100, 5, 460, 100}, {F32TileShape::k32, 32, 32, 145, 100, 8, 145, 100},
+                               {F32TileShape::k64x32, 64, 32, 227, 115, 6, 225, 370}, {F32TileShape::k128x64, 128, 64, 950, 0, 2, 950, 0}};
+  F32Choice best{F32TileShape::k64, 0, false};
   int64_t best_ns = INT64_MAX;
   for (int i = 0; i < (all_tiles ? 4 : 2); ++i) {
-    const int64_t per_cu = ceil_div(ceil_div(M, costs[i].bm) * ceil_div(N, costs[i].bn) * splits, 256);
-    const int64_t ns = costs[i].fixed + per_cu * costs[i].per_tile;
+    const int64_t tiles = ceil_div(M, costs[i].bm) * ceil_div(N, costs[i].bn) * splits, per_cu = ceil_div(tiles, 256);
+    if (costs[i].tile == F32TileShape::k128x64 && per_cu != 2) continue;
+    const Cost& c = costs[i];
+    const int64_t ns = per_cu <= c.resident ? c.fixed + per_cu * c.per_tile : c.more_fixed + per_cu * c.more_per_tile;
     if (ns < best_ns) {
       best_ns = ns;
-      best = F32Choice{costs[i].tile, (int)(ns < INT32_MAX ? ns : INT32_MAX)};
+      best = F32Choice{c.tile, (int)(ns < INT32_MAX ? ns : INT32_MAX), tiles <= (c.tile == F32TileShape::k32 ? 640 : 256)};
     }
   }
   return best;
