@@ -61,7 +61,7 @@ static inline GemmChoice pick_gemm_tile(int64_t M, int64_t N, int64_t K, bool pe
 // average over 84 outputs of at most one round of it (512 x 512 at rank 256 8.6 us against 3.8, 1032 x 1544 at rank 128 7.1
 // against 4.4, 3072 x 1024 at rank 256 9.1 against 5.7, 3072 x 3072 at 256 11.3 against 10.9).
 //   written        the least of base + (tiles of the fullest compute unit) x (tile + K tiles x time of one), in nanoseconds,
-//                  and from three K tiles on the persistent kernel's: 1.6 % behind the best of nine candidates on average over
+//                  and from three K tiles on the persistent kernel's: 1.3 % behind the best of nine candidates on average over
 //                  138 outputs (13 % at most), 3 % where C is float
 //   added to C     by size: the read of C counts more than the products.  The three-stage kernel requests C with its operands
 //                  and stays where its one round is nearly full (3072 x 3072 at rank 64: 10.6 us, 128 x 64 10.9) and at short ranks
@@ -88,7 +88,9 @@ static inline FactorTile pick_factor_tile(int64_t M, int64_t N, int64_t K, bool 
   int64_t best_ns = INT64_MAX;
   for (const Cost& c : costs) {
     if (c.tile == FactorTile::kPersist && !(bf16_c && K > 128)) continue;
-    const int64_t ns = c.base + ceil_div(tiles(c.bm, c.bn), 256) * (c.per_tile + kt * c.per_k);
+    const int64_t per_cu = ceil_div(tiles(c.bm, c.bn), 256);
+    int64_t ns = c.base + per_cu * (c.per_tile + kt * c.per_k);
+    if (c.tile == FactorTile::k128x64 && per_cu > 3) ns += 900;   // three are resident
     if (ns < best_ns) { best_ns = ns; best = c.tile; }
   }
   return best;
