@@ -945,8 +945,7 @@ void rsvd_factor_tuned(const acc_linear_desc* d, const Shape& s, const RsvdPlan&
   bf16* ut = (bf16*)(ws + pl.off_ut);
   float* part = (float*)(ws + pl.off_fact_part);
   if (U)  // backward: rebuild the transpose from the stored factor; forward wrote it with the last QR pass
-    L(transpose_pad_kernel<bf16>, dim3((unsigned)ceil_div(pl.n_pad * k, 256)), dim3(256), (const bf16*)U, s.n, (int)k,
-      pl.n_pad, ut);
+    L(transpose_pad_kernel<bf16>, dim3((unsigned)(pl.n_pad / 16 * ceil_div(k, 16))), dim3(256), (const bf16*)U, s.n, (int)k, pl.n_pad, ut);
   const int splits = fast_gemm_splitk<2, 4, false>(ut, A, part, k, channels, pl.n_pad, pl.n_pad, lda, channels,
                                                        s.n, L);
   const unsigned blocks = (unsigned)ceil_div(k * channels, 256);
