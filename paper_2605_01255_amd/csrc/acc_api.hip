@@ -536,6 +536,7 @@ struct SketchPlan {
   int ch, rc;            // tile: channels x sketch columns
   int n_cslab, n_js, G;  // channel slabs, column slices, token splits
   int tokens_per_split;
+  int room;              // partial tiles that the workspace holds, at least G
 };
 
 SketchPlan plan_sketch(const acc_linear_desc* d, int64_t n, int64_t channels, int64_t ld) {
@@ -543,9 +544,10 @@ SketchPlan plan_sketch(const acc_linear_desc* d, int64_t n, int64_t channels, in
   sp.fast = d->io_dtype == ACC_BF16 && n * ld * 2 <= kMaxOperandBytes &&
             channels * d->r * 4 <= kMaxOperandBytes / 2;
   if (!sp.fast) {
-    sp.G = generic_sketch_splits(n, channels, d->r);
+    sp.G = sp.room = generic_sketch_splits(n, channels, d->r);
     return sp;
   }
+  auto operand_fits = [&](int64_t tokens) { return tokens * ld * 2 + 64 * ld * 2 <= kMaxOperandBytes; };
   // 8-wave tiles of 512 channels as a rule, one work-group per compute unit.  64 sketch columns (64 accumulators per
   // lane) by default: half the partial bytes of the 128-column tile for the same generator and matrix work.
   // The 128-column tile stays where eight or more column slices would re-read a long token range from L2
@@ -561,15 +563,27 @@ SketchPlan plan_sketch(const acc_linear_desc* d, int64_t n, int64_t channels, in
   if (G > max_by_tokens) G = max_by_tokens;
   if (G > 64) G = 64;
   if (G < 1) G = 1;
-  sp.tokens_per_split = (int)round_up(ceil_div(n, G), 32);
-  sp.G = (int)ceil_div(n, sp.tokens_per_split);
-  // The token splits of few tokens leave compute units idle: the narrowest slab that still makes one work-group per compute
-  // unit at most (two of them on one get in each other's way: 4096 x 1024 at rank 256, 128 / 256 / 512 work-groups of 512 / 256 /
-  // 128 channels 12.2 / 10.6 / 11.5 us).  The splits, and with them the workspace and every sum's order, stay.
-  while (!wide && sp.ch > 128 && ceil_div(channels, sp.ch / 2) * sp.n_js * sp.G <= 256) sp.ch /= 2;
+  auto split_tokens = [&](int64_t splits) {
+    sp.tokens_per_split = (int)round_up(ceil_div(n, splits), 32);
+    sp.G = (int)ceil_div(n, sp.tokens_per_split);
+  };
+  split_tokens(G);
+  sp.room = sp.G;
+  const SketchSplit c = pick_sketch_split(n, channels, d->r, G);
+  if (!wide && d->factor_dtype == ACC_BF16 && operand_fits(round_up(ceil_div(n, c.splits), 32))) {
+    sp.ch = c.ch;
+    split_tokens(c.splits);
+  } else {
+    // A float factor shows the rounding of its running sums, so they stay as long as they are with slabs of 512: only the slabs
+    // are narrowed, as far as that makes one work-group per compute unit at most (two of them on one get in each other's way:
+    // 4096 x 1024 at rank 256, 128 / 256 / 512 work-groups of 512 / 256 / 128 channels 12.2 / 10.6 / 11.5 us).
+    while (!wide && sp.ch > 128 && ceil_div(channels, sp.ch / 2) * sp.n_js * sp.G <= 256) sp.ch /= 2;
+  }
   sp.n_cslab = (int)ceil_div(channels, sp.ch);
-  if ((int64_t)sp.tokens_per_split * ld * 2 + 64 * ld * 2 > kMaxOperandBytes) sp.fast = false;
-  if (!sp.fast) sp.G = generic_sketch_splits(n, channels, d->r);
+  if (!operand_fits(sp.tokens_per_split)) {
+    sp.fast = false;
+    sp.G = sp.room = generic_sketch_splits(n, channels, d->r);
+  }
   return sp;
 }
 
@@ -1121,7 +1135,7 @@ void lowrank_product(const F32Operand& a, const F32Operand& b, int64_t M, int64_
 size_t workspace_bytes(const acc_linear_desc* d, const Shape& s, bool backward) {
   const int64_t channels = backward ? s.d_out : s.d_in;
   const SketchPlan sp = plan_sketch(d, s.n, channels, backward ? s.ldy : s.ldx);
-  return (size_t)sp.G * (size_t)channels * (size_t)s.r * sizeof(float);
+  return (size_t)sp.room * (size_t)channels * (size_t)s.r * sizeof(float);
 }
 
 // Device address of this device's copy of `scratch`, looked up on the first call with that device current.

@@ -97,6 +97,37 @@ static inline FactorTile pick_factor_tile(int64_t M, int64_t N, int64_t K, bool 
 }
 constexpr int64_t kFactorMaxK = 256;   // above, pick_gemm_tile's estimates hold
 
+// Slabs and token splits of the bfloat16 sketch with bfloat16 factors (64 sketch columns, one work-group per compute unit at
+// most): the least of  start + iterations of 32 tokens x one + partial tiles written and read back,  in nanoseconds.  Narrow
+// slabs generate S more often, but their iterations are shorter, and half as many splits of twice the tokens write half as many
+// partials, which is what a sketch of a few thousand tokens spends a third of its time on.  `most`: the splits that 512
+// channels make; never more, the workspace holds those.  Two thirds of what fills the chip is the other choice.
+// Fitted to 95 forward passes with 1024 outputs (300 to 32768 tokens, 1024 to 8192 channels, rank 64 to 256): 0.4 % behind the
+// best of twelve forms on average, 2.6 % faster than slabs narrowed at the splits of 512 channels, at worst 2.4 % slower.
+// us of the pass, before / now: 4096 x 4096 at rank 128 54.8 / 49.1, 2048 x 4096 at 256 44.0 / 39.9, 600 x 8192 at 256 52.0 / 47.6,
+// 16384 x 4096 at 64 136 / 120, 4096 x 1024 at 256 24.9 / 23.8, 4096 x 3072 at 256 45.1 / 46.2; 16384 x 3072 at 256 stays (115.3).
+struct SketchSplit {
+  int ch;
+  int64_t splits;
+};
+static inline SketchSplit pick_sketch_split(int64_t n, int64_t channels, int64_t r, int64_t most) {
+  struct Cost { int ch, start, per_iteration; };
+  static const Cost costs[] = {{512, 1600, 495}, {256, 1000, 395}, {128, 0, 340}};
+  SketchSplit best{512, most};
+  int64_t best_ns = INT64_MAX;
+  for (const Cost& c : costs) {
+    int64_t full = 256 / (ceil_div(channels, c.ch) * ceil_div(r, 64));
+    if (full > most) full = most;
+    for (int64_t splits : {full, full * 2 / 3}) {
+      if (splits < 1) continue;
+      const int64_t iterations = ceil_div(ceil_div(n, splits), 32), made = ceil_div(n, iterations * 32);
+      const int64_t ns = c.start + iterations * c.per_iteration + made * channels * r * 4 / 1000 * 324 / 1000;
+      if (ns < best_ns) { best_ns = ns; best = SketchSplit{c.ch, splits}; }
+    }
+  }
+  return best;
+}
+
 // Which tile a float32 product takes: the least time of a K tile of 32, fixed + tiles per compute unit x per_tile
 // nanoseconds.  The matrix pipe bounds all of them, so the estimates follow the area, and a small tile only loses by its
 // operands' latency; what decides is how many tiles the fullest compute unit gets.  Two stages and as many work-groups as LDS

@@ -15,6 +15,8 @@ int gemm_tile(int64_t M, int64_t N, int64_t K, int persist_ok) { return (int)pic
 int gemm_one_round(int64_t M, int64_t N, int64_t K, int persist_ok) { return pick_gemm_tile(M, N, K, persist_ok != 0).one_round; }
 int f32_tile(int64_t M, int64_t N, int64_t splits, int all_tiles) { return (int)pick_f32_tile(M, N, splits, all_tiles != 0).tile; }
 int factor_tile(int64_t M, int64_t N, int64_t K, int form) { return (int)pick_factor_tile(M, N, K, (form & 1) != 0, (form & 2) != 0); }
+int sketch_channels(int64_t n, int64_t channels, int64_t r, int most) { return pick_sketch_split(n, channels, r, most).ch; }
+int sketch_splits(int64_t n, int64_t channels, int64_t r, int most) { return (int)pick_sketch_split(n, channels, r, most).splits; }
 int raised_capacity() { return RaisedLimits::kKernels; }
 int raised_lost(int kernels, int devices) {  // entries the table has forgotten after all were added
   static RaisedLimits table;
@@ -49,7 +51,8 @@ def lib():
             f.write(_SOURCE)
         subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-O1", "-shared", "-fPIC", "-I" + ROOT, src, "-o", out], check=True)
         so = ctypes.CDLL(out)
-    for name in ("gemm_tile", "gemm_one_round", "f32_tile", "f32_sketch_splits", "f32_sketch_fits", "factor_tile"):
+    for name in ("gemm_tile", "gemm_one_round", "f32_tile", "f32_sketch_splits", "f32_sketch_fits", "factor_tile",
+                 "sketch_channels", "sketch_splits"):
         getattr(so, name).argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int]
     return so
 
@@ -79,3 +82,8 @@ def factor_tile(m, n, k, bf16_c=True, added=False):
     """Kernel of a product of two gradient factors, k <= 256."""
     names = ("64x64", "128x64", "128x128", "192x128", "three-stage", "persistent")
     return names[lib().factor_tile(m, n, k, int(bf16_c) + 2 * int(added))]
+
+
+def sketch_split(n, channels, r, most):
+    """(channels of a slab, token splits) of the bfloat16 sketch with bfloat16 factors; `most` splits with 512 channels."""
+    return lib().sketch_channels(n, channels, r, most), lib().sketch_splits(n, channels, r, most)

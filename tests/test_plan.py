@@ -58,3 +58,16 @@ def test_stored_sketch_fits_the_workspace():
 def test_raised_lds_limits_are_remembered_for_every_kernel_and_device():
     """A launch whose kernel is not in the table sets the limit again."""
     assert plan.lib().raised_lost(plan.lib().raised_capacity(), 64) == 0
+
+
+def test_sketch_splits_fit_the_workspace_and_the_chip():
+    """Never more splits than the workspace holds, never more work-groups than compute units where 512 channels made no more."""
+    for n in (1, 31, 257, 300, 1030, 4096, 4097, 16384, 65536):
+        for channels in (8, 128, 136, 520, 1024, 3080, 8192, 14336, 40000):
+            for r in (8, 64, 72, 256, 512):
+                columns = -(-r // 64)
+                most = max(1, min(256 // (-(-channels // 512) * columns), -(-n // 256), 64))
+                ch, splits = plan.sketch_split(n, channels, r, most)
+                assert ch in (128, 256, 512) and 1 <= splits <= most
+                assert splits == 1 or -(-channels // ch) * columns * splits <= 256
+                assert ch == 512 or -(-channels // ch) * columns * splits <= 256
