@@ -28,12 +28,12 @@ __global__ __launch_bounds__(512) void fused_linear_kernel(FastGemmParams gp, Sk
   const int cyc = gi / cycle, pos = gi - cyc * cycle;
   if (cyc < fm.n_units) {
     if (pos < fm.period) {
-      gemm_bf16_tile<2, 4, 4, 2, B_KMAJOR, bf16>(gp, (cyc * fm.period + pos) * 8 + x8, smem);
+      gemm_bf16_tile<2, 4, 4, 2, B_KMAJOR>(gp, (cyc * fm.period + pos) * 8 + x8, smem);
     } else {
       sketch8_tile<TRANSPOSED>(sp, (cyc * fm.unit + (pos - fm.period)) * 8 + x8, smem);
     }
   } else {
-    gemm_bf16_tile<2, 4, 4, 2, B_KMAJOR, bf16>(gp, (gi - fm.n_units * fm.unit) * 8 + x8, smem);
+    gemm_bf16_tile<2, 4, 4, 2, B_KMAJOR>(gp, (gi - fm.n_units * fm.unit) * 8 + x8, smem);
   }
 }
 

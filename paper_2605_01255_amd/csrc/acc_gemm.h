@@ -1,4 +1,5 @@
-// Tuned bf16 MFMA GEMM for gfx950 (steps F1, B1, B3):  C[M, N] = A[M, K] . B, fp32 accumulate.
+// What the bf16 products share (transfers, LDS layouts, tile order) and the 32x32x16 tile of the one-launch variant
+// (acc_fused.h):  C[M, N] = A[M, K] . B, fp32 accumulate.
 //
 //   A is row-major with K contiguous (X, dY, Xs).
 //   B_KMAJOR = true : B is given as Bt[N, K], K contiguous      (dX = dY . W^T reads W as is)
@@ -138,7 +139,7 @@ __device__ __forceinline__ bool xcd_tile(const FastGemmParams& p, int b, int& tm
 }
 
 // The work of one work-group: output tile number b (see xcd_tile), using the dynamic LDS at smem.
-template <int WM, int WN, int TM, int TN, bool B_KMAJOR, typename TC>
+template <int WM, int WN, int TM, int TN, bool B_KMAJOR>
 __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, char* smem) {
   constexpr int NW = WM * WN;
   constexpr int BM = WM * TM * 32, BN = WN * TN * 32, BK = 64;
@@ -272,26 +273,10 @@ __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, c
       // B operand first: the product comes out transposed, lane = output row, 4 consecutive registers =
       // 4 consecutive output columns, which is what the epilogue packs
       acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cb[j], ca[i], acc[i][j], 0, 0, 0);
-      if constexpr (NM >= 2 * (TM + TN)) {  // enough MFMAs: one read on every second one (+0.4 % on a step
-                                            // against eight reads on the first eight MFMAs of sixteen)
-        // in the order the next k-step consumes them (its MFMA i * TN + j needs a[i] and b[j]): a0, every b,
-        // then the other a: each read is then at least ten MFMAs ahead of its use
-        if (q % 2 == 0) {
-          const int r = q / 2;
-          if (r == 0) read_a1(rd_stage, rd_s, 0, na);
-          else if (r <= TN) read_b1(rd_stage, rd_s, r - 1, nb);
-          else if (r < TM + TN) read_a1(rd_stage, rd_s, r - TN, na);
-        }
-      } else {
-        if (q < TM) read_a1(rd_stage, rd_s, q, na);
-        else if (q < TM + TN) read_b1(rd_stage, rd_s, q - TM, nb);
-      }
-      if constexpr (NM >= 2 * (TM + TN) && G_EVERY == 2) {  // transfers on the odd MFMAs, reads on the even ones
-        if (q % 2 == 1 && q / 2 < g_count && g_first + q / 2 < NG_TOTAL) issue_one(g_first + q / 2, kt_next, nxt);
-      } else {
-        if (q % G_EVERY == 0 && q / G_EVERY < g_count && g_first + q / G_EVERY < NG_TOTAL)
-          issue_one(g_first + q / G_EVERY, kt_next, nxt);
-      }
+      if (q < TM) read_a1(rd_stage, rd_s, q, na);
+      else if (q < TM + TN) read_b1(rd_stage, rd_s, q - TM, nb);
+      if (q % G_EVERY == 0 && q / G_EVERY < g_count && g_first + q / G_EVERY < NG_TOTAL)
+        issue_one(g_first + q / G_EVERY, kt_next, nxt);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -363,35 +348,26 @@ __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, c
 
   // ---- epilogue ----
   // Lane holds output row (lane & 31) of each 32 x 32 block and columns 8 * (e / 4) + 4 * (lane >> 5) +
-  // e % 4.  Each wave stages 32 rows of its tile in a private, padded LDS region (8- or 16-byte writes,
+  // e % 4.  Each wave stages 32 rows of its tile in a private, padded LDS region (8-byte writes,
   // conflict-free), reads them back row-contiguous and stores 16 bytes per lane: full cache lines.
-  constexpr int ES = sizeof(TC);
-  constexpr int ROW_B = TN * 32 * ES;            // bytes of one staged row
+  constexpr int ROW_B = TN * 32 * 2;             // bytes of one staged row
   constexpr int PITCH = ROW_B + 8;               // +2 banks per row: 32 rows land on distinct banks
   constexpr int CH16 = ROW_B / 16;               // 16-byte chunks per row
   constexpr int WAVE_B = 32 * PITCH;
   static_assert(NW * WAVE_B <= 2 * STAGE, "epilogue staging exceeds the pipeline's LDS");
   __syncthreads();                               // every wave is done with the pipeline's LDS
   char* stage_w = smem + wave * WAVE_B;
-  TC* __restrict__ C = (TC*)p.C;
+  bf16* __restrict__ C = (bf16*)p.C;
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
-        char* dst = stage_w + lrow * PITCH + (j * 32 + g4 * 8 + kg * 4) * ES;
-        if constexpr (ES == 2) {
-          bf16x4 v;
+        bf16x4 v;
 #pragma unroll
-          for (int t = 0; t < 4; ++t) v[t] = (bf16)acc[i][j][g4 * 4 + t];
-          *(bf16x4*)dst = v;
-        } else {
-          f32x4 v;
-#pragma unroll
-          for (int t = 0; t < 4; ++t) v[t] = acc[i][j][g4 * 4 + t];
-          *(f32x4*)dst = v;
-        }
+        for (int t = 0; t < 4; ++t) v[t] = (bf16)acc[i][j][g4 * 4 + t];
+        *(bf16x4*)(stage_w + lrow * PITCH + (j * 32 + g4 * 8 + kg * 4) * 2) = v;
       }
     }
 #pragma unroll
@@ -399,7 +375,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, c
       const int idx = t * 64 + lane, row = idx / CH16, ch = idx % CH16;
       const u32x4 v = *(const u32x4*)(stage_w + row * PITCH + ch * 16);
       const int64_t gm = m0 + (wm * TM + i) * 32 + row;
-      const int64_t gn = n0 + wn * TN * 32 + ch * (16 / ES);
+      const int64_t gn = n0 + wn * TN * 32 + ch * 8;
       if (gm < p.M && gn < p.N) {
         *(u32x4*)(C + gm * p.ldc + gn) = v;
       }
