@@ -75,7 +75,7 @@ template <int WJ, int CH> constexpr int sketch8_stages() { return WJ == 4 ? 7 : 
 // once per wave.  The narrow tile keeps half as many accumulators per compute unit: a work-group covers
 // twice the tokens and the launch writes (and the fold reads) half as many bytes of partial tiles.
 // Narrower slabs of the 64-column tile (CH = 256 or 128: four or two MFMAs) for launches that 512 channels leave short of
-// work-groups: each generates S for itself, on compute units that would be idle, and has a half or a quarter of the transfers,
+// work-groups, or that are better off with fewer token splits and their partial tiles (pick_sketch_split): each generates S for itself, on compute units that would be idle, and has a half or a quarter of the transfers,
 // matrix work and partial tile to wait for.  2049 x 1032 at rank 128: 54
 // work-groups of 512 channels 10.4 us, 162 of 128 7.0; 384 x 3072 at rank 64: 12 and 48, 8.4 and 5.6.
 template <bool TRANSPOSED, int WJ = 4, int CH = 512>
