@@ -296,8 +296,7 @@ bool f32_sketch(const acc_linear_desc* d, const void* A, int64_t lda, int64_t ch
   if (!f32_gemm_ok(transposed ? sm : x, transposed ? x : sm, M, N, n, dst, ldc)) return false;
   L(sketch_matrix_kernel, dim3((unsigned)ceil_div(ceil_div(n, 4) * r, 256)), dim3(256), make_sketch_params(d), n, r, ws);
   const F32Operand a{A, lda, true, false};
-  if (exact && f32_gemm_ok(a, exact->b, n, exact->N, exact->K, exact->C, exact->ldc) &&
-      pick_f32_tile(M, N, G, true).tile == F32TileShape::k32 && pick_f32_tile(n, exact->N, 1, true).tile == F32TileShape::k32) {
+  if (exact && f32_gemm_ok(a, exact->b, n, exact->N, exact->K, exact->C, exact->ldc) && f32_pair(M, N, G, n, exact->N)) {
     F32GemmParams p = f32_params(transposed ? sm : x, transposed ? x : sm, dst, ldc, M, N, n);
     p.k_per_split = k_per_split; p.c_split_stride = count;
     F32GemmParams q = f32_params(a, exact->b, exact->C, exact->ldc, n, exact->N, exact->K);

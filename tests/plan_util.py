@@ -34,6 +34,7 @@ int f32_sketch_splits(int64_t n, int64_t channels, int64_t r, int f32_factor) { 
   const F32SketchPlan p = plan_f32_sketch(n, channels, r, f32_factor != 0);
   return p.stored ? (int)p.splits : 0;
 }
+int f32_shared_launch(int64_t M, int64_t N, int64_t n, int64_t out_n, int splits) { return f32_pair(M, N, splits, n, out_n); }
 int f32_sketch_fits(int64_t n, int64_t channels, int64_t r, int f32_factor) {
   const F32SketchPlan p = plan_f32_sketch(n, channels, r, f32_factor != 0);
   const int64_t partials = p.splits == 1 && f32_factor ? 0 : p.splits * channels * r;
@@ -54,6 +55,7 @@ def lib():
     for name in ("gemm_tile", "gemm_one_round", "f32_tile", "f32_sketch_splits", "f32_sketch_fits", "factor_tile",
                  "sketch_channels", "sketch_splits"):
         getattr(so, name).argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int]
+    so.f32_shared_launch.argtypes = [ctypes.c_int64] * 4 + [ctypes.c_int]
     return so
 
 
@@ -76,6 +78,13 @@ def f32_sketch_splits(n, channels, r, f32_factor=True):
 def f32_sketch_fits(n, channels, r, f32_factor=True):
     """Whether S and the partial products fit the workspace of the generic form."""
     return bool(lib().f32_sketch_fits(n, channels, r, f32_factor))
+
+
+def f32_pair(n, channels, other, r, f32_factor=True):
+    """Token splits of a float32 layer's sketch (of `channels` columns) that shares a launch with the product of n tokens by
+    `other` columns; 0: they do not share one."""
+    splits = f32_sketch_splits(n, channels, r, f32_factor)
+    return splits if splits and lib().f32_shared_launch(channels, r, n, other, splits) else 0
 
 
 def factor_tile(m, n, k, bf16_c=True, added=False):

@@ -1,7 +1,8 @@
 """The launch that a small float32 layer's exact product shares with its sketch, at the edges of its 32 x 32 tiles: remainders in
-every dimension, one and several token splits, both weight orientations, padded rows, a bfloat16 factor; and one layer beyond it.
+every dimension, one and several token splits (their partial products lie behind S and are folded), both weight orientations,
+padded rows, a bfloat16 factor; and layers beyond it.
 
-Bound: running sums of at most 512 products in fp32, 4 2^-24 sqrt(512); a bfloat16 factor rounds once, 2^-8."""
+Bound: fp32 sums of 256 products, and of at most four of those, 4 2^-24 sqrt(512); a bfloat16 factor rounds once, 2^-8."""
 import pytest
 
 import plan_util as plan
@@ -18,20 +19,19 @@ def acc():
     return binding
 
 
+# fwd, bwd: token splits of the sketch that shares a launch with the pass's exact product, 0 where it shares none
 @pytest.mark.parametrize("w_oi", [False, True])
-@pytest.mark.parametrize("n,d_in,d_out,r,pad,bf16_factor,paired", [
-    (256, 256, 512, 16, 0, False, True), (33, 40, 24, 8, 0, False, True), (257, 136, 72, 40, 8, False, True),
-    (700, 64, 96, 32, 0, False, True), (1030, 200, 104, 24, 16, True, True), (1, 8, 8, 8, 0, False, True),
-    (2048, 1024, 1032, 64, 0, False, False),
+@pytest.mark.parametrize("n,d_in,d_out,r,pad,bf16_factor,fwd,bwd", [
+    (256, 256, 512, 16, 0, False, 1, 1), (33, 40, 264, 8, 0, False, 1, 1), (257, 136, 136, 40, 8, False, 1, 1), (1, 8, 8, 8, 0, False, 1, 1),
+    (257, 520, 136, 24, 16, True, 1, 0), (513, 136, 264, 24, 8, True, 0, 1),   # a bfloat16 factor is folded from one split too
+    (1500, 512, 512, 16, 0, False, 3, 3), (900, 776, 712, 40, 8, False, 2, 2), (900, 776, 712, 40, 0, True, 2, 2),
+    (1030, 520, 488, 24, 16, True, 3, 2), (2624, 384, 264, 64, 0, False, 4, 0), (2624, 264, 384, 64, 8, True, 0, 4),
+    (33, 40, 24, 8, 0, False, 1, 0), (700, 64, 96, 32, 0, False, 0, 0), (2048, 1024, 1032, 64, 0, False, 0, 0),
 ])
-def test_layer(acc, n, d_in, d_out, r, pad, bf16_factor, paired, w_oi):
+def test_layer(acc, n, d_in, d_out, r, pad, bf16_factor, fwd, bwd, w_oi):
     import torch
     dev = "cuda:0"
-    if not bf16_factor:
-        for channels, other in ((d_in, d_out), (d_out, d_in)):
-            splits = plan.f32_sketch_splits(n, channels, r)
-            both = splits > 0 and plan.f32_tile(channels, r, splits) == plan.f32_tile(n, other) == "32x32"
-            assert both == paired or not splits, (splits, plan.f32_tile(n, other))
+    assert (plan.f32_pair(n, d_in, d_out, r, not bf16_factor), plan.f32_pair(n, d_out, d_in, r, not bf16_factor)) == (fwd, bwd)
     g = torch.Generator(device=dev).manual_seed(n + r)
     rand = lambda rows, cols, ld: torch.randn(rows, ld, generator=g, device=dev)[:, :cols]   # padded rows hold other values
     X, dY = rand(n, d_in, d_in + pad), rand(n, d_out, d_out + pad)
