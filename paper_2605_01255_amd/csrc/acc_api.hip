@@ -140,8 +140,6 @@ SketchParams make_sketch_params(const acc_linear_desc* d) {
   return sk;
 }
 
-constexpr int64_t kMaxOperandBytes = 0xFFFFFFFFll;  // buffer resources address 4 GiB
-
 // ---- float32 path ---------------------------------------------------------------------------
 // An operand of the float32 kernel: X[rows, K] with K contiguous (kmajor), or Xt[K, rows] with the rows contiguous.
 struct F32Operand {
@@ -529,61 +527,8 @@ int fast_gemm_splitk(const void* A, const void* B, float* part, int64_t M, int64
   return (int)splits;
 }
 
-// Plan of the tuned sketch kernel for `channels` columns of a [n, ld] matrix.
-struct SketchPlan {
-  bool fast;
-  int ch, rc;            // tile: channels x sketch columns
-  int n_cslab, n_js, G;  // channel slabs, column slices, token splits
-  int tokens_per_split;
-  int room;              // partial tiles that the workspace holds, at least G
-};
-
 SketchPlan plan_sketch(const acc_linear_desc* d, int64_t n, int64_t channels, int64_t ld) {
-  SketchPlan sp{};
-  sp.fast = d->io_dtype == ACC_BF16 && n * ld * 2 <= kMaxOperandBytes &&
-            channels * d->r * 4 <= kMaxOperandBytes / 2;
-  if (!sp.fast) {
-    sp.G = sp.room = generic_sketch_splits(n, channels, d->r);
-    return sp;
-  }
-  auto operand_fits = [&](int64_t tokens) { return tokens * ld * 2 + 64 * ld * 2 <= kMaxOperandBytes; };
-  // 8-wave tiles of 512 channels as a rule, one work-group per compute unit.  64 sketch columns (64 accumulators per
-  // lane) by default: half the partial bytes of the 128-column tile for the same generator and matrix work.
-  // The 128-column tile stays where eight or more column slices would re-read a long token range from L2
-  // (measured: r = 512 at 65536 tokens), and in the one-launch kernel, which interleaves it with GEMM tiles;
-  // the choice must be the same in every call that sees this descriptor (workspace size, forward, backward).
-  sp.ch = 512;
-  const bool wide = d->r % 128 == 0 && ((d->flags & ACC_FLAG_ONE_LAUNCH) || (d->r > 256 && n > 32768));
-  sp.rc = wide ? 128 : 64;
-  sp.n_cslab = (int)ceil_div(channels, sp.ch);
-  sp.n_js = (int)ceil_div(d->r, sp.rc);  // the last column slice may be partly empty (rank % 64 != 0)
-  int64_t G = 256 / (sp.n_cslab * sp.n_js);  // never more work-groups than compute units
-  const int64_t max_by_tokens = ceil_div(n, 256);
-  if (G > max_by_tokens) G = max_by_tokens;
-  if (G > 64) G = 64;
-  if (G < 1) G = 1;
-  auto split_tokens = [&](int64_t splits) {
-    sp.tokens_per_split = (int)round_up(ceil_div(n, splits), 32);
-    sp.G = (int)ceil_div(n, sp.tokens_per_split);
-  };
-  split_tokens(G);
-  sp.room = sp.G;
-  const SketchSplit c = pick_sketch_split(n, channels, d->r, G);
-  if (!wide && d->factor_dtype == ACC_BF16 && operand_fits(round_up(ceil_div(n, c.splits), 32))) {
-    sp.ch = c.ch;
-    split_tokens(c.splits);
-  } else {
-    // A float factor shows the rounding of its running sums, so they stay as long as they are with slabs of 512: only the slabs
-    // are narrowed, as far as that makes one work-group per compute unit at most (two of them on one get in each other's way:
-    // 4096 x 1024 at rank 256, 128 / 256 / 512 work-groups of 512 / 256 / 128 channels 12.2 / 10.6 / 11.5 us).
-    while (!wide && sp.ch > 128 && ceil_div(channels, sp.ch / 2) * sp.n_js * sp.G <= 256) sp.ch /= 2;
-  }
-  sp.n_cslab = (int)ceil_div(channels, sp.ch);
-  if (!operand_fits(sp.tokens_per_split)) {
-    sp.fast = false;
-    sp.G = sp.room = generic_sketch_splits(n, channels, d->r);
-  }
-  return sp;
+  return acc::plan_sketch(n, channels, d->r, ld, d->io_dtype == ACC_BF16, d->factor_dtype == ACC_BF16, (d->flags & ACC_FLAG_ONE_LAUNCH) != 0);
 }
 
 void reduce_partials(const acc_linear_desc* d, const float* ws, int G, int64_t count, void* out, int64_t row,
@@ -609,14 +554,19 @@ void fast_sketch(const acc_linear_desc* d, const SketchPlan& sp, const void* A, 
     if (transposed) L.launch_lds(sketch8_kernel<true, 4>, grid, dim3(512), (size_t)sketch8_lds_bytes<4>(), p);
     else L.launch_lds(sketch8_kernel<false, 4>, grid, dim3(512), (size_t)sketch8_lds_bytes<4>(), p);
   } else {
-    auto go = [&](auto width) {
+    auto go = [&](auto width, auto two) {
       constexpr int CH = decltype(width)::value;
-      if (transposed) L.launch_lds(sketch8_kernel<true, 2, CH>, grid, dim3(512), (size_t)sketch8_lds_bytes<2, CH>(), p);
-      else L.launch_lds(sketch8_kernel<false, 2, CH>, grid, dim3(512), (size_t)sketch8_lds_bytes<2, CH>(), p);
+      constexpr bool TWO = decltype(two)::value;
+      if (transposed) L.launch_lds(sketch8_kernel<true, 2, CH, TWO>, grid, dim3(512), (size_t)sketch8_lds_bytes<2, CH>(), p);
+      else L.launch_lds(sketch8_kernel<false, 2, CH, TWO>, grid, dim3(512), (size_t)sketch8_lds_bytes<2, CH>(), p);
     };
-    if (sp.ch == 128) go(std::integral_constant<int, 128>{});
-    else if (sp.ch == 256) go(std::integral_constant<int, 256>{});
-    else go(std::integral_constant<int, 512>{});
+    auto slab = [&](auto two) {
+      if (sp.ch == 128) go(std::integral_constant<int, 128>{}, two);
+      else if (sp.ch == 256) go(std::integral_constant<int, 256>{}, two);
+      else go(std::integral_constant<int, 512>{}, two);
+    };
+    if (sp.two_sums) slab(std::true_type{});
+    else slab(std::false_type{});
   }
   if (defer) *defer = ReduceJob{ws, out, channels * d->r, sp.G, d->factor_dtype == ACC_BF16 ? 1 : 0, out_row, out_ld};
   else reduce_partials(d, ws, sp.G, channels * d->r, out, out_row, out_ld, L);

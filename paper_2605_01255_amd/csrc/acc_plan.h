@@ -97,35 +97,120 @@ static inline FactorTile pick_factor_tile(int64_t M, int64_t N, int64_t K, bool 
 }
 constexpr int64_t kFactorMaxK = 256;   // above, pick_gemm_tile's estimates hold
 
-// Slabs and token splits of the bfloat16 sketch with bfloat16 factors (64 sketch columns, one work-group per compute unit at
-// most): the least of  start + iterations of 32 tokens x one + partial tiles written and read back,  in nanoseconds.  Narrow
-// slabs generate S more often, but their iterations are shorter, and half as many splits of twice the tokens write half as many
-// partials, which is what a sketch of a few thousand tokens spends a third of its time on.  `most`: the splits that 512
-// channels make; never more, the workspace holds those.  Two thirds of what fills the chip is the other choice.
-// Fitted to 95 forward passes with 1024 outputs (300 to 32768 tokens, 1024 to 8192 channels, rank 64 to 256): 0.4 % behind the
-// best of twelve forms on average, 2.6 % faster than slabs narrowed at the splits of 512 channels, at worst 2.4 % slower.
-// us of the pass, before / now: 4096 x 4096 at rank 128 54.8 / 49.1, 2048 x 4096 at 256 44.0 / 39.9, 600 x 8192 at 256 52.0 / 47.6,
-// 16384 x 4096 at 64 136 / 120, 4096 x 1024 at 256 24.9 / 23.8, 4096 x 3072 at 256 45.1 / 46.2; 16384 x 3072 at 256 stays (115.3).
+// Token splits of the sketch contraction: enough work-groups to fill 256 CUs, at most 32 partials.
+static inline int generic_sketch_splits(int64_t n, int64_t c, int64_t r) {
+  const int64_t tiles = ceil_div(c, 64) * ceil_div(r, 64);
+  int64_t g = ceil_div(1024, tiles);
+  const int64_t max_by_k = ceil_div(n, 256);
+  if (g > max_by_k) g = max_by_k;
+  if (g > 32) g = 32;
+  if (g < 1) g = 1;
+  return (int)g;
+}
+
+constexpr int64_t kMaxOperandBytes = 0xFFFFFFFFll;  // buffer resources address 4 GiB
+
+// Slabs and token splits of the bfloat16 sketch with 64 sketch columns, one work-group per compute unit at most.  `most`: the splits
+// that slabs of 512 channels make; never more, the workspace holds those.
 struct SketchSplit {
-  int ch;
+  int ch;          // channels of a slab
   int64_t splits;
+  bool two_sums;   // fewer splits than `most`: even and odd stages are summed apart, so that no running sum gets longer
 };
+
+// The splits of 512 channels, on slabs narrowed as far as that makes one work-group per compute unit at most (two of them on one
+// get in each other's way: 4096 x 1024 at rank 256, 128 / 256 / 512 work-groups of 512 / 256 / 128 channels 12.2 / 10.6 / 11.5 us).
+static inline SketchSplit narrow_sketch_slabs(int64_t n, int64_t channels, int64_t r, int64_t most) {
+  const int64_t made = ceil_div(n, round_up(ceil_div(n, most), 32)), columns = ceil_div(r, 64);
+  int ch = 512;
+  while (ch > 128 && ceil_div(channels, ch / 2) * columns * made <= 256) ch /= 2;
+  return SketchSplit{ch, most, false};
+}
+
+// Or fewer splits on narrower slabs, where that is the less by an estimate,  start + iterations of 32 tokens x one + partial tiles
+// written and read back,  in nanoseconds: narrow slabs generate S more often, but half as many splits of twice the tokens write
+// half as many partials, which is what a sketch of a few thousand tokens spends a third of its time on.  Three quarters of the
+// splits at most (8 splits for 10 lose, 2500 x 2048 at rank 256 37.1 us against 34.4) and 0.3 us ahead; at most twice the stages, so
+// that neither of the two sums has more of them than a split had.
+// Fitted to 80 forward passes with 1024 outputs (300 to 32768 tokens, 640 to 14336 channels, rank 16 to 512): 2.0 % ahead of the
+// splits of 512 channels on average, 1.6 % behind at worst (4096 x 3072 at 256, 48.8 / 49.6), 1.3 % behind the best of twelve forms.  us, the
+// splits of 512 channels / chosen: 4096 x 4096 at rank 128 56.1 / 52.3, 2048 x 4096 at 256 46.8 / 41.8, 600 x 8192 at 256 53.0 / 49.6, 1500 x 5120 at 256 52.1 / 46.0,
+// 16384 x 4096 at 64 129.3 / 122.4, 4096 x 1024 at 256 27.1 / 26.0; 4096 x 3584, 6000 x 3072 and 16384 x 3072 at 256 stay.
 static inline SketchSplit pick_sketch_split(int64_t n, int64_t channels, int64_t r, int64_t most) {
   struct Cost { int ch, start, per_iteration; };
-  static const Cost costs[] = {{512, 1600, 495}, {256, 1000, 395}, {128, 0, 340}};
-  SketchSplit best{512, most};
+  static const Cost costs[] = {{512, 1800, 418}, {256, 800, 339}, {128, 0, 268}};
+  const int64_t stages = ceil_div(ceil_div(n, most), 32), made = ceil_div(n, stages * 32);
+  auto estimate = [&](const Cost& c, int64_t iterations, int64_t splits) {
+    return c.start + iterations * c.per_iteration + splits * channels * r * 4 / 1000 * 259 / 1000;
+  };
+  SketchSplit best = narrow_sketch_slabs(n, channels, r, most);
   int64_t best_ns = INT64_MAX;
+  for (const Cost& c : costs)
+    if (c.ch == best.ch) best_ns = estimate(c, stages, made) - 300;
   for (const Cost& c : costs) {
     int64_t full = 256 / (ceil_div(channels, c.ch) * ceil_div(r, 64));
     if (full > most) full = most;
-    for (int64_t splits : {full, full * 2 / 3}) {
+    for (int64_t splits : {full, full / 2}) {
       if (splits < 1) continue;
-      const int64_t iterations = ceil_div(ceil_div(n, splits), 32), made = ceil_div(n, iterations * 32);
-      const int64_t ns = c.start + iterations * c.per_iteration + made * channels * r * 4 / 1000 * 324 / 1000;
-      if (ns < best_ns) { best_ns = ns; best = SketchSplit{c.ch, splits}; }
+      const int64_t iterations = ceil_div(ceil_div(n, splits), 32), fewer = ceil_div(n, iterations * 32);
+      if (iterations > 2 * stages || 4 * fewer > 3 * made) continue;
+      const int64_t ns = estimate(c, iterations, fewer);
+      if (ns < best_ns) { best_ns = ns; best = SketchSplit{c.ch, splits, true}; }
     }
   }
   return best;
+}
+
+// Plan of the sketch of `channels` columns of an [n, ld] matrix.
+struct SketchPlan {
+  bool fast;             // the tuned kernel
+  int ch, rc;            // its tile: channels x sketch columns
+  int n_cslab, n_js, G;  // channel slabs, column slices, token splits
+  int tokens_per_split;
+  bool two_sums;
+  int room;              // partial tiles that the workspace holds, at least G
+};
+static inline SketchPlan plan_sketch(int64_t n, int64_t channels, int64_t r, int64_t ld, bool bf16_io, bool bf16_factor, bool one_launch) {
+  SketchPlan sp{};
+  sp.fast = bf16_io && n * ld * 2 <= kMaxOperandBytes && channels * r * 4 <= kMaxOperandBytes / 2;
+  if (!sp.fast) {
+    sp.G = sp.room = generic_sketch_splits(n, channels, r);
+    return sp;
+  }
+  auto operand_fits = [&](int64_t tokens) { return tokens * ld * 2 + 64 * ld * 2 <= kMaxOperandBytes; };
+  // 8-wave tiles of 512 channels as a rule, one work-group per compute unit.  64 sketch columns (64 accumulators per
+  // lane) by default: half the partial bytes of the 128-column tile for the same generator and matrix work.
+  // The 128-column tile stays where eight or more column slices would re-read a long token range from L2
+  // (measured: r = 512 at 65536 tokens), and in the one-launch kernel, which interleaves it with GEMM tiles;
+  // the choice must be the same in every call that sees this descriptor (workspace size, forward, backward).
+  sp.ch = 512;
+  const bool wide = r % 128 == 0 && (one_launch || (r > 256 && n > 32768));
+  sp.rc = wide ? 128 : 64;
+  sp.n_cslab = (int)ceil_div(channels, sp.ch);
+  sp.n_js = (int)ceil_div(r, sp.rc);  // the last column slice may be partly empty (rank % 64 != 0)
+  int64_t G = 256 / ((int64_t)sp.n_cslab * sp.n_js);  // never more work-groups than compute units
+  const int64_t max_by_tokens = ceil_div(n, 256);
+  if (G > max_by_tokens) G = max_by_tokens;
+  if (G > 64) G = 64;
+  if (G < 1) G = 1;
+  auto tokens = [&](int64_t splits) { return round_up(ceil_div(n, splits), 32); };
+  sp.room = (int)ceil_div(n, tokens(G));
+  if (!wide) {
+    // a float factor shows the order of its sums and keeps that of the splits of 512 channels
+    SketchSplit c = bf16_factor ? pick_sketch_split(n, channels, r, G) : narrow_sketch_slabs(n, channels, r, G);
+    if (c.two_sums && !operand_fits(tokens(c.splits))) c = narrow_sketch_slabs(n, channels, r, G);
+    sp.ch = c.ch;
+    sp.two_sums = c.two_sums;
+    G = c.splits;
+  }
+  sp.tokens_per_split = (int)tokens(G);
+  sp.G = (int)ceil_div(n, sp.tokens_per_split);
+  sp.n_cslab = (int)ceil_div(channels, sp.ch);
+  if (!operand_fits(sp.tokens_per_split)) {
+    sp.fast = false;
+    sp.G = sp.room = generic_sketch_splits(n, channels, r);
+  }
+  return sp;
 }
 
 // Which tile a float32 product takes: the least time of a K tile of 32, fixed + tiles per compute unit x per_tile
@@ -177,17 +262,6 @@ static inline F32Choice pick_f32_tile(int64_t M, int64_t N, int64_t splits, bool
 //   both deep:                     256 x 512, 256  11.8 / 7.5 / 7.4       1544 x 512, 512 26.5 / 25.7 / 21.6   3072 x 768, 300 38.6 / 43.0 / 34.5
 static inline bool f32_pair(int64_t M, int64_t N, int64_t splits, int64_t n, int64_t out_n) {
   return pick_f32_tile(M, N, splits, true).tile == F32TileShape::k32 && pick_f32_tile(n, out_n, 1, true).tile == F32TileShape::k32;
-}
-
-// Token splits of the sketch contraction: enough work-groups to fill 256 CUs, at most 32 partials.
-static inline int generic_sketch_splits(int64_t n, int64_t c, int64_t r) {
-  const int64_t tiles = ceil_div(c, 64) * ceil_div(r, 64);
-  int64_t g = ceil_div(1024, tiles);
-  const int64_t max_by_k = ceil_div(n, 256);
-  if (g > max_by_k) g = max_by_k;
-  if (g > 32) g = 32;
-  if (g < 1) g = 1;
-  return (int)g;
 }
 
 // How the sketch of a float32 layer is formed.  Stored: S is written once, into the part of the workspace that the partial

@@ -75,10 +75,13 @@ template <int WJ, int CH> constexpr int sketch8_stages() { return WJ == 4 ? 7 : 
 // once per wave.  The narrow tile keeps half as many accumulators per compute unit: a work-group covers
 // twice the tokens and the launch writes (and the fold reads) half as many bytes of partial tiles.
 // Narrower slabs of the 64-column tile (CH = 256 or 128: four or two MFMAs) for launches that 512 channels leave short of
-// work-groups, or that are better off with fewer token splits and their partial tiles (pick_sketch_split): each generates S for itself, on compute units that would be idle, and has a half or a quarter of the transfers,
-// matrix work and partial tile to wait for.  2049 x 1032 at rank 128: 54
-// work-groups of 512 channels 10.4 us, 162 of 128 7.0; 384 x 3072 at rank 64: 12 and 48, 8.4 and 5.6.
-template <bool TRANSPOSED, int WJ = 4, int CH = 512>
+// work-groups, or that are better off with fewer token splits and their partial tiles (plan_sketch): each generates S for
+// itself, on compute units that would be idle, and has a half or a quarter of the transfers, matrix work and partial tile to wait
+// for.  2049 x 1032 at rank 128: 54 work-groups of 512 channels 10.4 us, 162 of 128 7.0; 384 x 3072 at rank 64: 12 and 48, 8.4
+// and 5.6.
+// TWO_SUMS: even and odd stages have running sums of their own, added up at the end, so that half as many splits of twice the
+// tokens have running sums of the same length.
+template <bool TRANSPOSED, int WJ = 4, int CH = 512, bool TWO_SUMS = false>
 __device__ __forceinline__ void sketch8_tile(const SketchFastParams& p, int b, char* smem) {
   static_assert(WJ == 4 || WJ == 2, "column groups");
   static_assert(CH == 512 || (WJ == 2 && (CH == 256 || CH == 128)), "channel slabs");
@@ -196,18 +199,20 @@ __device__ __forceinline__ void sketch8_tile(const SketchFastParams& p, int b, c
     return o;
   };
 
-  f32x16 acc[CWB];
+  f32x16 sums[TWO_SUMS ? 2 : 1][CWB];   // of even and odd stages
 #pragma unroll
-  for (int i = 0; i < CWB; ++i)
+  for (auto& part : sums)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
+    for (int i = 0; i < CWB; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) part[i][e] = 0.f;
 
   // One iteration = stage t.  Start the transfer of stage t + DEPTH into the slot stage t - 1 used,
   // make sure stage t + 1 (and the S shares of iteration t + 1) are there for every wave, then in 8 slots:
   // MFMA on the operands in registers, the reads of the operands of iteration t + 1, and a slice of this
   // wave's share of S for iteration t + 2.  Branch-free: past the end the last stage is fetched again.
   HalfGen hg;
-  auto iteration = [&](int t, const bf16x8(&af)[SLOTS], const SOps& sf, bf16x8(&nf)[SLOTS], SOps& s_next) {
+  auto iteration = [&](int t, f32x16(&acc)[CWB], const bf16x8(&af)[SLOTS], const SOps& sf, bf16x8(&nf)[SLOTS], SOps& s_next) {
     const int t_load = t + DEPTH < NS ? t + DEPTH : NS - 1;
     __builtin_amdgcn_sched_barrier(0);
     issue_stage(t_load, smem_lds + ((t + DEPTH) % NSTAGE) * STAGE);
@@ -244,21 +249,25 @@ __device__ __forceinline__ void sketch8_tile(const SketchFastParams& p, int b, c
   SOps s_a = read_s(0), s_b = s_a;
   int t = 0;
   for (; t + 1 < NS; t += 2) {
-    iteration(t, fa, s_a, fb, s_b);
-    iteration(t + 1, fb, s_b, fa, s_a);
+    iteration(t, sums[0], fa, s_a, fb, s_b);
+    iteration(t + 1, sums[TWO_SUMS], fb, s_b, fa, s_a);
   }
-  if (t < NS) iteration(t, fa, s_a, fb, s_b);
+  if (t < NS) iteration(t, sums[0], fa, s_a, fb, s_b);
   wait_vmcnt0();  // no transfer may still be in flight when the work-group's LDS is released
 
-  store_partial_tile<TRANSPOSED, CWB>(acc, p.part + (int64_t)g * p.C * p.r, p.C, p.r, c0 + wc * CWB * 32,
+  if constexpr (TWO_SUMS) {
+#pragma unroll
+    for (int i = 0; i < CWB; ++i) sums[0][i] += sums[1][i];
+  }
+  store_partial_tile<TRANSPOSED, CWB>(sums[0], p.part + (int64_t)g * p.C * p.r, p.C, p.r, c0 + wc * CWB * 32,
                                       js * RC + wj * 32, lane);
 }
 
 // The 8-wave sketch tile as a kernel of its own: grid = 8 * n_js * ceil(n_cslab * G / 8) work-groups.
-template <bool TRANSPOSED, int WJ = 4, int CH = 512>
+template <bool TRANSPOSED, int WJ = 4, int CH = 512, bool TWO_SUMS = false>
 __global__ __launch_bounds__(512) void sketch8_kernel(SketchFastParams sp) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  sketch8_tile<TRANSPOSED, WJ, CH>(sp, blockIdx.x, smem);
+  sketch8_tile<TRANSPOSED, WJ, CH, TWO_SUMS>(sp, blockIdx.x, smem);
 }
 
 // Dynamic LDS of sketch8_kernel: the stage ring plus the S exchange (two slots of 4 KB; 128 KB with the 128-column tile, as the

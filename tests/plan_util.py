@@ -1,4 +1,5 @@
 """The library's host-side choices by size (csrc/acc_plan.h), compiled with the host compiler: which kernel a call takes."""
+import collections
 import ctypes
 import functools
 import os
@@ -15,8 +16,11 @@ int gemm_tile(int64_t M, int64_t N, int64_t K, int persist_ok) { return (int)pic
 int gemm_one_round(int64_t M, int64_t N, int64_t K, int persist_ok) { return pick_gemm_tile(M, N, K, persist_ok != 0).one_round; }
 int f32_tile(int64_t M, int64_t N, int64_t splits, int all_tiles) { return (int)pick_f32_tile(M, N, splits, all_tiles != 0).tile; }
 int factor_tile(int64_t M, int64_t N, int64_t K, int form) { return (int)pick_factor_tile(M, N, K, (form & 1) != 0, (form & 2) != 0); }
-int sketch_channels(int64_t n, int64_t channels, int64_t r, int most) { return pick_sketch_split(n, channels, r, most).ch; }
-int sketch_splits(int64_t n, int64_t channels, int64_t r, int most) { return (int)pick_sketch_split(n, channels, r, most).splits; }
+void sketch(int64_t n, int64_t channels, int64_t r, int64_t ld, int bf16_factor, int* out) {
+  const SketchPlan p = plan_sketch(n, channels, r, ld, true, bf16_factor != 0, false);
+  const int v[] = {p.fast, p.ch, p.rc, p.n_cslab * p.n_js, p.G, p.tokens_per_split, p.two_sums, p.room};
+  for (int i = 0; i < 8; ++i) out[i] = v[i];
+}
 int raised_capacity() { return RaisedLimits::kKernels; }
 int raised_lost(int kernels, int devices) {  // entries the table has forgotten after all were added
   static RaisedLimits table;
@@ -52,9 +56,9 @@ def lib():
             f.write(_SOURCE)
         subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-O1", "-shared", "-fPIC", "-I" + ROOT, src, "-o", out], check=True)
         so = ctypes.CDLL(out)
-    for name in ("gemm_tile", "gemm_one_round", "f32_tile", "f32_sketch_splits", "f32_sketch_fits", "factor_tile",
-                 "sketch_channels", "sketch_splits"):
+    for name in ("gemm_tile", "gemm_one_round", "f32_tile", "f32_sketch_splits", "f32_sketch_fits", "factor_tile"):
         getattr(so, name).argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int]
+    so.sketch.argtypes = [ctypes.c_int64] * 4 + [ctypes.c_int, ctypes.c_void_p]
     so.f32_shared_launch.argtypes = [ctypes.c_int64] * 4 + [ctypes.c_int]
     return so
 
@@ -93,6 +97,12 @@ def factor_tile(m, n, k, bf16_c=True, added=False):
     return names[lib().factor_tile(m, n, k, int(bf16_c) + 2 * int(added))]
 
 
-def sketch_split(n, channels, r, most):
-    """(channels of a slab, token splits) of the bfloat16 sketch with bfloat16 factors; `most` splits with 512 channels."""
-    return lib().sketch_channels(n, channels, r, most), lib().sketch_splits(n, channels, r, most)
+Sketch = collections.namedtuple("Sketch", "tuned slab columns tiles splits tokens two_sums room")
+
+
+def sketch(n, channels, r, bf16_factor=True, ld=0):
+    """Plan of the bfloat16 sketch: channels of a slab and sketch columns of a tile, tiles, token splits, tokens of a split, whether it
+    has two running sums, partial tiles that the workspace holds."""
+    out = (ctypes.c_int * 8)()
+    lib().sketch(n, channels, r, ld or channels, int(bf16_factor), out)
+    return Sketch(bool(out[0]), *out[1:6], bool(out[6]), out[7])

@@ -1,9 +1,11 @@
 """The bfloat16 sketch on slabs of 128, 256 and 512 channels: ragged last slab, ragged last token stage, surplus sketch columns, padded
 rows, both orientations, against a product in 64 bits with the device's own S.
 
-Bound: S and the input are exact in bfloat16 and the factor is float, so only the fp32 sums round: at most 512 tokens in a split's
-running sum and the splits' sum, 4 2^-24 sqrt(512) of the root mean square; 12 times that for the largest of many entries."""
+Bound: S and the input are exact in bfloat16 and the factor is float, so only the fp32 sums round: the tokens of a split's
+running sum and the splits' sum, 4 2^-24 sqrt(tokens + splits) of the root mean square; 12 times that for the largest of many entries."""
 import pytest
+
+import plan_util as plan
 
 pytestmark = pytest.mark.gpu
 
@@ -17,13 +19,15 @@ def acc():
     return binding
 
 
-@pytest.mark.parametrize("n,channels,r,pad", [
-    (300, 136, 8, 0), (257, 128, 64, 0), (31, 264, 24, 8), (2049, 1032, 128, 0), (1030, 2040, 72, 24),   # 128 channels
-    (4096, 1024, 256, 0), (1001, 3976, 200, 16), (2500, 2056, 152, 0),                                   # 256
-    (2048, 2040, 512, 0), (8190, 3080, 200, 8),                                                          # 512
+@pytest.mark.parametrize("n,channels,r,pad,slab", [
+    (300, 136, 8, 0, 128), (257, 128, 64, 0, 128), (31, 264, 24, 8, 128), (2049, 1032, 128, 0, 128), (1030, 2040, 72, 24, 128),
+    (4096, 1024, 256, 0, 256), (1001, 3976, 200, 16, 256), (2500, 1544, 152, 0, 256),
+    (2500, 2056, 152, 0, 512), (2048, 2040, 512, 0, 512), (8190, 3080, 200, 8, 512),
 ])
-def test_sketch(acc, n, channels, r, pad):
+def test_sketch(acc, n, channels, r, pad, slab):
     import torch
+    p = plan.sketch(n, channels, r, bf16_factor=False, ld=channels + pad)
+    assert p.slab == slab and not p.two_sums
     dev = "cuda:0"
     g = torch.Generator(device=dev).manual_seed(n + r)
     ld = channels + pad
@@ -45,7 +49,7 @@ def test_sketch(acc, n, channels, r, pad):
         got.append(Gr if w_oi else Gr.T)
     want = X.double().T @ S.double()
     rms = want.square().mean().sqrt()
-    tol = 4 * 2.0 ** -24 * 512 ** 0.5
+    tol = 4 * 2.0 ** -24 * (p.tokens + p.splits) ** 0.5
     for v in got:
         err, worst = float((v.double() - want).square().mean().sqrt() / rms), float((v.double() - want).abs().max() / rms)
         assert err <= tol and worst <= 12 * tol, (err, worst)

@@ -70,14 +70,34 @@ def test_raised_lds_limits_are_remembered_for_every_kernel_and_device():
     assert plan.lib().raised_lost(plan.lib().raised_capacity(), 64) == 0
 
 
+# us of a forward pass with 1024 outputs: the token splits of 512 channels, and the splits and slabs chosen
+@pytest.mark.parametrize("n,channels,r,slab,two_sums,before,now", [
+    (4096, 4096, 128, 256, True, 56.1, 52.3), (2048, 4096, 256, 256, True, 46.8, 41.8), (600, 8192, 256, 256, True, 53.0, 49.6),
+    (1500, 5120, 256, 256, True, 52.1, 46.0), (16384, 4096, 64, 256, True, 129.3, 122.4), (4096, 1024, 256, 128, True, 27.1, 26.0),
+    (4096, 3072, 256, 256, True, 48.8, 49.6), (2500, 2048, 256, 512, False, 34.4, 34.4), (6000, 3072, 256, 512, False, 60.8, 60.8),
+    (4096, 3584, 256, 512, False, 53.4, 53.4), (2049, 3072, 512, 512, False, 55.9, 55.9),
+])
+def test_sketch_splits_are_near_the_best(n, channels, r, slab, two_sums, before, now):
+    p = plan.sketch(n, channels, r)
+    assert (p.slab, p.two_sums) == (slab, two_sums)
+    assert now <= 1.02 * before
+
+
 def test_sketch_splits_fit_the_workspace_and_the_chip():
-    """Never more splits than the workspace holds, never more work-groups than compute units where 512 channels made no more."""
-    for n in (1, 31, 257, 300, 1030, 4096, 4097, 16384, 65536):
-        for channels in (8, 128, 136, 520, 1024, 3080, 8192, 14336, 40000):
+    """Never more splits than the workspace holds, never more work-groups than compute units where 512 channels made no more; no
+    running sum longer than one of the splits that 512 channels make, and those splits themselves with a float factor."""
+    for n in (1, 31, 257, 300, 700, 1030, 2049, 4096, 4097, 16384, 65536):
+        for channels in (8, 128, 136, 520, 1024, 3072, 3080, 8192, 14336, 40000):
             for r in (8, 64, 72, 256, 512):
                 columns = -(-r // 64)
                 most = max(1, min(256 // (-(-channels // 512) * columns), -(-n // 256), 64))
-                ch, splits = plan.sketch_split(n, channels, r, most)
-                assert ch in (128, 256, 512) and 1 <= splits <= most
-                assert splits == 1 or -(-channels // ch) * columns * splits <= 256
-                assert ch == 512 or -(-channels // ch) * columns * splits <= 256
+                tokens = -(--(-n // most) // 32) * 32
+                for bf16_factor in (True, False):
+                    p = plan.sketch(n, channels, r, bf16_factor)
+                    if not p.tuned or p.columns == 128:
+                        continue
+                    assert p.slab in (128, 256, 512) and p.tokens % 32 == 0
+                    assert p.splits == -(-n // p.tokens) <= p.room == -(-n // tokens)
+                    assert p.tiles * p.splits <= max(256, -(-channels // 512) * columns)
+                    assert -(-p.tokens // 32 // (2 if p.two_sums else 1)) * 32 <= tokens
+                    assert bf16_factor or (p.tokens == tokens and not p.two_sums)
