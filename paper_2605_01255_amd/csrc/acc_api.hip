@@ -426,9 +426,9 @@ void persist_gemm(FastGemmParams& p, Launcher& L) {
   else L.launch_lds(gemm16_persist_kernel<KMAJ>, dim3(256), dim3(256), (size_t)160 * 1024, p, (int)slots);
 }
 
-// The product of up to kFactorMaxK elements, on the kernel of pick_factor_tile.
+// On the kernel of pick_factor_tile; false, with nothing done, where that is the exact products' choice.
 template <bool KMAJ, typename TC, bool SUM>
-void short_gemm(FastGemmParams& p, Launcher& L) {
+bool factor_gemm(FastGemmParams& p, Launcher& L) {
   constexpr bool BF16_C = sizeof(TC) == 2;
   switch (pick_factor_tile(p.M, p.N, p.K, BF16_C, SUM)) {
     case FactorTile::k64: ring_gemm<2, 2, SUM ? 2 : 3, KMAJ, TC, SUM>(p, L); break;
@@ -441,7 +441,9 @@ void short_gemm(FastGemmParams& p, Launcher& L) {
     case FactorTile::kPersist:
       if constexpr (BF16_C && !SUM) persist_gemm<KMAJ>(p, L);
       break;
+    case FactorTile::kAsExact: return false;
   }
+  return true;
 }
 
 // SUM: C = beta C + alpha (A . B), rounded once, on the ring kernel whatever the size: its work-groups, two to a compute unit,
@@ -452,7 +454,10 @@ void fast_gemm(const void* A, const void* B, void* C, int64_t M, int64_t N, int6
                float beta = 1.f) {
   FastGemmParams p = fast_params(A, B, C, M, N, K, lda, ldb, ldc, job, alpha, beta);
   const bool persist_ok = sizeof(TC) == 2 && !SUM && K > 128;  // three K tiles
-  if (!SUM && K <= 128 && ceil_div(M, 256) * ceil_div(N, 256) >= 192) return short_gemm<KMAJ, TC, SUM>(p, L);
+  if (!SUM && K <= 128 && ceil_div(M, 256) * ceil_div(N, 256) >= 192) {
+    factor_gemm<KMAJ, TC, SUM>(p, L);
+    return;
+  }
   const GemmChoice c = pick_gemm_tile(M, N, K, persist_ok);
   switch (c.tile) {
     case GemmTile::k256:
@@ -963,17 +968,11 @@ void exact_backward_gemm(const acc_linear_desc* desc, const Shape& s, const void
 void factor_product(const acc_linear_desc* desc, const Shape& s, const void* Xs, const void* Gr,
                     const FactorProductOut& o, Launcher& L) {
   const bool w_oi = (desc->flags & ACC_FLAG_W_OUT_IN) != 0;
-  // Up to 256: pick_factor_tile.  Above, the estimates of the exact products; but a bf16 C that is added to keeps the three-stage
-  // kernel where that makes one full round (3072 x 3072 at r = 512 19.0 us, 128 x 64 tiles 20.0; at 1024 27.0 and 29.8).
   auto tuned = [&](auto kmaj, auto type, auto sum, const void* A, const void* B, int64_t M, int64_t N, int64_t ldb) {
     constexpr bool KMAJ = decltype(kmaj)::value, SUM = decltype(sum)::value;
     using TC = decltype(type);
     FastGemmParams p = fast_params(A, B, o.C, M, N, s.r, s.ldf, ldb, o.ld, nullptr, o.alpha, o.beta);
-    if (s.r <= kFactorMaxK) return short_gemm<KMAJ, TC, SUM>(p, L);
-    if constexpr (SUM && sizeof(TC) == 2) {
-      if (s.r <= 1024 && ceil_div(M, 192) * ceil_div(N, 192) <= 256 && ceil_div(M, 128) * ceil_div(N, 64) > 768)
-        return smallk_gemm<KMAJ>(p, L);
-    }
+    if (factor_gemm<KMAJ, TC, SUM>(p, L)) return;
     fast_gemm<KMAJ, TC, SUM>(A, B, o.C, M, N, s.r, s.ldf, ldb, o.ld, L, nullptr, o.alpha, o.beta);
   };
   auto typed = [&](auto kmaj, auto... args) {

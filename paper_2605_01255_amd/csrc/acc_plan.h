@@ -53,29 +53,36 @@ static inline GemmChoice pick_gemm_tile(int64_t M, int64_t N, int64_t K, bool pe
   return best;
 }
 
-// Which kernel a product of up to 256 elements takes (the product of two gradient factors, whose contraction is their rank).
-// With four K tiles at most there is no pipeline to fill: a tile costs its latency, its write and, where it is added to C, its
-// read, and work-groups that share a compute unit cover each other's.  So the ring kernel with two stages and as many
-// work-groups as LDS holds (128 x 64 three, 64 x 64 five), larger tiles where the output gives every compute unit several; one
-// work-group per compute unit with everything requested at once, the three-stage kernel of 192 x 192 tiles, lost by 41 % on
-// average over 84 outputs of at most one round of it (512 x 512 at rank 256 8.6 us against 3.8, 1032 x 1544 at rank 128 7.1
-// against 4.4, 3072 x 1024 at rank 256 9.1 against 5.7, 3072 x 3072 at 256 11.3 against 10.9).
+// Which kernel the product of two gradient factors takes, whose contraction is their rank.  Up to 256 elements there are four K
+// tiles at most and no pipeline to fill: a tile costs its latency, its write and, where it is added to C, its read, and work-groups
+// that share a compute unit cover each other's.  So the ring kernel with two stages and as many work-groups as LDS holds (128 x 64
+// three, 64 x 64 added to C five; written 64 x 64 tiles have three stages, three work-groups), larger tiles where the output gives
+// every compute unit several; one work-group per compute unit with everything requested at once, the three-stage kernel of 192 x 192
+// tiles, lost by 41 % on average over 84 outputs of at most one round of it (512 x 512 at rank 256 8.6 us against 3.8, 1032 x 1544
+// at rank 128 7.1 against 4.4, 3072 x 1024 at rank 256 9.1 against 5.7, 3072 x 3072 at 256 11.3 against 10.9, behind the exact products
+// of a pass 11.4 to 14.2 against 10.8 to 13.4).
 //   written        the least of base + (tiles of the fullest compute unit) x (tile + K tiles x time of one), in nanoseconds,
 //                  and from three K tiles on the persistent kernel's: 1.3 % behind the best of nine candidates on average over
-//                  138 outputs (13 % at most), 3 % where C is float
+//                  138 outputs (13 % at most), 3 % where C is float.  A fourth 128 x 64 tile on a compute unit, which holds three, is
+//                  priced as the second batch it is; 64 x 64, of which it holds three too, needs no such term: its time a tile is
+//                  fitted to many batches (8192 x 8192 at rank 256, 64 to a compute unit: 77.9 us both estimated and measured)
 //   added to C     by size: the read of C counts more than the products.  The three-stage kernel requests C with its operands
 //                  and stays where its one round is nearly full (3072 x 3072 at rank 64: 10.6 us, 128 x 64 10.9) and at short ranks
 //                  of outputs beyond 1024 of its tiles (8192 x 8192 at rank 64: 67 us, 128 x 64 88).  2.2 % behind the best on
 //                  average (14 % at most), 1 % where C is float
-enum class FactorTile { k64, k128x64, k128, k192x128, kThreeStage, kPersist };
+// Above 256 the estimates of the exact products (pick_gemm_tile) hold; but a bfloat16 C that is added to keeps the three-stage kernel
+// where that makes one full round (3072 x 3072 at r = 512 19.0 us, 128 x 64 tiles 20.0; at 1024 27.0 and 29.8).
+enum class FactorTile { k64, k128x64, k128, k192x128, kThreeStage, kPersist, kAsExact };
+constexpr int64_t kFactorMaxK = 256;
 static inline FactorTile pick_factor_tile(int64_t M, int64_t N, int64_t K, bool bf16_c, bool sum) {
   auto tiles = [&](int64_t bm, int64_t bn) { return ceil_div(M, bm) * ceil_div(N, bn); };
+  const int64_t t192 = tiles(192, 192);
+  const bool full_round = bf16_c && sum && t192 <= 256 && tiles(128, 64) > 768;   // of the three-stage kernel
+  if (K > kFactorMaxK) return full_round && K <= 1024 ? FactorTile::kThreeStage : FactorTile::kAsExact;
   if (sum) {
     if (K > 192 && tiles(192, 128) >= 2048) return FactorTile::k192x128;
     if (!bf16_c || tiles(64, 64) <= 768) return FactorTile::k64;
-    const int64_t t192 = tiles(192, 192);
-    if ((t192 <= 256 && tiles(128, 64) > 768) || (t192 > 1024 && K <= 128)) return FactorTile::kThreeStage;
-    return FactorTile::k128x64;
+    return full_round || (t192 > 1024 && K <= 128) ? FactorTile::kThreeStage : FactorTile::k128x64;
   }
   struct Cost { FactorTile tile; int bm, bn, base, per_tile, per_k; };
   static const Cost costs[] = {{FactorTile::k64, 64, 64, 3000, 450, 180},
@@ -95,7 +102,6 @@ static inline FactorTile pick_factor_tile(int64_t M, int64_t N, int64_t K, bool 
   }
   return best;
 }
-constexpr int64_t kFactorMaxK = 256;   // above, pick_gemm_tile's estimates hold
 
 // Token splits of the sketch contraction: enough work-groups to fill 256 CUs, at most 32 partials.
 static inline int generic_sketch_splits(int64_t n, int64_t c, int64_t r) {

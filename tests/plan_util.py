@@ -92,9 +92,9 @@ def f32_pair(n, channels, other, r, f32_factor=True):
 
 
 def factor_tile(m, n, k, bf16_c=True, added=False):
-    """Kernel of a product of two gradient factors, k <= 256."""
-    names = ("64x64", "128x64", "128x128", "192x128", "three-stage", "persistent")
-    return names[lib().factor_tile(m, n, k, int(bf16_c) + 2 * int(added))]
+    """Kernel of a product of two gradient factors."""
+    names = ("64x64", "128x64", "128x128", "192x128", "three-stage", "persistent", "")
+    return names[lib().factor_tile(m, n, k, int(bf16_c) + 2 * int(added))] or gemm_tile(m, n, k, added or not bf16_c)[0]
 
 
 Sketch = collections.namedtuple("Sketch", "tuned slab columns tiles splits tokens two_sums room")

@@ -6,6 +6,8 @@ Bound per element: half a unit in the last place of the exact sum in bfloat16, p
 2^-24 (sqrt(r) + 3) of the largest that the terms' absolute values can add up to."""
 import pytest
 
+import plan_util as plan
+
 pytestmark = pytest.mark.gpu
 
 
@@ -26,16 +28,21 @@ def _rounded_once(got, want, size, r):
 
 
 @pytest.mark.parametrize("w_oi", [False, True])
-@pytest.mark.parametrize("d_in,d_out,r", [
-    (200, 392, 32),      # three-stage kernel, half a K tile
-    (1000, 1160, 64),    # three-stage kernel, several tiles
-    (520, 1032, 1096),   # rank above 1024: the ring kernel, 64 x 64 tiles
-    (3264, 3080, 40),    # more tiles than compute units, too few of 256 x 256: the ring kernel
-    (4104, 3080, 32),    # 256 x 256 tiles
-    (4104, 3080, 128),
+@pytest.mark.parametrize("d_in,d_out,r,tile", [
+    (200, 392, 32, "64x64"),             # half a K tile
+    (1000, 1160, 64, "64x64"),
+    (520, 1032, 1096, "64x64"),
+    (3264, 3080, 40, "128x64"),
+    (4104, 3080, 32, "128x64"),
+    (4104, 3080, 128, "128x64"),
+    (3064, 2968, 40, "three-stage"),     # one K tile, masked
+    (2968, 3064, 264, "three-stage"),    # five, the last one masked
+    (8200, 8200, 64, "three-stage"),     # more tiles than compute units
+    (8200, 6152, 200, "192x128"),
 ])
-def test_accumulated_gradient(acc, d_in, d_out, r, w_oi):
+def test_accumulated_gradient(acc, d_in, d_out, r, tile, w_oi):
     import torch
+    assert plan.factor_tile(*((d_out, d_in) if w_oi else (d_in, d_out)), r, added=True) == tile
     dev = "cuda:0"
     g = torch.Generator(device=dev).manual_seed(d_in + r)
     left = torch.randn(d_in, r, generator=g, device=dev).bfloat16()

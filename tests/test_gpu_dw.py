@@ -1,7 +1,6 @@
 """The dense weight gradient from the two factors alone (acc_linear_dw: Sec. 4, update strategy (i)) against the
-oracle's product, over the shapes that choose between its kernels: the three-stage small-K kernel (at most 256
-tiles of 192 x 192), the kernels of the exact products (more tiles), the float32 kernel (fp32 factors), the generic kernels
-(factors beyond 4 GiB); ragged edges in both dimensions, both orientations, both output types, plain and accumulating."""
+oracle's product, over shapes that choose between its kernels: the ring kernel's tiles and the three-stage kernel, the float32
+kernel (fp32 factors), the generic kernels (factors beyond 4 GiB); ragged edges in both dimensions, both orientations, both output types, plain and accumulating."""
 import numpy as np
 import pytest
 
@@ -30,11 +29,11 @@ def _factors(d_in, d_out, r, dtype, seed):
 
 CASES = [
     # d_in, d_out, r, factor dtype, dW dtype
-    (3072, 3072, 256, "bf16", "bf16"),     # the benchmark's gradient: 16 x 16 tiles, one round
+    (3072, 3072, 256, "bf16", "bf16"),     # the benchmark's gradient: 192 x 128 tiles, accumulating the three-stage kernel
     (200, 392, 64, "bf16", "bf16"),        # ragged in both dimensions, one K tile
     (1000, 1160, 128, "bf16", "f32"),      # ragged, fp32 output
-    (3000, 3080, 512, "bf16", "bf16"),     # eight K tiles: the ring of three stages wraps twice
-    (3072, 8192, 192, "bf16", "bf16"),     # 688 tiles: the persistent kernel, accumulating the ring kernel
+    (3000, 3080, 512, "bf16", "bf16"),     # eight K tiles: 192 x 128 tiles
+    (3072, 8192, 192, "bf16", "bf16"),     # 192 x 128 tiles, accumulating 128 x 64
     (520, 264, 40, "bf16", "bf16"),        # K % 64 != 0: the last K tile masked
     (264, 520, 32, "f32", "f32"),          # fp32 factors: the float32 kernel
 ]

@@ -69,8 +69,7 @@ def test_ragged_contraction(acc, m, n, k, tile, one_round, out_in):
 @pytest.mark.parametrize("out_in", [False, True])
 @pytest.mark.parametrize("r", [8, 40, 72, 136, 200])
 def test_dense_gradient_at_ragged_ranks(acc, r, out_in):
-    """dW = Xs.Gr on the short-contraction kernel (one round of tiles) and on the tiled ones, written and accumulated;
-    the factor's padding columns are NaN."""
+    """dW = Xs.Gr of a small and of a large output, written and accumulated in float; the factor's padding columns are NaN."""
     import torch
     for d_in, d_out in ((200, 392), (4104, 3080)):
         g = torch.Generator(device="cuda").manual_seed(r + d_in)
@@ -92,21 +91,20 @@ def test_dense_gradient_at_ragged_ranks(acc, r, out_in):
 
 
 @pytest.mark.parametrize("out_in", [False, True])
-@pytest.mark.parametrize("d_in,d_out,r,tile", [
-    (3264, 3080, 40, "192x128"),     # 17 x 17 tiles of 192 x 192, 13 x 13 of 256 x 256: the ring kernel in every form
-    (3504, 3104, 200, "192x128"),
-    (520, 1032, 1096, "64x64"),      # rank above the short-contraction kernel's
-    (1400, 1032, 1032, "128x64"),
-    (1056, 3048, 1592, "128x128"),
-    (4096, 3072, 1032, "256x192"),
+@pytest.mark.parametrize("d_in,d_out,r,written,added,added_f32", [   # the kernel of each form; a float result is written as a bfloat16 one
+    (3264, 3080, 40, "192x128", "128x64", "64x64"),
+    (3504, 3104, 200, "192x128", "128x64", "64x64"),
+    (520, 1032, 1096, "64x64", "64x64", "64x64"),
+    (1400, 1032, 1032, "128x64", "128x64", "128x64"),
+    (1056, 3048, 1592, "128x128", "128x128", "128x128"),
+    (4096, 3072, 1032, "256x192", "256x192", "256x192"),
 ])
-def test_dense_gradient_on_the_ring_kernel(acc, d_in, d_out, r, tile, out_in):
+def test_dense_gradient_on_the_ring_kernel(acc, d_in, d_out, r, written, added, added_f32, out_in):
     """dW written and accumulated, in float and in bfloat16; the factor's padding columns are NaN, dW's neighbours stay."""
     import torch
     M, N = (d_out, d_in) if out_in else (d_in, d_out)
-    assert -(-d_in // 192) * -(-d_out // 192) > 256 or r > 1024
-    assert -(-d_in // 256) * -(-d_out // 256) < 192 or tile == "256x192"
-    assert out_in or plan.gemm_tile(M, N, r, float_or_sum=True)[0] == tile
+    taken = [plan.factor_tile(M, N, r, bf16_c, sums) for sums in (False, True) for bf16_c in (True, False)]
+    assert out_in or taken == [written, written, added, added_f32], taken
     g = torch.Generator(device="cuda").manual_seed(r + d_in)
     Xs = torch.randn(d_in, r, generator=g, device="cuda").bfloat16()
     Gr = (torch.randn(r, d_out, generator=g, device="cuda") * 0.01).bfloat16()

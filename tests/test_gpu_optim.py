@@ -113,7 +113,7 @@ def test_bf16_tuned_kernel_three_steps(acc, flags_name):
                                                     ("bf16", 24, 1e-2, 1e-2)])
 def test_projected_three_steps(acc, flags_name, dtype, k, w_tol, step_tol):
     """Through a fixed projector P [d_in, k]: R = (P^T left) Gr, moments [k, d_out], W moves inside range(P).
-    P . N is added to W on the short-contraction kernel (bf16; at k = 24 with a masked K tile) or the float32 kernel."""
+    P . N is added to W on 64 x 64 tiles of the ring kernel (bf16; at k = 24 with a masked K tile) or the float32 kernel."""
     flags = acc.ACC_FLAG_W_OUT_IN if flags_name == "w_out_in" else 0
     lin = inputs.Linear("opt.proj." + dtype, 2048, 712, 840, 128, dtype=dtype, x_kind="plain")
     # an orthonormal projector gives steps of size lr * scale * sqrt(k / d_in) per entry: lr is sized so that the

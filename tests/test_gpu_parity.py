@@ -160,9 +160,9 @@ def test_bf16_tuned_kernel_shapes(acc, n, d_in, d_out, r):
 @pytest.mark.parametrize("d_in,d_out,r", [(64, 3080, 64), (128, 4104, 128), (192, 3080, 192), (256, 3080, 64),
                                           (320, 3080, 64)])
 def test_tuned_gemm_with_one_to_five_k_tiles(acc, d_in, d_out, r):
-    """Short contractions through the 256 x 256 tile (n and d_out large enough for it): one to five K tiles, so
-    every combination of the steady-state loop and its two closing K tiles is taken (forward K = d_in, dense
-    gradient K = r, backward K = d_out long)."""
+    """Short contractions of a large output, forward K = d_in: one and two K tiles on the ring kernel, three to five on the
+    256 x 256 tile, so every combination of its steady-state loop and its two closing K tiles is taken; dense gradient K = r,
+    backward K = d_out long."""
     _check(acc, inputs.Linear(f"ktiles_{d_in}x{d_out}_r{r}", 4100, d_in, d_out, r, dtype="bf16"))
 
 
