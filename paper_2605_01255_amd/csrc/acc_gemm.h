@@ -10,8 +10,7 @@
 // Tiles travel global -> LDS directly (global_load_lds_dwordx4, no staging registers); LDS is double
 // buffered, one barrier per K tile, and the MFMAs run one k-step behind the LDS reads so that the
 // reads after the barrier are covered by the last k-step of the previous tile.
-// K % 8 == 0: the 16-byte chunks of the last K tile past K are sent out of the buffer's range and read as zero.
-// M and N arbitrary (loads past the last row read zero through the buffer resource,
+// K % 64 == 0; M and N arbitrary (loads past the last row read zero through the buffer resource,
 // stores are predicated); N % 8 == 0; every operand smaller than 4 GiB.
 #pragma once
 #include <type_traits>
@@ -138,7 +137,7 @@ __device__ __forceinline__ bool xcd_tile(const FastGemmParams& p, int b, int& tm
   return tm < p.tiles_m && tn < p.tiles_n;
 }
 
-// The work of one work-group: output tile number b (see xcd_tile), using the dynamic LDS at smem.
+// The work of one work-group: output tile number b (see xcd_tile), using the dynamic LDS at smem.  K % 64 == 0, bfloat16 C.
 template <int WM, int WN, int TM, int TN, bool B_KMAJOR>
 __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, char* smem) {
   constexpr int NW = WM * WN;
@@ -153,8 +152,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, c
   static_assert(B_KMAJOR || (BN_CHUNKS >= 16 && 64 % BN_CHUNKS == 0), "B tile shape");
 
   int tm, tn;
-  const bool has_tile = xcd_tile(p, b, tm, tn);
-  if (!has_tile && p.red_count == 0) return;
+  if (!xcd_tile(p, b, tm, tn)) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
@@ -192,10 +190,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, c
     }
   }
   const uint32_t b_kstep = B_KMAJOR ? BK * 2 : (uint32_t)(BK * p.ldb * 2);  // bytes per K tile
-  // last K tile: this lane's chunk lies past K (rows NW * 8 apart share their swizzle: NW is even)
-  static_assert(NW % 2 == 0, "swizzle period");
-  const int KT = (int)((p.K + BK - 1) / BK);
-  const uint32_t tail = ((lane & 7) ^ swz(wave * 8 + (lane >> 3))) * 8 >= p.K - (int64_t)(KT - 1) * BK ? 0xFFFFFFF0u : 0u;
+  const int KT = (int)(p.K / BK);
 
   // ---- LDS read offsets of this lane's MFMA operands ----
   const int lrow = lane & 31, kg = lane >> 5;
@@ -244,10 +239,8 @@ __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, c
     }
   };
   auto issue_one = [&](int g, int kt, uint32_t stage) {  // g-th wave-load of a K tile (A first, then B)
-    const uint32_t oob = kt == KT - 1 ? tail : 0u;
-    if (g < A_LOADS) buffer_to_lds_b128(a_rsrc, a_src[g] | oob, (uint32_t)kt * (BK * 2), stage + (g * NW + wave) * 1024);
-    else buffer_to_lds_b128(b_rsrc, B_KMAJOR ? b_src[g - A_LOADS] | oob : b_src[g - A_LOADS], (uint32_t)kt * b_kstep,
-                            stage + A_BYTES + ((g - A_LOADS) * NW + wave) * 1024);
+    if (g < A_LOADS) buffer_to_lds_b128(a_rsrc, a_src[g], (uint32_t)kt * (BK * 2), stage + (g * NW + wave) * 1024);
+    else buffer_to_lds_b128(b_rsrc, b_src[g - A_LOADS], (uint32_t)kt * b_kstep, stage + A_BYTES + ((g - A_LOADS) * NW + wave) * 1024);
   };
 
   // One k-step with a fixed instruction order: MFMA q of the step carries (at most) one operand read
@@ -283,27 +276,8 @@ __device__ __forceinline__ void gemm_bf16_tile(const FastGemmParams& p, int b, c
 
   // prologue: tile 0 -> stage 0, operands of its first k-step -> registers
   const uint32_t smem_lds = (uint32_t)(uintptr_t)smem;  // LDS byte address of the dynamic segment
-  if (has_tile) {
 #pragma unroll
-    for (int g = 0; g < NG_TOTAL; ++g) issue_one(g, 0, smem_lds);
-  }
-  if (p.red_count) {  // side job: this work-group's share of the partial sums, 4 elements per lane
-    for (int64_t e = ((int64_t)b * (NW * 64) + tid) * 4; e < p.red_count; e += p.red_stride) {
-      f32x4 sum = *(const f32x4*)(p.red_part + e);
-#pragma unroll 8
-      for (int g = 1; g < p.red_G; ++g) sum += *(const f32x4*)(p.red_part + (int64_t)g * p.red_count + e);
-      const int64_t eo = p.red_ld == p.red_row ? e : (e / p.red_row) * p.red_ld + e % p.red_row;
-      if (p.red_out_bf16) {
-        bf16x4 v;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) v[t] = (bf16)sum[t];
-        *(bf16x4*)((bf16*)p.red_out + eo) = v;
-      } else {
-        *(f32x4*)((float*)p.red_out + eo) = sum;
-      }
-    }
-    if (!has_tile) return;
-  }
+  for (int g = 0; g < NG_TOTAL; ++g) issue_one(g, 0, smem_lds);
   wait_vmcnt0();
   __syncthreads();
 #pragma unroll

@@ -16,9 +16,10 @@ def test_hot_kernels_use_no_scratch_memory():
     res = resources()
     hot = {n: r for n, r in res.items()
            if any(k in n for k in ("gemm16_persist_kernel", "gemm8_persist_kernel", "gemm16_smallk_kernel",
-                                   "sketch8_kernel", "gemm_bf16_kernel", "gemm_ring_kernel", "gemm_f32_kernel",
-                                   "chol_factor_kernel", "chol_solve_kernel"))}
-    for kind in ("gemm_ring_kernel", "gemm_f32_kernel", "chol_factor_kernel", "chol_solve_kernel", "gemm16_smallk_kernel"):
+                                   "sketch8_kernel", "fused_linear_kernel", "gemm_ring_kernel", "gemm_f32_kernel",
+                                   "gemm_f32_pair_kernel", "chol_factor_kernel", "chol_solve_kernel", "cholesky_qr_kernel"))}
+    for kind in ("gemm_ring_kernel", "gemm_f32_kernel", "gemm_f32_pair_kernel", "sketch8_kernel", "fused_linear_kernel",
+                 "chol_factor_kernel", "chol_solve_kernel", "cholesky_qr_kernel", "gemm16_smallk_kernel"):
         assert any(kind in n for n in hot), (kind, sorted(res))
     assert len(hot) >= 10, sorted(res)
     bad = {n: r for n, r in hot.items() if r.get("scratch", -1) != 0 or r.get("vgpr_spill", -1) != 0}
