@@ -50,6 +50,38 @@ struct FastGemmParams {
                           // zero-padded along K, the missing rows of B then read as zero
 };
 
+// The side job of a product's launch: this work-group's share of the pending partial sums.  Bound by the latency of the reads: all
+// splits of an element are requested together, eight at a time, what eight leave over as well.
+__device__ __forceinline__ void fold_pending(const FastGemmParams& p, int threads) {
+  for (int64_t e = ((int64_t)blockIdx.x * threads + threadIdx.x) * 4; e < p.red_count; e += p.red_stride) {
+    f32x4 sum = *(const f32x4*)(p.red_part + e);
+    int g = 1;
+    auto add = [&](auto count) {
+      constexpr int N = decltype(count)::value;
+      f32x4 v[N];
+#pragma unroll
+      for (int u = 0; u < N; ++u) v[u] = *(const f32x4*)(p.red_part + (int64_t)(g + u) * p.red_count + e);
+#pragma unroll
+      for (int u = 0; u < N; ++u) sum += v[u];
+      g += N;
+    };
+    while (g + 8 <= p.red_G) add(std::integral_constant<int, 8>{});
+    const int left = p.red_G - g;
+    static_for<1, 8>([&](auto n) {
+      if (left == decltype(n)::value) add(n);
+    });
+    const int64_t eo = p.red_ld == p.red_row ? e : (e / p.red_row) * p.red_ld + e % p.red_row;
+    if (p.red_out_bf16) {
+      bf16x4 v;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[t] = (bf16)sum[t];
+      *(bf16x4*)((bf16*)p.red_out + eo) = v;
+    } else {
+      *(f32x4*)((float*)p.red_out + eo) = sum;
+    }
+  }
+}
+
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 

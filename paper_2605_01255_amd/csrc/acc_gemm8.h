@@ -304,22 +304,7 @@ __global__ __launch_bounds__(256) void gemm8_persist_kernel(FastGemmParams p, in
 #pragma unroll
     for (int g = 0; g < NG; ++g) issue_one(cur_t, g, 1, smem_lds + STAGE);
   }
-  if (p.red_count) {  // side job: this work-group's share of the pending partial sums (see gemm_bf16_tile)
-    for (int64_t e = ((int64_t)blockIdx.x * (NW * 64) + tid) * 4; e < p.red_count; e += p.red_stride) {
-      f32x4 sum = *(const f32x4*)(p.red_part + e);
-#pragma unroll 8
-      for (int g = 1; g < p.red_G; ++g) sum += *(const f32x4*)(p.red_part + (int64_t)g * p.red_count + e);
-      const int64_t eo = p.red_ld == p.red_row ? e : (e / p.red_row) * p.red_ld + e % p.red_row;
-      if (p.red_out_bf16) {
-        bf16x4 v;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) v[t] = (bf16)sum[t];
-        *(bf16x4*)((bf16*)p.red_out + eo) = v;
-      } else {
-        *(f32x4*)((float*)p.red_out + eo) = sum;
-      }
-    }
-  }
+  if (p.red_count) fold_pending(p, NW * 64);
   if (!has_tile) return;
   wait_vmcnt0();
   __syncthreads();
