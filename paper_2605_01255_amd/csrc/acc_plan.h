@@ -124,12 +124,19 @@ struct SketchSplit {
   bool two_sums;   // fewer splits than `most`: even and odd stages are summed apart, so that no running sum gets longer
 };
 
+// Work-groups on the fullest of the eight dies: a die takes whole pairs of slab and split with all their column slices, and has 32
+// compute units.
+static inline int64_t sketch_groups_of_a_die(int64_t slabs, int64_t columns, int64_t splits) {
+  return ceil_div(slabs * splits, 8) * columns;
+}
+
 // The splits of 512 channels, on slabs narrowed as far as that makes one work-group per compute unit at most (two of them on one
-// get in each other's way: 4096 x 1024 at rank 256, 128 / 256 / 512 work-groups of 512 / 256 / 128 channels 12.2 / 10.6 / 11.5 us).
+// get in each other's way: 4096 x 1024 at rank 256, 128 / 256 / 512 work-groups of 512 / 256 / 128 channels 12.2 / 10.6 / 11.5 us;
+// 1622 x 1408 at rank 384, 36 work-groups of 256 channels on two dies 29.1 us of a pass, 18 of 512 27.0).
 static inline SketchSplit narrow_sketch_slabs(int64_t n, int64_t channels, int64_t r, int64_t most) {
   const int64_t made = ceil_div(n, round_up(ceil_div(n, most), 32)), columns = ceil_div(r, 64);
   int ch = 512;
-  while (ch > 128 && ceil_div(channels, ch / 2) * columns * made <= 256) ch /= 2;
+  while (ch > 128 && sketch_groups_of_a_die(ceil_div(channels, ch / 2), columns, made) <= 32) ch /= 2;
   return SketchSplit{ch, most, false};
 }
 
@@ -137,7 +144,8 @@ static inline SketchSplit narrow_sketch_slabs(int64_t n, int64_t channels, int64
 // written and read back,  in nanoseconds: narrow slabs generate S more often, but half as many splits of twice the tokens write
 // half as many partials, which is what a sketch of a few thousand tokens spends a third of its time on.  Three quarters of the
 // splits at most (8 splits for 10 lose, 2500 x 2048 at rank 256 37.1 us against 34.4) and 0.3 us ahead; at most twice the stages, so
-// that neither of the two sums has more of them than a split had.
+// that neither of the two sums has more of them than a split had; and no die with more work-groups than compute units (21418 x 448
+// at rank 384, 36 on two of them: 43.6 us of a pass against 38.6).
 // Fitted to 80 forward passes with 1024 outputs (300 to 32768 tokens, 640 to 14336 channels, rank 16 to 512): 2.0 % ahead of the
 // splits of 512 channels on average, 1.6 % behind at worst (4096 x 3072 at 256, 48.8 / 49.6), 1.3 % behind the best of twelve forms.  us, the
 // splits of 512 channels / chosen: 4096 x 4096 at rank 128 56.1 / 52.3, 2048 x 4096 at 256 46.8 / 41.8, 600 x 8192 at 256 53.0 / 49.6, 1500 x 5120 at 256 52.1 / 46.0,
@@ -160,6 +168,7 @@ static inline SketchSplit pick_sketch_split(int64_t n, int64_t channels, int64_t
       if (splits < 1) continue;
       const int64_t iterations = ceil_div(ceil_div(n, splits), 32), fewer = ceil_div(n, iterations * 32);
       if (iterations > 2 * stages || 4 * fewer > 3 * made) continue;
+      if (sketch_groups_of_a_die(ceil_div(channels, c.ch), ceil_div(r, 64), fewer) > 32) continue;
       const int64_t ns = estimate(c, iterations, fewer);
       if (ns < best_ns) { best_ns = ns; best = SketchSplit{c.ch, splits, true}; }
     }

@@ -76,6 +76,7 @@ def test_raised_lds_limits_are_remembered_for_every_kernel_and_device():
     (1500, 5120, 256, 256, True, 52.1, 46.0), (16384, 4096, 64, 256, True, 129.3, 122.4), (4096, 1024, 256, 128, True, 27.1, 26.0),
     (4096, 3072, 256, 256, True, 48.8, 49.6), (2500, 2048, 256, 512, False, 34.4, 34.4), (6000, 3072, 256, 512, False, 60.8, 60.8),
     (4096, 3584, 256, 512, False, 53.4, 53.4), (2049, 3072, 512, 512, False, 55.9, 55.9),
+    (21418, 448, 384, 512, False, 38.6, 38.6),
 ])
 def test_sketch_splits_are_near_the_best(n, channels, r, slab, two_sums, before, now):
     p = plan.sketch(n, channels, r)
@@ -86,9 +87,9 @@ def test_sketch_splits_are_near_the_best(n, channels, r, slab, two_sums, before,
 def test_sketch_splits_fit_the_workspace_and_the_chip():
     """Never more splits than the workspace holds, never more work-groups than compute units where 512 channels made no more; no
     running sum longer than one of the splits that 512 channels make, and those splits themselves with a float factor."""
-    for n in (1, 31, 257, 300, 700, 1030, 2049, 4096, 4097, 16384, 65536):
-        for channels in (8, 128, 136, 520, 1024, 3072, 3080, 8192, 14336, 40000):
-            for r in (8, 64, 72, 256, 512):
+    for n in (1, 31, 257, 300, 700, 1030, 2049, 4096, 4097, 16384, 21418, 65536):
+        for channels in (8, 128, 136, 448, 520, 1024, 3072, 3080, 8192, 14336, 40000):
+            for r in (8, 64, 72, 256, 384, 512):
                 columns = -(-r // 64)
                 most = max(1, min(256 // (-(-channels // 512) * columns), -(-n // 256), 64))
                 tokens = -(--(-n // most) // 32) * 32
@@ -99,5 +100,7 @@ def test_sketch_splits_fit_the_workspace_and_the_chip():
                     assert p.slab in (128, 256, 512) and p.tokens % 32 == 0
                     assert p.splits == -(-n // p.tokens) <= p.room == -(-n // tokens)
                     assert p.tiles * p.splits <= max(256, -(-channels // 512) * columns)
+                    if p.slab < 512:   # a die takes whole pairs of slab and split, with all their column slices, on 32 compute units
+                        assert -(-p.tiles // columns * p.splits // 8) * columns <= 32
                     assert -(-p.tokens // 32 // (2 if p.two_sums else 1)) * 32 <= tokens
                     assert bf16_factor or (p.tokens == tokens and not p.two_sums)
