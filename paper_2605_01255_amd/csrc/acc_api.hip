@@ -300,11 +300,11 @@ bool f32_sketch(const acc_linear_desc* d, const void* A, int64_t lda, int64_t ch
     F32GemmParams q = f32_params(a, exact->b, exact->C, exact->ldc, n, exact->N, exact->K);
     p.tile_blocks = (int)gemm_ring_plan(p, 32, 32);
     q.tile_blocks = (int)gemm_ring_plan(q, 32, 32);
-    const int sketch_blocks = p.tile_blocks * (int)G;
+    const int sketch_blocks = p.tile_blocks * (int)G, before = exact->K > k_per_split ? q.tile_blocks : 0;
     const dim3 grid((unsigned)(sketch_blocks + q.tile_blocks));
     const size_t lds = (size_t)gemm_f32_lds_bytes<1, 1, 4, float, float>();
-    if (exact->b.kmajor) L.launch_lds(gemm_f32_pair_kernel<true>, grid, dim3(256), lds, p, q, sketch_blocks);
-    else L.launch_lds(gemm_f32_pair_kernel<false>, grid, dim3(256), lds, p, q, sketch_blocks);
+    if (exact->b.kmajor) L.launch_lds(gemm_f32_pair_kernel<true>, grid, dim3(256), lds, p, q, sketch_blocks, before);
+    else L.launch_lds(gemm_f32_pair_kernel<false>, grid, dim3(256), lds, p, q, sketch_blocks, before);
     exact->done = true;
   } else {
     f32_gemm<float>(transposed ? sm : x, transposed ? x : sm, dst, ldc, M, N, n, L, false, 1.f, 1.f, k_per_split, count);

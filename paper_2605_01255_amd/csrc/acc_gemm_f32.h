@@ -278,15 +278,19 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32GemmParams p, Output o
 }
 
 // Two products that do not depend on each other in one launch, both on 32 x 32 tiles: the sketch's (both operands with their
-// rows contiguous; the first `sketch_blocks` work-groups, a multiple of eight) and the exact one.  A small layer's launch is its
-// latency: at 256 x 256 x 512, rank 16, the sketch's 5.1 us (backward 5.4) and the product's 5.5 (7.4) follow each other no
-// more; a forward and backward pass with the dense dW takes 20.4 us, 29.6 with seven launches instead of five.
+// rows contiguous; `sketch_blocks` work-groups) and the exact one.  A small layer's launch is its latency: at 256 x 256 x 512, rank 16,
+// the sketch's 5.1 us (backward 5.4) and the product's 5.5 (7.4) follow each other no more; a forward and backward pass with the dense
+// dW takes 20.4 us, 29.6 with seven launches instead of five.
+// `before`: work-groups of the exact product in front of the sketch's, all or none: those with the longer contraction start first, or
+// they are what the launch waits for at its end (854 x 2656 x 896 at rank 256, us of a forward pass: two launches 66.6 to 68.5, the
+// sketch first 69.3, the product first 60.5; 825 x 384 x 712 at rank 128, where the sketch's is the longer: 22.2, 15.6, 16.4).  All three
+// counts are multiples of eight, which keeps a product's tiles on their dies.
 template <bool B_KMAJOR>
-__global__ __launch_bounds__(256) void gemm_f32_pair_kernel(F32GemmParams sketch, F32GemmParams exact, int sketch_blocks) {
+__global__ __launch_bounds__(256) void gemm_f32_pair_kernel(F32GemmParams sketch, F32GemmParams exact, int sketch_blocks, int before) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  const int block = (int)blockIdx.x;
-  if (block < sketch_blocks) gemm_f32_block<1, 1, 4, false, false, float, float>(sketch, StoreProduct<float>{}, block, smem);
-  else gemm_f32_block<1, 1, 4, true, B_KMAJOR, float, float>(exact, StoreProduct<float>{}, block - sketch_blocks, smem);
+  const int block = (int)blockIdx.x, s = block - before;
+  if (s >= 0 && s < sketch_blocks) gemm_f32_block<1, 1, 4, false, false, float, float>(sketch, StoreProduct<float>{}, s, smem);
+  else gemm_f32_block<1, 1, 4, true, B_KMAJOR, float, float>(exact, StoreProduct<float>{}, s < 0 ? block : block - sketch_blocks, smem);
 }
 
 template <int TM, int TN, int NS, typename TA, typename TB>

@@ -272,7 +272,8 @@ static inline F32Choice pick_f32_tile(int64_t M, int64_t N, int64_t splits, bool
 // which has one tile for both: where each would take 32 x 32 by itself.  Always with four stages, also where one of them alone
 // has enough work-groups for two (`deep` is false): the other one's are there beside them, and a launch less is worth more than
 // either.  us of a forward pass, two launches / shared with two stages / with four, 108 measured, shared with four never behind
-// the two launches and at most 3 % behind two stages (d_in x d_out, tokens):
+// the two launches and at most 3 % behind two stages (d_in x d_out, tokens; the sketch's work-groups first, where the other order
+// is ahead by up to 13 %, see gemm_f32_pair_kernel):
 //   1 product of the two not deep: 256 x 512, 2624 19.1 / 14.6 / 14.9     384 x 768, 1024 23.5 / 18.5 / 17.9   3072 x 384, 256 40.2 / 45.8 / 36.7
 //   both deep:                     256 x 512, 256  11.8 / 7.5 / 7.4       1544 x 512, 512 26.5 / 25.7 / 21.6   3072 x 768, 300 38.6 / 43.0 / 34.5
 static inline bool f32_pair(int64_t M, int64_t N, int64_t splits, int64_t n, int64_t out_n) {

@@ -1,6 +1,7 @@
 """The launch that a small float32 layer's exact product shares with its sketch, at the edges of its 32 x 32 tiles: remainders in
 every dimension, one and several token splits (their partial products lie behind S and are folded), both weight orientations,
-padded rows, a bfloat16 factor; and layers beyond it.
+padded rows, a bfloat16 factor, the product's work-groups in front of the sketch's (where its contraction is longer than a split)
+and behind them; and layers beyond it.
 
 Bound: fp32 sums of 256 products, and of at most four of those, 4 2^-24 sqrt(512); a bfloat16 factor rounds once, 2^-8."""
 import pytest
@@ -25,7 +26,7 @@ def acc():
     (256, 256, 512, 16, 0, False, 1, 1), (33, 40, 264, 8, 0, False, 1, 1), (257, 136, 136, 40, 8, False, 1, 1), (1, 8, 8, 8, 0, False, 1, 1),
     (257, 520, 136, 24, 16, True, 1, 0), (513, 136, 264, 24, 8, True, 0, 1),   # a bfloat16 factor is folded from one split too
     (1500, 512, 512, 16, 0, False, 3, 3), (900, 776, 712, 40, 8, False, 2, 2), (900, 776, 712, 40, 0, True, 2, 2),
-    (1030, 520, 488, 24, 16, True, 3, 2), (2624, 384, 264, 64, 0, False, 4, 0), (2624, 264, 384, 64, 8, True, 0, 4),
+    (1030, 520, 488, 24, 16, True, 3, 2), (2624, 384, 264, 64, 0, False, 4, 0), (700, 1000, 904, 256, 8, False, 1, 0), (2624, 264, 384, 64, 8, True, 0, 4),
     (33, 40, 24, 8, 0, False, 1, 0), (700, 64, 96, 32, 0, False, 0, 0), (2048, 1024, 1032, 64, 0, False, 0, 0),
 ])
 def test_layer(acc, n, d_in, d_out, r, pad, bf16_factor, fwd, bwd, w_oi):

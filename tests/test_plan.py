@@ -51,7 +51,8 @@ def test_float32_sketch_takes_the_faster_form(n, channels, r, stored, generic):
 @pytest.mark.parametrize("n,d_in,d_out,r,shared,apart", [
     (256, 256, 512, 16, 7.4, 11.8), (256, 512, 2624, 16, 14.9, 19.1), (1024, 384, 768, 64, 18.0, 23.5),
     (2624, 384, 256, 128, 19.6, 24.2), (256, 3072, 384, 256, 36.7, 40.2), (1024, 3072, 256, 256, 45.8, 52.9), (256, 3072, 3072, 64, 56.6, 59.9),
-    (1500, 512, 512, 128, 20.8, 24.8), (300, 3072, 768, 16, 34.5, 38.6),
+    (1500, 512, 512, 128, 20.8, 24.8), (300, 3072, 768, 16, 34.5, 38.6), (854, 2656, 896, 256, 60.5, 66.6),
+    (512, 3072, 1536, 256, 60.3, 65.5),
 ])
 def test_float32_products_share_a_launch_where_that_is_faster(n, d_in, d_out, r, shared, apart):
     assert (plan.f32_pair(n, d_in, d_out, r) > 0) == (shared < apart)
