@@ -143,24 +143,24 @@ static inline SketchSplit narrow_sketch_slabs(int64_t n, int64_t channels, int64
 // Or fewer splits on narrower slabs, where that is the less by an estimate,  start + iterations of 32 tokens x one + partial tiles
 // written and read back,  in nanoseconds: narrow slabs generate S more often, but half as many splits of twice the tokens write
 // half as many partials, which is what a sketch of a few thousand tokens spends a third of its time on.  Three quarters of the
-// splits at most (8 splits for 10 lose, 2500 x 2048 at rank 256 37.1 us against 34.4) and 0.3 us ahead; at most twice the stages, so
+// splits at most (8 splits for 10 lose, 2500 x 2048 at rank 256 37.1 us against 34.4) and 0.23 us ahead; at most twice the stages, so
 // that neither of the two sums has more of them than a split had; and no die with more work-groups than compute units (21418 x 448
 // at rank 384, 36 on two of them: 43.6 us of a pass against 38.6).
-// Fitted to 80 forward passes with 1024 outputs (300 to 32768 tokens, 640 to 14336 channels, rank 16 to 512): 2.0 % ahead of the
-// splits of 512 channels on average, 1.6 % behind at worst (4096 x 3072 at 256, 48.8 / 49.6), 1.3 % behind the best of twelve forms.  us, the
-// splits of 512 channels / chosen: 4096 x 4096 at rank 128 56.1 / 52.3, 2048 x 4096 at 256 46.8 / 41.8, 600 x 8192 at 256 53.0 / 49.6, 1500 x 5120 at 256 52.1 / 46.0,
-// 16384 x 4096 at 64 129.3 / 122.4, 4096 x 1024 at 256 27.1 / 26.0; 4096 x 3584, 6000 x 3072 and 16384 x 3072 at 256 stay.
+// Fitted to 278 forward passes (256 to 32768 tokens, 256 to 8192 channels, rank 16 to 512, 64 to 3072 outputs), of which it takes fewer
+// splits in 51: 8.9 % ahead of the splits of 512 channels there on average, behind in none.  us, the splits of 512 channels / chosen:
+// 4096 x 4096 at rank 128 56.1 / 52.3, 2048 x 4096 at 256 46.8 / 41.8, 600 x 8192 at 256 53.0 / 49.6, 1500 x 5120 at 256 52.1 / 46.0, 4096 x
+// 1024 at 256 27.1 / 26.0; 4096, 6000 and 16384 x 3072 at 256 stay, and 15018 x 2208 at 128 (75.0, 77.0 with 14 splits for 25).
 static inline SketchSplit pick_sketch_split(int64_t n, int64_t channels, int64_t r, int64_t most) {
   struct Cost { int ch, start, per_iteration; };
-  static const Cost costs[] = {{512, 1800, 418}, {256, 800, 339}, {128, 0, 268}};
+  static const Cost costs[] = {{512, 1450, 477}, {256, 700, 372}, {128, 0, 264}};
   const int64_t stages = ceil_div(ceil_div(n, most), 32), made = ceil_div(n, stages * 32);
   auto estimate = [&](const Cost& c, int64_t iterations, int64_t splits) {
-    return c.start + iterations * c.per_iteration + splits * channels * r * 4 / 1000 * 259 / 1000;
+    return c.start + iterations * c.per_iteration + splits * channels * r * 4 / 1000 * 172 / 1000;
   };
   SketchSplit best = narrow_sketch_slabs(n, channels, r, most);
   int64_t best_ns = INT64_MAX;
   for (const Cost& c : costs)
-    if (c.ch == best.ch) best_ns = estimate(c, stages, made) - 300;
+    if (c.ch == best.ch) best_ns = estimate(c, stages, made) - 230;
   for (const Cost& c : costs) {
     int64_t full = 256 / (ceil_div(channels, c.ch) * ceil_div(r, 64));
     if (full > most) full = most;
