@@ -171,7 +171,7 @@ template <bool A_K, bool B_K, typename TA, typename TB, typename Output>
 void f32_tiled(F32GemmParams& p, const Output& out, Launcher& L) {
   const int splits = (int)ceil_div(p.K, p.k_per_split);
   constexpr bool both_f32 = sizeof(TA) == 4 && sizeof(TB) == 4;
-  const F32Choice c = pick_f32_tile(p.M, p.N, splits, both_f32);
+  const F32Choice c = pick_f32_tile(p.M, p.N, p.k_per_split < p.K ? p.k_per_split : p.K, splits, both_f32);
   if (c.tile == F32TileShape::k64) return f32_launch<2, 2, 2, A_K, B_K, TA, TB>(p, out, splits, L);
   if (c.tile == F32TileShape::k32) {
     if (c.deep) f32_launch<1, 1, 4, A_K, B_K, TA, TB>(p, out, splits, L);

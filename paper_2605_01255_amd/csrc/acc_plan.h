@@ -234,8 +234,10 @@ static inline SketchPlan plan_sketch(int64_t n, int64_t channels, int64_t r, int
 // holds (64 x 64 five, 64 x 32 six, 32 x 32 eight): they start, wait and store at different times, which is worth more than
 // transfers further ahead (2048 x 2048 x 1024 66.5 us against 70.7 on 128 x 64 with three stages, two work-groups; 2504 x 1000 x
 // 3000 128 against 160 on 64 x 32 with four).  Only where 32 x 32 tiles are 2.5 or fewer to a compute unit, or 64 x 32 one,
-// there is nobody to cover a wait: four stages.  128 x 64 where it is exactly two to a compute unit: as fast as four of 64 x 64, with a
-// quarter less to move.  Constants fitted to 150 measurements (50 shapes from 128 x 128 x 4096 to 4096 x 4096 x 1024 in three
+// there is nobody to cover a wait: four stages; so too up to four 32 x 32 to a compute unit where the contraction is long (1 to 4 % over
+// seven products of 1472 to 3392 elements: 405 x 1728 x 3392 58.2 us against 60.3; six shorter ones are 1 to 2 % ahead with two).  128 x 64 where
+// it is two or three to a compute unit, all of them resident: as fast as four of 64 x 64, with a quarter less to move, and ahead of
+// six, of which five are (2337 x 2496 x 1472 138 us and 158, 2500 x 2304 x 1024 96 and 111).  Constants fitted to 150 measurements (50 shapes from 128 x 128 x 4096 to 4096 x 4096 x 1024 in three
 // orders of the operands): the chosen form is 2.9 % behind the best of eleven on average, 13 % at
 // most (three and four stages everywhere and their own fit: 5.4 and 29 %).
 // Measured us, 64 x 64 / 64 x 32 / 32 x 32, the chosen one marked [before]:
@@ -249,20 +251,21 @@ struct F32Choice {
   int ns_per_k;   // estimate of a K tile
   bool deep;      // 32 x 32 and 64 x 32: four stages
 };
-static inline F32Choice pick_f32_tile(int64_t M, int64_t N, int64_t splits, bool all_tiles) {
+// k: elements of a split's contraction.
+static inline F32Choice pick_f32_tile(int64_t M, int64_t N, int64_t k, int64_t splits, bool all_tiles) {
   struct Cost { F32TileShape tile; int bm, bn, per_tile, fixed, resident, more_per_tile, more_fixed; };  // more: above `resident`
   static const Cost costs[] = {{F32TileShape::k64, 64, 64, 460, 100, 5, 460, 100}, {F32TileShape::k32, 32, 32, 145, 100, 8, 145, 100},
-                               {F32TileShape::k64x32, 64, 32, 227, 115, 6, 225, 370}, {F32TileShape::k128x64, 128, 64, 950, 0, 2, 950, 0}};
+                               {F32TileShape::k64x32, 64, 32, 227, 115, 6, 225, 370}, {F32TileShape::k128x64, 128, 64, 950, 0, 3, 950, 0}};
   F32Choice best{F32TileShape::k64, 0, false};
   int64_t best_ns = INT64_MAX;
   for (int i = 0; i < (all_tiles ? 4 : 2); ++i) {
     const int64_t tiles = ceil_div(M, costs[i].bm) * ceil_div(N, costs[i].bn) * splits, per_cu = ceil_div(tiles, 256);
-    if (costs[i].tile == F32TileShape::k128x64 && per_cu != 2) continue;
+    if (costs[i].tile == F32TileShape::k128x64 && (per_cu < 2 || per_cu > 3)) continue;
     const Cost& c = costs[i];
     const int64_t ns = per_cu <= c.resident ? c.fixed + per_cu * c.per_tile : c.more_fixed + per_cu * c.more_per_tile;
     if (ns < best_ns) {
       best_ns = ns;
-      best = F32Choice{c.tile, (int)(ns < INT32_MAX ? ns : INT32_MAX), tiles <= (c.tile == F32TileShape::k32 ? 640 : 256)};
+      best = F32Choice{c.tile, (int)(ns < INT32_MAX ? ns : INT32_MAX), tiles <= (c.tile != F32TileShape::k32 ? 256 : k < 1280 ? 640 : 1024)};
     }
   }
   return best;
@@ -277,7 +280,7 @@ static inline F32Choice pick_f32_tile(int64_t M, int64_t N, int64_t splits, bool
 //   1 product of the two not deep: 256 x 512, 2624 19.1 / 14.6 / 14.9     384 x 768, 1024 23.5 / 18.5 / 17.9   3072 x 384, 256 40.2 / 45.8 / 36.7
 //   both deep:                     256 x 512, 256  11.8 / 7.5 / 7.4       1544 x 512, 512 26.5 / 25.7 / 21.6   3072 x 768, 300 38.6 / 43.0 / 34.5
 static inline bool f32_pair(int64_t M, int64_t N, int64_t splits, int64_t n, int64_t out_n) {
-  return pick_f32_tile(M, N, splits, true).tile == F32TileShape::k32 && pick_f32_tile(n, out_n, 1, true).tile == F32TileShape::k32;
+  return pick_f32_tile(M, N, 0, splits, true).tile == F32TileShape::k32 && pick_f32_tile(n, out_n, 0, 1, true).tile == F32TileShape::k32;
 }
 
 // How the sketch of a float32 layer is formed.  Stored: S is written once, into the part of the workspace that the partial
@@ -311,7 +314,7 @@ static inline F32SketchPlan plan_f32_sketch(int64_t n, int64_t channels, int64_t
   }
   plan.k_per_split = round_up(ceil_div(n, G), 32);
   plan.splits = ceil_div(n, plan.k_per_split);
-  const double k_tile = 1.15 * pick_f32_tile(channels, r, plan.splits, true).ns_per_k;
+  const double k_tile = 1.15 * pick_f32_tile(channels, r, plan.k_per_split, plan.splits, true).ns_per_k;
   const double stored = 4600 + 0.004 * s_size + plan.k_per_split / 32 * k_tile + (plan.splits > 1 || !f32_factor ? 5000 : 0);
   const int64_t groups = ceil_div(generic_splits * ceil_div(channels, 64) * ceil_div(r, 64), 256);
   const double generic = 5000 + ceil_div(n, generic_splits) / 256.0 * (20000 + 8000 * groups);

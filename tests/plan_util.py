@@ -14,7 +14,8 @@ using namespace acc;
 extern "C" {
 int gemm_tile(int64_t M, int64_t N, int64_t K, int persist_ok) { return (int)pick_gemm_tile(M, N, K, persist_ok != 0).tile; }
 int gemm_one_round(int64_t M, int64_t N, int64_t K, int persist_ok) { return pick_gemm_tile(M, N, K, persist_ok != 0).one_round; }
-int f32_tile(int64_t M, int64_t N, int64_t splits, int all_tiles) { return (int)pick_f32_tile(M, N, splits, all_tiles != 0).tile; }
+int f32_tile(int64_t M, int64_t N, int64_t splits, int all_tiles) { return (int)pick_f32_tile(M, N, 0, splits, all_tiles != 0).tile; }
+int f32_four_stages(int64_t M, int64_t N, int64_t k, int splits) { return pick_f32_tile(M, N, k, splits, true).deep; }
 int factor_tile(int64_t M, int64_t N, int64_t K, int form) { return (int)pick_factor_tile(M, N, K, (form & 1) != 0, (form & 2) != 0); }
 void sketch(int64_t n, int64_t channels, int64_t r, int64_t ld, int bf16_factor, int* out) {
   const SketchPlan p = plan_sketch(n, channels, r, ld, true, bf16_factor != 0, false);
@@ -56,7 +57,7 @@ def lib():
             f.write(_SOURCE)
         subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-O1", "-shared", "-fPIC", "-I" + ROOT, src, "-o", out], check=True)
         so = ctypes.CDLL(out)
-    for name in ("gemm_tile", "gemm_one_round", "f32_tile", "f32_sketch_splits", "f32_sketch_fits", "factor_tile"):
+    for name in ("gemm_tile", "gemm_one_round", "f32_tile", "f32_sketch_splits", "f32_sketch_fits", "factor_tile", "f32_four_stages"):
         getattr(so, name).argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int]
     so.sketch.argtypes = [ctypes.c_int64] * 4 + [ctypes.c_int, ctypes.c_void_p]
     so.f32_shared_launch.argtypes = [ctypes.c_int64] * 4 + [ctypes.c_int]
@@ -72,6 +73,11 @@ def gemm_tile(m, n, k, float_or_sum=False):
 
 def f32_tile(m, n, splits=1, both_f32=True):
     return ("64x64", "32x32", "128x64", "64x32")[lib().f32_tile(m, n, splits, both_f32)]
+
+
+def f32_four_stages(m, n, k, splits=1):
+    """Whether a float32 product on 32 x 32 or 64 x 32 tiles has four stages, two otherwise."""
+    return bool(lib().f32_four_stages(m, n, k, splits))
 
 
 def f32_sketch_splits(n, channels, r, f32_factor=True):

@@ -48,6 +48,7 @@ def _check(name, got, want, k, extra=0.0):
     (776, 2048, 2048, 24, ["64x64", "64x64", "128x64", "32x32"]),     # dW: one K tile of a ring of three
     (2044, 2040, 2040, 40, ["128x64", "128x64", "128x64", "32x32"]),  # K ends inside a K tile
     (300, 2040, 2040, 2040, ["32x32", "32x32", "128x64", "128x64"]),  # 128 x 64 with both operands' rows contiguous
+    (2330, 1480, 2504, 24, ["128x64", "128x64", "128x64", "64x32"]),  # Y: three 128 x 64 tiles to a compute unit
 ])
 def test_layer(acc, n, d_in, d_out, r, tiles, out_in):
     import torch

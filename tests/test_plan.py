@@ -26,10 +26,22 @@ TILES = ("128x64", "64x64", "64x32", "32x32")
     (384, 3072, 3072, (105.3, 107.1, 83.9, 88.1)),
     (1024, 64, 4096, (139.0, 82.5, 51.7, 39.5)),
     (1536, 1024, 2048, (71.7, 71.6, 56.8, 66.8)),
+    (2337, 2496, 1472, (138.1, 158.8, 156.4, 166.9)), (2500, 2304, 1024, (95.9, 110.8, 101.8, 117.1)), (2453, 2304, 1408, (132.3, 144.7, 138.9, 152.8)),
+    (2236, 2240, 640, (62.0, 53.5, 57.2, 65.8)),   # 2.5 of 128 x 64 to a compute unit, five of 64 x 64, all resident
 ])
 def test_float32_tile_is_near_the_best(m, n, k, us):
     tile = plan.f32_tile(m, n)
     assert us[TILES.index(tile)] <= 1.12 * min(us), tile
+
+
+# us of a product on 32 x 32 tiles with two stages and with four
+@pytest.mark.parametrize("m,n,k,two,four", [
+    (405, 1728, 3392, 60.3, 58.2), (531, 1280, 2432, 43.7, 42.6), (391, 2392, 1472, 35.0, 34.0), (339, 2112, 1536, 30.1, 29.6),
+    (726, 1024, 384, 9.6, 9.8), (873, 832, 720, 15.8, 16.1), (1463, 448, 576, 12.6, 12.8), (448, 1176, 392, 10.1, 10.3), (913, 640, 3056, 55.7, 54.4),
+])
+def test_stages_of_32_x_32_tiles(m, n, k, two, four):
+    assert plan.f32_tile(m, n) == "32x32"
+    assert (four if plan.f32_four_stages(m, n, k) else two) <= 1.02 * min(two, four)
 
 
 # us of the sketch with a stored S and with the generic kernel, tokens x channels at rank
