@@ -64,8 +64,9 @@ static inline GemmChoice pick_gemm_tile(int64_t M, int64_t N, int64_t K, bool pe
 //   written        the least of base + (tiles of the fullest compute unit) x (tile + K tiles x time of one), in nanoseconds,
 //                  and from three K tiles on the persistent kernel's: 1.3 % behind the best of nine candidates on average over
 //                  138 outputs (13 % at most), 3 % where C is float.  A fourth 128 x 64 tile on a compute unit, which holds three, is
-//                  priced as the second batch it is; 64 x 64, of which it holds three too, needs no such term: its time a tile is
-//                  fitted to many batches (8192 x 8192 at rank 256, 64 to a compute unit: 77.9 us both estimated and measured)
+//                  priced as the second batch it is; a fourth 64 x 64, of which it holds three too, by less, its time a tile being
+//                  fitted to many batches (8192 x 8192 at rank 256, 64 to a compute unit: 77.9 us; 4672 x 1792 at rank 32, eight: 8.3
+//                  us, 192 x 128 7.2)
 //   added to C     by size: the read of C counts more than the products.  The three-stage kernel requests C with its operands
 //                  and stays where its one round is nearly full (3072 x 3072 at rank 64: 10.6 us, 128 x 64 10.9) and at short ranks
 //                  of outputs beyond 1024 of its tiles (8192 x 8192 at rank 64: 67 us, 128 x 64 88).  2.2 % behind the best on
@@ -97,7 +98,7 @@ static inline FactorTile pick_factor_tile(int64_t M, int64_t N, int64_t K, bool 
     if (c.tile == FactorTile::kPersist && !(bf16_c && K > 128)) continue;
     const int64_t per_cu = ceil_div(tiles(c.bm, c.bn), 256);
     int64_t ns = c.base + per_cu * (c.per_tile + kt * c.per_k);
-    if (c.tile == FactorTile::k128x64 && per_cu > 3) ns += 900;   // three are resident
+    if (per_cu > 3) ns += c.tile == FactorTile::k128x64 ? 900 : c.tile == FactorTile::k64 ? 200 : 0;   // three are resident
     if (ns < best_ns) { best_ns = ns; best = c.tile; }
   }
   return best;

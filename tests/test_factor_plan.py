@@ -32,6 +32,8 @@ TILES = ("64x64", "128x64", "128x128", "192x128", "three-stage", "persistent")
     (14336, 4096, 128, False, True, (110.4, 124.8, 126.3, 126.1, None, None)),
     (2048, 3072, 256, False, True, (14.1, 12.8, 15.0, 18.6, None, None)),
     (1032, 1544, 128, False, True, (6.4, 7.4, 10.8, 13.8, None, None)),
+    (4672, 1792, 32, True, False, (8.3, 7.5, 8.4, 7.2, None, None)), (4096, 2048, 32, True, False, (8.4, 7.2, 6.6, 7.3, None, None)),
+    (8192, 1088, 32, True, False, (9.0, 7.7, 8.7, 7.3, None, None)),
     (3072, 3072, 512, True, True, (None, 20.0, None, None, 19.0, None)), (3072, 3072, 1024, True, True, (None, 29.8, None, None, 27.0, None)),
 ])
 def test_factor_product_is_near_the_best(m, n, k, bf16_c, added, us):
