@@ -147,10 +147,11 @@ static inline SketchSplit narrow_sketch_slabs(int64_t n, int64_t channels, int64
 // splits at most (8 splits for 10 lose, 2500 x 2048 at rank 256 37.1 us against 34.4) and 0.23 us ahead; at most twice the stages, so
 // that neither of the two sums has more of them than a split had; and no die with more work-groups than compute units (21418 x 448
 // at rank 384, 36 on two of them: 43.6 us of a pass against 38.6).
-// Fitted to 278 forward passes (256 to 32768 tokens, 256 to 8192 channels, rank 16 to 512, 64 to 3072 outputs), of which it takes fewer
-// splits in 51: 8.9 % ahead of the splits of 512 channels there on average, behind in none.  us, the splits of 512 channels / chosen:
-// 4096 x 4096 at rank 128 56.1 / 52.3, 2048 x 4096 at 256 46.8 / 41.8, 600 x 8192 at 256 53.0 / 49.6, 1500 x 5120 at 256 52.1 / 46.0, 4096 x
-// 1024 at 256 27.1 / 26.0; 4096, 6000 and 16384 x 3072 at 256 stay, and 15018 x 2208 at 128 (75.0, 77.0 with 14 splits for 25).
+// Fitted to 278 forward passes (256 to 32768 tokens, 256 to 8192 channels, rank 16 to 512, 64 to 3072 outputs), of which it
+// takes fewer splits in 51: 8.9 % ahead of the splits of 512 channels there on average, behind in none.  us, the splits of 512
+// channels / chosen: 4096 x 4096 at rank 128 56.1 / 52.3, 2048 x 4096 at 256 46.8 / 41.8, 600 x 8192 at 256 53.0 / 49.6, 1500 x
+// 5120 at 256 52.1 / 46.0, 4096 x 1024 at 256 27.1 / 26.0; 4096, 6000 and 16384 x 3072 at 256 stay, and 15018 x 2208 at 128
+// (75.0, 77.0 with 14 splits for 25).
 static inline SketchSplit pick_sketch_split(int64_t n, int64_t channels, int64_t r, int64_t most) {
   struct Cost { int ch, start, per_iteration; };
   static const Cost costs[] = {{512, 1450, 477}, {256, 700, 372}, {128, 0, 264}};
@@ -229,18 +230,18 @@ static inline SketchPlan plan_sketch(int64_t n, int64_t channels, int64_t r, int
   return sp;
 }
 
-// Which tile a float32 product takes: the least time of a K tile of 32, fixed + tiles per compute unit x per_tile
-// nanoseconds.  The matrix pipe bounds all of them, so the estimates follow the area, and a small tile only loses by its
-// operands' latency; what decides is how many tiles the fullest compute unit gets.  Two stages and as many work-groups as LDS
-// holds (64 x 64 five, 64 x 32 six, 32 x 32 eight): they start, wait and store at different times, which is worth more than
-// transfers further ahead (2048 x 2048 x 1024 66.5 us against 70.7 on 128 x 64 with three stages, two work-groups; 2504 x 1000 x
-// 3000 128 against 160 on 64 x 32 with four).  Only where 32 x 32 tiles are 2.5 or fewer to a compute unit, or 64 x 32 one,
-// there is nobody to cover a wait: four stages; so too up to four 32 x 32 to a compute unit where the contraction is long (1 to 4 % over
-// seven products of 1472 to 3392 elements: 405 x 1728 x 3392 58.2 us against 60.3; six shorter ones are 1 to 2 % ahead with two).  128 x 64 where
-// it is two or three to a compute unit, all of them resident: as fast as four of 64 x 64, with a quarter less to move, and ahead of
-// six, of which five are (2337 x 2496 x 1472 138 us and 158, 2500 x 2304 x 1024 96 and 111).  Constants fitted to 150 measurements (50 shapes from 128 x 128 x 4096 to 4096 x 4096 x 1024 in three
-// orders of the operands): the chosen form is 2.9 % behind the best of eleven on average, 13 % at
-// most (three and four stages everywhere and their own fit: 5.4 and 29 %).
+// Which tile a float32 product takes: the least time of a K tile of 32, fixed + tiles per compute unit x per_tile nanoseconds.
+// The matrix pipe bounds all of them, so the estimates follow the area, and a small tile only loses by its operands' latency;
+// what decides is how many tiles the fullest compute unit gets.  Two stages and as many work-groups as LDS holds (64 x 64 five,
+// 64 x 32 six, 32 x 32 eight): they start, wait and store at different times, which is worth more than transfers further ahead
+// (2048 x 2048 x 1024 66.5 us against 70.7 on 128 x 64 with three stages, two work-groups; 2504 x 1000 x 3000 128 against 160
+// on 64 x 32 with four).  Only where 32 x 32 tiles are 2.5 or fewer to a compute unit, or 64 x 32 one, there is nobody to cover
+// a wait: four stages; so too up to four 32 x 32 to a compute unit where the contraction is long (1 to 4 % over seven products
+// of 1472 to 3392 elements: 405 x 1728 x 3392 58.2 us against 60.3; six shorter ones are 1 to 2 % ahead with two).  128 x 64
+// where it is two or three to a compute unit, all of them resident: as fast as four of 64 x 64, with a quarter less to move,
+// and ahead of six, of which five are (2337 x 2496 x 1472 138 us and 158, 2500 x 2304 x 1024 96 and 111).  Constants fitted to
+// 150 measurements (50 shapes from 128 x 128 x 4096 to 4096 x 4096 x 1024 in three orders of the operands): the chosen form is
+// 2.9 % behind the best of eleven on average, 13 % at most (three and four stages everywhere and their own fit: 5.4 and 29 %).
 // Measured us, 64 x 64 / 64 x 32 / 32 x 32, the chosen one marked [before]:
 //   2048 x 2048 x 1024  68 / 79  / 85 (67* on 128 x 64) [69-71]     2048 x 1024 x 2048  71* / 73 / 89 [72]
 //   300 x 4096 x 2048   70  / 56* / 58 [57]                         2504 x 1000 x 3000  143 / 129* / 166 [159]
